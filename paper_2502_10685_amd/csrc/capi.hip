@@ -397,6 +397,7 @@ struct pp_circuit {
     std::vector<uint64_t> ox, oz;
     std::vector<double> oc;
     bool have_obs = false;
+    bool obs_distinct = false;  // no string of the observable is repeated
     uint64_t *d_ox = nullptr, *d_oz = nullptr;
     double *d_oc = nullptr;
 
@@ -829,6 +830,7 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
             d.nops = (int32_t)P.ops.size();
             d.n = c->n;
             d.nterms = (int32_t)c->ox.size();
+            d.distinct = c->obs_distinct;
             HIPCHK(dalloc(&c->d_res, 1));
             HIPCHK(hipMemcpy(c->d_res, &d, sizeof(d), hipMemcpyHostToDevice));
         } else {
@@ -923,7 +925,7 @@ pp_status enqueue_dense_body(pp_circuit *c, hipStream_t s, double *out) {
             HIPCHK(pp::launch_frame_pass(c->fb, c->dbytes, c->fplan.passes[(size_t)i], c->d_theta, i, s));
         }
         ProfScope ps(PC_INIT, s);
-        HIPCHK(pp::launch_dense_init(c->coef, nullptr, c->n, c->dbytes, c->d_ox, c->d_oz, c->d_oc, 0, s));
+        HIPCHK(pp::launch_dense_init(c->coef, nullptr, c->n, c->dbytes, c->d_ox, c->d_oz, c->d_oc, 0, true, s));
         HIPCHK(pp::launch_frame_to_dense(c->fb, c->dbytes, c->d_codes, (int)c->splan.codes.size(), np, c->coef, s));
     }
     if (P.nmaps() > 0) {
@@ -942,7 +944,7 @@ pp_status enqueue_dense_body(pp_circuit *c, hipStream_t s, double *out) {
     if (c->ramp_gate < 0) {
         ProfScope ps(PC_INIT, s);
         HIPCHK(pp::launch_dense_init(c->coef, c->track ? c->pres : nullptr, c->n, c->dbytes, c->d_ox, c->d_oz,
-                                     c->d_oc, (int)c->ox.size(), s));
+                                     c->d_oc, (int)c->ox.size(), c->obs_distinct, s));
     }
     const int shift = 2 * (c->n - P.k);
     TileSpan span;
@@ -1257,6 +1259,23 @@ pp_status pp_circuit_set_theta(pp_circuit *c, const double *theta, int32_t on_de
     return PP_OK;
 }
 
+// Whether no string appears twice (its kernels then write the start weights
+// in parallel).  Ascending input, the canonical order, needs no sort.
+static bool strings_distinct(const std::vector<uint64_t> &x, const std::vector<uint64_t> &z) {
+    const size_t m = x.size();
+    size_t i = 1;
+    while (i < m && (z[i - 1] < z[i] || (z[i - 1] == z[i] && x[i - 1] < x[i]))) ++i;
+    if (i >= m) return true;
+    try {
+        std::vector<std::pair<uint64_t, uint64_t>> v(m);
+        for (size_t j = 0; j < m; ++j) v[j] = {z[j], x[j]};
+        std::sort(v.begin(), v.end());
+        return std::adjacent_find(v.begin(), v.end()) == v.end();
+    } catch (const std::bad_alloc &) {
+        return false;  // no memory to tell: the kernels sum in order
+    }
+}
+
 pp_status pp_circuit_set_observable(pp_circuit *c, int64_t n_terms, const uint64_t *x, const uint64_t *z,
                                     const double *coeff) {
     if (!c) return fail(PP_ERR_INVALID, "null circuit");
@@ -1282,6 +1301,7 @@ pp_status pp_circuit_set_observable(pp_circuit *c, int64_t n_terms, const uint64
     c->ox.assign(x, x + n_terms);
     c->oz.assign(z, z + n_terms);
     c->oc.assign(coeff, coeff + n_terms);
+    c->obs_distinct = strings_distinct(c->ox, c->oz);
     c->have_obs = true;
     c->obs_gen++;
     free_plan_buffers(c);  // descriptors hold the observable pointers
@@ -1429,7 +1449,8 @@ pp_status pp_evaluate_noalloc(pp_circuit *c, void *stream, double *d_expval) {
         HIPCHK(pp::launch_resident(res, 1, c->n, c->dbytes, false, s));
         return PP_OK;
     }
-    HIPCHK(pp::launch_dense_init(coef, nullptr, c->n, c->dbytes, c->d_ox, c->d_oz, c->d_oc, (int)c->ox.size(), s));
+    HIPCHK(pp::launch_dense_init(coef, nullptr, c->n, c->dbytes, c->d_ox, c->d_oz, c->d_oc, (int)c->ox.size(),
+                                 c->obs_distinct, s));
     const int shift = 2 * (c->n - P.k);
     for (size_t p = 0; p < npass; ++p) {
         pp::TileGroups grp{};
@@ -1810,7 +1831,7 @@ extern "C" pp_status pp_evaluate_batch(pp_circuit *const *cs, int64_t count, voi
             for (int i : B.tiled) {
                 pp_circuit *c = cs[i];
                 io.push_back(pp::DenseIODesc{c->coef, c->d_ox, c->d_oz, c->d_oc, d_expvals + i, c->n,
-                                             (int32_t)c->ox.size()});
+                                             (int32_t)c->ox.size(), c->obs_distinct, 0});
                 B.io_max_n = std::max(B.io_max_n, c->n);
             }
             B.io_off = append(io.data(), io.size() * sizeof(io[0]));
@@ -1995,6 +2016,7 @@ pp_status ensure_grad(pp_circuit *c, int64_t every) {
             d.nops = ps.op_end - ps.op_begin;
             d.n = n;
             d.nterms = (int32_t)c->ox.size();
+            d.distinct = c->obs_distinct;
             rd.push_back(d);
         }
         if ((r = upload_vec(&G.hres, rd)) != PP_OK) return r;
@@ -2160,7 +2182,7 @@ extern "C" pp_status pp_evaluate_thetas(pp_circuit *c, int64_t count, const doub
     {
         ProfScope ps(PC_INIT, s);
         HIPCHK(pp::launch_dense_init(W.coef, nullptr, c->n, c->dbytes, c->d_ox, c->d_oz, c->d_oc, (int)c->ox.size(),
-                                     s, (int)count));
+                                     c->obs_distinct, s, (int)count));
     }
     const int shift = 2 * (c->n - P.k);
     const int64_t ntiles = (int64_t)1 << shift;
@@ -2340,7 +2362,8 @@ pp_status enqueue_gradient_body(pp_circuit *c, hipStream_t s, double *d_expval, 
         } else {
             if (sg + 1 == S) {
                 ProfScope ps(PC_INIT, s);
-                HIPCHK(pp::launch_dense_init(c->coef, nullptr, n, 8, c->d_ox, c->d_oz, c->d_oc, (int)c->ox.size(), s));
+                HIPCHK(pp::launch_dense_init(c->coef, nullptr, n, 8, c->d_ox, c->d_oz, c->d_oc, (int)c->ox.size(),
+                                             c->obs_distinct, s));
             }
             const int shift = 2 * (n - G.k_heis);
             TileSpan span;
@@ -2600,7 +2623,7 @@ pp_status start_request(pp_server *S, ServedReq *r) {
     if ((st = after_theta(c, S->main)) != PP_OK) return st;
     if (c->dplan.nmaps() > 0) HIPCHK(pp::launch_compose(c->d_comp, 1, S->main, c->dplan.nmaps()));
     HIPCHK(pp::launch_dense_init(r->buf, nullptr, c->n, c->dbytes, c->d_ox, c->d_oz, c->d_oc, (int)c->ox.size(),
-                                 S->main));
+                                 c->obs_distinct, S->main));
     r->pass = 0;
     return PP_OK;
 }

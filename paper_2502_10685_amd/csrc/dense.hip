@@ -735,8 +735,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((N >= 7 &
     if (d.coef_in) {
         const T *in = reinterpret_cast<const T *>(d.coef_in);
         for (int i = tid; i < size; i += BLOCK) lc[sw(i)] = in[i];
-    } else if (tid == 0) {
-        for (int t = 0; t < d.nterms; ++t) {
+    } else if (d.distinct || tid == 0) {
+        // repeated strings are summed in input order by one thread
+        for (int t = tid; t < d.nterms; t += d.distinct ? BLOCK : 1) {
             const int s = (int)morton_slot(d.obs_x[t], d.obs_z[t], n);
             lc[sw(s)] = (T)((double)lc[sw(s)] + d.obs_c[t]);
             if (TRACK) lp[sw(s)] = 1;
@@ -1662,13 +1663,17 @@ __device__ void gate_matrix(int op, double th, double G[9]) {
 
 // Maps are composed by one lane when their recipe is short and by a whole
 // wave when it is long (the rule depends on the map alone, so a circuit's
-// maps are the same bits however it is batched).  A wave takes 64
-// consecutive maps: each lane folds its short recipe in order; then for each
+// maps are the same bits however it is batched).  Block (d, y) serves
+// descriptor d; wave w of its W waves takes maps w, w + W, w + 2W, ..., 64 of
+// them at a time: each lane folds its short recipe in order; then for each
 // long recipe of the 64, the lanes build the matrices of 64 consecutive
 // gates at once (their parameter loads and sincos in parallel), an ordered
 // tree of 3x3 products over the lanes multiplies them (later gates on the
-// left), and the chunk products are applied in recipe order.  Block (d, y)
-// serves descriptor d; its y blocks and their waves share its maps.
+// left), and the chunk products are applied in recipe order.  What bounds it
+// is that chain, about 2 us per 64 gates, so long recipes must spread over
+// waves: with 64 consecutive maps per wave the 200 maps of 300 gates of a
+// 60,200-gate chain ran on four waves in 354 us; one map per wave takes
+// 17 us.
 constexpr int kShortRecipe = 8;
 
 __device__ __forceinline__ void mat3_mul(const double A[9], const double B[9], double C[9]) {
@@ -1694,9 +1699,9 @@ __global__ __launch_bounds__(256) void compose_kernel(const ComposeDesc *__restr
     const bool fwd = d.reserved == 1;
     const int lane = threadIdx.x & 63;
     const int wpb = blockDim.x >> 6;
-    const int wstride = gridDim.y * wpb;
-    for (int w0 = (blockIdx.y * wpb + (threadIdx.x >> 6)) * 64; w0 < d.nmaps; w0 += wstride * 64) {
-        const int i = w0 + lane;
+    const int W = gridDim.y * wpb;
+    for (int w0 = blockIdx.y * wpb + (threadIdx.x >> 6); w0 < d.nmaps; w0 += W * 64) {
+        const int i = w0 + lane * W;
         bool longr = false;
         if (i < d.nmaps) {
             const int r0 = d.roff[i], r1 = d.roff[i + 1];
@@ -1717,7 +1722,7 @@ __global__ __launch_bounds__(256) void compose_kernel(const ComposeDesc *__restr
         while (todo) {
             const int l = __builtin_ctzll(todo);
             todo &= todo - 1;
-            const int m = w0 + l;
+            const int m = w0 + l * W;
             const int r0 = d.roff[m], r1 = d.roff[m + 1];
             double M[9] = {1, 0, 0, 0, 1, 0, 0, 0, 1};
             for (int c0 = r0; c0 < r1; c0 += 64) {
@@ -1765,18 +1770,28 @@ __global__ void dense_fill_kernel(T *coef, uint8_t *pres, long long size) {
     }
 }
 
-// Sequential so that repeated strings are summed in input order; block b
-// fills the weights at coef + b * stride (one block per parameter set).
+// The observable's strings into zeroed weights.  Without repeated strings
+// every term has a slot of its own and the threads take them in parallel;
+// with repeats one thread sums them in input order.  (One thread for all,
+// each term waiting for the last one's store, took 603 us for the 1,024
+// strings of a 10-qubit density matrix; in parallel they take 4 us.)
 template <typename T>
-__global__ void dense_scatter_kernel(T *coef, uint8_t *pres, int n, const uint64_t *x, const uint64_t *z,
-                                     const double *c, int nterms, long long stride) {
-    if (threadIdx.x != 0) return;
-    coef += blockIdx.x * stride;
-    for (int t = 0; t < nterms; ++t) {
+__device__ __forceinline__ void scatter_terms(T *coef, uint8_t *pres, int n, const uint64_t *x, const uint64_t *z,
+                                              const double *c, int nterms, bool distinct) {
+    if (!distinct && threadIdx.x != 0) return;
+    for (int t = threadIdx.x; t < nterms; t += distinct ? (int)blockDim.x : 1) {
         const long long s = morton_slot(x[t], z[t], n);
-        coef[s] = (T)((double)coef[s] + c[t]);
+        coef[s] = (T)((distinct ? 0.0 : (double)coef[s]) + c[t]);
         if (pres) pres[s] = 1;
     }
+}
+
+// Block b fills the weights at coef + b * stride (one block per parameter set).
+template <typename T>
+__global__ __launch_bounds__(256) void dense_scatter_kernel(T *coef, uint8_t *pres, int n, const uint64_t *x,
+                                                            const uint64_t *z, const double *c, int nterms,
+                                                            int distinct, long long stride) {
+    scatter_terms<T>(coef + blockIdx.x * stride, pres, n, x, z, c, nterms, distinct != 0);
 }
 
 // Block b reads out the weights at coef + b * stride into out[b]; the same
@@ -1802,14 +1817,10 @@ __global__ void many_fill_kernel(const DenseIODesc *__restrict__ descs) {
 }
 
 template <typename T>
-__global__ void many_scatter_kernel(const DenseIODesc *__restrict__ descs) {
-    if (threadIdx.x != 0) return;
+__global__ __launch_bounds__(256) void many_scatter_kernel(const DenseIODesc *__restrict__ descs) {
     const DenseIODesc &d = descs[blockIdx.x];
-    T *coef = reinterpret_cast<T *>(d.coef);
-    for (int t = 0; t < d.nterms; ++t) {
-        const long long s = morton_slot(d.obs_x[t], d.obs_z[t], d.n);
-        coef[s] = (T)((double)coef[s] + d.obs_c[t]);
-    }
+    scatter_terms<T>(reinterpret_cast<T *>(d.coef), nullptr, d.n, d.obs_x, d.obs_z, d.obs_c, d.nterms,
+                     d.distinct != 0);
 }
 
 template <typename T>
@@ -1920,11 +1931,12 @@ size_t resident_lds_bytes(int n, int dtype_bytes, bool track) {
 
 hipError_t launch_compose(const ComposeDesc *d_descs, int ndescs, hipStream_t s, int max_maps) {
     if (ndescs <= 0) return hipSuccess;
-    // 256 maps per block (64 per wave); enough blocks per descriptor for its
-    // maps, at most 1024 across the launch's y dimension
-    int ychunks = (max_maps + 255) / 256;
-    ychunks = ychunks < 1 ? 1 : (ychunks > 1024 ? 1024 : ychunks);
-    if ((long long)ychunks * ndescs > 65536) ychunks = (int)std::max<long long>(1, 65536 / ndescs);
+    // four waves per block; one map per wave while that takes at most 1,024
+    // blocks (four per CU), so that long recipes run side by side; more maps
+    // than that fill the chip with up to 64 maps per wave
+    const long long per_desc = std::max<long long>(1, 1024 / ndescs);
+    const long long one = (max_maps + 3) / 4, many = (max_maps + 255) / 256;
+    const int ychunks = (int)std::max<long long>(1, std::min<long long>(std::max(std::min(one, per_desc), many), 1024));
     hipLaunchKernelGGL(compose_kernel, dim3(ndescs, ychunks), dim3(256), 0, s, d_descs);
     return hipGetLastError();
 }
@@ -2145,18 +2157,19 @@ hipError_t launch_copy_f64(const double *src, double *dst, long long count, hipS
 }
 
 hipError_t launch_dense_init(void *coef, uint8_t *pres, int n, int dtype_bytes, const uint64_t *x,
-                             const uint64_t *z, const double *c, int nterms, hipStream_t s, int count) {
+                             const uint64_t *z, const double *c, int nterms, bool distinct, hipStream_t s,
+                             int count) {
     const long long size = 1ll << (2 * n);
     const long long total = size * count;
     const int grid = (int)((total + 255) / 256 < 8192 ? (total + 255) / 256 : 8192);
     if (dtype_bytes == 8) {
         hipLaunchKernelGGL(dense_fill_kernel<double>, dim3(grid), dim3(256), 0, s, (double *)coef, pres, total);
-        hipLaunchKernelGGL(dense_scatter_kernel<double>, dim3(count), dim3(64), 0, s, (double *)coef, pres, n, x, z,
-                           c, nterms, size);
+        hipLaunchKernelGGL(dense_scatter_kernel<double>, dim3(count), dim3(256), 0, s, (double *)coef, pres, n, x,
+                           z, c, nterms, (int)distinct, size);
     } else {
         hipLaunchKernelGGL(dense_fill_kernel<float>, dim3(grid), dim3(256), 0, s, (float *)coef, pres, total);
-        hipLaunchKernelGGL(dense_scatter_kernel<float>, dim3(count), dim3(64), 0, s, (float *)coef, pres, n, x, z, c,
-                           nterms, size);
+        hipLaunchKernelGGL(dense_scatter_kernel<float>, dim3(count), dim3(256), 0, s, (float *)coef, pres, n, x, z,
+                           c, nterms, (int)distinct, size);
     }
     return hipGetLastError();
 }
@@ -2178,10 +2191,10 @@ hipError_t launch_dense_init_many(const DenseIODesc *d_descs, int nd, int max_n,
     const int gx = (int)((size + 255) / 256 < 1024 ? (size + 255) / 256 : 1024);
     if (dtype_bytes == 8) {
         hipLaunchKernelGGL(many_fill_kernel<double>, dim3(gx, nd), dim3(256), 0, s, d_descs);
-        hipLaunchKernelGGL(many_scatter_kernel<double>, dim3(nd), dim3(64), 0, s, d_descs);
+        hipLaunchKernelGGL(many_scatter_kernel<double>, dim3(nd), dim3(256), 0, s, d_descs);
     } else {
         hipLaunchKernelGGL(many_fill_kernel<float>, dim3(gx, nd), dim3(256), 0, s, d_descs);
-        hipLaunchKernelGGL(many_scatter_kernel<float>, dim3(nd), dim3(64), 0, s, d_descs);
+        hipLaunchKernelGGL(many_scatter_kernel<float>, dim3(nd), dim3(256), 0, s, d_descs);
     }
     return hipGetLastError();
 }

@@ -53,7 +53,7 @@ struct ResidentDesc {
     int32_t nops;
     int32_t n;
     int32_t nterms;
-    int32_t reserved;
+    int32_t distinct;  // 1: no string is repeated among the nterms
 };
 
 // One pass of one circuit over its 4^(n-k) tiles of 4^k slots.
@@ -110,6 +110,8 @@ struct DenseIODesc {
     const double *obs_c;
     double *out;
     int32_t n, nterms;
+    int32_t distinct;  // 1: no string is repeated among the nterms
+    int32_t reserved;
 };
 
 // Per-circuit composition job: maps[i] = product of the gate matrices of
@@ -190,9 +192,11 @@ hipError_t launch_grad_reduce(const double *partials, int nslots, int ntiles, do
 hipError_t launch_grad_accumulate(const double *rot_grad, const int32_t *slot_param, int nslots, double *grad,
                                   int nparams, hipStream_t s);
 hipError_t launch_copy_f64(const double *src, double *dst, long long count, hipStream_t s);
-// count > 1: count weight arrays of 4^n slots back to back (parameter sets)
+// count > 1: count weight arrays of 4^n slots back to back (parameter sets);
+// distinct: no string is repeated among the nterms
 hipError_t launch_dense_init(void *coef, uint8_t *pres, int n, int dtype_bytes, const uint64_t *x,
-                             const uint64_t *z, const double *c, int nterms, hipStream_t s, int count = 1);
+                             const uint64_t *z, const double *c, int nterms, bool distinct, hipStream_t s,
+                             int count = 1);
 hipError_t launch_dense_readout(const void *coef, int n, int dtype_bytes, double *out, hipStream_t s,
                                 int count = 1);
 // the same for the nd circuits of a batch (one fill, one scatter launch;
