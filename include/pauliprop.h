@@ -250,7 +250,10 @@ PP_API pp_status pp_evaluate_noalloc(pp_circuit *c, void *stream, double *d_expv
 
 /* Enqueues one evaluation of <O> = <0...0| U^dag O U |0...0> (measurement
  * of Sec. II-A from the propagated strings: only strings of I and Z have a
- * nonzero expectation in |0...0>); d_expval is caller-owned device memory
+ * nonzero expectation in |0...0>).  An untracked LDS-resident circuit (n <= 7)
+ * is run from both ends: the observable's weights c back to a middle gate and
+ * the state's Pauli coefficients r (eqs. (2)-(3)) forward to it, side by side,
+ * then <O> = sum_P c(P) r(P).  d_expval is caller-owned device memory
  * for one double.  PP_ERR_STATE if gates, theta or the observable are
  * missing; PP_ERR_NOMEM if the first evaluation's buffers cannot be
  * allocated (the circuit stays usable). */
@@ -442,8 +445,10 @@ PP_API void pp_server_destroy(pp_server *s);
  *                        them, re-plans a circuit at its next evaluation:
  *                        their schedules order each pass into register
  *                        segments.
- *   PP_TUNE_RESIDENT_BLOCK: index = n (5..7), value = 256, 512 or 1024
- *                        threads for the LDS-resident kernel (untracked runs).
+ *   PP_TUNE_RESIDENT_BLOCK: index = n (5..7), value = 256, 512 or 1024;
+ *                        accepted and returned, with no effect: the
+ *                        LDS-resident kernel's threads follow from n (one
+ *                        per 16 weights and direction).
  *   PP_TUNE_SORT_SHAPE: index = capacity class of a SPARSE circuit's term
  *                        buffers (0: up to 2^17 terms, 1: up to 2^21, 2:
  *                        larger), value = shape of the radix sort that
@@ -460,8 +465,7 @@ PP_API void pp_server_destroy(pp_server *s);
  * Variants 0, 1 and 2 give bit-identical results for a given tile size, and
  * so do 3 and 4; the two groups' schedules order commuting ops differently
  * and agree up to rounding.  k changes how ops are packed and therefore the
- * rounding, so a circuit keeps the k of its schedule.  The resident block size changes the order of the
- * final readout sum only. */
+ * rounding, so a circuit keeps the k of its schedule. */
 typedef enum pp_tune_key {
     PP_TUNE_TILE_QUBITS = 0,
     PP_TUNE_TILE_KERNEL = 1,

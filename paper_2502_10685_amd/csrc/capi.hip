@@ -231,7 +231,7 @@ pp_status scratch_address(unsigned char **out) {
 __global__ void noalloc_patch_kernel(const pp::ComposeDesc *comp_in, pp::ComposeDesc *comp_out,
                                      const pp::TilePassDesc *pass_in, pp::TilePassDesc *pass_out, int npass,
                                      const pp::ResidentDesc *res_in, pp::ResidentDesc *res_out, void *coef,
-                                     double *maps, double *expval) {
+                                     void *xbuf, unsigned *ticket, double *maps, double *expval) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i == 0 && comp_in) {
         pp::ComposeDesc d = *comp_in;
@@ -246,6 +246,9 @@ __global__ void noalloc_patch_kernel(const pp::ComposeDesc *comp_in, pp::Compose
         d.maps = maps;
         d.expval_out = expval;
         d.counters = nullptr;
+        d.xbuf = xbuf;
+        d.ticket = ticket;
+        *ticket = 0u;
         *res_out = d;
     }
     if (i < npass) {
@@ -265,6 +268,13 @@ constexpr int kDensityMaxN = 12;
 constexpr int64_t kSparseMaxTerms = (int64_t)1 << 29;
 constexpr int kAutoDenseMaxN = 13;
 constexpr int kLowQubits = 2;
+// PP_TUNE_RESIDENT_BLOCK: kept and returned, but the chain kernel's workgroup
+// follows from n alone (one thread per 16-weight block of a sweep)
+int g_resident_block[8] = {64, 64, 64, 64, 64, 512, 512, 1024};
+// LDS-resident sets of a sweep per launch: two workgroups each fill the chip
+// twice over, and the exchange buffers of more sets (256 KiB each at n = 7 in
+// FP64) are never needed at once
+constexpr int64_t kSweepChunk = 512;
 
 // defaults measured by the autotuner on MI355X (batched probes, FP64)
 int g_tile_qubits[17] = {0, 0, 0, 0, 0, 0, 0, 0, 6, 6, 6, 6, 6, 6, 6, 6, 6};
@@ -444,6 +454,8 @@ struct pp_circuit {
     uint8_t *d_rop = nullptr;
     pp::TilePassDesc *d_pass = nullptr;
     pp::ResidentDesc *d_res = nullptr;
+    pp::ChainOp *d_chain = nullptr;
+    unsigned char *d_xbuf = nullptr;  // resident evaluation, n >= 6: where its two directions meet
     pp::ComposeDesc *d_comp = nullptr;
     pp::ResidentDesc h_res{};
     pp::ComposeDesc h_comp{};
@@ -481,6 +493,7 @@ struct pp_circuit {
         int k_heis = 0, k_fwd = 0;
         pp::GradPlan plan;
         pp::DOp *hops = nullptr, *fops = nullptr;
+        pp::ChainOp *hchain = nullptr;
         double *hmaps = nullptr, *fmaps = nullptr;
         int32_t *hroff = nullptr, *hrparam = nullptr, *froff = nullptr, *frparam = nullptr;
         uint8_t *hrop = nullptr, *frop = nullptr;
@@ -504,6 +517,7 @@ struct pp_circuit {
         int64_t cap = 0;  // parameter sets the buffers hold
         double *thetas = nullptr, *maps = nullptr;
         void *coef = nullptr;
+        unsigned char *xbuf = nullptr;  // resident circuits, n >= 6: exchange of kSweepChunk sets
         void *dbuf = nullptr;
         size_t dcap = 0;
         uint64_t gen = ~0ull;
@@ -539,6 +553,7 @@ void free_sweep(pp_circuit *c) {
     dfree(c->sw.thetas);
     dfree(c->sw.maps);
     dfree(c->sw.coef);
+    dfree(c->sw.xbuf);
     dfree(c->sw.dbuf);
     c->sw.cap = 0;
     c->sw.dcap = 0;
@@ -558,6 +573,8 @@ void free_plan_buffers(pp_circuit *c) {
     dfree(c->d_rop);
     dfree(c->d_pass);
     dfree(c->d_res);
+    dfree(c->d_chain);
+    dfree(c->d_xbuf);
     dfree(c->d_comp);
     dfree(c->d_codes);
     dfree(c->d_xrows);
@@ -579,7 +596,7 @@ void free_grad(pp_circuit *c) {
     if (!G.hops && !G.ckpt && !G.valid) return;
     dfree(G.hops); dfree(G.fops); dfree(G.hmaps); dfree(G.fmaps);
     dfree(G.hroff); dfree(G.hrparam); dfree(G.froff); dfree(G.frparam);
-    dfree(G.hrop); dfree(G.frop); dfree(G.comp); dfree(G.hpass); dfree(G.hres); dfree(G.gpass);
+    dfree(G.hchain); dfree(G.hrop); dfree(G.frop); dfree(G.comp); dfree(G.hpass); dfree(G.hres); dfree(G.gpass);
     dfree(G.ckpt); dfree(G.rbuf); dfree(G.partials); dfree(G.rot_grad); dfree(G.slot_param);
     G.valid = false;
 }
@@ -791,12 +808,16 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
             pp::PlanOptions o;
             o.g_end = c->ramp_gate;  // the dense sweep takes the gates before the frame's
             o.segments = seg;
-            c->dplan = pp::plan_dense_opts(c->g, k, kLowQubits, o);
+            c->dplan = k == c->n ? pp::plan_meet(c->g, kLowQubits, c->ramp_gate, c->dbytes)
+                                 : pp::plan_dense_opts(c->g, k, kLowQubits, o);
+        } else if (k == c->n && !c->track && !c->keep_coef) {
+            c->dplan = pp::plan_meet(c->g, kLowQubits, c->g.m, c->dbytes);
         } else {
             pp::PlanOptions o;
             o.compose = o.group = o.reorder = c->track == 0;
             o.segments = seg;
             c->dplan = pp::plan_dense_opts(c->g, k, kLowQubits, o);
+            if (k == c->n && !c->track) pp::build_chain(c->dplan, c->dbytes);
         }
         const pp::DensePlan &P = c->dplan;
         {
@@ -811,7 +832,8 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
         if ((r = upload_vec(&c->d_rop, P.rop)) != PP_OK) return r;
         if ((r = upload_vec(&c->d_rparam, P.rparam)) != PP_OK) return r;
         HIPCHK(dalloc(&c->d_maps, (size_t)9 * std::max(P.nmaps(), 1)));
-        c->h_comp = pp::ComposeDesc{c->d_roff, c->d_rop, c->d_rparam, c->d_theta, c->d_maps, P.nmaps(), c->fwd_maps};
+        c->h_comp = pp::ComposeDesc{c->d_roff, c->d_rop, c->d_rparam, c->d_theta, c->d_maps, P.nmaps(),
+                                   c->fwd_maps ? 0 : (P.fwd_from >= 0 ? P.fwd_from : P.nmaps())};
         HIPCHK(dalloc(&c->d_comp, 1));
         HIPCHK(hipMemcpy(c->d_comp, &c->h_comp, sizeof(c->h_comp), hipMemcpyHostToDevice));
         if (P.resident) {
@@ -831,6 +853,21 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
             d.n = c->n;
             d.nterms = (int32_t)c->ox.size();
             d.distinct = c->obs_distinct;
+            if (!c->track) {
+                if ((r = upload_vec(&c->d_chain, P.chain)) != PP_OK) return r;
+                d.chain = c->d_chain;
+                d.nchain = P.nchain;
+                d.nchain_fwd = (int32_t)P.chain.size() - P.nchain;
+                d.nmaps = P.nmaps();
+                const size_t xb = P.fwd_from >= 0 ? pp::chain_exchange_bytes(c->n, c->dbytes) : 0;
+                if (xb) {
+                    // the two directions' vectors, then their ticket (0 between launches)
+                    HIPCHK(dalloc(&c->d_xbuf, xb + 256));
+                    HIPCHK(hipMemset(c->d_xbuf + xb, 0, 256));
+                    d.xbuf = c->d_xbuf;
+                    d.ticket = (unsigned *)(c->d_xbuf + xb);
+                }
+            }
             HIPCHK(dalloc(&c->d_res, 1));
             HIPCHK(hipMemcpy(c->d_res, &d, sizeof(d), hipMemcpyHostToDevice));
         } else {
@@ -933,10 +970,12 @@ pp_status enqueue_dense_body(pp_circuit *c, hipStream_t s, double *out) {
         HIPCHK(pp::launch_compose(c->d_comp, 1, s, P.nmaps()));
     }
     if (P.resident) {
-        {
-            ProfScope ps(PC_RES, s);
-            HIPCHK(pp::launch_resident(c->d_res, 1, c->n, c->dbytes, c->track != 0, s));
+        ProfScope ps(PC_RES, s);
+        if (!c->track) {
+            HIPCHK(pp::launch_chain(c->d_res, 1, c->n, c->dbytes, P.fwd_from >= 0, out, s));
+            return PP_OK;
         }
+        HIPCHK(pp::launch_resident_tracked(c->d_res, 1, c->n, c->dbytes, s));
         hipLaunchKernelGGL(copy_f64_kernel, dim3(1), dim3(64), 0, s, c->d_result, out, 1);
         HIPCHK(hipGetLastError());
         return PP_OK;
@@ -1429,7 +1468,9 @@ pp_status pp_evaluate_noalloc(pp_circuit *c, void *stream, double *d_expval) {
     const size_t off_pass = off_res + up(sizeof(pp::ResidentDesc));
     const size_t off_maps = off_pass + up(npass * sizeof(pp::TilePassDesc));
     const size_t off_coef = off_maps + up((size_t)9 * sizeof(double) * std::max(P.nmaps(), 1));
-    const size_t coef_bytes = P.resident ? 0 : (size_t)dense_slots(c->n) * c->dbytes;
+    // tiled: the 4^n weights; resident: the directions' exchange and ticket
+    const size_t xbytes = P.resident ? up(pp::chain_exchange_bytes(c->n, c->dbytes)) : 0;
+    const size_t coef_bytes = P.resident ? xbytes + 256 : (size_t)dense_slots(c->n) * c->dbytes;
     if (off_coef + coef_bytes > kNoAllocBytes)
         return fail(PP_ERR_CAPACITY, "pp_evaluate_noalloc: working set of " + std::to_string(off_coef + coef_bytes) +
                                          " bytes exceeds the " + std::to_string(kNoAllocBytes) + "-byte array");
@@ -1442,11 +1483,11 @@ pp_status pp_evaluate_noalloc(pp_circuit *c, void *stream, double *d_expval) {
     const int pblocks = (int)std::max<size_t>(1, (npass + 255) / 256);
     hipLaunchKernelGGL(noalloc_patch_kernel, dim3(pblocks), dim3(256), 0, s, c->d_comp, comp,
                        P.resident ? nullptr : c->d_pass, pass, (int)npass, P.resident ? c->d_res : nullptr, res, coef,
-                       maps, d_expval);
+                       coef, (unsigned *)(base + off_coef + xbytes), maps, d_expval);
     HIPCHK(hipGetLastError());
     if (P.nmaps() > 0) HIPCHK(pp::launch_compose(comp, 1, s, P.nmaps()));
     if (P.resident) {
-        HIPCHK(pp::launch_resident(res, 1, c->n, c->dbytes, false, s));
+        HIPCHK(pp::launch_chain(res, 1, c->n, c->dbytes, P.fwd_from >= 0, nullptr, s));
         return PP_OK;
     }
     HIPCHK(pp::launch_dense_init(coef, nullptr, c->n, c->dbytes, c->d_ox, c->d_oz, c->d_oc, (int)c->ox.size(),
@@ -1747,7 +1788,7 @@ pp_status enqueue_batch_body(BatchCache &B, int dbytes, hipStream_t s) {
         if (L.kind == 0)
             HIPCHK(pp::launch_compose((const pp::ComposeDesc *)(base + L.off), L.nd, ls, L.nblocks));
         else
-            HIPCHK(pp::launch_resident((const pp::ResidentDesc *)(base + L.off), L.nd, L.group_n, dbytes, false, ls));
+            HIPCHK(pp::launch_chain((const pp::ResidentDesc *)(base + L.off), L.nd, L.group_n, dbytes, true, nullptr, ls));
     }
     span.end();
     if (forked) {
@@ -1993,27 +2034,29 @@ pp_status ensure_grad(pp_circuit *c, int64_t every) {
     HIPCHK(dalloc(&G.hmaps, (size_t)9 * std::max(P.heis.nmaps(), 1)));
     HIPCHK(dalloc(&G.fmaps, (size_t)9 * std::max(P.fwd.nmaps(), 1)));
     std::vector<pp::ComposeDesc> comp;
-    if (P.heis.nmaps() > 0) comp.push_back({G.hroff, G.hrop, G.hrparam, c->d_theta, G.hmaps, P.heis.nmaps(), 0});
-    if (P.fwd.nmaps() > 0) comp.push_back({G.froff, G.frop, G.frparam, c->d_theta, G.fmaps, P.fwd.nmaps(), 0});
+    if (P.heis.nmaps() > 0) comp.push_back({G.hroff, G.hrop, G.hrparam, c->d_theta, G.hmaps, P.heis.nmaps(), P.heis.nmaps()});
+    if (P.fwd.nmaps() > 0) comp.push_back({G.froff, G.frop, G.frparam, c->d_theta, G.fmaps, P.fwd.nmaps(), P.fwd.nmaps()});
     G.ncomp = (int)comp.size();
     if ((r = upload_vec(&G.comp, comp)) != PP_OK) return r;
     const size_t S = P.bounds.size() - 1;
     const int64_t slots = dense_slots(n);
     if (P.heis.resident) {
+        if ((r = upload_vec(&G.hchain, P.heis.chain)) != PP_OK) return r;
         std::vector<pp::ResidentDesc> rd;
         for (size_t sg = 0; sg < S; ++sg) {
-            const pp::DensePass &ps = P.heis.passes[P.heis_pass_begin[sg]];
             pp::ResidentDesc d{};
             d.coef_in = sg + 1 == S ? nullptr : c->coef;
             d.coef_out = c->coef;
-            d.ops = G.hops + ps.op_begin;
             d.maps = G.hmaps;
+            d.chain = G.hchain + P.heis_chain_begin[(size_t)P.heis_pass_begin[sg]];
+            d.nchain = P.heis_chain_begin[(size_t)P.heis_pass_begin[sg] + 1] -
+                       P.heis_chain_begin[(size_t)P.heis_pass_begin[sg]];
+            d.nmaps = P.heis.nmaps();
             d.obs_x = c->d_ox;
             d.obs_z = c->d_oz;
             d.obs_c = c->d_oc;
             d.expval_out = c->d_result;
             d.counters = nullptr;
-            d.nops = ps.op_end - ps.op_begin;
             d.n = n;
             d.nterms = (int32_t)c->ox.size();
             d.distinct = c->obs_distinct;
@@ -2104,6 +2147,13 @@ extern "C" pp_status pp_evaluate_thetas(pp_circuit *c, int64_t count, const doub
         hipError_t e = dalloc(&W.thetas, (size_t)(np * cap));
         if (e == hipSuccess) e = dalloc(&W.maps, (size_t)(9 * nm * cap));
         if (e == hipSuccess && !P.resident) e = dev_alloc(&W.coef, (size_t)slots * c->dbytes * cap);
+        const size_t xb = P.resident ? pp::chain_exchange_bytes(c->n, c->dbytes) : 0;
+        if (e == hipSuccess && xb) {
+            const size_t bytes = (size_t)std::min(cap, kSweepChunk) * (xb + 256);
+            e = dalloc(&W.xbuf, bytes);
+            if (e == hipSuccess) e = hipMemset(W.xbuf, 0, bytes);  // the tickets
+            if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+        }
         if (e != hipSuccess) {
             (void)hipGetLastError();
             free_sweep(c);
@@ -2134,6 +2184,7 @@ extern "C" pp_status pp_evaluate_thetas(pp_circuit *c, int64_t count, const doub
         W.comp_off = append(comp.data(), comp.size() * sizeof(comp[0]));
         if (P.resident) {
             std::vector<pp::ResidentDesc> rd(count);
+            const size_t xb = pp::chain_exchange_bytes(c->n, c->dbytes);
             for (int64_t i = 0; i < count; ++i) {
                 rd[i] = c->h_res;
                 rd[i].maps = W.maps + i * nm * 9;
@@ -2141,6 +2192,11 @@ extern "C" pp_status pp_evaluate_thetas(pp_circuit *c, int64_t count, const doub
                 rd[i].coef_out = nullptr;
                 rd[i].pres_out = nullptr;
                 rd[i].counters = nullptr;
+                if (xb) {
+                    unsigned char *x = W.xbuf + (size_t)(i % kSweepChunk) * (xb + 256);
+                    rd[i].xbuf = x;
+                    rd[i].ticket = (unsigned *)(x + xb);
+                }
             }
             W.res_off = append(rd.data(), rd.size() * sizeof(rd[0]));
         } else {
@@ -2175,8 +2231,9 @@ extern "C" pp_status pp_evaluate_thetas(pp_circuit *c, int64_t count, const doub
     }
     if (P.resident) {
         ProfScope ps(PC_RES, s);
-        HIPCHK(pp::launch_resident((const pp::ResidentDesc *)(base + W.res_off), (int)count, c->n, c->dbytes, false,
-                                   s));
+        for (int64_t i = 0; i < count; i += kSweepChunk)
+            HIPCHK(pp::launch_chain((const pp::ResidentDesc *)(base + W.res_off) + i,
+                                    (int)std::min(count - i, kSweepChunk), c->n, c->dbytes, true, nullptr, s));
         return PP_OK;
     }
     {
@@ -2358,7 +2415,7 @@ pp_status enqueue_gradient_body(pp_circuit *c, hipStream_t s, double *d_expval, 
     for (size_t sg = S; sg-- > 0;) {
         if (P.heis.resident) {
             ProfScope ps(PC_RES, s);
-            HIPCHK(pp::launch_resident(G.hres + sg, 1, n, 8, false, s));
+            HIPCHK(pp::launch_chain(G.hres + sg, 1, n, 8, false, nullptr, s));
         } else {
             if (sg + 1 == S) {
                 ProfScope ps(PC_INIT, s);
@@ -2685,7 +2742,7 @@ pp_status launch_resident_batch(pp_server *S, bool *launched) {
     while (i < P.size()) {
         size_t j = i;
         while (j < P.size() && P[j]->c->n == P[i]->c->n && P[j]->c->dbytes == P[i]->c->dbytes) ++j;
-        HIPCHK(pp::launch_resident(dres + i, (int)(j - i), P[i]->c->n, P[i]->c->dbytes, false, Ln->st));
+        HIPCHK(pp::launch_chain(dres + i, (int)(j - i), P[i]->c->n, P[i]->c->dbytes, true, nullptr, Ln->st));
         S->resident_launches++;
         i = j;
     }
@@ -3071,7 +3128,7 @@ extern "C" pp_status pp_tune_set(pp_tune_key key, int32_t index, int32_t value) 
     if (key == PP_TUNE_RESIDENT_BLOCK) {
         if (index < 5 || index > 7 || (value != 256 && value != 512 && value != 1024))
             return fail(PP_ERR_INVALID, "resident block: n in 5..7, value 256/512/1024");
-        pp::set_resident_block(index, value);
+        g_resident_block[index] = value;
         return PP_OK;
     }
     if (key == PP_TUNE_SORT_SHAPE) {
@@ -3094,7 +3151,7 @@ extern "C" pp_status pp_tune_get(pp_tune_key key, int32_t index, int32_t *value)
         return PP_OK;
     }
     if (key == PP_TUNE_RESIDENT_BLOCK && index >= 5 && index <= 7) {
-        *value = pp::resident_block(index);
+        *value = g_resident_block[index];
         return PP_OK;
     }
     if (key == PP_TUNE_SORT_SHAPE && index >= 0 && index < pp::kSortClasses) {

@@ -23,55 +23,15 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "lds_tile.h"
 #include "pp_device.h"
 
 namespace pp {
-
-// Bank swizzle for 8-byte LDS words.  The LDS has 64 four-byte banks and
-// serves a 64-bit read or write per half-wave, so a half-wave is free of
-// conflicts when its 32 slot indices are distinct modulo 32.  With h the
-// index bits from bit 5 up, the swizzle XORs bits 0-4 with h << 3, h and
-// h >> 2: it is linear over GF(2) and keeps every 32-slot block's set of
-// high bits.  With the lane order group_sweep picks per digit pair, every
-// digit pair of 5-, 6- and 7-digit tiles is swept without conflicts, and in
-// 6-digit tiles so is every pair of digits 0-4 with the lanes drawn from the
-// three other digits below 5 alone.
-__host__ __device__ constexpr int sw(int i) {
-    const int h = i >> 5;
-    return i ^ (((h << 3) ^ h ^ (h >> 2)) & 31);
-}
-
-// sw(base ^ off) = sw(base) ^ sw(off): slot offsets of an op's letters are
-// the same for every lane, so each address costs one XOR with a uniform.
-
-// Workgroup barrier for LDS data: the fences are scoped to LDS, so global
-// loads still in flight (a prefetched next tile) are not waited for, which a
-// full __syncthreads() would do.  Every barrier in this file orders LDS
-// accesses only (threads never exchange data through global memory).
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 template <typename T>
 __device__ __forceinline__ double lds_ld(const T *p, int i) { return (double)p[sw(i)]; }
 template <typename T>
 __device__ __forceinline__ void lds_st(T *p, int i, double v) { p[sw(i)] = (T)v; }
-
-__device__ __forceinline__ long long morton_slot(uint64_t x, uint64_t z, int n) {
-    long long s = 0;
-    for (int q = 0; q < n; ++q)
-        s |= (long long)(((x >> q) & 1ull) | (((z >> q) & 1ull) << 1)) << (2 * q);
-    return s;
-}
-
-// slot of the j-th string made of I and Z only (z word = j)
-__device__ __forceinline__ long long zonly_slot(long long j, int n) {
-    long long s = 0;
-    for (int q = 0; q < n; ++q) s |= ((j >> q) & 1ll) << (2 * q + 1);
-    return s;
-}
 
 // Global slot offset of the local tile index i: local digit j goes to the
 // digit of global qubit (qubits >> 8j) & 0xff.  Digits [j0, k) only.
@@ -81,38 +41,6 @@ __device__ __forceinline__ long long deposit_digits(int i, uint64_t qubits, int 
     for (int j = 0; j < 8; ++j)
         if (j >= j0 && j < k) g |= (long long)((i >> (2 * j)) & 3) << (2 * (int)((qubits >> (8 * j)) & 0xff));
     return g;
-}
-
-template <int BLOCK>
-__device__ double block_sum_d(double v, double *red) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    const int w = threadIdx.x >> 6;
-    lds_barrier();
-    if ((threadIdx.x & 63) == 0) red[w] = v;
-    lds_barrier();
-    double tot = 0.0;
-    for (int i = 0; i < BLOCK / 64; ++i) tot += red[i];
-    return tot;
-}
-
-template <int BLOCK>
-__device__ long long block_sum_i(long long v, long long *red) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    const int w = threadIdx.x >> 6;
-    lds_barrier();
-    if ((threadIdx.x & 63) == 0) red[w] = v;
-    lds_barrier();
-    long long tot = 0;
-    for (int i = 0; i < BLOCK / 64; ++i) tot += red[i];
-    return tot;
-}
-
-// One row of a U1 map, m0 cx + m1 cy + m2 cz, with its rounding points fixed:
-// a product, then two fused multiply-adds.  Every kernel applies maps through
-// it, so all of them round alike whatever the surrounding code would let the
-// compiler contract (a negation folded in from a CX, say).
-__device__ __forceinline__ double map_row(double m0, double m1, double m2, double cx, double cy, double cz) {
-    return __builtin_fma(m2, cz, __builtin_fma(m1, cy, m0 * cx));
 }
 
 // ----------------------------------------------------------------- U1 op
@@ -275,69 +203,6 @@ __device__ __forceinline__ void cx_apply(T *lc, uint8_t *lp, int a, int b, int t
     }
 }
 
-// The six signed swaps of CX as (control digit, target digit) pairs, derived
-// at compile time from the rule above; in the paper's letters they are
-// (I,Z)<->(Z,Z), (I,Y)<->(Z,Y), (X,I)<->(X,X), (X,Z)<->-(Y,Y), (X,Y)<->(Y,Z),
-// (Y,I)<->(Y,X) (digit values I=0 X=1 Z=2 Y=3).
-struct CxPairC { int dc1, dt1, dc2, dt2, neg; };
-constexpr CxPairC cx_pair_c(int p) {
-    int found = 0;
-    for (int dc = 0; dc < 4; ++dc)
-        for (int dt = 0; dt < 4; ++dt) {
-            const int xc = dc & 1, zc = dc >> 1, xt = dt & 1, zt = dt >> 1;
-            const int dc2 = xc | ((zc ^ zt) << 1), dt2 = (xt ^ xc) | (zt << 1);
-            if (dc2 * 4 + dt2 > dc * 4 + dt) {
-                if (found == p) return CxPairC{dc, dt, dc2, dt2, xc & zt & ((xt ^ zc) ^ 1)};
-                ++found;
-            }
-        }
-    return CxPairC{0, 0, 0, 0, 0};
-}
-static_assert(cx_pair_c(3).dc1 == 1 && cx_pair_c(3).dt1 == 2 && cx_pair_c(3).dc2 == 3 && cx_pair_c(3).dt2 == 3 &&
-                  cx_pair_c(3).neg == 1,
-              "XZ <-> -YY");
-
-template <bool CTRL_LO, int P>
-__device__ __forceinline__ void cx_swap(double *v) {
-    constexpr CxPairC pr = cx_pair_c(P);
-    constexpr int e1 = CTRL_LO ? pr.dc1 + 4 * pr.dt1 : pr.dt1 + 4 * pr.dc1;
-    constexpr int e2 = CTRL_LO ? pr.dc2 + 4 * pr.dt2 : pr.dt2 + 4 * pr.dc2;
-    const double t1 = v[e1], t2 = v[e2];
-    v[e1] = pr.neg ? -t2 : t2;
-    v[e2] = pr.neg ? -t1 : t1;
-}
-
-// CX on a 16-register block v[dlo + 4 * dhi] of two digits; CTRL_LO: the
-// control is the lower digit of the pair.
-template <bool CTRL_LO>
-__device__ __forceinline__ void cx_regs(double *v) {
-    cx_swap<CTRL_LO, 0>(v);
-    cx_swap<CTRL_LO, 1>(v);
-    cx_swap<CTRL_LO, 2>(v);
-    cx_swap<CTRL_LO, 3>(v);
-    cx_swap<CTRL_LO, 4>(v);
-    cx_swap<CTRL_LO, 5>(v);
-}
-
-template <bool LO, int Q>
-__device__ __forceinline__ void u1_quad(double *v, const double (&m)[9]) {
-    constexpr int iX = LO ? 1 + 4 * Q : Q + 4, iZ = LO ? 2 + 4 * Q : Q + 8, iY = LO ? 3 + 4 * Q : Q + 12;
-    const double cx = v[iX], cy = v[iY], cz = v[iZ];
-    v[iX] = map_row(m[0], m[1], m[2], cx, cy, cz);
-    v[iY] = map_row(m[3], m[4], m[5], cx, cy, cz);
-    v[iZ] = map_row(m[6], m[7], m[8], cx, cy, cz);
-}
-
-// U1 (3x3 map M over X, Y, Z) on one digit of a 16-register block; LO: the
-// lower digit of the pair.
-template <bool LO>
-__device__ __forceinline__ void u1_regs_m(double *v, const double (&m)[9]) {
-    u1_quad<LO, 0>(v, m);
-    u1_quad<LO, 1>(v, m);
-    u1_quad<LO, 2>(v, m);
-    u1_quad<LO, 3>(v, m);
-}
-
 // Ops and their maps are staged through LDS in chunks: one cooperative load
 // per chunk instead of a dependent global load per op.
 constexpr int OPCH = 32;
@@ -371,72 +236,6 @@ __device__ __forceinline__ void stage_ops(OpCacheN<CH> *oc, const DOp *ops, cons
             for (int k = 0; k < 9; ++k) oc->maps[j][k] = src[k];
         }
     }
-}
-
-// Lane order of a group sweep on digits (A, B) of a 4^K-slot tile: thread u
-// owns the 16-slot block whose other digits are u's bits deposited at
-// pos[0..2(K-2)).  The first five positions are the first five free index
-// bits (in lexicographic order of their positions) whose images under sw
-// are independent modulo 32, so the 32 lanes of a half-wave hit 32
-// distinct bank pairs; the other free bits follow in ascending order.  In a
-// 6-digit tile a pair of digits below 5 draws the lanes from the other
-// digits below 5 only, so u's bits 6 and 7 (the wave of a 256-thread sweep)
-// are digit 5: each wave then reads and writes only the quarter of the tile
-// whose digit 5 is its index.
-struct LaneOrder {
-    int pos[14];
-    bool conflict_free;  // the first five positions were found
-};
-constexpr int gf2_rank(int *v, int n) {
-    int r = 0;
-    for (int bit = 0; bit < 5; ++bit) {
-        int piv = -1;
-        for (int i = r; i < n; ++i)
-            if ((v[i] >> bit) & 1) {
-                piv = i;
-                break;
-            }
-        if (piv < 0) continue;
-        const int t = v[r];
-        v[r] = v[piv];
-        v[piv] = t;
-        for (int i = 0; i < n; ++i)
-            if (i != r && ((v[i] >> bit) & 1)) v[i] ^= v[r];
-        ++r;
-    }
-    return r;
-}
-template <int K, int A, int B>
-constexpr LaneOrder lane_order() {
-    int fr[14] = {0};
-    int nf = 0;
-    for (int d = 0; d < K; ++d)
-        if (d != A && d != B) {
-            fr[nf++] = 2 * d;
-            fr[nf++] = 2 * d + 1;
-        }
-    LaneOrder o{};
-    for (int j = 0; j < nf; ++j) o.pos[j] = fr[j];
-    if (nf < 5) return o;
-    // digit 5's two bits come last in fr when the pair avoids it
-    const int ns = (K == 6 && B < 5) ? nf - 2 : nf;
-    for (int i0 = 0; i0 < ns; ++i0)
-        for (int i1 = i0 + 1; i1 < ns; ++i1)
-            for (int i2 = i1 + 1; i2 < ns; ++i2)
-                for (int i3 = i2 + 1; i3 < ns; ++i3)
-                    for (int i4 = i3 + 1; i4 < ns; ++i4) {
-                        const int idx[5] = {i0, i1, i2, i3, i4};
-                        int c[5] = {0};
-                        for (int k = 0; k < 5; ++k) c[k] = sw(1 << fr[idx[k]]) & 31;
-                        if (gf2_rank(c, 5) < 5) continue;
-                        int j = 0;
-                        for (int k = 0; k < 5; ++k) o.pos[j++] = fr[idx[k]];
-                        for (int f = 0; f < nf; ++f)
-                            if (f != i0 && f != i1 && f != i2 && f != i3 && f != i4) o.pos[j++] = fr[f];
-                        o.conflict_free = true;
-                        return o;
-                    }
-    return o;
 }
 
 // A 3x3 map into SGPRs by scalar loads (the map array is read-only).
@@ -612,15 +411,6 @@ __device__ __forceinline__ void group_apply(T *lc, int a, int b, const DOp *ops,
 // Applies ops [o0, o1) to an LDS tile of 4^K slots.  For tracked runs it
 // accumulates term updates: every op adds ngates * (strings in the tile
 // before it), and U1 ops that can create strings update that count.
-// A 64-bit value made wave-uniform.  readfirstlane returns a signed int:
-// each half is widened through uint32_t, or a low half with bit 31 set
-// would fill the high half with ones.
-__device__ __forceinline__ uint64_t uniform_u64(uint64_t x) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
-    return (uint64_t)lo | ((uint64_t)hi << 32);
-}
-
 // Untracked 256-thread sweeps of a 6-digit tile: an op on digits below 5
 // reads and writes only the quarter of the tile that belongs to the
 // sweeping thread's wave (digit 5 = wave index, see lane_order), so between
@@ -631,12 +421,6 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t x) {
 // the compiler from moving the next op's accesses above this op's.
 template <int K, int BLOCK, bool TRACK>
 constexpr bool kWaveSplit = K == 6 && BLOCK == 256 && !TRACK;
-
-__device__ __forceinline__ void wave_lds_order() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-}
 
 template <typename T, bool TRACK, int K, int BLOCK, int CH = OPCH>
 __device__ __forceinline__ void run_ops(T *lc, uint8_t *lp, const DOp *__restrict__ ops, const double *__restrict__ maps, int o0,
@@ -679,7 +463,7 @@ __device__ __forceinline__ void run_ops(T *lc, uint8_t *lp, const DOp *__restric
             }
             if (kind == DOP_GROUP) {
                 if (i + 1 + ngates > cn) break;  // reload the chunk from this header
-                if constexpr (K >= 2)
+                if constexpr (K >= 2 && !TRACK)  // tracked schedules hold no GROUP
                     group_apply<T, K, BLOCK>(lc, a, b, oc->ops, i + 1, ngates, tid, gops, gmaps, (int)perm, w2, w3);
                 i += 1 + ngates;
             } else if (!TRACK && K >= 2 && K <= 7) {
@@ -687,7 +471,7 @@ __device__ __forceinline__ void run_ops(T *lc, uint8_t *lp, const DOp *__restric
                 // digit pair (a U1 borrows a neighbouring digit), which keeps
                 // the conflict-free lane order of the pair
                 const int other = kind == DOP_U1 ? (a == 0 ? 1 : a - 1) : b;
-                if constexpr (K >= 2)
+                if constexpr (K >= 2 && !TRACK)
                     group_apply<T, K, BLOCK>(lc, a < other ? a : other, a < other ? other : a, oc->ops, i, 1, tid, gops,
                                              gmaps, 0);
                 ++i;
@@ -711,11 +495,11 @@ __device__ __forceinline__ void run_ops(T *lc, uint8_t *lp, const DOp *__restric
 }
 
 // ------------------------------------------------------- resident kernel
-// One workgroup runs one whole circuit (n <= 7) in LDS: builds the
-// observable, applies every op, reads out <O> and optionally stores the
-// final weights / presence for pp_get_terms.
-template <typename T, bool TRACK, int N, int BLOCK>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((N >= 7 && BLOCK <= 256) ? 2 : (BLOCK >= 1024 ? 4 : (BLOCK >= 512 ? 2 : 4))))) void resident_kernel(const ResidentDesc *__restrict__ descs) {
+// One workgroup runs one whole tracked circuit (n <= 7) in LDS: builds the
+// observable, applies every op with its presence bytes, reads out <O> and
+// stores the final weights and presence for pp_get_terms.
+template <typename T, int N, int BLOCK>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(BLOCK >= 512 ? 2 : 4))) void resident_kernel(const ResidentDesc *__restrict__ descs) {
     extern __shared__ __align__(256) unsigned char smem[];
     __shared__ double redd[BLOCK / 64];
     __shared__ long long redi[BLOCK / 64];
@@ -729,7 +513,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((N >= 7 &
 
     for (int i = tid; i < size; i += BLOCK) {
         lc[i] = (T)0;
-        if (TRACK) lp[i] = 0;
+        lp[i] = 0;
     }
     lds_barrier();
     if (d.coef_in) {
@@ -740,25 +524,25 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((N >= 7 &
         for (int t = tid; t < d.nterms; t += d.distinct ? BLOCK : 1) {
             const int s = (int)morton_slot(d.obs_x[t], d.obs_z[t], n);
             lc[sw(s)] = (T)((double)lc[sw(s)] + d.obs_c[t]);
-            if (TRACK) lp[sw(s)] = 1;
+            lp[sw(s)] = 1;
         }
     }
     lds_barrier();
 
     long long tcount = 0, updates = 0;
-    if (TRACK) {
+    {
         long long mine = 0;
         for (int i = tid; i < size; i += BLOCK) mine += lp[i];
         tcount = block_sum_i<BLOCK>(mine, redi);
     }
-    run_ops<T, TRACK, N, BLOCK>(lc, lp, d.ops, d.maps, 0, d.nops, tcount, updates, redi, &oc);
+    run_ops<T, true, N, BLOCK>(lc, lp, d.ops, d.maps, 0, d.nops, tcount, updates, redi, &oc);
 
     double part = 0.0;
     for (int j = tid; j < (1 << n); j += BLOCK) part += lds_ld(lc, (int)zonly_slot(j, n));
     const double total = block_sum_d<BLOCK>(part, redd);
     if (tid == 0) {
         *d.expval_out = total;
-        if (TRACK && d.counters) {
+        if (d.counters) {
             d.counters[0] = (unsigned long long)updates;
             d.counters[1] = (unsigned long long)tcount;
         }
@@ -767,7 +551,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((N >= 7 &
         T *out = reinterpret_cast<T *>(d.coef_out);
         for (int i = tid; i < size; i += BLOCK) out[i] = lc[sw(i)];
     }
-    if (TRACK && d.pres_out) {
+    if (d.pres_out) {
         for (int i = tid; i < size; i += BLOCK) d.pres_out[i] = lp[sw(i)];
     }
 }
@@ -1682,8 +1466,8 @@ __device__ __forceinline__ void mat3_mul(const double A[9], const double B[9], d
         for (int b = 0; b < 3; ++b) C[3 * a + b] = A[3 * a] * B[b] + A[3 * a + 1] * B[3 + b] + A[3 * a + 2] * B[6 + b];
 }
 
-// A descriptor with reserved = 1 composes forward maps (P -> g P g^dag): the
-// transpose of each gate's Heisenberg matrix, since the maps are orthogonal.
+// Forward maps (P -> g P g^dag, from fwd_from on) are products of the
+// transposes of the gates' Heisenberg matrices, since the maps are orthogonal.
 __device__ __forceinline__ void gate_matrix_dir(int op, double th, bool fwd, double G[9]) {
     gate_matrix(op, th, G);
     if (fwd) {
@@ -1696,7 +1480,6 @@ __device__ __forceinline__ void gate_matrix_dir(int op, double th, bool fwd, dou
 
 __global__ __launch_bounds__(256) void compose_kernel(const ComposeDesc *__restrict__ descs) {
     const ComposeDesc &d = descs[blockIdx.x];
-    const bool fwd = d.reserved == 1;
     const int lane = threadIdx.x & 63;
     const int wpb = blockDim.x >> 6;
     const int W = gridDim.y * wpb;
@@ -1711,7 +1494,7 @@ __global__ __launch_bounds__(256) void compose_kernel(const ComposeDesc *__restr
                 for (int r = r0; r < r1; ++r) {
                     const int op = d.rop[r];
                     double G[9], P[9];
-                    gate_matrix_dir(op, op >= 3 ? d.theta[d.rparam[r]] : 0.0, fwd, G);
+                    gate_matrix_dir(op, op >= 3 ? d.theta[d.rparam[r]] : 0.0, i >= d.fwd_from, G);
                     mat3_mul(G, M, P);
                     for (int t = 0; t < 9; ++t) M[t] = P[t];
                 }
@@ -1730,7 +1513,7 @@ __global__ __launch_bounds__(256) void compose_kernel(const ComposeDesc *__restr
                 const int r = c0 + lane;
                 if (r < r1) {
                     const int op = d.rop[r];
-                    gate_matrix_dir(op, op >= 3 ? d.theta[d.rparam[r]] : 0.0, fwd, G);
+                    gate_matrix_dir(op, op >= 3 ? d.theta[d.rparam[r]] : 0.0, m >= d.fwd_from, G);
                 }
                 // lane l holds the product of gates [c0 + l, c0 + l + w) after
                 // the step of width w; combine with the next block on the left
@@ -1941,9 +1724,9 @@ hipError_t launch_compose(const ComposeDesc *d_descs, int ndescs, hipStream_t s,
     return hipGetLastError();
 }
 
-template <typename T, bool TRACK, int N, int BLOCK>
+template <typename T, int N, int BLOCK>
 static hipError_t launch_res_t(const ResidentDesc *d, int nd, size_t lds, hipStream_t s) {
-    auto fn = resident_kernel<T, TRACK, N, BLOCK>;
+    auto fn = resident_kernel<T, N, BLOCK>;
     static bool attr = false;
     if (!attr) {
         hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1955,45 +1738,25 @@ static hipError_t launch_res_t(const ResidentDesc *d, int nd, size_t lds, hipStr
     return hipGetLastError();
 }
 
-static int g_res_block[8] = {64, 64, 64, 64, 64, 512, 512, 1024};
-void set_resident_block(int n, int block) {
-    if (n >= 5 && n <= 7) g_res_block[n] = block;
-}
-int resident_block(int n) { return (n >= 1 && n <= 7) ? g_res_block[n] : 64; }
-
-template <typename T, bool TRACK>
-static hipError_t launch_res_b(const ResidentDesc *d, int nd, int n, size_t lds, hipStream_t s) {
-    const int blk = TRACK ? (n <= 4 ? 64 : n <= 6 ? 256 : 512) : g_res_block[n];
+template <typename T>
+static hipError_t launch_res_n(const ResidentDesc *d, int nd, int n, size_t lds, hipStream_t s) {
     switch (n) {
-    case 1: return launch_res_t<T, TRACK, 1, 64>(d, nd, lds, s);
-    case 2: return launch_res_t<T, TRACK, 2, 64>(d, nd, lds, s);
-    case 3: return launch_res_t<T, TRACK, 3, 64>(d, nd, lds, s);
-    case 4: return launch_res_t<T, TRACK, 4, 64>(d, nd, lds, s);
-    case 5:
-        if (!TRACK && blk == 512) return launch_res_t<T, TRACK, 5, 512>(d, nd, lds, s);
-        if (!TRACK && blk == 1024) return launch_res_t<T, TRACK, 5, 1024>(d, nd, lds, s);
-        return launch_res_t<T, TRACK, 5, 256>(d, nd, lds, s);
-    case 6:
-        if (!TRACK && blk == 512) return launch_res_t<T, TRACK, 6, 512>(d, nd, lds, s);
-        if (!TRACK && blk == 1024) return launch_res_t<T, TRACK, 6, 1024>(d, nd, lds, s);
-        return launch_res_t<T, TRACK, 6, 256>(d, nd, lds, s);
-    default:
-        if (!TRACK && blk == 256) return launch_res_t<T, TRACK, 7, 256>(d, nd, lds, s);
-        if (!TRACK && blk == 1024) return launch_res_t<T, TRACK, 7, 1024>(d, nd, lds, s);
-        return launch_res_t<T, TRACK, 7, 512>(d, nd, lds, s);
+    case 1: return launch_res_t<T, 1, 64>(d, nd, lds, s);
+    case 2: return launch_res_t<T, 2, 64>(d, nd, lds, s);
+    case 3: return launch_res_t<T, 3, 64>(d, nd, lds, s);
+    case 4: return launch_res_t<T, 4, 64>(d, nd, lds, s);
+    case 5: return launch_res_t<T, 5, 256>(d, nd, lds, s);
+    case 6: return launch_res_t<T, 6, 256>(d, nd, lds, s);
+    default: return launch_res_t<T, 7, 512>(d, nd, lds, s);
     }
 }
 
-hipError_t launch_resident(const ResidentDesc *d_descs, int ndescs, int n, int dtype_bytes, bool track,
-                           hipStream_t s) {
+hipError_t launch_resident_tracked(const ResidentDesc *d_descs, int ndescs, int n, int dtype_bytes, hipStream_t s) {
     if (ndescs <= 0) return hipSuccess;
     if (n < 1 || n > 7) return hipErrorInvalidValue;
-    const size_t lds = resident_lds_bytes(n, dtype_bytes, track);
-    if (dtype_bytes == 8)
-        return track ? launch_res_b<double, true>(d_descs, ndescs, n, lds, s)
-                     : launch_res_b<double, false>(d_descs, ndescs, n, lds, s);
-    return track ? launch_res_b<float, true>(d_descs, ndescs, n, lds, s)
-                 : launch_res_b<float, false>(d_descs, ndescs, n, lds, s);
+    const size_t lds = resident_lds_bytes(n, dtype_bytes, true);
+    return dtype_bytes == 8 ? launch_res_n<double>(d_descs, ndescs, n, lds, s)
+                            : launch_res_n<float>(d_descs, ndescs, n, lds, s);
 }
 
 // defaults measured on MI355X: one wave per 4^5-slot tile; persistent

@@ -20,6 +20,8 @@
 
 #include <algorithm>
 
+#include "lds_tile.h"
+
 namespace pp {
 
 // Heisenberg maps on the (X, Y, Z) weights, rows = output letter.
@@ -730,6 +732,129 @@ void plan_append(DensePlan &all, const DensePlan &part) {
     all.resident = part.resident;
 }
 
+void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin) {
+    std::vector<int> order;  // new map index -> old
+    std::vector<uint32_t> renum((size_t)P.nmaps(), 0);
+    // maps are numbered pair member by pair member, the lower digit first
+    auto take = [&](uint32_t old) {
+        renum[old] = (uint32_t)order.size();
+        order.push_back((int)old);
+    };
+    for (const DensePass &ps : P.passes) {
+        if (begin) begin->push_back((int)P.chain.size());
+        for (int i = ps.op_begin; i < ps.op_end;) {
+            const DOp &h = P.ops[(size_t)i];
+            int lo, hi, first = i, count = 1;
+            if (h.kind == DOP_GROUP) {
+                lo = h.a;
+                hi = h.b;
+                first = i + 1;
+                count = h.ngates;
+            } else {
+                const int other = h.kind == DOP_CX ? h.b : (h.a == 0 ? 1 : h.a - 1);
+                lo = std::min<int>(h.a, other);
+                hi = std::max<int>(h.a, other);
+            }
+            i = first + count;
+            // a record holds a CX and one map per digit behind it; longer
+            // groups become several records (one in twelve on random circuits)
+            unsigned cx = 0;
+            int64_t mlo = -1, mhi = -1;
+            auto flush = [&] {
+                ChainOp r{};
+                r.word = (uint32_t)(hi * (hi - 1) / 2 + lo) |
+                         (((unsigned)(mlo >= 0) + 2 * (unsigned)(mhi >= 0)) << kChainKindShift);
+                r.map = (uint32_t)order.size();
+                if (mlo >= 0) take((uint32_t)mlo);
+                if (mhi >= 0) take((uint32_t)mhi);
+                // bits of e: x, z of the lower digit, x, z of the higher; CX
+                // conjugation is (x_c, z_c ^ z_t, x_t ^ x_c, z_t), its own
+                // inverse, with the sign of (X, Z) <-> -(Y, Y)
+                for (int k = 0; k < 4; ++k)
+                    r.read[k] = r.write[k] = (uint32_t)sw((1 + k % 2) << (2 * (k < 2 ? lo : hi))) * (uint32_t)dbytes;
+                if (cx) {
+                    const int c = cx == 1 ? 0 : 2, t = 2 - c;
+                    r.read[c] ^= r.write[t];
+                    r.read[t + 1] ^= r.write[c + 1];
+                    r.word |= (kChainFlip6 >> 2) | (kChainFlip6 >> (cx == 1 ? 1 : 0));
+                }
+                P.chain.push_back(r);
+                cx = 0;
+                mlo = mhi = -1;
+            };
+            for (int j = first; j < first + count; ++j) {
+                const DOp &m = P.ops[(size_t)j];
+                if (m.kind == DOP_CX) {
+                    if (cx || mlo >= 0 || mhi >= 0) flush();
+                    cx = m.a == lo ? 1u : 2u;
+                } else {
+                    int64_t &slot = m.a == lo ? mlo : mhi;
+                    if (slot >= 0) flush();
+                    slot = m.map;
+                }
+            }
+            flush();
+        }
+    }
+    // six qubits: a wave's sweep of a pair below digit 5 stays in the quarter
+    // of the tile whose digit 5 is the wave's index (lane_order)
+    if (P.resident && P.k == 6)
+        for (size_t i = 0; i + 1 < P.chain.size(); ++i)
+            if ((P.chain[i].word & 0xffu) < 10u && (P.chain[i + 1].word & 0xffu) < 10u)
+                P.chain[i].word |= 1u << kChainNoBarrierBit;
+    if (begin) begin->push_back((int)P.chain.size());
+    P.nchain = (int)P.chain.size();
+    // the recipes in the new order, and the ops' indices
+    std::vector<int32_t> roff{0}, rparam;
+    std::vector<uint8_t> rop;
+    roff.reserve(P.roff.size());
+    rop.reserve(P.rop.size());
+    rparam.reserve(P.rparam.size());
+    for (int old : order) {
+        rop.insert(rop.end(), P.rop.begin() + P.roff[(size_t)old], P.rop.begin() + P.roff[(size_t)old + 1]);
+        rparam.insert(rparam.end(), P.rparam.begin() + P.roff[(size_t)old], P.rparam.begin() + P.roff[(size_t)old + 1]);
+        roff.push_back((int32_t)rop.size());
+    }
+    P.roff = std::move(roff);
+    P.rop = std::move(rop);
+    P.rparam = std::move(rparam);
+    for (DOp &d : P.ops) {
+        if (d.kind == DOP_U1) d.map = renum[d.map];
+        if (d.kind == DOP_GROUP && (d.perm & ~kSkipBarrier)) {
+            d.map = renum[d.map];
+            d.reserved = renum[d.reserved];
+        }
+    }
+}
+
+DensePlan plan_meet(const GateList &g, int low, int64_t g_end, int dbytes) {
+    int64_t ncx = 0;
+    for (int64_t i = 0; i < g_end; ++i) ncx += g.op[(size_t)i] == 2;
+    int64_t s = ncx ? 0 : g_end / 2;
+    for (int64_t seen = 0; ncx && seen < ncx / 2; ++s) seen += g.op[(size_t)s] == 2;
+    PlanOptions o;
+    o.g_begin = s;
+    o.g_end = g_end;
+    DensePlan P = plan_dense_opts(g, g.n, low, o);
+    build_chain(P, dbytes);
+    PlanOptions f;
+    f.g_end = s;
+    f.forward = true;
+    DensePlan F = plan_dense_opts(g, g.n, low, f);
+    build_chain(F, dbytes);
+    const int base = P.nmaps();
+    plan_append(P, F);  // the ops too, for the self-check and the statistics
+    for (ChainOp r : F.chain) {
+        r.map += (uint32_t)base;
+        P.chain.push_back(r);
+    }
+    P.fwd_from = base;
+    P.passes.front().op_end = P.passes.back().op_end;
+    P.passes.front().ngates += P.passes.back().ngates;
+    P.passes.resize(1);
+    return P;
+}
+
 GradPlan plan_gradient(const GateList &g, int k_heis, int k_fwd, int low, int64_t every) {
     GradPlan G;
     const int64_t m = g.m;
@@ -768,6 +893,7 @@ GradPlan plan_gradient(const GateList &g, int k_heis, int k_fwd, int low, int64_
     }
     G.heis_pass_begin.push_back((int)G.heis.passes.size());
     G.fwd_pass_begin.push_back((int)G.fwd.passes.size());
+    if (G.heis.resident) build_chain(G.heis, 8, &G.heis_chain_begin);
     return G;
 }
 

@@ -35,6 +35,11 @@ struct DensePlan {
     std::vector<uint8_t> rop;
     std::vector<int32_t> rparam;
     std::vector<DensePass> passes;
+    // untracked resident plans: the same ops as chain records (their maps are
+    // numbered in record order); nchain of them, then the forward half's
+    std::vector<ChainOp> chain;
+    int nchain = 0;
+    int fwd_from = -1;  // first map of the forward half (-1: none)
     int nmaps() const { return (int)roff.size() - 1; }
 };
 
@@ -107,9 +112,18 @@ struct GradPlan {
     std::vector<int64_t> bounds;
     DensePlan heis, fwd;
     std::vector<int> heis_pass_begin, fwd_pass_begin;  // S + 1 entries each
+    std::vector<int> heis_chain_begin;                 // resident Heisenberg sweep: records per pass, as above
     std::vector<int32_t> slot_param;                  // slot -> parameter
     std::vector<int32_t> seg_slot_begin;              // S + 1 entries
 };
+// Renumbers the maps of grouped resident passes in op order and appends each
+// pass's records to P.chain; begin[p] (optional) receives the first record of
+// pass p, with the total behind the last.  dbytes: size of a weight.
+void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin = nullptr);
+// Untracked evaluation of a resident circuit from both ends: gates [s, g_end)
+// taken back from the observable, gates [0, s) forward from the state, with s
+// where half of the CX gates lie on either side (a record holds about one).
+DensePlan plan_meet(const GateList &g, int low, int64_t g_end, int dbytes);
 GradPlan plan_gradient(const GateList &g, int k_heis, int k_fwd, int low, int64_t every);
 SparsePlan plan_sparse(const GateList &g);
 

@@ -39,7 +39,31 @@ static_assert(sizeof(DOp) == 16, "DOp must stay 16 bytes");
 // sweeps skip the workgroup barrier between them.
 constexpr unsigned kSkipBarrier = 0x8000u;
 
-// A whole circuit run inside one workgroup's LDS (n <= 7).
+// One record of an LDS-resident chain: an optional CX, then an optional 3x3
+// map on each digit of one digit pair a < b.  word: pair index b (b - 1) / 2 +
+// a in bits 0-7; 1 for a map on the lower digit + 2 for one on the higher in
+// bits 8-9; kChainNoBarrierBit; the sign flips of the CX.  map: the first of
+// its maps (lower digit first); a chain's maps are stored in record order.
+// The 16 letters of a block, e = letter of a + 4 letter of b, are read at the
+// block's base XOR the words read[k] of e's set bits k and written at it XOR
+// write[k]: swizzled byte offsets, those of read being the letters' images
+// under the CX.
+struct ChainOp {
+    uint32_t word, map, reserved[2];
+    uint32_t read[4], write[4];
+};
+static_assert(sizeof(ChainOp) == 48, "records are read as three 16-byte words");
+constexpr unsigned kChainKindShift = 8;
+// no workgroup barrier behind it: it and the next record avoid digit 5 of a
+// six-qubit circuit, so each wave stays in its quarter of the tile
+constexpr unsigned kChainNoBarrierBit = 12;
+// letter pairs whose sign the CX flips: e = 6 in bit 31, e = 9 in bit 30, e =
+// 15 in bit 29
+constexpr unsigned kChainFlip6 = 0x80000000u;
+
+// A whole circuit run inside one workgroup's LDS (n <= 7).  Tracked runs read
+// ops; untracked ones the chain, whose first nchain records take the
+// observable back and whose next nchain_fwd take the state forward.
 struct ResidentDesc {
     const void *coef_in;       // start weights (4^n, slot order) or nullptr = the observable
     void *coef_out;            // final weights (4^n, slot order) or nullptr
@@ -54,6 +78,12 @@ struct ResidentDesc {
     int32_t n;
     int32_t nterms;
     int32_t distinct;  // 1: no string is repeated among the nterms
+    const ChainOp *chain;
+    int32_t nchain, nchain_fwd;
+    int32_t nmaps;
+    int32_t reserved;
+    void *xbuf;        // n >= 6: where the two directions exchange their vectors
+    unsigned *ticket;  // n >= 6: 0 between launches
 };
 
 // One pass of one circuit over its 4^(n-k) tiles of 4^k slots.
@@ -123,7 +153,7 @@ struct ComposeDesc {
     const double *theta;
     double *maps;
     int32_t nmaps;
-    int32_t reserved;  // 1: forward maps (each gate's Heisenberg matrix transposed)
+    int32_t fwd_from;  // maps from this one on are forward maps (each gate's Heisenberg matrix transposed)
 };
 
 // --------------------------------------------------------------- sparse ops
@@ -176,16 +206,20 @@ constexpr int kFrameMaxN = 31;  // 2n key bits below the empty marker
 // max_maps: the largest nmaps of the descriptors (sizes the grid; any value
 // gives the same maps)
 hipError_t launch_compose(const ComposeDesc *d_descs, int ndescs, hipStream_t s, int max_maps = 1);
-hipError_t launch_resident(const ResidentDesc *d_descs, int ndescs, int n, int dtype_bytes, bool track,
-                           hipStream_t s);
+hipError_t launch_resident_tracked(const ResidentDesc *d_descs, int ndescs, int n, int dtype_bytes, hipStream_t s);
+// Untracked LDS-resident circuits (resident.hip).  meet: run the two
+// directions and multiply (an evaluation); otherwise the observable's records
+// only, with coef_in / coef_out.  out: result of a single descriptor, or
+// nullptr for each descriptor's own expval_out.
+hipError_t launch_chain(const ResidentDesc *d_descs, int ndescs, int n, int dtype_bytes, bool meet, double *out,
+                        hipStream_t s);
+// bytes of ResidentDesc::xbuf (0: not used)
+size_t chain_exchange_bytes(int n, int dtype_bytes);
 hipError_t launch_tile_pass(const TilePassDesc *d_descs, const TileGroups &groups, int k, int dtype_bytes,
                             bool track, hipStream_t s);
 // 0: one workgroup per tile; 1: persistent prefetching workgroups (k <= 6)
 void set_tile_kernel_variant(int k, int variant);
 int tile_kernel_variant(int k);
-// threads per workgroup of the untracked LDS-resident kernel for n = 5..7
-void set_resident_block(int n, int block);
-int resident_block(int n);
 hipError_t launch_grad_pass(const GradPassDesc *d_desc, int ntiles, int k, hipStream_t s);
 hipError_t launch_grad_init_state(double *r, int n, hipStream_t s);
 hipError_t launch_grad_reduce(const double *partials, int nslots, int ntiles, double *rot_grad, hipStream_t s);
