@@ -234,7 +234,8 @@ PP_API pp_status pp_circuit_set_option(pp_circuit *c, pp_option key, int64_t val
  * evaluation as pp_evaluate for a DENSE circuit without term tracking, with
  * the same result bit for bit, but every working buffer (the 4^n weights,
  * the composed per-wire maps, the launch descriptors) in a static device
- * array of the library, 24 MiB per device, held until the process ends.
+ * array of the library (24 MiB for what follows, and the rest of its
+ * descriptors) per device, held until the process ends.
  * The call allocates nothing and copies nothing from the host: it enqueues
  * kernel launches on `stream` only.  It reads the circuit's schedule from the
  * device, so the circuit must have been evaluated once with pp_evaluate (or

@@ -199,8 +199,9 @@ __global__ void compact_to_sparse_count_kernel(const unsigned long long *total, 
 // held until the process ends).  In host code `scratch` names a host-side
 // stand-in, so its device address is resolved once per device with
 // hipGetSymbolAddress and only that address is passed to kernels.
-constexpr size_t kNoAllocBytes = (size_t)24 << 20;
-static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
+constexpr size_t kNoAllocBytes = (size_t)24 << 20;  // for 4^n weights, 72 bytes per map, 80 per pass
+constexpr size_t kScratchBytes = kNoAllocBytes + ((size_t)2 << 20);  // and the rest of each descriptor
+static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 constexpr int kScratchDevices = 64;
 unsigned char *g_scratch_dev[kScratchDevices] = {};
 std::mutex g_scratch_mu;
@@ -276,8 +277,12 @@ int g_resident_block[8] = {64, 64, 64, 64, 64, 512, 512, 1024};
 // FP64) are never needed at once
 constexpr int64_t kSweepChunk = 512;
 
-// defaults measured by the autotuner on MI355X (batched probes, FP64)
-int g_tile_qubits[17] = {0, 0, 0, 0, 0, 0, 0, 0, 6, 6, 6, 6, 6, 6, 6, 6, 6};
+// Tile qubits by n.  7-qubit tiles take about a third fewer passes, but a
+// workgroup of 1,024 threads per tile: they pay from the n whose 4^(n - 7)
+// tiles fill the 256 CUs (3,000 random gates, FP64, 6 against 7 qubits: n = 10
+// 1.12 against 1.27 ms, n = 11 1.76 against 1.56, n = 12 6.3 against 4.8, n =
+// 13 26.6 against 19.6; FP32 alike), up to the kernel's 14 qubits.
+int g_tile_qubits[17] = {0, 0, 0, 0, 0, 0, 0, 0, 6, 6, 6, 7, 7, 7, 7, 6, 6};
 int default_tile_qubits(int n) { return n >= 8 && n <= 16 ? g_tile_qubits[n] : (n > 16 ? 6 : 5); }
 
 // pinned staging for small asynchronous uploads, reused once the previous
@@ -455,6 +460,7 @@ struct pp_circuit {
     pp::TilePassDesc *d_pass = nullptr;
     pp::ResidentDesc *d_res = nullptr;
     pp::ChainOp *d_chain = nullptr;
+    std::vector<int> pass_recs;  // first record of each pass over 7-qubit tiles, with the total behind the last
     unsigned char *d_xbuf = nullptr;  // resident evaluation, n >= 6: where its two directions meet
     pp::ComposeDesc *d_comp = nullptr;
     pp::ResidentDesc h_res{};
@@ -762,6 +768,16 @@ bool wants_frame(const pp_circuit *c) {
            c->trunc_w >= c->n && c->fb.keys;
 }
 
+// Records [r0, r1) of P.chain for a pass over 7-qubit tiles.
+void set_chain(pp::TilePassDesc &d, const pp::DensePlan &P, const pp::DensePass &ps, const pp::ChainOp *d_chain, int r0,
+               int r1, int dbytes) {
+    d.chain = d_chain + r0;
+    d.nrec = r1 - r0;
+    d.nmaps = (uint32_t)P.nmaps();
+    pp::record_offsets(P.chain[(size_t)r0], ps, dbytes, false, d.in);
+    pp::record_offsets(P.chain[(size_t)r1 - 1], ps, dbytes, true, d.out);
+}
+
 pp_status ensure_plan(pp_circuit *c, bool weights = true) {
     pp_status r = ensure_state(c, weights);
     if (r != PP_OK) return r;
@@ -819,6 +835,8 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
             c->dplan = pp::plan_dense_opts(c->g, k, kLowQubits, o);
             if (k == c->n && !c->track) pp::build_chain(c->dplan, c->dbytes);
         }
+        c->pass_recs.clear();
+        if (k < c->n && k == pp::kChainTileDigits && !c->track) pp::build_chain(c->dplan, c->dbytes, &c->pass_recs);
         const pp::DensePlan &P = c->dplan;
         {
             // the kernels trust the schedule's digits and segment bounds
@@ -872,9 +890,16 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
             HIPCHK(hipMemcpy(c->d_res, &d, sizeof(d), hipMemcpyHostToDevice));
         } else {
             c->h_pass.clear();
+            std::vector<int> rec;
+            if (k == pp::kChainTileDigits && !c->track) {
+                if ((r = upload_vec(&c->d_chain, P.chain)) != PP_OK) return r;
+                rec = c->pass_recs;
+            }
             const int ntiles = (int)((int64_t)1 << (2 * (c->n - k)));
-            for (const pp::DensePass &ps : P.passes) {
+            for (size_t pi = 0; pi < P.passes.size(); ++pi) {
+                const pp::DensePass &ps = P.passes[pi];
                 pp::TilePassDesc d{};
+                if (!rec.empty()) set_chain(d, P, ps, c->d_chain, rec[pi], rec[pi + 1], c->dbytes);
                 d.coef = c->coef;
                 d.pres = c->track ? c->pres : nullptr;
                 d.ops = c->d_ops;
@@ -1471,8 +1496,10 @@ pp_status pp_evaluate_noalloc(pp_circuit *c, void *stream, double *d_expval) {
     // tiled: the 4^n weights; resident: the directions' exchange and ticket
     const size_t xbytes = P.resident ? up(pp::chain_exchange_bytes(c->n, c->dbytes)) : 0;
     const size_t coef_bytes = P.resident ? xbytes + 256 : (size_t)dense_slots(c->n) * c->dbytes;
-    if (off_coef + coef_bytes > kNoAllocBytes)
-        return fail(PP_ERR_CAPACITY, "pp_evaluate_noalloc: working set of " + std::to_string(off_coef + coef_bytes) +
+    const size_t counted = 512 + up(npass * 80) + up((size_t)72 * std::max(P.nmaps(), 1)) +
+                           (P.resident ? 0 : (size_t)dense_slots(c->n) * c->dbytes);
+    if (counted > kNoAllocBytes || off_coef + coef_bytes > kScratchBytes)
+        return fail(PP_ERR_CAPACITY, "pp_evaluate_noalloc: working set of " + std::to_string(counted) +
                                          " bytes exceeds the " + std::to_string(kNoAllocBytes) + "-byte array");
     hipStream_t s = (hipStream_t)stream;
     pp::ComposeDesc *comp = (pp::ComposeDesc *)(base + off_comp);
@@ -2064,6 +2091,7 @@ pp_status ensure_grad(pp_circuit *c, int64_t every) {
         }
         if ((r = upload_vec(&G.hres, rd)) != PP_OK) return r;
     } else {
+        if (k_heis == pp::kChainTileDigits && (r = upload_vec(&G.hchain, P.heis.chain)) != PP_OK) return r;
         std::vector<pp::TilePassDesc> td;
         for (const pp::DensePass &ps : P.heis.passes) {
             pp::TilePassDesc d{};
@@ -2077,6 +2105,8 @@ pp_status ensure_grad(pp_circuit *c, int64_t every) {
             d.ntiles = (int)((int64_t)1 << (2 * (n - k_heis)));
             for (int j = 0; j < k_heis; ++j) d.qubits |= (uint64_t)ps.qubit[j] << (8 * j);
             d.reg_entry = pp::pass_reg_entry(P.heis, ps);
+            if (k_heis == pp::kChainTileDigits)
+                set_chain(d, P.heis, ps, G.hchain, P.heis_chain_begin[td.size()], P.heis_chain_begin[td.size() + 1], 8);
             td.push_back(d);
         }
         if ((r = upload_vec(&G.hpass, td)) != PP_OK) return r;

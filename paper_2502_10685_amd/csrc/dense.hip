@@ -25,6 +25,7 @@
 
 #include "lds_tile.h"
 #include "pp_device.h"
+#include "tile_io.h"
 
 namespace pp {
 
@@ -236,13 +237,6 @@ __device__ __forceinline__ void stage_ops(OpCacheN<CH> *oc, const DOp *ops, cons
             for (int k = 0; k < 9; ++k) oc->maps[j][k] = src[k];
         }
     }
-}
-
-// A 3x3 map into SGPRs by scalar loads (the map array is read-only).
-typedef const __attribute__((address_space(4))) double *ConstMaps;
-__device__ __forceinline__ void load_map(double (&m)[9], ConstMaps src) {
-#pragma unroll
-    for (int q = 0; q < 9; ++q) m[q] = src[q];
 }
 
 // The eight common GROUP shapes (see the planner's group_shape): the CX,
@@ -625,41 +619,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((BLOCK ==
     if (TRACK && tid == 0 && updates) atomicAdd(d.counters, (unsigned long long)updates);
 }
 
-// Weights are read and written with buffer instructions: one resource per
-// tile (base = the tile's first slot), the lane's slot offset in a VGPR and
-// the register's in an SGPR, so the 64 accesses of a lane need no address
-// registers.  Both offsets are below 2^31 bytes when the tile's qubits are
-// all below 14 (the launcher only picks this kernel for n <= 14).  Every
-// weight is read once and written once per pass, so both carry the
-// non-temporal hint (nt): the streamed array then does not push the op
-// lists and maps, which every tile re-reads, out of L2.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(void *p) {
-    return __builtin_amdgcn_make_buffer_rsrc(p, (short)0, -1, 0x00020000);
-}
-// cache-policy operand of the buffer builtins: bit 1 is nt on gfx950
-constexpr int kNonTemporal = 2;
-template <typename T>
-struct BufIO;
-template <>
-struct BufIO<double> {
-    typedef unsigned V __attribute__((ext_vector_type(2)));
-    static __device__ __forceinline__ double ld(__amdgpu_buffer_rsrc_t r, unsigned vo, unsigned so) {
-        return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, vo, so, kNonTemporal));
-    }
-    static __device__ __forceinline__ void st(__amdgpu_buffer_rsrc_t r, unsigned vo, unsigned so, double v) {
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(V, v), r, vo, so, kNonTemporal);
-    }
-};
-template <>
-struct BufIO<float> {
-    static __device__ __forceinline__ float ld(__amdgpu_buffer_rsrc_t r, unsigned vo, unsigned so) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, vo, so, kNonTemporal));
-    }
-    static __device__ __forceinline__ void st(__amdgpu_buffer_rsrc_t r, unsigned vo, unsigned so, float v) {
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, vo, so, kNonTemporal);
-    }
-};
-
 // ------------------------------------------------- streaming tile kernel
 // Persistent form of tile_kernel for untracked runs: a co-resident grid
 // walks the launch's tiles with stride gridDim.x, and every workgroup issues
@@ -671,44 +630,24 @@ struct BufIO<float> {
 // up) is uniform, so the prefetch costs no address registers; the launcher
 // takes this kernel only for n <= 14, where both offsets fit 31 bits.
 struct TileLoc {
-    const TilePassDesc *d;
-    long long base;
+    TileBase at;
     unsigned voff;  // bytes
 };
 
 template <typename T, int K, int BLOCK>
 __device__ __forceinline__ TileLoc locate_tile(const TilePassDesc *__restrict__ descs, const TileGroups &grp, int b,
                                                int tid) {
-    int g = 0;
-    while (g + 1 < grp.ngroups && b >= grp.first_block[g + 1]) ++g;
-    const int rel = b - grp.first_block[g];
-    const TilePassDesc *d = descs + grp.first_desc[g] + (rel >> grp.shift[g]);
-    const long long tile = rel & ((1 << grp.shift[g]) - 1);
-    const uint64_t qubits = d->qubits;
-    const int n = d->n;
-    unsigned inmask = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        if (j < K) inmask |= 1u << (unsigned)((qubits >> (8 * j)) & 0xff);
-    // the tile index's digits go to the qubits outside the tile, lowest
-    // first: one step per outside qubit
-    long long base = 0, t = tile;
-    unsigned out = ~inmask & ((1u << n) - 1u);
-    while (out) {
-        const int q = __builtin_ctz(out);
-        out &= out - 1u;
-        base |= (t & 3ll) << (2 * q);
-        t >>= 2;
-    }
-    // the thread index supplies the low bits of the slot index (digits 0-3,
-    // and the low bit of digit 4 for 512 threads); deposits of disjoint bits
-    // OR.  In 32 bits (the offset is below 2^31 bytes): 64-bit digit values
-    // would be hoisted out of the tile loop and spilled.
+    const TileBase at = tile_base<K>(descs, grp, b);
+    const uint64_t qubits = at.d->qubits;
+    // the thread index supplies the low bits of the slot index (digits 0-3);
+    // deposits of disjoint bits OR.  In 32 bits (the offset is below 2^31
+    // bytes): 64-bit digit values would be hoisted out of the tile loop and
+    // spilled.
     unsigned voff = 0;
 #pragma unroll
-    for (int j = 0; j < (BLOCK > 256 ? 5 : 4); ++j)
+    for (int j = 0; j < 4; ++j)
         voff |= (((unsigned)tid >> (2 * j)) & 3u) << (2 * (unsigned)((qubits >> (8 * j)) & 0xff));
-    return TileLoc{d, base, voff * (unsigned)sizeof(T)};
+    return TileLoc{at, voff * (unsigned)sizeof(T)};
 }
 
 // Byte offset (uniform) of row r of a thread's slots: the row supplies the
@@ -723,13 +662,12 @@ __device__ __forceinline__ unsigned stream_soff(uint64_t qubits, int r) {
     return g;
 }
 
-// 256 threads for tiles up to 4^6 slots (four workgroups per CU: at most 128
-// VGPRs, and 4 x 37 KiB of LDS in FP64); 512 threads and one workgroup per
-// CU for 4^7 slots (its LDS tile is 128 KiB in FP64)
+// 256 threads, four workgroups per CU: at most 128 VGPRs, and 4 x 37 KiB of
+// LDS in FP64 at K = 6
 template <int K>
-constexpr int kStreamBlock = K >= 7 ? 512 : 256;
+constexpr int kStreamBlock = 256;
 template <int K>
-constexpr int kStreamWaves = K >= 7 ? 2 : 4;
+constexpr int kStreamWaves = 4;
 
 // ops held per workgroup: every 6-qubit pass of the planner fits (its passes
 // have at most 64 op entries); longer passes reload chunks inside run_ops
@@ -758,8 +696,8 @@ void tile_stream_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) 
     TileLoc cur = locate_tile<T, K, BLOCK>(descs, grp, blk, tid);
     T pre[PER];
     {
-        const __amdgpu_buffer_rsrc_t rs = tile_rsrc(reinterpret_cast<T *>(cur.d->coef) + cur.base);
-        const uint64_t qubits = cur.d->qubits;
+        const __amdgpu_buffer_rsrc_t rs = tile_rsrc(reinterpret_cast<T *>(cur.at.d->coef) + cur.at.base);
+        const uint64_t qubits = cur.at.d->qubits;
 #pragma unroll
         for (int r = 0; r < PER; ++r) pre[r] = BufIO<T>::ld(rs, cur.voff, stream_soff<T, K, BLOCK>(qubits, r));
 #pragma unroll
@@ -785,11 +723,11 @@ void tile_stream_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) 
     typedef const __attribute__((address_space(1))) OpW *GOpW;
     OpW opw = {0u, 0u, 0u, 0u};
     for (;;) {
-        const int o0 = cur.d->op_begin, o1 = cur.d->op_end;
+        const int o0 = cur.at.d->op_begin, o1 = cur.at.d->op_end;
         const bool fits = o1 - o0 <= kStreamOps;
-        if (cur.d != cached) {
-            stage_ops<kStreamOps>(&oc, cur.d->ops, cur.d->maps, o0, fits ? o1 - o0 : kStreamOps, tid, BLOCK);
-            cached = fits ? cur.d : nullptr;
+        if (cur.at.d != cached) {
+            stage_ops<kStreamOps>(&oc, cur.at.d->ops, cur.at.d->maps, o0, fits ? o1 - o0 : kStreamOps, tid, BLOCK);
+            cached = fits ? cur.at.d : nullptr;
         }
         const int nblk = blk + gridDim.x;
         const bool has_next = nblk < total;
@@ -805,24 +743,24 @@ void tile_stream_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) 
         if (has_next) {
             nxt = locate_tile<T, K, BLOCK>(descs, grp, nblk, tid);
             if constexpr (kOpPrefetch) {
-                const int n0 = nxt.d->op_begin;
-                next_ops = nxt.d->op_end - n0;
-                op_pref = nxt.d != cur.d && next_ops <= kStreamOps;
-                if (op_pref && tid < next_ops) opw = ((GOpW)nxt.d->ops)[n0 + tid];
+                const int n0 = nxt.at.d->op_begin;
+                next_ops = nxt.at.d->op_end - n0;
+                op_pref = nxt.at.d != cur.at.d && next_ops <= kStreamOps;
+                if (op_pref && tid < next_ops) opw = ((GOpW)nxt.at.d->ops)[n0 + tid];
                 else opw = OpW{0u, 0u, 0u, 0u};
             }
-            const __amdgpu_buffer_rsrc_t rs = tile_rsrc(reinterpret_cast<T *>(nxt.d->coef) + nxt.base);
-            const uint64_t qubits = nxt.d->qubits;
+            const __amdgpu_buffer_rsrc_t rs = tile_rsrc(reinterpret_cast<T *>(nxt.at.d->coef) + nxt.at.base);
+            const uint64_t qubits = nxt.at.d->qubits;
 #pragma unroll
             for (int r = 0; r < PE; ++r) pre[r] = BufIO<T>::ld(rs, nxt.voff, stream_soff<T, K, BLOCK>(qubits, r));
         }
-        run_ops<T, false, K, BLOCK, kStreamOps>(lc, nullptr, cur.d->ops, cur.d->maps, o0, o1, tcount, updates, redi, &oc,
+        run_ops<T, false, K, BLOCK, kStreamOps>(lc, nullptr, cur.at.d->ops, cur.at.d->maps, o0, o1, tcount, updates, redi, &oc,
                                                 true);
         if (!fits) cached = nullptr;  // run_ops reloaded later chunks into oc
         if constexpr (PE < PER) {
             if (has_next) {
-                const __amdgpu_buffer_rsrc_t rs = tile_rsrc(reinterpret_cast<T *>(nxt.d->coef) + nxt.base);
-                const uint64_t qubits = nxt.d->qubits;
+                const __amdgpu_buffer_rsrc_t rs = tile_rsrc(reinterpret_cast<T *>(nxt.at.d->coef) + nxt.at.base);
+                const uint64_t qubits = nxt.at.d->qubits;
 #pragma unroll
                 for (int r = PE; r < PER; ++r) pre[r] = BufIO<T>::ld(rs, nxt.voff, stream_soff<T, K, BLOCK>(qubits, r));
             } else {
@@ -841,8 +779,8 @@ void tile_stream_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) 
 #pragma unroll
         for (int r = 0; r < PER; ++r) out[r] = lc[st ^ sw(r * BLOCK)];
         {
-            const __amdgpu_buffer_rsrc_t rs = tile_rsrc(reinterpret_cast<T *>(cur.d->coef) + cur.base);
-            const uint64_t qubits = cur.d->qubits;
+            const __amdgpu_buffer_rsrc_t rs = tile_rsrc(reinterpret_cast<T *>(cur.at.d->coef) + cur.at.base);
+            const uint64_t qubits = cur.at.d->qubits;
 #pragma unroll
             for (int r = 0; r < PER; ++r) BufIO<T>::st(rs, cur.voff, stream_soff<T, K, BLOCK>(qubits, r), out[r]);
         }
@@ -850,7 +788,7 @@ void tile_stream_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) 
         lds_barrier();  // every thread has read this tile and is done with oc
         if (op_pref) {
             if (tid < next_ops) reinterpret_cast<OpW *>(oc.ops)[tid] = opw;
-            cached = nxt.d;  // published by run_ops' first barrier
+            cached = nxt.at.d;  // published by run_ops' first barrier
         }
         st = stid;
         __asm__ volatile("" : "+v"(st));
@@ -1814,7 +1752,9 @@ static hipError_t launch_tile_t(const TilePassDesc *d, const TileGroups &grp, si
         hipLaunchKernelGGL(fn, dim3(nblocks), dim3(64), lds, s, d, grp);
         return hipGetLastError();
     }
-    if (!TRACK && g_tile_variant[K] == 1 && max_n <= 14) {
+    if constexpr (!TRACK && K == 7)
+        if (g_tile_variant[7] == 1 && max_n <= 14) return launch_tile7(d, grp, (int)sizeof(T), s);
+    if constexpr (!TRACK && K <= 6) if (g_tile_variant[K] == 1 && max_n <= 14) {
         auto fn = tile_stream_kernel<T, K>;
         constexpr int SB = kStreamBlock<K>;
         static int rb = 0;

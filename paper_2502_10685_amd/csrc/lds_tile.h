@@ -218,6 +218,13 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t x) {
     return (uint64_t)lo | ((uint64_t)hi << 32);
 }
 
+// A 3x3 map into SGPRs by scalar loads (the map array is read-only).
+typedef const __attribute__((address_space(4))) double *ConstMaps;
+__device__ __forceinline__ void load_map(double (&m)[9], ConstMaps src) {
+#pragma unroll
+    for (int q = 0; q < 9; ++q) m[q] = src[q];
+}
+
 // Orders a wave's LDS accesses: the LDS completes a wave's instructions in
 // issue order, and the fences keep the compiler from moving them.
 __device__ __forceinline__ void wave_lds_order() {

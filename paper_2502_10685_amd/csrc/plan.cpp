@@ -299,21 +299,111 @@ void split_waves(std::vector<DOp> &ops, DensePass &ps) {
     }
 }
 
+// 7-digit tiles run as record chains: a group becomes groups of one CX and at
+// most one map per digit behind it, the lower digit's first (maps on different
+// digits commute).  Then a unit (group or lone op) on digits above 1 that
+// commutes with every unit before it comes first, and one that commutes with
+// every unit behind it last: those two are applied between registers and HBM,
+// where the 128-byte runs need digits 0 and 1 across the lanes.
+// One entry per piece of at most kTile7Units units.
+std::vector<std::vector<DOp>> chain_order(const std::vector<DOp> &in) {
+    std::vector<std::vector<DOp>> all;
+    for (size_t i = 0; i < in.size();) {
+        if (in[i].kind != DOP_GROUP) {
+            all.push_back({in[i]});
+            ++i;
+            continue;
+        }
+        const DOp head = in[i];
+        std::vector<DOp> cur;
+        int nlo = 0, nhi = 0;
+        auto flush = [&] {
+            if (cur.empty()) return;
+            std::stable_sort(cur.begin(), cur.end(), [&](const DOp &a, const DOp &b) {
+                return a.kind == DOP_U1 && b.kind == DOP_U1 && a.a < b.a;
+            });
+            all.push_back(cur);
+            cur.clear();
+            nlo = nhi = 0;
+        };
+        for (int j = 1; j <= head.ngates; ++j) {
+            const DOp &m = in[i + j];
+            if (m.kind == DOP_CX ? !cur.empty() : (m.a == head.a ? nlo : nhi) != 0) flush();
+            if (m.kind == DOP_U1) ++(m.a == head.a ? nlo : nhi);
+            cur.push_back(m);
+        }
+        flush();
+        i += 1 + head.ngates;
+    }
+    auto digits = [](const std::vector<DOp> &u) {
+        unsigned d = 0;
+        for (const DOp &m : u) d |= op_digits(m);
+        return d;
+    };
+    auto piece = [&](std::vector<std::vector<DOp>> units) {
+        unsigned seen = 0;
+        for (size_t i = 0; i < units.size(); ++i) {
+            const unsigned d = digits(units[i]);
+            if (!(d & 3u) && !(d & seen)) {
+                std::rotate(units.begin(), units.begin() + (long)i, units.begin() + (long)i + 1);
+                break;
+            }
+            seen |= d;
+        }
+        seen = 0;
+        for (size_t i = units.size(); i-- > 1;) {  // never the first again
+            const unsigned d = digits(units[i]);
+            if (!(d & 3u) && !(d & seen)) {
+                std::rotate(units.begin() + (long)i, units.begin() + (long)i + 1, units.end());
+                break;
+            }
+            seen |= d;
+        }
+        std::vector<DOp> out;
+        for (const auto &u : units) {
+            if (u.size() > 1) {
+                const unsigned d = digits(u);
+                DOp h{};
+                h.kind = DOP_GROUP;
+                h.a = (uint8_t)__builtin_ctz(d);
+                h.b = (uint8_t)(31 - __builtin_clz(d));
+                h.ngates = (uint8_t)u.size();
+                h.perm = (uint16_t)group_shape(u.data(), (int)u.size(), h.a);
+                set_shape_maps(h, u.data());
+                out.push_back(h);
+            }
+            out.insert(out.end(), u.begin(), u.end());
+        }
+        return out;
+    };
+    std::vector<std::vector<DOp>> pieces;
+    for (size_t u = 0; u < all.size(); u += kTile7Units)
+        pieces.push_back(piece({all.begin() + (long)u,
+                                all.begin() + (long)std::min(all.size(), u + (size_t)kTile7Units)}));
+    return pieces;
+}
+
 void group_all(DensePlan &P, bool segments) {
-    int shift = 0;
+    std::vector<DOp> ops;
+    std::vector<DensePass> passes;
     for (DensePass &ps : P.passes) {
-        ps.op_begin += shift;
-        ps.op_end += shift;
         const std::vector<DOp> in(P.ops.begin() + ps.op_begin, P.ops.begin() + ps.op_end);
         std::vector<DOp> out =
             (segments && !P.resident && ps.k == kSegTileDigits) ? segment_ops(in, ps.k) : group_ops(in, ps.k);
         if (!P.resident && ps.k == 6) split_waves(out, ps);
-        P.ops.erase(P.ops.begin() + ps.op_begin, P.ops.begin() + ps.op_end);
-        P.ops.insert(P.ops.begin() + ps.op_begin, out.begin(), out.end());
-        const int added = (int)out.size() - (int)in.size();
-        ps.op_end += added;
-        shift += added;
+        std::vector<std::vector<DOp>> pieces;
+        if (!P.resident && ps.k == kChainTileDigits && !out.empty()) pieces = chain_order(out);
+        else pieces.push_back(std::move(out));
+        for (const auto &piece : pieces) {
+            ps.op_begin = (int)ops.size();
+            ops.insert(ops.end(), piece.begin(), piece.end());
+            ps.op_end = (int)ops.size();
+            passes.push_back(ps);
+            ps.ngates = 0;  // counted in the first piece
+        }
     }
+    P.ops = std::move(ops);
+    P.passes = std::move(passes);
 }
 
 }  // namespace
@@ -741,7 +831,20 @@ void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin) {
         order.push_back((int)old);
     };
     for (const DensePass &ps : P.passes) {
-        if (begin) begin->push_back((int)P.chain.size());
+        const size_t first_rec = P.chain.size();
+        if (begin) begin->push_back((int)first_rec);
+        // a record that only moves the tile between its layout in HBM (pair
+        // k - 2, k - 1 in registers) and LDS
+        auto pass_through = [&] {
+            ChainOp r{};
+            const int b = ps.k - 1, a = b - 1;
+            r.word = (uint32_t)(b * (b - 1) / 2 + a);
+            r.map = (uint32_t)order.size();
+            for (int k = 0; k < 4; ++k)
+                r.read[k] = r.write[k] = (uint32_t)sw((1 + k % 2) << (2 * (k < 2 ? a : b))) * (uint32_t)dbytes;
+            return r;
+        };
+        bool ends_high = false;  // the last unit's pair avoids digits 0 and 1
         for (int i = ps.op_begin; i < ps.op_end;) {
             const DOp &h = P.ops[(size_t)i];
             int lo, hi, first = i, count = 1;
@@ -751,11 +854,14 @@ void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin) {
                 first = i + 1;
                 count = h.ngates;
             } else {
-                const int other = h.kind == DOP_CX ? h.b : (h.a == 0 ? 1 : h.a - 1);
+                int other = h.kind == DOP_CX ? h.b : (h.a == 0 ? 1 : h.a - 1);
+                if (!P.resident && h.kind == DOP_U1 && h.a == 2) other = 3;  // away from digits 0 and 1
                 lo = std::min<int>(h.a, other);
                 hi = std::max<int>(h.a, other);
             }
             i = first + count;
+            ends_high = lo >= 2;
+            if (!P.resident && P.chain.size() == first_rec && !ends_high) P.chain.push_back(pass_through());
             // a record holds a CX and one map per digit behind it; longer
             // groups become several records (one in twelve on random circuits)
             unsigned cx = 0;
@@ -764,6 +870,7 @@ void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin) {
                 ChainOp r{};
                 r.word = (uint32_t)(hi * (hi - 1) / 2 + lo) |
                          (((unsigned)(mlo >= 0) + 2 * (unsigned)(mhi >= 0)) << kChainKindShift);
+                r.word |= (4 * cx + ((r.word >> kChainKindShift) & 3u)) << kChainSelectShift;
                 r.map = (uint32_t)order.size();
                 if (mlo >= 0) take((uint32_t)mlo);
                 if (mhi >= 0) take((uint32_t)mhi);
@@ -795,6 +902,10 @@ void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin) {
             }
             flush();
         }
+        if (!P.resident && (!ends_high || P.chain.size() < first_rec + 2)) {
+            while (P.chain.size() < first_rec + 1) P.chain.push_back(pass_through());
+            P.chain.push_back(pass_through());
+        }
     }
     // six qubits: a wave's sweep of a pair below digit 5 stays in the quarter
     // of the tile whose digit 5 is the wave's index (lane_order)
@@ -824,6 +935,20 @@ void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin) {
             d.map = renum[d.map];
             d.reserved = renum[d.reserved];
         }
+    }
+}
+
+void record_offsets(const ChainOp &r, const DensePass &ps, int dbytes, bool after, uint32_t out[4]) {
+    int b = 1;
+    while (b * (b + 1) / 2 <= (int)(r.word & 0xffu)) ++b;
+    const int a = (int)(r.word & 0xffu) - b * (b - 1) / 2;
+    for (int k = 0; k < 4; ++k)
+        out[k] = (uint32_t)(((uint64_t)(1 + k % 2) << (2 * ps.qubit[k < 2 ? a : b])) * (uint64_t)dbytes);
+    if (!after && (r.word & (kChainFlip6 >> 2))) {  // the CX's letter map, as in build_chain
+        const int c = r.word & (kChainFlip6 >> 1) ? 0 : 2, t = 2 - c;
+        const uint32_t w[4] = {out[0], out[1], out[2], out[3]};
+        out[c] ^= w[t];
+        out[t + 1] ^= w[c + 1];
     }
 }
 
@@ -893,7 +1018,7 @@ GradPlan plan_gradient(const GateList &g, int k_heis, int k_fwd, int low, int64_
     }
     G.heis_pass_begin.push_back((int)G.heis.passes.size());
     G.fwd_pass_begin.push_back((int)G.fwd.passes.size());
-    if (G.heis.resident) build_chain(G.heis, 8, &G.heis_chain_begin);
+    if (G.heis.resident || k_heis == kChainTileDigits) build_chain(G.heis, 8, &G.heis_chain_begin);
     return G;
 }
 

@@ -68,6 +68,14 @@ int group_shape(const DOp *members, int count, int lo);
 // segments (see segment_ops in plan.cpp).
 constexpr int kSegTileDigits = 6;
 
+// Tile size whose untracked passes run as record chains (tile7.hip).
+constexpr int kChainTileDigits = 7;
+// Records of a pass at most (one per lane of a wave); a pass with more units
+// than kTile7Units, which leaves room for the records that only move the
+// tile, is split.
+constexpr int kTile7Records = 64;
+constexpr int kTile7Units = kTile7Records - 2;
+
 // General form: gates [g_begin, g_end) only; forward = g_begin first (the
 // adjoint sweep) instead of Heisenberg order; slot (optional, size m): for
 // each rotation gate its join slot, stored in DOp::reserved with DOp::b set
@@ -116,13 +124,19 @@ struct GradPlan {
     std::vector<int32_t> slot_param;                  // slot -> parameter
     std::vector<int32_t> seg_slot_begin;              // S + 1 entries
 };
-// Renumbers the maps of grouped resident passes in op order and appends each
-// pass's records to P.chain; begin[p] (optional) receives the first record of
-// pass p, with the total behind the last.  dbytes: size of a weight.
+// Renumbers the maps of grouped passes (resident, or over 7-qubit tiles) in op
+// order and appends each pass's records to P.chain; begin[p] (optional)
+// receives the first record of pass p, with the total behind the last.
+// dbytes: size of a weight.  A tiled pass begins and ends with records whose
+// pairs avoid digits 0 and 1 (without a CX or map where the schedule has no
+// such op there), and has at least two.
 void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin = nullptr);
 // Untracked evaluation of a resident circuit from both ends: gates [s, g_end)
 // taken back from the observable, gates [0, s) forward from the state, with s
 // where half of the CX gates lie on either side (a record holds about one).
+// Byte offsets, in the 4^n array, of the letters of record r's pair: as it
+// reads them (after = false) or writes them.
+void record_offsets(const ChainOp &r, const DensePass &ps, int dbytes, bool after, uint32_t out[4]);
 DensePlan plan_meet(const GateList &g, int low, int64_t g_end, int dbytes);
 GradPlan plan_gradient(const GateList &g, int k_heis, int k_fwd, int low, int64_t every);
 SparsePlan plan_sparse(const GateList &g);

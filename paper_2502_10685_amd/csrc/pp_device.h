@@ -42,7 +42,8 @@ constexpr unsigned kSkipBarrier = 0x8000u;
 // One record of an LDS-resident chain: an optional CX, then an optional 3x3
 // map on each digit of one digit pair a < b.  word: pair index b (b - 1) / 2 +
 // a in bits 0-7; 1 for a map on the lower digit + 2 for one on the higher in
-// bits 8-9; kChainNoBarrierBit; the sign flips of the CX.  map: the first of
+// bits 8-9; kChainNoBarrierBit; 4 x the CX (0 none, 1 control = lower digit, 2
+// control = higher) + bits 8-9 in bits 16-19; the sign flips of the CX.  map: the first of
 // its maps (lower digit first); a chain's maps are stored in record order.
 // The 16 letters of a block, e = letter of a + 4 letter of b, are read at the
 // block's base XOR the words read[k] of e's set bits k and written at it XOR
@@ -54,6 +55,7 @@ struct ChainOp {
 };
 static_assert(sizeof(ChainOp) == 48, "records are read as three 16-byte words");
 constexpr unsigned kChainKindShift = 8;
+constexpr unsigned kChainSelectShift = 16;
 // no workgroup barrier behind it: it and the next record avoid digit 5 of a
 // six-qubit circuit, so each wave stays in its quarter of the tile
 constexpr unsigned kChainNoBarrierBit = 12;
@@ -99,7 +101,14 @@ struct TilePassDesc {
     int32_t ntiles;
     uint64_t qubits;               // byte j = global qubit of local digit j (ascending)
     uint32_t reg_entry;            // register-tile kernel: digit triple (bit mask) to load into registers
-    uint32_t reserved;
+    uint32_t nmaps;                // maps of the schedule (7-qubit tiles)
+    // 7-qubit tiles: the pass's records; its first is applied to the weights
+    // as they come from HBM and its last as they go there, so these are byte
+    // offsets in the 4^n array of the letters of their digit pairs, as in
+    // ChainOp (in: read words of the first, out: write words of the last)
+    const ChainOp *chain;
+    int32_t nrec;
+    uint32_t in[4], out[4];
 };
 
 // One pass of the adjoint sweep over tiles of 4^k slots (k = n: one tile).
@@ -217,6 +226,9 @@ hipError_t launch_chain(const ResidentDesc *d_descs, int ndescs, int n, int dtyp
 size_t chain_exchange_bytes(int n, int dtype_bytes);
 hipError_t launch_tile_pass(const TilePassDesc *d_descs, const TileGroups &groups, int k, int dtype_bytes,
                             bool track, hipStream_t s);
+// Untracked passes over 7-qubit tiles of at most 14 qubits (tile7.hip).
+hipError_t launch_tile7(const TilePassDesc *d_descs, const TileGroups &groups, int dtype_bytes, hipStream_t s);
+int num_cus();
 // 0: one workgroup per tile; 1: persistent prefetching workgroups (k <= 6)
 void set_tile_kernel_variant(int k, int variant);
 int tile_kernel_variant(int k);
