@@ -73,9 +73,10 @@ typedef enum pp_dtype { PP_F64 = 0, PP_F32 = 1 } pp_dtype;
  *          host into the axis of the next rotation (a multi-qubit Pauli),
  *          so the stored strings never move and a rotation splits them in
  *          one kernel, pairing duplicates through a hash index.  Otherwise
- *          each pass applies a run of Clifford gates and one rotation,
- *          appends the split strings by wave-ballot compaction, then merges
- *          duplicates with a radix sort and a segmented FP64 sum.
+ *          each pass, one kernel too, applies one rotation and the run of
+ *          Clifford gates before the next, pairs duplicates through a hash
+ *          table and writes the list anew; a radix sort at the end gives it
+ *          the canonical order.
  *          n <= 64; the capacity is set with PP_OPT_MAX_TERMS.
  *  AUTO  : DENSE when 4^n slots fit the memory budget, else SPARSE. */
 typedef enum pp_engine { PP_ENGINE_AUTO = 0, PP_ENGINE_DENSE = 1, PP_ENGINE_SPARSE = 2 } pp_engine;
@@ -106,10 +107,10 @@ typedef enum pp_option {
                                propagates in the Clifford frame (Clifford
                                gates folded into the rotation axes on the
                                host, one kernel per rotation, duplicates
-                               found through a hash index); 0 uses the
-                               sort-merge pass of every rotation.  Same
-                               strings and weights; truncated runs and
-                               n > 31 always use sort-merge */
+                               found through a hash index); 0 takes the
+                               strings through every gate.  Same strings
+                               and weights; truncated runs and n > 31
+                               always do the latter */
     PP_OPT_FRAME_RAMP = 6   /* DENSE without term tracking: t in 1..24 starts
                                the Heisenberg sweep in the Clifford frame,
                                where the set holds only its strings (it grows

@@ -622,6 +622,8 @@ void free_state_buffers(pp_circuit *c) {
     dfree(c->sb.updates);
     dfree(c->sb.hist);
     dfree(c->sb.tile_flags);
+    dfree(c->sb.lens);
+    dfree(c->sb.table);
     dfree(c->d_dropped);
     c->sb = pp::SparseBuffers{};
     dfree(c->fb.keys);
@@ -720,6 +722,13 @@ pp_status ensure_state(pp_circuit *c, bool weights = true) {
         HIPCHK(dalloc(&c->sb.updates, 1));
         HIPCHK(dalloc(&c->sb.hist, (size_t)pp::sort_hist_entries(cap2)));
         HIPCHK(dalloc(&c->sb.tile_flags, (size_t)tiles));
+        HIPCHK(dalloc(&c->sb.lens, 4));
+        c->sb.table_bits = 8;
+        while (((int64_t)1 << c->sb.table_bits) <= cap2) ++c->sb.table_bits;
+        if (dalloc(&c->sb.table, (size_t)pp::kListTables << c->sb.table_bits) != hipSuccess) {
+            c->sb.table = nullptr;
+            return fail(PP_ERR_NOMEM, "sparse term tables");
+        }
         HIPCHK(dalloc(&c->d_dropped, (size_t)tiles + 1));
         HIPCHK(dalloc(&c->d_partials, 256));
     }
@@ -971,7 +980,7 @@ void fill_plan_stats(pp_circuit *c) {
         if (c->plan_frame)  // clear + init, one per pass, x0 + sort + readout
             s.launches = 2 + (int64_t)P.passes.size() + 2 + (3 * dig + 4) + 2;
         else
-            s.launches = 2 + 3 * (int64_t)P.passes.size() + (int64_t)(rot + 1) * (3 * dig + 3) + 2;
+            s.launches = 2 + rot + 1 + (4 * dig + 5) + 2;  // clear + enter, one per rotation, leave, sort, readout
         s.bytes_per_eval = 0;  // known after the run (48 or 40 bytes per update)
     }
 }
@@ -1068,24 +1077,39 @@ pp_status enqueue_sparse(pp_circuit *c, hipStream_t s, double *out) {
     tr.max_weight = c->trunc_w;
     tr.eps = c->trunc_eps;
     tr.dropped = c->d_dropped;
-    HIPCHK(pp::launch_sparse_init(c->sb, c->dbytes, c->d_ox, c->d_oz, c->d_oc, (int)c->ox.size(), s,
-                                  c->d_dropped + c->sb.max_tiles));
-    bool merged_last = true;
-    for (const pp::SparsePassDesc &p : P.passes) {
+    const int np = (int)P.passes.size(), m = (int)c->ox.size();
+    const uint32_t *codes = c->d_codes;
+    int first = 0;  // the list passes begin here
+    if (np == 0 || !c->obs_distinct)
+        HIPCHK(pp::launch_sparse_init(c->sb, c->dbytes, c->d_ox, c->d_oz, c->d_oc, m, s,
+                                      c->d_dropped + c->sb.max_tiles));
+    if (np > 0 && !c->obs_distinct) {
+        // repeated strings pass the first rotation apart and are summed by sorting
         {
             ProfScope ps(PC_SPASS, s);
-            HIPCHK(pp::launch_sparse_pass(c->sb, c->dbytes, c->d_codes, p, c->d_theta, s, tr));
+            HIPCHK(pp::launch_sparse_pass(c->sb, c->dbytes, codes, P.passes[0], c->d_theta, s, tr));
         }
-        merged_last = false;
-        if (p.rot_op >= 3) {
-            ProfScope ps(PC_SMERGE, s);
-            HIPCHK(pp::launch_sparse_merge(c->sb, c->n, c->dbytes, s, tr));
-            merged_last = true;
-        }
-    }
-    if (!merged_last) {
         ProfScope ps(PC_SMERGE, s);
         HIPCHK(pp::launch_sparse_merge(c->sb, c->n, c->dbytes, s, tr));
+        first = 1;
+    }
+    if (first < np) {
+        const pp::SparsePassDesc *clifford_only = P.passes.back().rot_op < 3 ? &P.passes.back() : nullptr;
+        {
+            ProfScope ps(PC_INIT, s);
+            HIPCHK(pp::launch_list_enter(c->sb, c->dbytes, first ? nullptr : c->d_ox, c->d_oz, c->d_oc, m, codes,
+                                         P.passes[(size_t)first], s, tr));
+        }
+        int step = 0;
+        for (int i = first; i < np && P.passes[(size_t)i].rot_op >= 3; ++i, ++step) {
+            ProfScope ps(PC_SPASS, s);
+            HIPCHK(pp::launch_list_pass(c->sb, c->dbytes, codes, P.passes[(size_t)i],
+                                        i + 1 < np ? &P.passes[(size_t)i + 1] : nullptr, step, c->d_theta, s, tr));
+        }
+        ProfScope ps(PC_SMERGE, s);
+        HIPCHK(pp::launch_list_leave(c->sb, clifford_only, step, s));
+        // canonical order; a closing Clifford run may have made strings heavier
+        HIPCHK(pp::launch_sparse_merge(c->sb, c->n, c->dbytes, s, clifford_only ? tr : pp::SparseTrunc{}));
     }
     {
         ProfScope ps(PC_READOUT, s);

@@ -271,9 +271,10 @@ struct SparseBuffers {
     long long *scan;      // per-workgroup sums of the multi-workgroup scan (256)
     unsigned long long *updates;
     unsigned int *hist;   // radix histograms (sort_hist_entries(cap2) entries)
-    int *tile_flags;      // decoupled look-back state
-    unsigned long long *tile_vals;
-    int *ticket;
+    int *tile_flags;      // per-tile counts
+    uint32_t *table;      // list passes: three hash tables of 2^table_bits positions
+    int table_bits;       // 2^table_bits > cap2
+    unsigned long long *lens;  // list lengths, rotating over four passes
     int64_t cap2;         // capacity of each array (2x the term capacity)
     int64_t max_tiles;
 };
@@ -294,7 +295,8 @@ long long sort_hist_entries(long long cap2);
 // more than max_weight non-identity letters is not written, and a merged
 // string with more letters or with |weight| < eps is dropped.  The absolute
 // weight dropped is summed per tile into dropped[0, tiles) and added, in a
-// fixed order, to dropped[max_tiles] (reset by launch_sparse_init).
+// fixed order, to dropped[max_tiles] (reset by launch_sparse_init; the list
+// passes add theirs per wave, in no fixed order).
 struct SparseTrunc {
     int32_t on = 0;
     int32_t max_weight = 64;
@@ -306,6 +308,21 @@ hipError_t launch_sparse_pass(SparseBuffers &b, int dtype_bytes, const uint32_t 
                               const SparseTrunc &tr = SparseTrunc{});
 hipError_t launch_sparse_merge(SparseBuffers &b, int n, int dtype_bytes, hipStream_t s,
                                const SparseTrunc &tr = SparseTrunc{});
+// Rotations without a sort: strings that differ by the rotation's letter find
+// each other through a hash table.  launch_list_enter takes nterms distinct
+// strings (or, with x null, the merged list in b) through pass 0's Clifford
+// run; launch_list_pass then runs pass `step` (it closes with a rotation) and
+// the Clifford run of `next`, if there is one, and leaves the merged,
+// truncated list in an order of its own; launch_list_leave ends it (last: the
+// Clifford-only pass that the list has been taken through, or null).
+hipError_t launch_list_enter(SparseBuffers &b, int dtype_bytes, const uint64_t *x, const uint64_t *z, const double *c,
+                             int nterms, const uint32_t *cliff_codes, const SparsePassDesc &first, hipStream_t s,
+                             const SparseTrunc &tr);
+hipError_t launch_list_pass(SparseBuffers &b, int dtype_bytes, const uint32_t *cliff_codes, const SparsePassDesc &p,
+                            const SparsePassDesc *next, int step, const double *theta, hipStream_t s,
+                            const SparseTrunc &tr);
+hipError_t launch_list_leave(SparseBuffers &b, const SparsePassDesc *last, int step, hipStream_t s);
+constexpr int kListTables = 3;
 hipError_t launch_sparse_readout(SparseBuffers &b, int dtype_bytes, double *partials, double *out,
                                  hipStream_t s);
 // Clifford-frame engine (sparse.hip)
