@@ -315,18 +315,27 @@ void chain_kernel(const ResidentDesc *__restrict__ descs, int meet, double *out)
     } else {
         // each workgroup publishes its vector; the one that arrives second
         // multiplies the two (the product and its order do not depend on
-        // which one that is)
+        // which one that is).  Agent-scope stores and loads pass the L2 by,
+        // so nothing has to be written back: with a __threadfence() of every
+        // wave instead, each a write-back of the whole L2, 46 parameter sets
+        // of 7 qubits and 7 layers in FP32 took 108 us, not 55.
         T *mine = reinterpret_cast<T *>(d.xbuf) + dir * S::SIZE;
         const T *theirs = reinterpret_cast<const T *>(d.xbuf) + (1 - dir) * S::SIZE;
-        for (int i = tid; i < S::SIZE; i += S::BLOCK) mine[i] = lc[i];
-        __threadfence();
+        for (int i = tid; i < S::SIZE; i += S::BLOCK)
+            __hip_atomic_store(mine + i, lc[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores are at the agent's point of coherence
         __syncthreads();
         unsigned *flag = reinterpret_cast<unsigned *>(red + S::BLOCK / 64 + 1);
-        if (tid == 0) *flag = __hip_atomic_fetch_add(d.ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) *flag = __hip_atomic_fetch_add(d.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         if (*flag == 0u) return;
-        __threadfence();
-        for (int i = tid; i < S::SIZE; i += S::BLOCK) part += (double)lc[i] * (double)theirs[i];
+        constexpr int PER = S::SIZE / S::BLOCK;
+        T v[PER];  // all in flight at once
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            v[j] = __hip_atomic_load(theirs + tid + j * S::BLOCK, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int j = 0; j < PER; ++j) part += (double)lc[tid + j * S::BLOCK] * (double)v[j];
         if (tid == 0) *d.ticket = 0u;  // for the next launch
     }
     const double total = block_sum_d<S::BLOCK>(part, red);
