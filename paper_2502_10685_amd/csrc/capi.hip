@@ -499,8 +499,8 @@ struct pp_circuit {
         int64_t every = -1;
         int k_heis = 0, k_fwd = 0;
         pp::GradPlan plan;
-        pp::DOp *hops = nullptr, *fops = nullptr;
-        pp::ChainOp *hchain = nullptr;
+        pp::DOp *hops = nullptr;
+        pp::ChainOp *hchain = nullptr, *fchain = nullptr;
         double *hmaps = nullptr, *fmaps = nullptr;
         int32_t *hroff = nullptr, *hrparam = nullptr, *froff = nullptr, *frparam = nullptr;
         uint8_t *hrop = nullptr, *frop = nullptr;
@@ -509,7 +509,8 @@ struct pp_circuit {
         pp::ResidentDesc *hres = nullptr;  // one per segment (resident Heisenberg sweep)
         pp::GradPassDesc *gpass = nullptr;
         double *ckpt = nullptr, *rbuf = nullptr, *partials = nullptr, *rot_grad = nullptr;
-        int32_t *slot_param = nullptr;
+        int32_t *rslot = nullptr, *param_off = nullptr, *param_slot = nullptr;
+        int64_t partial_rows = 0;  // rows of ntiles sums that partials holds
         int ncomp = 0;
         // graph of one gradient (PP_OPT_USE_GRAPH): results land in out
         // (<O>, then the gradient) and are copied to the caller's arrays
@@ -601,10 +602,11 @@ void free_grad(pp_circuit *c) {
     auto &G = c->gr;
     free_grad_graph(c);
     if (!G.hops && !G.ckpt && !G.valid) return;
-    dfree(G.hops); dfree(G.fops); dfree(G.hmaps); dfree(G.fmaps);
+    dfree(G.hops); dfree(G.fchain); dfree(G.hmaps); dfree(G.fmaps);
     dfree(G.hroff); dfree(G.hrparam); dfree(G.froff); dfree(G.frparam);
     dfree(G.hchain); dfree(G.hrop); dfree(G.frop); dfree(G.comp); dfree(G.hpass); dfree(G.hres); dfree(G.gpass);
-    dfree(G.ckpt); dfree(G.rbuf); dfree(G.partials); dfree(G.rot_grad); dfree(G.slot_param);
+    dfree(G.ckpt); dfree(G.rbuf); dfree(G.partials); dfree(G.rot_grad); dfree(G.rslot);
+    dfree(G.param_off); dfree(G.param_slot);
     G.valid = false;
 }
 
@@ -2159,16 +2161,18 @@ pp_status ensure_grad(pp_circuit *c, int64_t every) {
     if ((r = upload_vec(&G.hroff, P.heis.roff)) != PP_OK) return r;
     if ((r = upload_vec(&G.hrop, P.heis.rop)) != PP_OK) return r;
     if ((r = upload_vec(&G.hrparam, P.heis.rparam)) != PP_OK) return r;
-    if ((r = upload_vec(&G.fops, P.fwd.ops)) != PP_OK) return r;
+    if ((r = upload_vec(&G.fchain, P.fwd.chain)) != PP_OK) return r;
     if ((r = upload_vec(&G.froff, P.fwd.roff)) != PP_OK) return r;
     if ((r = upload_vec(&G.frop, P.fwd.rop)) != PP_OK) return r;
     if ((r = upload_vec(&G.frparam, P.fwd.rparam)) != PP_OK) return r;
-    if ((r = upload_vec(&G.slot_param, P.slot_param)) != PP_OK) return r;
+    if ((r = upload_vec(&G.rslot, P.rslot)) != PP_OK) return r;
+    if ((r = upload_vec(&G.param_off, P.param_off)) != PP_OK) return r;
+    if ((r = upload_vec(&G.param_slot, P.param_slot)) != PP_OK) return r;
     HIPCHK(dalloc(&G.hmaps, (size_t)9 * std::max(P.heis.nmaps(), 1)));
     HIPCHK(dalloc(&G.fmaps, (size_t)9 * std::max(P.fwd.nmaps(), 1)));
     std::vector<pp::ComposeDesc> comp;
     if (P.heis.nmaps() > 0) comp.push_back({G.hroff, G.hrop, G.hrparam, c->d_theta, G.hmaps, P.heis.nmaps(), P.heis.nmaps()});
-    if (P.fwd.nmaps() > 0) comp.push_back({G.froff, G.frop, G.frparam, c->d_theta, G.fmaps, P.fwd.nmaps(), P.fwd.nmaps()});
+    if (P.fwd.nmaps() > 0) comp.push_back({G.froff, G.frop, G.frparam, c->d_theta, G.fmaps, P.fwd.nmaps(), 0});
     G.ncomp = (int)comp.size();
     if ((r = upload_vec(&G.comp, comp)) != PP_OK) return r;
     const size_t S = P.bounds.size() - 1;
@@ -2220,29 +2224,36 @@ pp_status ensure_grad(pp_circuit *c, int64_t every) {
     HIPCHK(dalloc(&G.ckpt, (size_t)slots * std::max<size_t>(S, 1)));
     HIPCHK(dalloc(&G.rbuf, (size_t)slots));
     const int ntiles_f = (int)((int64_t)1 << (2 * (n - k_fwd)));
-    int max_seg = 1;
-    for (size_t sg = 0; sg < S; ++sg) max_seg = std::max(max_seg, P.seg_slot_begin[sg + 1] - P.seg_slot_begin[sg]);
-    HIPCHK(dalloc(&G.partials, (size_t)max_seg * ntiles_f));
-    HIPCHK(dalloc(&G.rot_grad, (size_t)std::max<size_t>(P.slot_param.size(), 1)));
-    std::vector<pp::GradPassDesc> gd;
+    // sums of one segment's maps at least, of as many segments as fit in 64 MiB
+    int64_t rows = 3, all_rows = 3 * (int64_t)P.fwd.nmaps();
     for (size_t sg = 0; sg < S; ++sg)
+        rows = std::max<int64_t>(rows, 3 * (int64_t)(P.fwd_map_begin[sg + 1] - P.fwd_map_begin[sg]));
+    rows = std::max(rows, std::min<int64_t>(all_rows, ((int64_t)64 << 20) / (8 * (int64_t)ntiles_f)));
+    G.partial_rows = rows;
+    HIPCHK(dalloc(&G.partials, (size_t)rows * ntiles_f));
+    HIPCHK(dalloc(&G.rot_grad, (size_t)std::max(P.nslots, 1)));
+    std::vector<pp::GradPassDesc> gd;
+    int map_base = 0;
+    for (size_t sg = 0; sg < S; ++sg) {
+        if (3 * (int64_t)(P.fwd_map_begin[sg + 1] - map_base) > rows) map_base = P.fwd_map_begin[sg];
         for (int p = P.fwd_pass_begin[sg]; p < P.fwd_pass_begin[sg + 1]; ++p) {
             const pp::DensePass &ps = P.fwd.passes[p];
             pp::GradPassDesc d{};
             d.c = (double *)c->coef;
             d.r = G.rbuf;
-            d.ops = G.fops;
+            d.chain = G.fchain + P.fwd_chain_begin[(size_t)p];
+            d.nrec = P.fwd_chain_begin[(size_t)p + 1] - P.fwd_chain_begin[(size_t)p];
             d.maps = G.fmaps;
+            d.nmaps = P.fwd.nmaps();
             d.partials = G.partials;
             d.n = n;
             d.k = k_fwd;
-            d.op_begin = ps.op_begin;
-            d.op_end = ps.op_end;
             d.ntiles = ntiles_f;
-            d.slot_base = P.seg_slot_begin[sg];
+            d.map_base = map_base;
             for (int j = 0; j < k_fwd; ++j) d.qubits |= (uint64_t)ps.qubit[j] << (8 * j);
             gd.push_back(d);
         }
+    }
     if ((r = upload_vec(&G.gpass, gd)) != PP_OK) return r;
     G.k_heis = k_heis;
     G.k_fwd = k_fwd;
@@ -2581,19 +2592,25 @@ pp_status enqueue_gradient_body(pp_circuit *c, hipStream_t s, double *d_expval, 
     // forward sweep of (c, r) with the joins of every rotation
     HIPCHK(pp::launch_grad_init_state(G.rbuf, n, s));
     const int ntiles_f = (int)((int64_t)1 << (2 * (n - G.k_fwd)));
-    int gp = 0;
+    const pp::GradRunsDesc runs{G.froff, G.frparam, G.rslot, G.frop, c->d_theta, G.partials, G.rot_grad};
+    int map_base = 0;
     for (size_t sg = 0; sg < S; ++sg) {
-        if (sg > 0) HIPCHK(pp::launch_copy_f64(G.ckpt + (size_t)sg * slots, coef, slots, s));
-        for (int p = P.fwd_pass_begin[sg]; p < P.fwd_pass_begin[sg + 1]; ++p, ++gp) {
-            ProfScope ps(PC_TILE, s);
-            HIPCHK(pp::launch_grad_pass(G.gpass + gp, ntiles_f, G.k_fwd, s));
+        if (3 * (int64_t)(P.fwd_map_begin[sg + 1] - map_base) > G.partial_rows) {
+            HIPCHK(pp::launch_grad_runs(runs, map_base, P.fwd_map_begin[sg], ntiles_f, s));
+            map_base = P.fwd_map_begin[sg];
         }
-        const int nsl = P.seg_slot_begin[sg + 1] - P.seg_slot_begin[sg];
-        HIPCHK(pp::launch_grad_reduce(G.partials, nsl, ntiles_f, G.rot_grad + P.seg_slot_begin[sg], s));
+        if (sg > 0) HIPCHK(pp::launch_copy_f64(G.ckpt + (size_t)sg * slots, coef, slots, s));
+        TileSpan span;
+        span.begin(s);
+        for (int p = P.fwd_pass_begin[sg]; p < P.fwd_pass_begin[sg + 1]; ++p) {
+            HIPCHK(pp::launch_grad_pass(G.gpass + p, ntiles_f, G.k_fwd, s));
+            span.count();
+        }
+        span.end();
     }
+    HIPCHK(pp::launch_grad_runs(runs, map_base, P.fwd.nmaps(), ntiles_f, s));
     if (c->g.n_params > 0)
-        HIPCHK(pp::launch_grad_accumulate(G.rot_grad, G.slot_param, (int)P.slot_param.size(), d_grad, c->g.n_params,
-                                          s));
+        HIPCHK(pp::launch_grad_accumulate(G.rot_grad, G.param_off, G.param_slot, d_grad, c->g.n_params, s));
     return PP_OK;
 }
 

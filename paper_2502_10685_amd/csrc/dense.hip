@@ -1166,121 +1166,6 @@ __global__ __launch_bounds__(64) void tile_reg_kernel(const TilePassDesc *__rest
     }
 }
 
-// ------------------------------------------------------ adjoint sweep
-// Forward propagation of the observable weights c and the state
-// coefficients r through one pass.  U1 ops hold the Heisenberg matrix M of a
-// single gate; the forward map (Table I) is its transpose because the maps
-// are orthogonal.  For a rotation R_sigma(theta) the derivative of <O> is
-// c^T (0 + A_sigma) r taken just before the gate, where A_sigma = R'(0) is the
-// generator of the forward rotation on (X, Y, Z):
-//   RX: c_Z r_Y - c_Y r_Z,  RY: c_X r_Z - c_Z r_X,  RZ: c_Y r_X - c_X r_Y.
-template <int K, int BLOCK>
-__device__ double join_part(const double *lc, const double *lr, int a, int axis, int tid) {
-    constexpr int NQ = 1 << (2 * (K - 1));
-    const int sh = 2 * a;
-    const int lowmask = (1 << sh) - 1;
-    double acc = 0.0;
-    for (int u = tid; u < NQ; u += BLOCK) {
-        const int base = ((u & ~lowmask) << 2) | (u & lowmask);
-        const int iX = sw(base | (1 << sh)), iZ = sw(base | (2 << sh)), iY = sw(base | (3 << sh));
-        if (axis == 3) acc += lc[iZ] * lr[iY] - lc[iY] * lr[iZ];
-        else if (axis == 4) acc += lc[iX] * lr[iZ] - lc[iZ] * lr[iX];
-        else acc += lc[iY] * lr[iX] - lc[iX] * lr[iY];
-    }
-    return acc;
-}
-
-template <int K, int BLOCK>
-__global__ __launch_bounds__(BLOCK) void grad_kernel(const GradPassDesc *__restrict__ desc) {
-    extern __shared__ __align__(256) unsigned char smem[];
-    __shared__ double redd[BLOCK / 64];
-    __shared__ OpCache oc;
-    const GradPassDesc d = *desc;
-    constexpr int size = 1 << (2 * K);
-    double *lc = reinterpret_cast<double *>(smem);
-    double *lr = lc + size;
-    const int tid = threadIdx.x;
-    const long long tile = blockIdx.x;
-    unsigned inmask = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        if (j < K) inmask |= 1u << (unsigned)((d.qubits >> (8 * j)) & 0xff);
-    long long base = 0;
-    {
-        long long t = tile;
-        for (int q = 0; q < d.n; ++q) {
-            if ((inmask >> q) & 1u) continue;
-            base |= (t & 3ll) << (2 * q);
-            t >>= 2;
-        }
-    }
-    for (int i = tid; i < size; i += BLOCK) {
-        const long long gi = base | deposit_digits(i, d.qubits, 0, K);
-        lc[sw(i)] = d.c[gi];
-        lr[sw(i)] = d.r[gi];
-    }
-    for (int cb = d.op_begin; cb < d.op_end; cb += OPCH) {
-        const int cn = (d.op_end - cb) < OPCH ? (d.op_end - cb) : OPCH;
-        lds_barrier();
-        stage_ops<OPCH>(&oc, d.ops, d.maps, cb, cn, tid, BLOCK);
-        lds_barrier();
-        for (int i = 0; i < cn; ++i) {
-            const uint32_t w0 = __builtin_amdgcn_readfirstlane(reinterpret_cast<const uint32_t *>(&oc.ops[i])[0]);
-            const uint32_t slot = __builtin_amdgcn_readfirstlane(reinterpret_cast<const uint32_t *>(&oc.ops[i])[3]);
-            const int kind = w0 & 0xff, a = (w0 >> 8) & 0xff, b = (w0 >> 16) & 0xff;
-            if (kind == DOP_U1) {
-                if (b >= 3) {
-                    const double part = block_sum_d<BLOCK>(join_part<K, BLOCK>(lc, lr, a, b, tid), redd);
-                    if (tid == 0) d.partials[(long long)(slot - d.slot_base) * d.ntiles + tile] = part;
-                    lds_barrier();
-                }
-                const double *M = oc.maps[i];
-                const double Mt[9] = {M[0], M[3], M[6], M[1], M[4], M[7], M[2], M[5], M[8]};
-                u1_apply<double, false, K, BLOCK>(lc, nullptr, a, Mt, 0u, tid);
-                u1_apply<double, false, K, BLOCK>(lr, nullptr, a, Mt, 0u, tid);
-            } else {
-                if constexpr (K >= 2) {
-                    cx_apply<double, false, K, BLOCK>(lc, nullptr, a, b, tid);
-                    cx_apply<double, false, K, BLOCK>(lr, nullptr, a, b, tid);
-                }
-            }
-            lds_barrier();
-        }
-    }
-    lds_barrier();
-    for (int i = tid; i < size; i += BLOCK) {
-        const long long gi = base | deposit_digits(i, d.qubits, 0, K);
-        d.c[gi] = lc[sw(i)];
-        d.r[gi] = lr[sw(i)];
-    }
-}
-
-// r of |0...0><0...0|: Tr(P rho) = 1 for strings of I and Z only, else 0
-__global__ void grad_init_state_kernel(double *r, int n, long long size) {
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < size;
-         i += (long long)gridDim.x * blockDim.x) {
-        bool zonly = true;
-        for (int q = 0; q < n; ++q) zonly = zonly && !((i >> (2 * q)) & 1);
-        r[i] = zonly ? 1.0 : 0.0;
-    }
-}
-
-__global__ void grad_reduce_kernel(const double *partials, int nslots, int ntiles, double *rot_grad) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= nslots) return;
-    double s = 0.0;
-    for (int t = 0; t < ntiles; ++t) s += partials[(long long)j * ntiles + t];
-    rot_grad[j] = s;
-}
-
-// sequential so that gates sharing a parameter are summed in gate order
-__global__ void grad_accumulate_kernel(const double *rot_grad, const int32_t *slot_param, int nslots, double *grad,
-                                       int nparams) {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    for (int p = 0; p < nparams; ++p) grad[p] = 0.0;
-    for (int j = 0; j < nslots; ++j) grad[slot_param[j]] += rot_grad[j];
-}
-
 __global__ void copy_f64_n_kernel(const double *src, double *dst, long long count) {
     for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < count;
          i += (long long)gridDim.x * blockDim.x)
@@ -1804,53 +1689,6 @@ hipError_t launch_tile_pass(const TilePassDesc *d_descs, const TileGroups &grp, 
                      : launch_tile_k<double, false>(d_descs, grp, k, lds, s);
     return track ? launch_tile_k<float, true>(d_descs, grp, k, lds, s)
                  : launch_tile_k<float, false>(d_descs, grp, k, lds, s);
-}
-
-template <int K, int BLOCK>
-static hipError_t launch_grad_t(const GradPassDesc *d, int ntiles, hipStream_t s) {
-    auto fn = grad_kernel<K, BLOCK>;
-    static bool attr = false;
-    if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           max_lds_bytes() - (int)kStaticLdsReserve);
-        if (e != hipSuccess) return e;
-        attr = true;
-    }
-    const size_t lds = 2 * sizeof(double) * ((size_t)1 << (2 * K));
-    hipLaunchKernelGGL(fn, dim3(ntiles), dim3(BLOCK), lds, s, d);
-    return hipGetLastError();
-}
-
-hipError_t launch_grad_pass(const GradPassDesc *d_desc, int ntiles, int k, hipStream_t s) {
-    switch (k) {
-    case 1: return launch_grad_t<1, 64>(d_desc, ntiles, s);
-    case 2: return launch_grad_t<2, 64>(d_desc, ntiles, s);
-    case 3: return launch_grad_t<3, 64>(d_desc, ntiles, s);
-    case 4: return launch_grad_t<4, 64>(d_desc, ntiles, s);
-    case 5: return launch_grad_t<5, 256>(d_desc, ntiles, s);
-    case 6: return launch_grad_t<6, 256>(d_desc, ntiles, s);
-    default: return hipErrorInvalidValue;
-    }
-}
-
-hipError_t launch_grad_init_state(double *r, int n, hipStream_t s) {
-    const long long size = 1ll << (2 * n);
-    const int grid = (int)((size + 255) / 256 < 4096 ? (size + 255) / 256 : 4096);
-    hipLaunchKernelGGL(grad_init_state_kernel, dim3(grid), dim3(256), 0, s, r, n, size);
-    return hipGetLastError();
-}
-
-hipError_t launch_grad_reduce(const double *partials, int nslots, int ntiles, double *rot_grad, hipStream_t s) {
-    if (nslots <= 0) return hipSuccess;
-    hipLaunchKernelGGL(grad_reduce_kernel, dim3((nslots + 255) / 256), dim3(256), 0, s, partials, nslots, ntiles,
-                       rot_grad);
-    return hipGetLastError();
-}
-
-hipError_t launch_grad_accumulate(const double *rot_grad, const int32_t *slot_param, int nslots, double *grad,
-                                  int nparams, hipStream_t s) {
-    hipLaunchKernelGGL(grad_accumulate_kernel, dim3(1), dim3(64), 0, s, rot_grad, slot_param, nslots, grad, nparams);
-    return hipGetLastError();
 }
 
 hipError_t launch_copy_f64(const double *src, double *dst, long long count, hipStream_t s) {

@@ -412,7 +412,7 @@ static DensePlan plan_dense_core(const GateList &g, int k, int low, const PlanOp
 
 DensePlan plan_dense_opts(const GateList &g, int k, int low, const PlanOptions &o) {
     DensePlan P = plan_dense_core(g, k, low, o);
-    if (o.group && o.compose && !o.slot) group_all(P, o.segments);
+    if (o.group && o.compose) group_all(P, o.segments);
     return P;
 }
 
@@ -427,12 +427,6 @@ static DensePlan plan_dense_core(const GateList &g, int k, int low, const PlanOp
     const int64_t m = ge - gb;
     // position h in processing order <-> gate index
     auto gate_of = [&](int64_t h) { return o.forward ? gb + h : ge - 1 - h; };
-    auto tag = [&](DOp &d, int64_t gi) {
-        if (o.slot && g.op[gi] >= 3) {
-            d.b = g.op[gi];
-            d.reserved = (uint32_t)(*o.slot)[gi];
-        }
-    };
 
     if (P.resident) {
         DensePass pass;
@@ -466,7 +460,7 @@ static DensePlan plan_dense_core(const GateList &g, int k, int low, const PlanOp
                 d.ngates++;
                 d.smask = (uint16_t)smask_compose(gate_smask(op), d.smask);
                 if (rot) d.perm = 0;
-                pend[d.map].gates.push_back({op, rot ? g.param[gi] : -1});
+                pend[d.map].gates.push_back({op, (int32_t)gi});
             } else {
                 DOp d{};
                 d.kind = DOP_U1;
@@ -475,8 +469,7 @@ static DensePlan plan_dense_core(const GateList &g, int k, int low, const PlanOp
                 d.smask = (uint16_t)gate_smask(op);
                 d.perm = rot ? 0 : 1;
                 d.map = (uint32_t)pend.size();
-                tag(d, gi);
-                pend.push_back({q, {{op, rot ? g.param[gi] : -1}}});
+                pend.push_back({q, {{op, (int32_t)gi}}});
                 open[q] = (int)ops.size();
                 ops.push_back(d);
             }
@@ -484,7 +477,8 @@ static DensePlan plan_dense_core(const GateList &g, int k, int low, const PlanOp
         for (auto &pd : pend) {
             for (auto &e : pd.gates) {
                 P.rop.push_back(e.first);
-                P.rparam.push_back(e.second);
+                P.rparam.push_back(e.first >= 3 ? g.param[(size_t)e.second] : -1);
+                P.rgate.push_back(e.second);
             }
             P.roff.push_back((int32_t)P.rop.size());
         }
@@ -668,7 +662,7 @@ static DensePlan plan_dense_core(const GateList &g, int k, int low, const PlanOp
                 d.ngates++;
                 d.smask = (uint16_t)smask_compose(gate_smask(op), d.smask);
                 if (rot) d.perm = 0;
-                pend[d.map - map_base].gates.push_back({op, rot ? g.param[gi] : -1});
+                pend[d.map - map_base].gates.push_back({op, (int32_t)gi});
             } else {
                 DOp d{};
                 d.kind = DOP_U1;
@@ -677,8 +671,7 @@ static DensePlan plan_dense_core(const GateList &g, int k, int low, const PlanOp
                 d.smask = (uint16_t)gate_smask(op);
                 d.perm = rot ? 0 : 1;
                 d.map = (uint32_t)(map_base + pend.size());
-                tag(d, gi);
-                pend.push_back({{{op, rot ? g.param[gi] : -1}}});
+                pend.push_back({{{op, (int32_t)gi}}});
                 open[dg] = (int)P.ops.size();
                 P.ops.push_back(d);
             }
@@ -686,7 +679,8 @@ static DensePlan plan_dense_core(const GateList &g, int k, int low, const PlanOp
         for (auto &pd : pend) {
             for (auto &e : pd.gates) {
                 P.rop.push_back(e.first);
-                P.rparam.push_back(e.second);
+                P.rparam.push_back(e.first >= 3 ? g.param[(size_t)e.second] : -1);
+                P.rgate.push_back(e.second);
             }
             P.roff.push_back((int32_t)P.rop.size());
         }
@@ -813,6 +807,7 @@ void plan_append(DensePlan &all, const DensePlan &part) {
     for (size_t i = 1; i < part.roff.size(); ++i) all.roff.push_back(part.roff[i] + rec_off);
     all.rop.insert(all.rop.end(), part.rop.begin(), part.rop.end());
     all.rparam.insert(all.rparam.end(), part.rparam.begin(), part.rparam.end());
+    all.rgate.insert(all.rgate.end(), part.rgate.begin(), part.rgate.end());
     for (DensePass ps : part.passes) {
         ps.op_begin += op_off;
         ps.op_end += op_off;
@@ -823,6 +818,7 @@ void plan_append(DensePlan &all, const DensePlan &part) {
 }
 
 void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin) {
+    const bool tile7 = !P.resident && P.k == kChainTileDigits;
     std::vector<int> order;  // new map index -> old
     std::vector<uint32_t> renum((size_t)P.nmaps(), 0);
     // maps are numbered pair member by pair member, the lower digit first
@@ -855,13 +851,13 @@ void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin) {
                 count = h.ngates;
             } else {
                 int other = h.kind == DOP_CX ? h.b : (h.a == 0 ? 1 : h.a - 1);
-                if (!P.resident && h.kind == DOP_U1 && h.a == 2) other = 3;  // away from digits 0 and 1
+                if (tile7 && h.kind == DOP_U1 && h.a == 2) other = 3;  // away from digits 0 and 1
                 lo = std::min<int>(h.a, other);
                 hi = std::max<int>(h.a, other);
             }
             i = first + count;
             ends_high = lo >= 2;
-            if (!P.resident && P.chain.size() == first_rec && !ends_high) P.chain.push_back(pass_through());
+            if (tile7 && P.chain.size() == first_rec && !ends_high) P.chain.push_back(pass_through());
             // a record holds a CX and one map per digit behind it; longer
             // groups become several records (one in twelve on random circuits)
             unsigned cx = 0;
@@ -902,21 +898,21 @@ void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin) {
             }
             flush();
         }
-        if (!P.resident && (!ends_high || P.chain.size() < first_rec + 2)) {
+        if (tile7 && (!ends_high || P.chain.size() < first_rec + 2)) {
             while (P.chain.size() < first_rec + 1) P.chain.push_back(pass_through());
             P.chain.push_back(pass_through());
         }
     }
     // six qubits: a wave's sweep of a pair below digit 5 stays in the quarter
     // of the tile whose digit 5 is the wave's index (lane_order)
-    if (P.resident && P.k == 6)
+    if (P.k == 6)
         for (size_t i = 0; i + 1 < P.chain.size(); ++i)
             if ((P.chain[i].word & 0xffu) < 10u && (P.chain[i + 1].word & 0xffu) < 10u)
                 P.chain[i].word |= 1u << kChainNoBarrierBit;
     if (begin) begin->push_back((int)P.chain.size());
     P.nchain = (int)P.chain.size();
     // the recipes in the new order, and the ops' indices
-    std::vector<int32_t> roff{0}, rparam;
+    std::vector<int32_t> roff{0}, rparam, rgate;
     std::vector<uint8_t> rop;
     roff.reserve(P.roff.size());
     rop.reserve(P.rop.size());
@@ -924,11 +920,13 @@ void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin) {
     for (int old : order) {
         rop.insert(rop.end(), P.rop.begin() + P.roff[(size_t)old], P.rop.begin() + P.roff[(size_t)old + 1]);
         rparam.insert(rparam.end(), P.rparam.begin() + P.roff[(size_t)old], P.rparam.begin() + P.roff[(size_t)old + 1]);
+        rgate.insert(rgate.end(), P.rgate.begin() + P.roff[(size_t)old], P.rgate.begin() + P.roff[(size_t)old + 1]);
         roff.push_back((int32_t)rop.size());
     }
     P.roff = std::move(roff);
     P.rop = std::move(rop);
     P.rparam = std::move(rparam);
+    P.rgate = std::move(rgate);
     for (DOp &d : P.ops) {
         if (d.kind == DOP_U1) d.map = renum[d.map];
         if (d.kind == DOP_GROUP && (d.perm & ~kSkipBarrier)) {
@@ -987,37 +985,43 @@ GradPlan plan_gradient(const GateList &g, int k_heis, int k_fwd, int low, int64_
     for (int64_t b = 0; b < m; b += every) G.bounds.push_back(b);
     G.bounds.push_back(m);
     if (G.bounds.size() == 1) G.bounds.push_back(m);  // m == 0: one empty segment
-    std::vector<int32_t> slot(m, -1);
-    int32_t ns = 0;
-    const size_t S = G.bounds.size() - 1;
-    for (size_t s = 0; s < S; ++s) {
-        G.seg_slot_begin.push_back(ns);
-        for (int64_t gi = G.bounds[s]; gi < G.bounds[s + 1]; ++gi)
-            if (g.op[gi] >= 3) {
-                slot[gi] = ns++;
-                G.slot_param.push_back(g.param[gi]);
-            }
+    std::vector<int32_t> slot((size_t)m, -1), param_of;
+    for (int64_t gi = 0; gi < m; ++gi)
+        if (g.op[(size_t)gi] >= 3) {
+            slot[(size_t)gi] = (int32_t)param_of.size();
+            param_of.push_back(g.param[(size_t)gi]);
+        }
+    G.nslots = (int)param_of.size();
+    G.param_off.assign((size_t)g.n_params + 1, 0);
+    for (int32_t p : param_of) ++G.param_off[(size_t)p + 1];
+    for (int32_t p = 0; p < g.n_params; ++p) G.param_off[(size_t)p + 1] += G.param_off[(size_t)p];
+    G.param_slot.resize(param_of.size());
+    {
+        std::vector<int32_t> at(G.param_off.begin(), G.param_off.end() - 1);
+        for (size_t j = 0; j < param_of.size(); ++j) G.param_slot[(size_t)at[(size_t)param_of[j]]++] = (int32_t)j;
     }
-    G.seg_slot_begin.push_back(ns);
     G.heis.roff.push_back(0);
     G.fwd.roff.push_back(0);
-    for (size_t s = 0; s < S; ++s) {
+    for (size_t s = 0; s + 1 < G.bounds.size(); ++s) {
         PlanOptions h;
         h.g_begin = G.bounds[s];
         h.g_end = G.bounds[s + 1];
         G.heis_pass_begin.push_back((int)G.heis.passes.size());
         plan_append(G.heis, plan_dense_opts(g, k_heis, low, h));
         PlanOptions f;
-        f.compose = false;
         f.forward = true;
+        f.segments = false;
         f.g_begin = G.bounds[s];
         f.g_end = G.bounds[s + 1];
-        f.slot = &slot;
         G.fwd_pass_begin.push_back((int)G.fwd.passes.size());
+        G.fwd_map_begin.push_back(G.fwd.nmaps());
         plan_append(G.fwd, plan_dense_opts(g, k_fwd, low, f));
     }
     G.heis_pass_begin.push_back((int)G.heis.passes.size());
     G.fwd_pass_begin.push_back((int)G.fwd.passes.size());
+    G.fwd_map_begin.push_back(G.fwd.nmaps());
+    build_chain(G.fwd, 8, &G.fwd_chain_begin);
+    for (size_t r = 0; r < G.fwd.rgate.size(); ++r) G.rslot.push_back(slot[(size_t)G.fwd.rgate[r]]);
     if (G.heis.resident || k_heis == kChainTileDigits) build_chain(G.heis, 8, &G.heis_chain_begin);
     return G;
 }

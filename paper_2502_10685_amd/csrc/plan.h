@@ -34,6 +34,7 @@ struct DensePlan {
     std::vector<int32_t> roff;  // nmaps + 1
     std::vector<uint8_t> rop;
     std::vector<int32_t> rparam;
+    std::vector<int32_t> rgate;  // gate index
     std::vector<DensePass> passes;
     // untracked resident plans: the same ops as chain records (their maps are
     // numbered in record order); nchain of them, then the forward half's
@@ -91,7 +92,6 @@ struct PlanOptions {
     bool segments = true;
     bool forward = false;
     int64_t g_begin = 0, g_end = -1;
-    const std::vector<int32_t> *slot = nullptr;
 };
 DensePlan plan_dense_opts(const GateList &g, int k, int low, const PlanOptions &o);
 
@@ -121,8 +121,11 @@ struct GradPlan {
     DensePlan heis, fwd;
     std::vector<int> heis_pass_begin, fwd_pass_begin;  // S + 1 entries each
     std::vector<int> heis_chain_begin;                 // resident Heisenberg sweep: records per pass, as above
-    std::vector<int32_t> slot_param;                  // slot -> parameter
-    std::vector<int32_t> seg_slot_begin;              // S + 1 entries
+    std::vector<int> fwd_chain_begin;                  // records per forward pass, as above
+    std::vector<int> fwd_map_begin;                    // S + 1 entries
+    int nslots = 0;                                    // rotations, numbered in gate order
+    std::vector<int32_t> rslot;                        // rotation of every entry of fwd's recipes (-1: a Clifford)
+    std::vector<int32_t> param_off, param_slot;        // each parameter's rotations, in gate order
 };
 // Renumbers the maps of grouped passes (resident, or over 7-qubit tiles) in op
 // order and appends each pass's records to P.chain; begin[p] (optional)

@@ -119,13 +119,22 @@ struct TilePassDesc {
 struct GradPassDesc {
     double *c;
     double *r;
-    const DOp *ops;
-    const double *maps;
-    double *partials;
+    const ChainOp *chain;
+    const double *maps;   // forward maps
+    double *partials;     // [3 (map - map_base) + letter][tile]: sums of c x r before the map
     int32_t n, k;
-    int32_t op_begin, op_end;
-    int32_t ntiles, slot_base;
+    int32_t nrec, nmaps;
+    int32_t ntiles, map_base;
     uint64_t qubits;
+};
+// Maps [m0, m1): their sums over the tiles, then the derivative of every
+// rotation in their recipes.
+struct GradRunsDesc {
+    const int32_t *roff, *rparam, *rslot;
+    const uint8_t *rop;
+    const double *theta;
+    const double *partials;
+    double *rot_grad;
 };
 
 // Block -> descriptor mapping of one tile-pass launch.  Descriptors are
@@ -234,8 +243,9 @@ void set_tile_kernel_variant(int k, int variant);
 int tile_kernel_variant(int k);
 hipError_t launch_grad_pass(const GradPassDesc *d_desc, int ntiles, int k, hipStream_t s);
 hipError_t launch_grad_init_state(double *r, int n, hipStream_t s);
-hipError_t launch_grad_reduce(const double *partials, int nslots, int ntiles, double *rot_grad, hipStream_t s);
-hipError_t launch_grad_accumulate(const double *rot_grad, const int32_t *slot_param, int nslots, double *grad,
+hipError_t launch_grad_runs(const GradRunsDesc &d, int m0, int m1, int ntiles, hipStream_t s);
+// grad[p] = sum, in order, of the rotations slots[off[p], off[p + 1])
+hipError_t launch_grad_accumulate(const double *rot_grad, const int32_t *off, const int32_t *slots, double *grad,
                                   int nparams, hipStream_t s);
 hipError_t launch_copy_f64(const double *src, double *dst, long long count, hipStream_t s);
 // count > 1: count weight arrays of 4^n slots back to back (parameter sets);
