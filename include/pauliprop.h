@@ -235,8 +235,9 @@ PP_API pp_status pp_circuit_set_option(pp_circuit *c, pp_option key, int64_t val
  * evaluation as pp_evaluate for a DENSE circuit without term tracking, with
  * the same result bit for bit, but every working buffer (the 4^n weights,
  * the composed per-wire maps, the launch descriptors) in a static device
- * array of the library (24 MiB for what follows, and the rest of its
- * descriptors) per device, held until the process ends.
+ * array of the library (24 MiB for what follows; the rest of its descriptors
+ * and the state's coefficients of circuits evaluated from both ends beside
+ * it) per device, held until the process ends.
  * The call allocates nothing and copies nothing from the host: it enqueues
  * kernel launches on `stream` only.  It reads the circuit's schedule from the
  * device, so the circuit must have been evaluated once with pp_evaluate (or
@@ -373,12 +374,14 @@ typedef struct pp_server pp_server;
  * current device, with four preparation threads that build and upload each
  * request's schedule as it is submitted.  Prepared requests are admitted in
  * submission order while at most max_active are in flight and the sum of
- * their footprints (4^n weights for tiled DENSE requests, the term capacity
- * for SPARSE or tracked ones, none for LDS-resident ones) stays within
- * mem_budget_bytes.  Tiled DENSE requests run in weight buffers of the
- * server's pool, returned at completion and reused; the pool (buffers in
- * use and free) never exceeds mem_budget_bytes, so the budget bounds the
- * device memory of the served weights.  Admitted requests share work: every
+ * their footprints (4^n weights for tiled DENSE requests, twice that for n
+ * <= 10, which are evaluated from both ends; the term capacity for SPARSE or
+ * tracked ones, none for LDS-resident ones) stays within mem_budget_bytes.
+ * Tiled DENSE requests run in weight buffers of the server's pool, returned
+ * at completion and reused; the pool (buffers in use and free) never exceeds
+ * mem_budget_bytes, so the budget bounds the device memory of the served
+ * weights (under a budget below both arrays of a request, one spare array of
+ * its size, at most 8 MiB, is held beside the pool).  Admitted requests share work: every
  * loop iteration issues one batched tile pass per (tile size, weight type)
  * holding the next pass of every active tiled request (requests join and
  * leave between iterations), while circuits that fit one workgroup's LDS run

@@ -200,7 +200,9 @@ __global__ void compact_to_sparse_count_kernel(const unsigned long long *total, 
 // stand-in, so its device address is resolved once per device with
 // hipGetSymbolAddress and only that address is passed to kernels.
 constexpr size_t kNoAllocBytes = (size_t)24 << 20;  // for 4^n weights, 72 bytes per map, 80 per pass
-constexpr size_t kScratchBytes = kNoAllocBytes + ((size_t)2 << 20);  // and the rest of each descriptor
+// and the rest of each descriptor, and the second 4^n array of a circuit run
+// from both ends
+constexpr size_t kScratchBytes = kNoAllocBytes + ((size_t)20 << 20);
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 constexpr int kScratchDevices = 64;
 unsigned char *g_scratch_dev[kScratchDevices] = {};
@@ -232,8 +234,10 @@ pp_status scratch_address(unsigned char **out) {
 __global__ void noalloc_patch_kernel(const pp::ComposeDesc *comp_in, pp::ComposeDesc *comp_out,
                                      const pp::TilePassDesc *pass_in, pp::TilePassDesc *pass_out, int npass,
                                      const pp::ResidentDesc *res_in, pp::ResidentDesc *res_out, void *coef,
-                                     void *xbuf, unsigned *ticket, double *maps, double *expval) {
+                                     void *state, double *part, void *xbuf, unsigned *ticket, double *maps,
+                                     double *expval) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0 && part) *(unsigned *)(part + pp::kMeetBlocks) = 0u;
     if (i == 0 && comp_in) {
         pp::ComposeDesc d = *comp_in;
         d.maps = maps;
@@ -254,7 +258,7 @@ __global__ void noalloc_patch_kernel(const pp::ComposeDesc *comp_in, pp::Compose
     }
     if (i < npass) {
         pp::TilePassDesc d = pass_in[i];
-        d.coef = coef;
+        d.coef = d.forward ? state : coef;
         d.pres = nullptr;
         d.maps = maps;
         d.counters = nullptr;
@@ -276,6 +280,9 @@ int g_resident_block[8] = {64, 64, 64, 64, 64, 512, 512, 1024};
 // twice over, and the exchange buffers of more sets (256 KiB each at n = 7 in
 // FP64) are never needed at once
 constexpr int64_t kSweepChunk = 512;
+// Weights and states of a sweep's tiled circuits run from both ends that are
+// held at once: 64 sets of 10 qubits in FP64 give 32,768 tiles per launch
+constexpr int64_t kSweepMeetBytes = (int64_t)1 << 30;
 
 // Tile qubits by n.  7-qubit tiles take about a third fewer passes, but a
 // workgroup of 1,024 threads per tile: they pay from the n whose 4^(n - 7)
@@ -454,6 +461,19 @@ struct pp_circuit {
     // dense buffers
     void *coef = nullptr;
     uint8_t *pres = nullptr;
+    // tiled circuits run from both ends: the state's coefficients, and where
+    // the product of the two is summed
+    void *rcoef = nullptr;
+    double *d_part = nullptr;
+    // descriptors of step l of an evaluation (a pass of each half that has
+    // one): d_pass[step[l], step[l + 1])
+    std::vector<int> step;
+    // coef holds the observable's weights at the gate where the halves met;
+    // pp_get_terms takes them the rest of the way with the maps of that
+    // evaluation (met_maps once the schedule they belong to is gone)
+    bool met = false;
+    double *met_maps = nullptr;
+    pp::DensePlan met_plan;
     pp::DOp *d_ops = nullptr;
     double *d_maps = nullptr;
     int32_t *d_roff = nullptr, *d_rparam = nullptr;
@@ -525,6 +545,11 @@ struct pp_circuit {
         int64_t cap = 0;  // parameter sets the buffers hold
         double *thetas = nullptr, *maps = nullptr;
         void *coef = nullptr;
+        // run from both ends: the state's coefficients and the products' sums
+        // of `chunk` sets, which are evaluated one chunk after the other
+        void *state = nullptr;
+        double *part = nullptr;
+        int64_t chunk = 0;
         unsigned char *xbuf = nullptr;  // resident circuits, n >= 6: exchange of kSweepChunk sets
         void *dbuf = nullptr;
         size_t dcap = 0;
@@ -561,6 +586,8 @@ void free_sweep(pp_circuit *c) {
     dfree(c->sw.thetas);
     dfree(c->sw.maps);
     dfree(c->sw.coef);
+    dfree(c->sw.state);
+    dfree(c->sw.part);
     dfree(c->sw.xbuf);
     dfree(c->sw.dbuf);
     c->sw.cap = 0;
@@ -570,10 +597,23 @@ void free_sweep(pp_circuit *c) {
     c->sw.out = nullptr;
 }
 
+// The rest of a met evaluation is no longer wanted.
+void drop_met(pp_circuit *c) {
+    c->met = false;
+    dfree(c->met_maps);
+    c->met_plan = pp::DensePlan{};
+}
+
 void free_plan_buffers(pp_circuit *c) {
     free_graph(c);
     free_grad(c);
     free_sweep(c);
+    if (c->met && !c->met_maps && c->plan_valid) {
+        c->met_maps = c->d_maps;
+        c->d_maps = nullptr;
+        c->met_plan = std::move(c->dplan);
+        c->dplan = pp::DensePlan{};
+    }
     dfree(c->d_ops);
     dfree(c->d_maps);
     dfree(c->d_roff);
@@ -613,7 +653,11 @@ void free_grad(pp_circuit *c) {
 void free_state_buffers(pp_circuit *c) {
     free_graph(c);
     free_grad_graph(c);  // captured with this circuit's weight buffer
+    drop_met(c);
     dfree(c->coef);
+    dev_free(c->rcoef);
+    c->rcoef = nullptr;
+    dfree(c->d_part);
     dfree(c->pres);
     dfree(c->d_counters);
     dfree(c->d_result);
@@ -637,6 +681,13 @@ void free_state_buffers(pp_circuit *c) {
 }
 
 int64_t dense_slots(int n) { return (int64_t)1 << (2 * n); }
+
+// Tiled circuits of up to kMeetMaxN qubits are evaluated from both ends: their
+// 4^(n - k) tiles leave most of the chip idle and each pass is mostly latency,
+// so two halves side by side take half the launches.  From 11 qubits on a
+// pass fills the chip, and the second array would double a circuit's memory.
+constexpr int kMeetMaxN = 10;
+bool meets(const pp_circuit *c, int k) { return k < c->n && c->n <= kMeetMaxN && !c->track && !c->keep_coef; }
 
 std::atomic<uint64_t> g_plan_gen{0};
 
@@ -801,7 +852,8 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
     const bool seg = c->engine == PP_ENGINE_DENSE && (tv6 == 3 || tv6 == 4);
     // the descriptors hold the weight pointer they were built with
     if (c->plan_valid && c->plan_track == c->track && c->plan_k == k && c->plan_coef == c->coef &&
-        c->plan_frame == frame && c->plan_ramp_opt == c->ramp_opt && c->plan_seg == seg)
+        c->plan_frame == frame && c->plan_ramp_opt == c->ramp_opt && c->plan_seg == seg &&
+        (!weights || c->dplan.fwd_pass < 0 || c->rcoef))
         return PP_OK;
     free_plan_buffers(c);
     if (c->track && c->engine == PP_ENGINE_DENSE && !c->pres) HIPCHK(dalloc(&c->pres, (size_t)dense_slots(c->n)));
@@ -814,6 +866,7 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
         }
     } else {
         c->ramp_gate = -1;
+        c->pass_recs.clear();
         if (ramp_wanted(c)) {
             const int64_t sw = ramp_switch_gate(c);
             if (sw < c->g.m) {
@@ -836,10 +889,11 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
             pp::PlanOptions o;
             o.g_end = c->ramp_gate;  // the dense sweep takes the gates before the frame's
             o.segments = seg;
-            c->dplan = k == c->n ? pp::plan_meet(c->g, kLowQubits, c->ramp_gate, c->dbytes)
-                                 : pp::plan_dense_opts(c->g, k, kLowQubits, o);
-        } else if (k == c->n && !c->track && !c->keep_coef) {
-            c->dplan = pp::plan_meet(c->g, kLowQubits, c->g.m, c->dbytes);
+            c->dplan = k == c->n || meets(c, k)
+                           ? pp::plan_meet(c->g, k, kLowQubits, c->ramp_gate, seg, c->dbytes, &c->pass_recs)
+                           : pp::plan_dense_opts(c->g, k, kLowQubits, o);
+        } else if ((k == c->n && !c->track && !c->keep_coef) || meets(c, k)) {
+            c->dplan = pp::plan_meet(c->g, k, kLowQubits, c->g.m, seg, c->dbytes, &c->pass_recs);
         } else {
             pp::PlanOptions o;
             o.compose = o.group = o.reorder = c->track == 0;
@@ -847,8 +901,8 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
             c->dplan = pp::plan_dense_opts(c->g, k, kLowQubits, o);
             if (k == c->n && !c->track) pp::build_chain(c->dplan, c->dbytes);
         }
-        c->pass_recs.clear();
-        if (k < c->n && k == pp::kChainTileDigits && !c->track) pp::build_chain(c->dplan, c->dbytes, &c->pass_recs);
+        if (k < c->n && k == pp::kChainTileDigits && !c->track && c->dplan.fwd_from < 0)
+            pp::build_chain(c->dplan, c->dbytes, &c->pass_recs);
         const pp::DensePlan &P = c->dplan;
         {
             // the kernels trust the schedule's digits and segment bounds
@@ -908,25 +962,43 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
                 rec = c->pass_recs;
             }
             const int ntiles = (int)((int64_t)1 << (2 * (c->n - k)));
-            for (size_t pi = 0; pi < P.passes.size(); ++pi) {
-                const pp::DensePass &ps = P.passes[pi];
-                pp::TilePassDesc d{};
-                if (!rec.empty()) set_chain(d, P, ps, c->d_chain, rec[pi], rec[pi + 1], c->dbytes);
-                d.coef = c->coef;
-                d.pres = c->track ? c->pres : nullptr;
-                d.ops = c->d_ops;
-                d.maps = c->d_maps;
-                d.counters = c->d_counters;
-                d.n = c->n;
-                d.k = k;
-                d.op_begin = ps.op_begin;
-                d.op_end = ps.op_end;
-                d.tile_begin = 0;
-                d.ntiles = ntiles;
-                d.qubits = 0;
-                for (int j = 0; j < k; ++j) d.qubits |= (uint64_t)ps.qubit[j] << (8 * j);
-                d.reg_entry = pp::pass_reg_entry(P, ps);
-                c->h_pass.push_back(d);
+            const size_t nh = P.fwd_pass >= 0 ? (size_t)P.fwd_pass : P.passes.size();
+            const size_t nf = P.passes.size() - nh;
+            if (P.fwd_pass >= 0) {
+                if (weights && !c->rcoef && dev_alloc(&c->rcoef, (size_t)dense_slots(c->n) * c->dbytes) != hipSuccess) {
+                    c->rcoef = nullptr;
+                    return fail(PP_ERR_NOMEM, "state coefficients");
+                }
+                if (!c->d_part) {
+                    HIPCHK(dalloc(&c->d_part, (size_t)pp::kMeetDoubles));
+                    HIPCHK(hipMemset(c->d_part, 0, sizeof(double) * pp::kMeetDoubles));  // the ticket
+                }
+            }
+            c->step.assign(1, 0);
+            for (size_t l = 0; l < std::max(nh, nf); ++l) {
+                for (size_t pi : {l < nh ? l : SIZE_MAX, l < nf ? nh + l : SIZE_MAX}) {
+                    if (pi == SIZE_MAX) continue;
+                    const pp::DensePass &ps = P.passes[pi];
+                    pp::TilePassDesc d{};
+                    if (!rec.empty()) set_chain(d, P, ps, c->d_chain, rec[pi], rec[pi + 1], c->dbytes);
+                    d.forward = pi >= nh;
+                    d.coef = d.forward ? c->rcoef : c->coef;
+                    d.pres = c->track ? c->pres : nullptr;
+                    d.ops = c->d_ops;
+                    d.maps = c->d_maps;
+                    d.counters = c->d_counters;
+                    d.n = c->n;
+                    d.k = k;
+                    d.op_begin = ps.op_begin;
+                    d.op_end = ps.op_end;
+                    d.tile_begin = 0;
+                    d.ntiles = ntiles;
+                    d.qubits = 0;
+                    for (int j = 0; j < k; ++j) d.qubits |= (uint64_t)ps.qubit[j] << (8 * j);
+                    d.reg_entry = pp::pass_reg_entry(P, ps);
+                    c->h_pass.push_back(d);
+                }
+                c->step.push_back((int)c->h_pass.size());
             }
             if ((r = upload_vec(&c->d_pass, c->h_pass)) != PP_OK) return r;
         }
@@ -960,7 +1032,9 @@ void fill_plan_stats(pp_circuit *c) {
         const pp::DensePlan &P = c->dplan;
         s.ops = 0;
         for (const pp::DOp &d : P.ops) s.ops += d.kind != pp::DOP_GROUP && d.kind != pp::DOP_SEG;
-        s.passes = (int64_t)P.passes.size() + (c->ramp_gate >= 0 ? (int64_t)c->fplan.passes.size() : 0);
+        // tiled: launches over the tiles (of both halves of a circuit run from both ends)
+        const int64_t steps = P.resident ? (int64_t)P.passes.size() : (int64_t)c->step.size() - 1;
+        s.passes = steps + (c->ramp_gate >= 0 ? (int64_t)c->fplan.passes.size() : 0);
         s.tile_qubits = P.k;
         const int64_t slots = dense_slots(c->n);
         const int64_t per = 2 * slots * (c->dbytes + (c->track ? 1 : 0));
@@ -968,7 +1042,7 @@ void fill_plan_stats(pp_circuit *c) {
             s.launches = 1 + (P.nmaps() > 0 ? 1 : 0);
             s.bytes_per_eval = 0;
         } else {
-            s.launches = (int64_t)P.passes.size() + 3 + (P.nmaps() > 0 ? 1 : 0) + (c->track ? 1 : 0);
+            s.launches = steps + 3 + (P.nmaps() > 0 ? 1 : 0) + (c->track ? 1 : 0);
             s.bytes_per_eval = per * (int64_t)P.passes.size();
         }
     } else {
@@ -987,6 +1061,25 @@ void fill_plan_stats(pp_circuit *c) {
     }
 }
 
+// An evaluation that leaves its weights with the circuit was enqueued.
+void mark_evaluated(pp_circuit *c) {
+    c->evaluated = true;
+    c->last_track = c->track;
+    drop_met(c);
+    c->met = c->engine == PP_ENGINE_DENSE && c->dplan.fwd_pass >= 0;
+}
+
+// The tiles of step l of an evaluation (descriptors in c->d_pass's order).
+pp::TileGroups step_groups(const pp_circuit *c, size_t l) {
+    pp::TileGroups grp{};
+    const int shift = 2 * (c->n - c->dplan.k);
+    grp.ngroups = 1;
+    grp.first_block[1] = (c->step[l + 1] - c->step[l]) << shift;
+    grp.first_desc[0] = c->step[l];
+    grp.shift[0] = shift;
+    return grp;
+}
+
 pp_status enqueue_dense_body(pp_circuit *c, hipStream_t s, double *out) {
     const pp::DensePlan &P = c->dplan;
     if (c->track) hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, s, c->d_counters, 4);
@@ -1001,7 +1094,8 @@ pp_status enqueue_dense_body(pp_circuit *c, hipStream_t s, double *out) {
             HIPCHK(pp::launch_frame_pass(c->fb, c->dbytes, c->fplan.passes[(size_t)i], c->d_theta, i, s));
         }
         ProfScope ps(PC_INIT, s);
-        HIPCHK(pp::launch_dense_init(c->coef, nullptr, c->n, c->dbytes, c->d_ox, c->d_oz, c->d_oc, 0, true, s));
+        HIPCHK(pp::launch_dense_init(c->coef, nullptr, c->n, c->dbytes, c->d_ox, c->d_oz, c->d_oc, 0, true, s, 1,
+                                     P.fwd_pass >= 0 ? c->rcoef : nullptr));
         HIPCHK(pp::launch_frame_to_dense(c->fb, c->dbytes, c->d_codes, (int)c->splan.codes.size(), np, c->coef, s));
     }
     if (P.nmaps() > 0) {
@@ -1019,28 +1113,23 @@ pp_status enqueue_dense_body(pp_circuit *c, hipStream_t s, double *out) {
         HIPCHK(hipGetLastError());
         return PP_OK;
     }
+    const bool meet = P.fwd_pass >= 0;
     if (c->ramp_gate < 0) {
         ProfScope ps(PC_INIT, s);
         HIPCHK(pp::launch_dense_init(c->coef, c->track ? c->pres : nullptr, c->n, c->dbytes, c->d_ox, c->d_oz,
-                                     c->d_oc, (int)c->ox.size(), c->obs_distinct, s));
+                                     c->d_oc, (int)c->ox.size(), c->obs_distinct, s, 1, meet ? c->rcoef : nullptr));
     }
-    const int shift = 2 * (c->n - P.k);
     TileSpan span;
     span.begin(s);
-    for (size_t p = 0; p < P.passes.size(); ++p) {
-        pp::TileGroups grp{};
-        grp.ngroups = 1;
-        grp.first_block[0] = 0;
-        grp.first_block[1] = 1 << shift;
-        grp.first_desc[0] = (int32_t)p;
-        grp.shift[0] = shift;
-        HIPCHK(pp::launch_tile_pass(c->d_pass, grp, P.k, c->dbytes, c->track != 0, s));
+    for (size_t l = 0; l + 1 < c->step.size(); ++l) {
+        HIPCHK(pp::launch_tile_pass(c->d_pass, step_groups(c, l), P.k, c->dbytes, c->track != 0, s));
         span.count();
     }
     span.end();
     {
         ProfScope ps(PC_READOUT, s);
-        HIPCHK(pp::launch_dense_readout(c->coef, c->n, c->dbytes, out, s));
+        if (meet) HIPCHK(pp::launch_meet_readout(c->coef, c->rcoef, c->n, c->dbytes, c->d_part, out, s));
+        else HIPCHK(pp::launch_dense_readout(c->coef, c->n, c->dbytes, out, s));
     }
     if (c->track) HIPCHK(pp::launch_dense_count(c->pres, c->n, c->d_counters + 1, s));
     return PP_OK;
@@ -1196,6 +1285,7 @@ void pp_circuit_destroy(pp_circuit *c) {
     dfree(c->d_psr_rot);
     dfree(c->d_psr_thetas);
     dfree(c->d_psr_vals);
+    c->met = false;
     free_plan_buffers(c);
     free_state_buffers(c);
     dfree(c->d_theta);
@@ -1325,7 +1415,9 @@ pp_status pp_circuit_load_gates(pp_circuit *c, int64_t m, const uint8_t *op, con
     if (n_params == 0) c->have_theta = true;
     c->have_gates = true;
     c->gates_gen++;
+    c->met = false;
     free_plan_buffers(c);
+    drop_met(c);
     c->evaluated = false;
     return PP_OK;
 }
@@ -1493,8 +1585,7 @@ pp_status pp_evaluate(pp_circuit *c, void *stream, double *d_expval) {
         r = enqueue_dense_body(c, s, d_expval);
     }
     if (r != PP_OK) return r;
-    c->evaluated = true;
-    c->last_track = c->track;
+    mark_evaluated(c);
     c->frame_ran = sparse && c->plan_frame;
     c->frame_terms = false;
     return PP_OK;
@@ -1516,7 +1607,7 @@ pp_status pp_evaluate_noalloc(pp_circuit *c, void *stream, double *d_expval) {
     unsigned char *base = nullptr;
     if ((r = scratch_address(&base)) != PP_OK) return r;
     auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
-    const size_t npass = P.resident ? 0 : P.passes.size();
+    const size_t npass = P.resident ? 0 : c->h_pass.size();
     const size_t off_comp = 0;
     const size_t off_res = up(sizeof(pp::ComposeDesc));
     const size_t off_pass = off_res + up(sizeof(pp::ResidentDesc));
@@ -1524,9 +1615,13 @@ pp_status pp_evaluate_noalloc(pp_circuit *c, void *stream, double *d_expval) {
     const size_t off_coef = off_maps + up((size_t)9 * sizeof(double) * std::max(P.nmaps(), 1));
     // tiled: the 4^n weights; resident: the directions' exchange and ticket
     const size_t xbytes = P.resident ? up(pp::chain_exchange_bytes(c->n, c->dbytes)) : 0;
-    const size_t coef_bytes = P.resident ? xbytes + 256 : (size_t)dense_slots(c->n) * c->dbytes;
+    const bool meet = P.fwd_pass >= 0;  // then the state's coefficients and the product's sums
+    const size_t slot_bytes = (size_t)dense_slots(c->n) * c->dbytes;
+    const size_t off_state = off_coef + up(slot_bytes), off_part = off_state + up(slot_bytes);
+    const size_t coef_bytes = P.resident ? xbytes + 256
+                                         : (meet ? off_part - off_coef + sizeof(double) * pp::kMeetDoubles : slot_bytes);
     const size_t counted = 512 + up(npass * 80) + up((size_t)72 * std::max(P.nmaps(), 1)) +
-                           (P.resident ? 0 : (size_t)dense_slots(c->n) * c->dbytes);
+                           (P.resident ? 0 : slot_bytes);
     if (counted > kNoAllocBytes || off_coef + coef_bytes > kScratchBytes)
         return fail(PP_ERR_CAPACITY, "pp_evaluate_noalloc: working set of " + std::to_string(counted) +
                                          " bytes exceeds the " + std::to_string(kNoAllocBytes) + "-byte array");
@@ -1536,10 +1631,12 @@ pp_status pp_evaluate_noalloc(pp_circuit *c, void *stream, double *d_expval) {
     pp::TilePassDesc *pass = (pp::TilePassDesc *)(base + off_pass);
     double *maps = (double *)(base + off_maps);
     void *coef = base + off_coef;
+    void *state = meet ? base + off_state : nullptr;
+    double *part = meet ? (double *)(base + off_part) : nullptr;
     const int pblocks = (int)std::max<size_t>(1, (npass + 255) / 256);
     hipLaunchKernelGGL(noalloc_patch_kernel, dim3(pblocks), dim3(256), 0, s, c->d_comp, comp,
                        P.resident ? nullptr : c->d_pass, pass, (int)npass, P.resident ? c->d_res : nullptr, res, coef,
-                       coef, (unsigned *)(base + off_coef + xbytes), maps, d_expval);
+                       state, part, coef, (unsigned *)(base + off_coef + xbytes), maps, d_expval);
     HIPCHK(hipGetLastError());
     if (P.nmaps() > 0) HIPCHK(pp::launch_compose(comp, 1, s, P.nmaps()));
     if (P.resident) {
@@ -1547,18 +1644,11 @@ pp_status pp_evaluate_noalloc(pp_circuit *c, void *stream, double *d_expval) {
         return PP_OK;
     }
     HIPCHK(pp::launch_dense_init(coef, nullptr, c->n, c->dbytes, c->d_ox, c->d_oz, c->d_oc, (int)c->ox.size(),
-                                 c->obs_distinct, s));
-    const int shift = 2 * (c->n - P.k);
-    for (size_t p = 0; p < npass; ++p) {
-        pp::TileGroups grp{};
-        grp.ngroups = 1;
-        grp.first_block[0] = 0;
-        grp.first_block[1] = 1 << shift;
-        grp.first_desc[0] = (int32_t)p;
-        grp.shift[0] = shift;
-        HIPCHK(pp::launch_tile_pass(pass, grp, P.k, c->dbytes, false, s));
-    }
-    HIPCHK(pp::launch_dense_readout(coef, c->n, c->dbytes, d_expval, s));
+                                 c->obs_distinct, s, 1, state));
+    for (size_t l = 0; l + 1 < c->step.size(); ++l)
+        HIPCHK(pp::launch_tile_pass(pass, step_groups(c, l), P.k, c->dbytes, false, s));
+    if (meet) HIPCHK(pp::launch_meet_readout(coef, state, c->n, c->dbytes, part, d_expval, s));
+    else HIPCHK(pp::launch_dense_readout(coef, c->n, c->dbytes, d_expval, s));
     return PP_OK;
 }
 
@@ -1596,6 +1686,62 @@ pp_status pp_get_stats(pp_circuit *c, pp_stats *out) {
     return PP_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// Takes the weights of a circuit run from both ends the rest of the way: the
+// forward half's gates, last first, with the maps of the evaluation that left
+// them (the forward maps' transposes).
+pp_status finish_met(pp_circuit *c, hipStream_t s) {
+    const pp::DensePlan &P = c->met_maps ? c->met_plan : c->dplan;
+    const double *maps = c->met_maps ? c->met_maps : c->d_maps;
+    const pp::DensePlan R = pp::plan_reversed_forward(P);
+    pp::DOp *ops = nullptr;
+    pp::TilePassDesc *pass = nullptr;
+    double *back = nullptr;
+    std::vector<pp::TilePassDesc> td;
+    const int shift = 2 * (c->n - R.k);
+    pp_status r = upload_vec(&ops, R.ops);
+    hipError_t e = r == PP_OK ? dalloc(&back, (size_t)9 * std::max(P.nmaps(), 1)) : hipErrorOutOfMemory;
+    if (e == hipSuccess) {
+        for (const pp::DensePass &ps : R.passes) {
+            pp::TilePassDesc d{};
+            d.coef = c->coef;
+            d.ops = ops;
+            d.maps = back;
+            d.n = c->n;
+            d.k = R.k;
+            d.op_begin = ps.op_begin;
+            d.op_end = ps.op_end;
+            d.ntiles = 1 << shift;
+            for (int j = 0; j < R.k; ++j) d.qubits |= (uint64_t)ps.qubit[j] << (8 * j);
+            td.push_back(d);
+        }
+        if ((r = upload_vec(&pass, td)) == PP_OK) e = pp::launch_transpose_maps(maps, back, P.fwd_from, P.nmaps(), s);
+        for (size_t p = 0; r == PP_OK && e == hipSuccess && p < td.size(); ++p) {
+            pp::TileGroups grp{};
+            grp.ngroups = 1;
+            grp.first_block[1] = 1 << shift;
+            grp.first_desc[0] = (int32_t)p;
+            grp.shift[0] = shift;
+            e = pp::launch_tile_pass_plain(pass, grp, R.k, c->dbytes, s);
+        }
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+    }
+    dfree(ops);
+    dfree(pass);
+    dfree(back);
+    if (r != PP_OK) return r;
+    if (e != hipSuccess) return fail(PP_ERR_DEVICE, std::string("rest of the evaluation: ") + hipGetErrorString(e));
+    drop_met(c);
+    return PP_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
 pp_status pp_get_terms(pp_circuit *c, void *stream, int64_t capacity, uint64_t *x, uint64_t *z, double *coeff,
                        int64_t *n_out) {
     if (!c || !n_out) return fail(PP_ERR_INVALID, "null argument");
@@ -1605,6 +1751,10 @@ pp_status pp_get_terms(pp_circuit *c, void *stream, int64_t capacity, uint64_t *
     if (c->engine == PP_ENGINE_DENSE && !c->last_track && c->dplan.resident)
         return fail(PP_ERR_STATE, "an untracked LDS-resident evaluation keeps its weights on chip: set "
                                   "PP_OPT_TRACK_TERMS = 1 for the evaluation");
+    if (c->met) {
+        pp_status mr = finish_met(c, s);
+        if (mr != PP_OK) return mr;
+    }
     const uint64_t *sx = nullptr, *sz = nullptr;
     const void *sc = nullptr;
     int cbytes = c->dbytes;
@@ -1807,6 +1957,7 @@ struct BatchCache {
     std::vector<Launch> tiles;     // tile passes
     size_t io_off = 0;             // start/readout descriptors of the tiled circuits
     int io_max_n = 0;
+    int io_meet = 0;               // the first io_meet of them are run from both ends
     std::vector<int> tiled;        // indices of tiled circuits
     std::vector<int> single;       // indices evaluated one by one
     // the whole step captured once (every circuit sets PP_OPT_USE_GRAPH)
@@ -1870,8 +2021,9 @@ pp_status enqueue_batch_tail(BatchCache &B, int dbytes, hipStream_t s) {
     }
     if (!B.tiled.empty()) {
         ProfScope ps(PC_READOUT, s);
-        HIPCHK(pp::launch_dense_readout_many((const pp::DenseIODesc *)(base + B.io_off), (int)B.tiled.size(), dbytes,
-                                             s));
+        const pp::DenseIODesc *io = (const pp::DenseIODesc *)(base + B.io_off);
+        HIPCHK(pp::launch_meet_readout_many(io, B.io_meet, kMeetMaxN, dbytes, s));
+        HIPCHK(pp::launch_dense_readout_many(io + B.io_meet, (int)B.tiled.size() - B.io_meet, dbytes, s));
     }
     return PP_OK;
 }
@@ -1936,7 +2088,7 @@ pp_status build_batch(BatchCache &B, pp_circuit *const *cs, int64_t count, doubl
     for (int i : B.tiled) {
         const int k = cs[i]->dplan.k;
         by_k[k].push_back(i);
-        maxp[k] = std::max(maxp[k], cs[i]->h_pass.size());
+        maxp[k] = std::max(maxp[k], cs[i]->step.size() - 1);
         bytes += cs[i]->h_pass.size() * sizeof(pp::TilePassDesc);
     }
     for (int k = 4; k <= 7; ++k) {
@@ -1956,11 +2108,18 @@ pp_status build_batch(BatchCache &B, pp_circuit *const *cs, int64_t count, doubl
     BatchWriter out{(unsigned char *)U.staging.host, (unsigned char *)U.d};
     if (!comp.empty()) B.head.push_back({0, 0, out.put(comp), (int)comp.size(), comp_max, {}});
     if (!B.tiled.empty()) {
+        // those run from both ends first: the two kinds are read out apart
+        std::vector<int> by_end(B.tiled);
+        std::stable_partition(by_end.begin(), by_end.end(), [&](int i) { return cs[i]->dplan.fwd_pass >= 0; });
         std::vector<pp::DenseIODesc> io;
-        for (int i : B.tiled) {
+        B.io_meet = 0;
+        for (int i : by_end) {
             pp_circuit *c = cs[i];
+            const bool meet = c->dplan.fwd_pass >= 0;
             io.push_back(pp::DenseIODesc{c->coef, c->d_ox, c->d_oz, c->d_oc, d_expvals + i, c->n,
-                                         (int32_t)c->ox.size(), c->obs_distinct, 0});
+                                         (int32_t)c->ox.size(), c->obs_distinct, 0, meet ? c->rcoef : nullptr,
+                                         meet ? c->d_part : nullptr});
+            B.io_meet += meet;
             B.io_max_n = std::max(B.io_max_n, c->n);
         }
         B.io_off = out.put(io);
@@ -1998,19 +2157,21 @@ pp_status build_batch(BatchCache &B, pp_circuit *const *cs, int64_t count, doubl
     // descriptors are grouped by tile count, and within one n circuits whose
     // pass l holds more ops come first: workgroups take tiles with a fixed
     // stride, so the last round of tiles is the light one
-    std::vector<std::pair<uint64_t, int>> order;
+    std::vector<std::pair<uint64_t, const pp::TilePassDesc *>> order;
     std::vector<pp::TilePassDesc> td;
     for (int k = 4; k <= 7 && r == PP_OK; ++k) {
         for (size_t l = 0; l < maxp[k] && r == PP_OK; ++l) {
             order.clear();
             for (size_t j = 0; j < by_k[k].size(); ++j) {
                 const pp_circuit *c = cs[by_k[k][j]];
-                if (l >= c->h_pass.size()) continue;
-                const pp::TilePassDesc &p = c->h_pass[l];
-                order.push_back({((uint64_t)(64 - c->n) << 48) | ((uint64_t)(0xffff - std::min(p.op_end - p.op_begin, 0xffff)) << 32) | j,
-                                 by_k[k][j]});
+                if (l + 1 >= c->step.size()) continue;
+                for (int q = c->step[l]; q < c->step[l + 1]; ++q) {
+                    const pp::TilePassDesc &p = c->h_pass[(size_t)q];
+                    const uint64_t light = 0xffff - std::min(p.op_end - p.op_begin, 0xffff);
+                    order.push_back({((uint64_t)(64 - c->n) << 48) | (light << 32) | j, &p});
+                }
             }
-            std::sort(order.begin(), order.end());
+            std::stable_sort(order.begin(), order.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
             td.clear();
             pp::TileGroups tg{};
             int run = 0, last_n = -1;
@@ -2022,7 +2183,7 @@ pp_status build_batch(BatchCache &B, pp_circuit *const *cs, int64_t count, doubl
                 run = 0;
             };
             for (const auto &o : order) {
-                pp::TilePassDesc d = cs[o.second]->h_pass[l];
+                pp::TilePassDesc d = *o.second;
                 if (d.n != last_n) {
                     if (tg.ngroups == pp::kMaxTileGroups) close();
                     tg.first_block[tg.ngroups] = run;
@@ -2134,8 +2295,7 @@ extern "C" pp_status pp_evaluate_batch(pp_circuit *const *cs, int64_t count, voi
     if (!U.done) HIPCHK(hipEventCreateWithFlags(&U.done, hipEventDisableTiming));
     HIPCHK(hipEventRecord(U.done, s));
     for (int64_t i = 0; i < count; ++i) {
-        cs[i]->evaluated = true;
-        cs[i]->last_track = cs[i]->track;
+        mark_evaluated(cs[i]);
     }
     return PP_OK;
 }
@@ -2287,13 +2447,21 @@ extern "C" pp_status pp_evaluate_thetas(pp_circuit *c, int64_t count, const doub
     const int64_t np = std::max<int64_t>(c->g.n_params, 1);
     const int64_t nm = std::max(P.nmaps(), 1);
     const int64_t slots = dense_slots(c->n);
+    const bool meet = P.fwd_pass >= 0;
     if (count > W.cap || W.gen != c->plan_gen) {
         HIPCHK(hipStreamSynchronize(s));
         if (W.gen != c->plan_gen || count > W.cap) free_sweep(c);
         const int64_t cap = count;
         hipError_t e = dalloc(&W.thetas, (size_t)(np * cap));
         if (e == hipSuccess) e = dalloc(&W.maps, (size_t)(9 * nm * cap));
-        if (e == hipSuccess && !P.resident) e = dev_alloc(&W.coef, (size_t)slots * c->dbytes * cap);
+        W.chunk = meet ? std::min(cap, std::max<int64_t>(1, kSweepMeetBytes / (2 * slots * c->dbytes))) : cap;
+        if (e == hipSuccess && !P.resident) e = dev_alloc(&W.coef, (size_t)slots * c->dbytes * W.chunk);
+        if (e == hipSuccess && meet) e = dev_alloc(&W.state, (size_t)slots * c->dbytes * W.chunk);
+        if (e == hipSuccess && meet) {
+            e = dalloc(&W.part, (size_t)(pp::kMeetDoubles * W.chunk));
+            if (e == hipSuccess) e = hipMemset(W.part, 0, sizeof(double) * pp::kMeetDoubles * W.chunk);  // the tickets
+            if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+        }
         const size_t xb = P.resident ? pp::chain_exchange_bytes(c->n, c->dbytes) : 0;
         if (e == hipSuccess && xb) {
             const size_t bytes = (size_t)std::min(cap, kSweepChunk) * (xb + 256);
@@ -2348,15 +2516,18 @@ extern "C" pp_status pp_evaluate_thetas(pp_circuit *c, int64_t count, const doub
             W.res_off = append(rd.data(), rd.size() * sizeof(rd[0]));
         } else {
             std::vector<pp::TilePassDesc> td;
-            td.reserve((size_t)count * P.passes.size());
-            for (size_t l = 0; l < P.passes.size(); ++l)
-                for (int64_t i = 0; i < count; ++i) {
-                    pp::TilePassDesc d = c->h_pass[l];
-                    d.coef = (unsigned char *)W.coef + (size_t)i * slots * c->dbytes;
-                    d.maps = W.maps + i * nm * 9;
-                    d.tile_begin = (int32_t)(i * d.ntiles);
-                    td.push_back(d);
-                }
+            td.reserve((size_t)count * c->h_pass.size());
+            for (int64_t i0 = 0; i0 < count; i0 += W.chunk) {
+                const int64_t cs = std::min(count - i0, W.chunk);
+                for (size_t q = 0; q < c->h_pass.size(); ++q)
+                    for (int64_t i = 0; i < cs; ++i) {
+                        pp::TilePassDesc d = c->h_pass[q];
+                        d.coef = (unsigned char *)(d.forward ? W.state : W.coef) + (size_t)i * slots * c->dbytes;
+                        d.maps = W.maps + (i0 + i) * nm * 9;
+                        d.tile_begin = (int32_t)(i * d.ntiles);
+                        td.push_back(d);
+                    }
+            }
             W.pass_off = td.empty() ? 0 : append(td.data(), td.size() * sizeof(td[0]));
         }
         if (blob.size() > W.dcap) {
@@ -2383,32 +2554,35 @@ extern "C" pp_status pp_evaluate_thetas(pp_circuit *c, int64_t count, const doub
                                     (int)std::min(count - i, kSweepChunk), c->n, c->dbytes, true, nullptr, s));
         return PP_OK;
     }
-    {
-        ProfScope ps(PC_INIT, s);
-        HIPCHK(pp::launch_dense_init(W.coef, nullptr, c->n, c->dbytes, c->d_ox, c->d_oz, c->d_oc, (int)c->ox.size(),
-                                     c->obs_distinct, s, (int)count));
-    }
     const int shift = 2 * (c->n - P.k);
     const int64_t ntiles = (int64_t)1 << shift;
-    if (count * ntiles > INT32_MAX) return fail(PP_ERR_INVALID, "too many tiles in one sweep launch");
-    TileSpan span;
-    span.begin(s);
-    for (size_t l = 0; l < P.passes.size(); ++l) {
-        // one launch: the sets' descriptors of pass l are consecutive
-        pp::TileGroups grp{};
-        grp.ngroups = 1;
-        grp.first_block[0] = 0;
-        grp.first_block[1] = (int32_t)(count * ntiles);
-        grp.first_desc[0] = 0;
-        grp.shift[0] = shift;
-        HIPCHK(pp::launch_tile_pass((const pp::TilePassDesc *)(base + W.pass_off) + l * count, grp, P.k, c->dbytes,
-                                    false, s));
-        span.count();
-    }
-    span.end();
-    {
+    if (2 * std::min(count, W.chunk) * ntiles > INT32_MAX) return fail(PP_ERR_INVALID, "too many tiles in one sweep launch");
+    for (int64_t i0 = 0; i0 < count; i0 += W.chunk) {
+        const int cs = (int)std::min(count - i0, W.chunk);
+        {
+            ProfScope ps(PC_INIT, s);
+            HIPCHK(pp::launch_dense_init(W.coef, nullptr, c->n, c->dbytes, c->d_ox, c->d_oz, c->d_oc,
+                                         (int)c->ox.size(), c->obs_distinct, s, cs, W.state));
+        }
+        const pp::TilePassDesc *pass =
+            (const pp::TilePassDesc *)(base + W.pass_off) + (size_t)i0 * c->h_pass.size();
+        TileSpan span;
+        span.begin(s);
+        for (size_t l = 0; l + 1 < c->step.size(); ++l) {
+            // one launch: the sets' descriptors of a pass are consecutive
+            pp::TileGroups grp{};
+            grp.ngroups = 1;
+            grp.first_block[1] = (int32_t)((c->step[l + 1] - c->step[l]) * cs * ntiles);
+            grp.shift[0] = shift;
+            HIPCHK(pp::launch_tile_pass(pass + (size_t)c->step[l] * cs, grp, P.k, c->dbytes, false, s));
+            span.count();
+        }
+        span.end();
         ProfScope ps(PC_READOUT, s);
-        HIPCHK(pp::launch_dense_readout(W.coef, c->n, c->dbytes, d_expvals, s, (int)count));
+        if (meet)
+            HIPCHK(pp::launch_meet_readout(W.coef, W.state, c->n, c->dbytes, W.part, d_expvals + i0, s, cs));
+        else
+            HIPCHK(pp::launch_dense_readout(W.coef, c->n, c->dbytes, d_expvals + i0, s, cs));
     }
     return PP_OK;
 }
@@ -2463,6 +2637,7 @@ extern "C" pp_status pp_gradient(pp_circuit *c, void *stream, int32_t checkpoint
     }
     fill_plan_stats(c);
     c->evaluated = false;  // the dense weights now hold the forward-swept set
+    drop_met(c);
     return PP_OK;
 }
 
@@ -2670,9 +2845,10 @@ struct ServedReq {
     bool resident = false;  // runs whole in one LDS-resident launch
     bool pooled = false;    // tiled DENSE: weights in a buffer of the server's pool
     void *buf = nullptr;    // the pool buffer while active
+    bool spare = false;     // its state's coefficients are in the server's spare array
     int64_t foot = 0;       // bytes counted against the budget while active
     double t_submit = 0, t_done = 0;
-    size_t pass = 0;
+    size_t step = 0;
     int slot = -1;
     hipEvent_t ev = nullptr;
     double result = 0;
@@ -2712,6 +2888,8 @@ struct pp_server {
     // weight buffers of tiled requests: returned at completion and reused;
     // held (in use + free) never exceeds the budget
     std::multimap<size_t, void *> pool_free;
+    void *spare = nullptr;  // see prepare_request
+    size_t spare_bytes = 0;
     int64_t pool_held = 0, pool_peak = 0;
     struct Ring {
         void *d = nullptr, *h = nullptr;
@@ -2804,7 +2982,7 @@ pp_status after_theta(const pp_circuit *c, hipStream_t st) {
 // (the circuit's own 4^n weights are not allocated for DENSE circuits
 // without term tracking: tiled ones run in pool buffers, LDS-resident ones
 // need none).
-pp_status prepare_request(ServedReq *r) {
+pp_status prepare_request(ServedReq *r, int64_t budget) {
     pp_circuit *c = r->c;
     const bool dense_fast = c->engine == PP_ENGINE_DENSE && !c->track && !ramp_wanted(c);
     pp_status st = ensure_plan(c, !dense_fast);
@@ -2813,7 +2991,18 @@ pp_status prepare_request(ServedReq *r) {
     r->resident = dense_fast && c->dplan.resident;
     r->pooled = dense_fast && !c->dplan.resident;
     r->foot = r->resident ? 0 : footprint_bytes(c);
+    // run from both ends: the state's coefficients too.  Where the budget is
+    // below both arrays they go into the server's spare one: two such requests
+    // do not fit the budget together, so one is enough
+    r->spare = r->pooled && c->dplan.fwd_pass >= 0 && 2 * r->foot > budget;
+    if (r->pooled && c->dplan.fwd_pass >= 0 && !r->spare) r->foot *= 2;
     return PP_OK;
+}
+
+// the state's coefficients of a request run from both ends
+void *state_of(const pp_server *S, const ServedReq *r) {
+    if (r->c->dplan.fwd_pass < 0) return nullptr;
+    return r->spare ? S->spare : (unsigned char *)r->buf + r->foot / 2;
 }
 
 // Starts an admitted request: the whole evaluation for requests outside the
@@ -2830,12 +3019,30 @@ pp_status start_request(pp_server *S, ServedReq *r) {
     }
     pp_status st = pool_take(S, (size_t)r->foot, &r->buf);
     if (st != PP_OK) return st;
+    if (r->spare && S->spare_bytes < (size_t)r->foot) {
+        dev_free(S->spare);
+        S->spare = nullptr;
+        S->spare_bytes = 0;
+        HIPCHK(dev_alloc(&S->spare, (size_t)r->foot));
+        S->spare_bytes = (size_t)r->foot;
+    }
     if ((st = after_theta(c, S->main)) != PP_OK) return st;
     if (c->dplan.nmaps() > 0) HIPCHK(pp::launch_compose(c->d_comp, 1, S->main, c->dplan.nmaps()));
     HIPCHK(pp::launch_dense_init(r->buf, nullptr, c->n, c->dbytes, c->d_ox, c->d_oz, c->d_oc, (int)c->ox.size(),
-                                 c->obs_distinct, S->main));
-    r->pass = 0;
+                                 c->obs_distinct, S->main, 1, state_of(S, r)));
+    r->step = 0;
     return PP_OK;
+}
+
+// The readout of a tiled request, behind its last pass.
+pp_status finish_tiled(pp_server *S, ServedReq *r) {
+    pp_circuit *c = r->c;
+    double *out = S->d_results + r->slot;
+    if (c->dplan.fwd_pass >= 0)
+        HIPCHK(pp::launch_meet_readout(r->buf, state_of(S, r), c->n, c->dbytes, c->d_part, out, S->main));
+    else
+        HIPCHK(pp::launch_dense_readout(r->buf, c->n, c->dbytes, out, S->main));
+    return finish_async(S, r, S->main);
 }
 
 // Launches every pending resident request on an idle side lane: the maps of
@@ -2925,7 +3132,9 @@ void complete(pp_server *S, ServedReq *r, pp_status st) {
         S->pool_free.emplace((size_t)r->foot, r->buf);
         r->buf = nullptr;
     }
-    // a pooled run keeps no final weights with the circuit
+    // a pooled run keeps no final weights with the circuit, and its maps have
+    // taken the place of those of an evaluation before
+    if (r->pooled || r->resident) c->met = false;
     c->evaluated = !r->pooled && !r->resident && st == PP_OK;
     c->last_track = c->track;
     S->live.erase(c);
@@ -2947,7 +3156,7 @@ void prep_loop(pp_server *S) {
             S->prep_queue.pop_front();
             S->preparing++;
         }
-        const pp_status st = prepare_request(r);
+        const pp_status st = prepare_request(r, S->budget);
         std::lock_guard<std::mutex> lk(S->mu);
         S->preparing--;
         if (st != PP_OK) {
@@ -3026,7 +3235,7 @@ void server_loop(pp_server *S) {
             for (int k = 4; k <= 7 && !tiled.empty(); ++k) {
                 std::vector<ServedReq *> grp;
                 for (ServedReq *r : tiled)
-                    if (r->c->dplan.k == k && r->c->dbytes == db && r->pass < r->c->h_pass.size()) grp.push_back(r);
+                    if (r->c->dplan.k == k && r->c->dbytes == db && r->step + 1 < r->c->step.size()) grp.push_back(r);
                 if (grp.empty()) continue;
                 std::stable_sort(grp.begin(), grp.end(), [](ServedReq *a, ServedReq *b) { return a->c->n > b->c->n; });
                 size_t i0 = 0;
@@ -3036,19 +3245,22 @@ void server_loop(pp_server *S) {
                     int run = 0, last_n = -1;
                     size_t i = i0;
                     for (; i < grp.size(); ++i) {
-                        pp::TilePassDesc d = grp[i]->c->h_pass[grp[i]->pass];
-                        d.coef = grp[i]->buf;
-                        if (d.n != last_n) {
+                        const pp_circuit *gc = grp[i]->c;
+                        if (gc->n != last_n) {
                             if (tg.ngroups == pp::kMaxTileGroups) break;
                             tg.first_block[tg.ngroups] = run;
                             tg.first_desc[tg.ngroups] = (int32_t)td.size();
-                            tg.shift[tg.ngroups] = 2 * (d.n - k);
+                            tg.shift[tg.ngroups] = 2 * (gc->n - k);
                             tg.ngroups++;
-                            last_n = d.n;
+                            last_n = gc->n;
                         }
-                        d.tile_begin = run;
-                        run += d.ntiles;
-                        td.push_back(d);
+                        for (int q = gc->step[grp[i]->step]; q < gc->step[grp[i]->step + 1]; ++q) {
+                            pp::TilePassDesc d = gc->h_pass[(size_t)q];
+                            d.coef = d.forward ? state_of(S, grp[i]) : grp[i]->buf;
+                            d.tile_begin = run;
+                            run += d.ntiles;
+                            td.push_back(d);
+                        }
                     }
                     tg.first_block[tg.ngroups] = run;
                     std::vector<unsigned char> blob(td.size() * sizeof(pp::TilePassDesc));
@@ -3068,11 +3280,8 @@ void server_loop(pp_server *S) {
                             complete(S, r, st);
                             continue;
                         }
-                        if (++r->pass == r->c->h_pass.size()) {
-                            pp_circuit *c = r->c;
-                            if (pp::launch_dense_readout(r->buf, c->n, c->dbytes, S->d_results + r->slot, S->main) !=
-                                    hipSuccess ||
-                                finish_async(S, r, S->main) != PP_OK) {
+                        if (++r->step + 1 == r->c->step.size()) {
+                            if (finish_tiled(S, r) != PP_OK) {
                                 (void)hipStreamSynchronize(S->main);
                                 std::lock_guard<std::mutex> lk(S->mu);
                                 complete(S, r, PP_ERR_DEVICE);
@@ -3087,9 +3296,7 @@ void server_loop(pp_server *S) {
         // tiled requests with no passes at all (empty circuits)
         for (ServedReq *r : tiled)
             if (r->state == RQ_ACTIVE && r->c->h_pass.empty()) {
-                pp_circuit *c = r->c;
-                if (pp::launch_dense_readout(r->buf, c->n, c->dbytes, S->d_results + r->slot, S->main) != hipSuccess ||
-                    finish_async(S, r, S->main) != PP_OK) {
+                if (finish_tiled(S, r) != PP_OK) {
                     (void)hipStreamSynchronize(S->main);
                     std::lock_guard<std::mutex> lk(S->mu);
                     complete(S, r, PP_ERR_DEVICE);
@@ -3252,6 +3459,7 @@ extern "C" void pp_server_destroy(pp_server *S) {
         if (R.h) (void)hipHostFree(R.h);
     }
     for (auto &kv : S->pool_free) dev_free(kv.second);
+    dev_free(S->spare);
     dfree(S->d_results);
     (void)hipHostFree(S->h_results);
     for (auto &Ln : S->lane) {

@@ -1367,12 +1367,18 @@ __global__ __launch_bounds__(256) void compose_kernel(const ComposeDesc *__restr
 }
 
 // -------------------------------------------------------- small kernels
+// 1 at the slots of the strings made of I and Z (no X bit in any digit)
+__device__ __forceinline__ bool zonly(long long slot) { return (slot & 0x5555555555555555ll) == 0; }
+
+// coef: zeros; state (optional): the coefficients of |0...0> in each array of
+// 4^n = mask + 1 slots
 template <typename T>
-__global__ void dense_fill_kernel(T *coef, uint8_t *pres, long long size) {
+__global__ void dense_fill_kernel(T *coef, uint8_t *pres, long long size, T *state, long long mask) {
     for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < size;
          i += (long long)gridDim.x * blockDim.x) {
         coef[i] = (T)0;
         if (pres) pres[i] = 0;
+        if (state) state[i] = zonly(i & mask) ? (T)1 : (T)0;
     }
 }
 
@@ -1418,8 +1424,10 @@ __global__ void many_fill_kernel(const DenseIODesc *__restrict__ descs) {
     T *coef = reinterpret_cast<T *>(d.coef);
     const long long size = 1ll << (2 * d.n);
     for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < size;
-         i += (long long)gridDim.x * blockDim.x)
+         i += (long long)gridDim.x * blockDim.x) {
         coef[i] = (T)0;
+        if (d.state) reinterpret_cast<T *>(d.state)[i] = zonly(i) ? (T)1 : (T)0;
+    }
 }
 
 template <typename T>
@@ -1427,6 +1435,60 @@ __global__ __launch_bounds__(256) void many_scatter_kernel(const DenseIODesc *__
     const DenseIODesc &d = descs[blockIdx.x];
     scatter_terms<T>(reinterpret_cast<T *>(d.coef), nullptr, d.n, d.obs_x, d.obs_z, d.obs_c, d.nterms,
                      d.distinct != 0);
+}
+
+// Readout of a circuit run from both ends: block b of nb sums its part of
+// c . r, and the block that ends last adds the parts in order.  The blocks
+// and their sums follow from n alone, so a result does not depend on how the
+// circuit is batched.
+constexpr int meet_blocks(int n) { return n >= 9 ? kMeetBlocks : (n >= 8 ? 16 : 1); }
+
+template <typename T>
+__device__ void meet_readout(const T *__restrict__ c, const T *__restrict__ r, int n, double *part, double *out) {
+    __shared__ double redd[4];
+    __shared__ unsigned last;
+    const int nb = meet_blocks(n), b = blockIdx.x;
+    if (b >= nb) return;
+    const long long per = (1ll << (2 * n)) / nb;
+    double sum = 0.0;
+    for (long long i = threadIdx.x; i < per; i += 256) sum += (double)c[b * per + i] * (double)r[b * per + i];
+    const double tot = block_sum_d<256>(sum, redd);
+    unsigned *ticket = reinterpret_cast<unsigned *>(part + kMeetBlocks);
+    if (threadIdx.x == 0) {
+        // agent-scope accesses pass the L2 by: no fence has to write it back
+        __hip_atomic_store(part + b, tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (last != (unsigned)(nb - 1)) return;
+    const double v =
+        threadIdx.x < nb ? __hip_atomic_load(part + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+    const double all = block_sum_d<256>(v, redd);
+    if (threadIdx.x == 0) {
+        *out = all;
+        *ticket = 0u;  // for the next launch
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void meet_readout_kernel(const T *coef, const T *state, int n, double *part,
+                                                           double *out, long long stride) {
+    const int i = blockIdx.y;
+    meet_readout<T>(coef + i * stride, state + i * stride, n, part + (size_t)i * kMeetDoubles, out + i);
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void many_meet_readout_kernel(const DenseIODesc *__restrict__ descs) {
+    const DenseIODesc &d = descs[blockIdx.y];
+    meet_readout<T>(reinterpret_cast<const T *>(d.coef), reinterpret_cast<const T *>(d.state), d.n, d.part, d.out);
+}
+
+__global__ void transpose_maps_kernel(const double *__restrict__ src, double *__restrict__ dst, int first, int nmaps) {
+    const int i = first * 9 + blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= 9 * nmaps) return;
+    const int m = i / 9, e = i - 9 * m;
+    dst[i] = src[9 * m + 3 * (e % 3) + e / 3];
 }
 
 template <typename T>
@@ -1600,6 +1662,40 @@ int num_cus() {
 }
 
 template <typename T, bool TRACK, int K>
+static hipError_t launch_tile_plain_t(const TilePassDesc *d, const TileGroups &grp, size_t lds, hipStream_t s) {
+    constexpr int TB = K >= 7 ? 512 : 256;
+    auto fn = tile_kernel<T, TRACK, K, TB>;
+    static bool attr = false;
+    if (!attr) {
+        hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           max_lds_bytes() - (int)kStaticLdsReserve);
+        if (e != hipSuccess) return e;
+        attr = true;
+    }
+    hipLaunchKernelGGL(fn, dim3(grp.first_block[grp.ngroups]), dim3(TB), lds, s, d, grp);
+    return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t launch_tile_plain(const TilePassDesc *d, const TileGroups &grp, int k, size_t lds, hipStream_t s) {
+    switch (k) {
+    case 4: return launch_tile_plain_t<T, false, 4>(d, grp, lds, s);
+    case 5: return launch_tile_plain_t<T, false, 5>(d, grp, lds, s);
+    case 6: return launch_tile_plain_t<T, false, 6>(d, grp, lds, s);
+    default: return launch_tile_plain_t<T, false, 7>(d, grp, lds, s);
+    }
+}
+
+hipError_t launch_tile_pass_plain(const TilePassDesc *d_descs, const TileGroups &grp, int k, int dtype_bytes,
+                                  hipStream_t s) {
+    if (grp.ngroups <= 0 || grp.first_block[grp.ngroups] <= 0) return hipSuccess;
+    if (k < 4 || k > 7) return hipErrorInvalidValue;
+    const size_t lds = resident_lds_bytes(k, dtype_bytes, false);
+    return dtype_bytes == 8 ? launch_tile_plain<double>(d_descs, grp, k, lds, s)
+                            : launch_tile_plain<float>(d_descs, grp, k, lds, s);
+}
+
+template <typename T, bool TRACK, int K>
 static hipError_t launch_tile_t(const TilePassDesc *d, const TileGroups &grp, size_t lds, hipStream_t s) {
     const int nblocks = grp.first_block[grp.ngroups];
     // the register-tile kernel's 32-bit buffer offsets hold registers of at
@@ -1656,17 +1752,7 @@ static hipError_t launch_tile_t(const TilePassDesc *d, const TileGroups &grp, si
         hipLaunchKernelGGL(fn, dim3(grid), dim3(SB), lds, s, d, grp);
         return hipGetLastError();
     }
-    constexpr int TB = K >= 7 ? 512 : 256;
-    auto fn = tile_kernel<T, TRACK, K, TB>;
-    static bool attr = false;
-    if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           max_lds_bytes() - (int)kStaticLdsReserve);
-        if (e != hipSuccess) return e;
-        attr = true;
-    }
-    hipLaunchKernelGGL(fn, dim3(nblocks), dim3(TB), lds, s, d, grp);
-    return hipGetLastError();
+    return launch_tile_plain_t<T, TRACK, K>(d, grp, lds, s);
 }
 
 template <typename T, bool TRACK>
@@ -1699,16 +1785,18 @@ hipError_t launch_copy_f64(const double *src, double *dst, long long count, hipS
 
 hipError_t launch_dense_init(void *coef, uint8_t *pres, int n, int dtype_bytes, const uint64_t *x,
                              const uint64_t *z, const double *c, int nterms, bool distinct, hipStream_t s,
-                             int count) {
+                             int count, void *state) {
     const long long size = 1ll << (2 * n);
     const long long total = size * count;
     const int grid = (int)((total + 255) / 256 < 8192 ? (total + 255) / 256 : 8192);
     if (dtype_bytes == 8) {
-        hipLaunchKernelGGL(dense_fill_kernel<double>, dim3(grid), dim3(256), 0, s, (double *)coef, pres, total);
+        hipLaunchKernelGGL(dense_fill_kernel<double>, dim3(grid), dim3(256), 0, s, (double *)coef, pres, total,
+                           (double *)state, size - 1);
         hipLaunchKernelGGL(dense_scatter_kernel<double>, dim3(count), dim3(256), 0, s, (double *)coef, pres, n, x,
                            z, c, nterms, (int)distinct, size);
     } else {
-        hipLaunchKernelGGL(dense_fill_kernel<float>, dim3(grid), dim3(256), 0, s, (float *)coef, pres, total);
+        hipLaunchKernelGGL(dense_fill_kernel<float>, dim3(grid), dim3(256), 0, s, (float *)coef, pres, total,
+                           (float *)state, size - 1);
         hipLaunchKernelGGL(dense_scatter_kernel<float>, dim3(count), dim3(256), 0, s, (float *)coef, pres, n, x, z,
                            c, nterms, (int)distinct, size);
     }
@@ -1723,6 +1811,36 @@ hipError_t launch_dense_readout(const void *coef, int n, int dtype_bytes, double
     else
         hipLaunchKernelGGL(dense_readout_kernel<float>, dim3(count), dim3(256), 0, s, (const float *)coef, n, out,
                            size);
+    return hipGetLastError();
+}
+
+hipError_t launch_meet_readout(const void *coef, const void *state, int n, int dtype_bytes, double *part, double *out,
+                               hipStream_t s, int count) {
+    const dim3 grid(meet_blocks(n), count);
+    const long long size = 1ll << (2 * n);
+    if (dtype_bytes == 8)
+        hipLaunchKernelGGL(meet_readout_kernel<double>, grid, dim3(256), 0, s, (const double *)coef,
+                           (const double *)state, n, part, out, size);
+    else
+        hipLaunchKernelGGL(meet_readout_kernel<float>, grid, dim3(256), 0, s, (const float *)coef,
+                           (const float *)state, n, part, out, size);
+    return hipGetLastError();
+}
+
+hipError_t launch_meet_readout_many(const DenseIODesc *d_descs, int nd, int max_n, int dtype_bytes, hipStream_t s) {
+    if (nd <= 0) return hipSuccess;
+    const dim3 grid(meet_blocks(max_n), nd);
+    if (dtype_bytes == 8)
+        hipLaunchKernelGGL(many_meet_readout_kernel<double>, grid, dim3(256), 0, s, d_descs);
+    else
+        hipLaunchKernelGGL(many_meet_readout_kernel<float>, grid, dim3(256), 0, s, d_descs);
+    return hipGetLastError();
+}
+
+hipError_t launch_transpose_maps(const double *src, double *dst, int first, int nmaps, hipStream_t s) {
+    const int count = 9 * (nmaps - first);
+    if (count <= 0) return hipSuccess;
+    hipLaunchKernelGGL(transpose_maps_kernel, dim3((count + 255) / 256), dim3(256), 0, s, src, dst, first, nmaps);
     return hipGetLastError();
 }
 

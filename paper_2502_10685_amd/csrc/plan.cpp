@@ -950,32 +950,66 @@ void record_offsets(const ChainOp &r, const DensePass &ps, int dbytes, bool afte
     }
 }
 
-DensePlan plan_meet(const GateList &g, int low, int64_t g_end, int dbytes) {
+DensePlan plan_meet(const GateList &g, int k, int low, int64_t g_end, bool segments, int dbytes,
+                    std::vector<int> *rec) {
     int64_t ncx = 0;
     for (int64_t i = 0; i < g_end; ++i) ncx += g.op[(size_t)i] == 2;
     int64_t s = ncx ? 0 : g_end / 2;
     for (int64_t seen = 0; ncx && seen < ncx / 2; ++s) seen += g.op[(size_t)s] == 2;
+    const bool chains = k == g.n || k == kChainTileDigits;
+    std::vector<int> hrec, frec;
     PlanOptions o;
     o.g_begin = s;
     o.g_end = g_end;
-    DensePlan P = plan_dense_opts(g, g.n, low, o);
-    build_chain(P, dbytes);
+    o.segments = segments;
+    DensePlan P = plan_dense_opts(g, k, low, o);
+    if (chains) build_chain(P, dbytes, &hrec);
     PlanOptions f;
     f.g_end = s;
     f.forward = true;
-    DensePlan F = plan_dense_opts(g, g.n, low, f);
-    build_chain(F, dbytes);
+    f.segments = segments;
+    DensePlan F = plan_dense_opts(g, k, low, f);
+    if (chains) build_chain(F, dbytes, &frec);
     const int base = P.nmaps();
-    plan_append(P, F);  // the ops too, for the self-check and the statistics
+    const size_t hpass = P.passes.size();
+    plan_append(P, F);
     for (ChainOp r : F.chain) {
         r.map += (uint32_t)base;
         P.chain.push_back(r);
     }
     P.fwd_from = base;
-    P.passes.front().op_end = P.passes.back().op_end;
-    P.passes.front().ngates += P.passes.back().ngates;
-    P.passes.resize(1);
+    if (k == g.n) {  // the ops of both, for the self-check and the statistics
+        P.passes.front().op_end = P.passes.back().op_end;
+        P.passes.front().ngates += P.passes.back().ngates;
+        P.passes.resize(1);
+        return P;
+    }
+    P.fwd_pass = (int)hpass;
+    if (rec && chains) {
+        *rec = hrec;
+        rec->pop_back();
+        for (int v : frec) rec->push_back(v + P.nchain);
+    }
     return P;
+}
+
+DensePlan plan_reversed_forward(const DensePlan &P) {
+    DensePlan R;
+    R.k = P.k;
+    for (size_t p = P.passes.size(); p-- > (size_t)P.fwd_pass;) {
+        DensePass ps = P.passes[p];
+        const int begin = (int)R.ops.size();
+        for (int i = ps.op_end; i-- > ps.op_begin;) {
+            DOp d = P.ops[(size_t)i];
+            if (d.kind == DOP_GROUP || d.kind == DOP_SEG) continue;
+            d.perm = 0;
+            R.ops.push_back(d);
+        }
+        ps.op_begin = begin;
+        ps.op_end = (int)R.ops.size();
+        R.passes.push_back(ps);
+    }
+    return R;
 }
 
 GradPlan plan_gradient(const GateList &g, int k_heis, int k_fwd, int low, int64_t every) {

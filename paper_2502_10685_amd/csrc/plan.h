@@ -41,6 +41,7 @@ struct DensePlan {
     std::vector<ChainOp> chain;
     int nchain = 0;
     int fwd_from = -1;  // first map of the forward half (-1: none)
+    int fwd_pass = -1;  // tiled plans: first pass of the forward half (-1: none)
     int nmaps() const { return (int)roff.size() - 1; }
 };
 
@@ -134,13 +135,20 @@ struct GradPlan {
 // pairs avoid digits 0 and 1 (without a CX or map where the schedule has no
 // such op there), and has at least two.
 void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin = nullptr);
-// Untracked evaluation of a resident circuit from both ends: gates [s, g_end)
-// taken back from the observable, gates [0, s) forward from the state, with s
-// where half of the CX gates lie on either side (a record holds about one).
 // Byte offsets, in the 4^n array, of the letters of record r's pair: as it
 // reads them (after = false) or writes them.
 void record_offsets(const ChainOp &r, const DensePass &ps, int dbytes, bool after, uint32_t out[4]);
-DensePlan plan_meet(const GateList &g, int low, int64_t g_end, int dbytes);
+// Untracked evaluation from both ends: gates [s, g_end) taken back from the
+// observable, gates [0, s) forward from the state, with s where half of the
+// CX gates lie on either side (a record holds about one).  k = n: one pass
+// of both halves' chains; k < n: tile passes, the forward half's from fwd_pass
+// on; rec receives the first record of each pass over 7-qubit tiles.
+DensePlan plan_meet(const GateList &g, int k, int low, int64_t g_end, bool segments, int dbytes,
+                    std::vector<int> *rec = nullptr);
+// The forward half of a tiled meet plan run backwards, as the Heisenberg
+// schedule of the same gates: its passes and ops in reverse order (no GROUP or
+// SEG headers), whose maps are the transposes of the forward maps.
+DensePlan plan_reversed_forward(const DensePlan &P);
 GradPlan plan_gradient(const GateList &g, int k_heis, int k_fwd, int low, int64_t every);
 SparsePlan plan_sparse(const GateList &g);
 

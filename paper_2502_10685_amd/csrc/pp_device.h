@@ -100,6 +100,7 @@ struct TilePassDesc {
     int32_t tile_begin;            // first block of this desc in the launch
     int32_t ntiles;
     uint64_t qubits;               // byte j = global qubit of local digit j (ascending)
+    uint32_t forward;              // 1: a pass of the forward half (coef holds the state's coefficients)
     uint32_t reg_entry;            // register-tile kernel: digit triple (bit mask) to load into registers
     uint32_t nmaps;                // maps of the schedule (7-qubit tiles)
     // 7-qubit tiles: the pass's records; its first is applied to the weights
@@ -160,7 +161,15 @@ struct DenseIODesc {
     int32_t n, nterms;
     int32_t distinct;  // 1: no string is repeated among the nterms
     int32_t reserved;
+    void *state;       // the state's coefficients of a circuit run from both ends, or nullptr
+    double *part;      // and kMeetDoubles for the product of the two
 };
+
+// Where the product c . r of a circuit run from both ends is summed up: one
+// sum per block (at most kMeetBlocks), then the blocks' ticket (0 between
+// launches).
+constexpr int kMeetBlocks = 64;
+constexpr int kMeetDoubles = kMeetBlocks + 8;
 
 // Per-circuit composition job: maps[i] = product of the gate matrices of
 // recipe entries [roff[i], roff[i+1]) in Heisenberg order.
@@ -249,10 +258,21 @@ hipError_t launch_grad_accumulate(const double *rot_grad, const int32_t *off, co
                                   int nparams, hipStream_t s);
 hipError_t launch_copy_f64(const double *src, double *dst, long long count, hipStream_t s);
 // count > 1: count weight arrays of 4^n slots back to back (parameter sets);
-// distinct: no string is repeated among the nterms
+// distinct: no string is repeated among the nterms; state (optional): count
+// arrays that receive the coefficients of |0...0>
 hipError_t launch_dense_init(void *coef, uint8_t *pres, int n, int dtype_bytes, const uint64_t *x,
                              const uint64_t *z, const double *c, int nterms, bool distinct, hipStream_t s,
-                             int count = 1);
+                             int count = 1, void *state = nullptr);
+// <O> = sum over the strings of coef x state, for count pairs of arrays back
+// to back; part: count x kMeetDoubles
+hipError_t launch_meet_readout(const void *coef, const void *state, int n, int dtype_bytes, double *part, double *out,
+                               hipStream_t s, int count = 1);
+hipError_t launch_meet_readout_many(const DenseIODesc *d_descs, int nd, int max_n, int dtype_bytes, hipStream_t s);
+// transposes of the 3x3 maps [first, nmaps) of src into dst
+hipError_t launch_transpose_maps(const double *src, double *dst, int first, int nmaps, hipStream_t s);
+// one workgroup per tile, whatever the tuned launch shape (untracked)
+hipError_t launch_tile_pass_plain(const TilePassDesc *d_descs, const TileGroups &groups, int k, int dtype_bytes,
+                                  hipStream_t s);
 hipError_t launch_dense_readout(const void *coef, int n, int dtype_bytes, double *out, hipStream_t s,
                                 int count = 1);
 // the same for the nd circuits of a batch (one fill, one scatter launch;

@@ -1,0 +1,139 @@
+"""Tiled circuits of 8 to 10 qubits, evaluated from both ends: the result is
+the same bits however it is asked for (alone, replayed, in a batch, in a
+sweep's chunks, without allocation, served), at every tile size, at circuits
+whose halves are empty, and pp_get_terms still gives the weights taken all the
+way back, also after the schedule or the angles have changed.
+
+Bars: <O> as the repository's 1e-12 (FP64) and 1e-5 (FP32); a weight of an
+observable of unit 2-norm passes m gates, 4 units in the last place each:
+8 m 2^-53."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2502_10685_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def api():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a visible HIP device"
+    from paper_2502_10685_amd import api as A
+    return A
+
+
+def _circ(n, m, seed, obs=None):
+    return W.random_circuit(np.random.default_rng(seed), n, m, obs or W.obs_tfim(n))
+
+
+def _edge(n, kind):
+    """Circuits with an empty half, or none but CX."""
+    if kind == "empty":
+        g = [[], [], [], []]
+    elif kind == "one":
+        g = [[W.RY], [n - 1], [-1], [0]]
+    elif kind == "cx":
+        g = [[W.CX], [0], [n - 1], [-1]]
+    else:  # rotations, then a CX at the very end
+        g = [[W.RX] * n + [W.CX], list(range(n)) + [1], [-1] * n + [n - 1], list(range(n)) + [-1]]
+    arr = tuple(np.array(a, dtype=t) for a, t in zip(g, (np.uint8, np.int32, np.int32, np.int32)))
+    p = int((arr[0] >= 3).sum())
+    return W.make_circuit(n, arr, p, W.obs_tfim(n), np.linspace(0.3, 1.1, p))
+
+
+@pytest.mark.parametrize("kind", ["empty", "one", "cx", "tail"])
+@pytest.mark.parametrize("n", [8, 10])
+def test_halves_at_the_edge(api, n, kind):
+    print(f"meet edge n={n} {kind}", flush=True)
+    wc = _edge(n, kind)
+    c = api.Circuit.from_workload(wc)
+    for _ in range(2):
+        assert abs(float(c.evaluate().item()) - oracle.expval_sv(wc)) <= 1e-12
+    c.close()
+
+
+@pytest.mark.parametrize("n,k,dtype", [(8, 4, "f64"), (8, 5, "f64"), (8, 6, "f64"), (8, 7, "f64"), (9, 6, "f32"),
+                                       (9, 7, "f32"), (10, 6, "f64"), (10, 7, "f64")])
+def test_same_bits_however_asked(api, n, k, dtype):
+    import torch
+    from paper_2502_10685_amd import _lib as L
+    print(f"meet n={n} k={k} {dtype}", flush=True)
+    ws = [_circ(n, m, 10 * n + i) for i, m in enumerate((37, 300, 900))]
+    cs = []
+    for w in ws:
+        c = api.Circuit.from_workload(w, dtype=dtype)
+        c.set_option(L.PP_OPT_TILE_QUBITS, k)
+        cs.append(c)
+    solo = [float(c.evaluate().item()) for c in cs]
+    for w, v in zip(ws, solo):
+        assert abs(v - oracle.expval_sv(w)) <= (1e-12 if dtype == "f64" else 1e-5)
+    out = torch.empty(len(cs), dtype=torch.float64, device="cuda")
+    for _ in range(2):
+        api.evaluate_batch(cs, out)
+        assert out.cpu().tolist() == solo
+    for c, w, v in zip(cs, ws, solo):
+        c.set_option(L.PP_OPT_USE_GRAPH, 1)
+        for _ in range(3):
+            assert float(c.evaluate().item()) == v
+        c.set_option(L.PP_OPT_USE_GRAPH, 0)
+        th = np.stack([w.theta, w.theta + 0.1, w.theta])
+        sw = c.evaluate_thetas(torch.tensor(th, device="cuda")).cpu().tolist()
+        assert sw[0] == v and sw[2] == v and sw[1] != v
+    srv = api.Server(mem_budget_bytes=4 ** n * (8 if dtype == "f64" else 4), max_active=4)  # one array: the spare
+    ts = [srv.submit(c) for c in cs]
+    srv.drain()
+    assert [srv.poll(t)[0] for t in ts] == solo
+    assert srv.pool_bytes()[1] <= 4 ** n * (8 if dtype == "f64" else 4)
+    srv.close()
+    for c in cs:
+        c.close()
+
+
+def test_sweep_in_chunks(api):
+    """n = 10 in FP64: 64 sets are held at once."""
+    import torch
+    print("meet sweep n=10 x 67", flush=True)
+    wc = _circ(10, 60, 3)
+    th = np.random.default_rng(1).uniform(0, 6, size=(67, wc.n_params))
+    c = api.Circuit.from_workload(wc)
+    got = c.evaluate_thetas(torch.tensor(th, device="cuda")).cpu().tolist()
+    for i in (0, 1, 63, 64, 66):
+        c.set_theta(th[i])
+        assert float(c.evaluate().item()) == got[i]
+    assert abs(got[66] - oracle.expval_sv(wc.with_theta(th[66]))) <= 1e-12
+    c.close()
+
+
+@pytest.mark.parametrize("n,k", [(8, 4), (8, 6), (9, 7), (10, 6)])
+@pytest.mark.parametrize("between", ["nothing", "theta", "observable", "option", "batch"])
+def test_terms_after_an_evaluation(api, n, k, between):
+    import torch
+    from paper_2502_10685_amd import _lib as L
+    print(f"meet terms n={n} k={k} {between}", flush=True)
+    wc = _circ(n, 150, 7 * n, W.obs_z(n, [0, n - 1]))
+    ref = oracle.propagate(wc)
+    c = api.Circuit.from_workload(wc)
+    c.set_option(L.PP_OPT_TILE_QUBITS, k)
+    if between == "batch":
+        api.evaluate_batch([c], torch.empty(1, dtype=torch.float64, device="cuda"))
+    else:
+        c.evaluate()
+    if between == "theta":
+        c.set_theta(wc.theta + 1.0)
+    elif between == "observable":
+        c.set_observable(*W.obs_tfim(n))
+    elif between == "option":
+        c.set_option(L.PP_OPT_TILE_QUBITS, 5)
+        c.evaluate_thetas(torch.tensor(np.stack([wc.theta]), device="cuda"))  # another schedule
+    want = {(int(x), int(z)): float(v) for x, z, v in zip(ref.x, ref.z, ref.c)}
+    for _ in range(2):
+        x, z, v = c.terms(capacity=4 ** n)
+        got = {(int(a), int(b)): float(w) for a, b, w in zip(x, z, v)}
+        tol = 8 * wc.m * 2.0 ** -53
+        assert max(abs(got.get(s, 0.0) - w) for s, w in want.items()) <= tol
+        assert max([abs(w) for s, w in got.items() if s not in want], default=0.0) <= tol
+    if between in ("nothing", "batch"):
+        assert abs(float(c.evaluate().item()) - oracle.expval_sv(wc)) <= 1e-12
+    c.close()
