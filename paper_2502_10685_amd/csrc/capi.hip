@@ -285,11 +285,12 @@ constexpr int64_t kSweepChunk = 512;
 constexpr int64_t kSweepMeetBytes = (int64_t)1 << 30;
 
 // Tile qubits by n.  7-qubit tiles take about a third fewer passes, but a
-// workgroup of 1,024 threads per tile: they pay from the n whose 4^(n - 7)
-// tiles fill the 256 CUs (3,000 random gates, FP64, 6 against 7 qubits: n = 10
-// 1.12 against 1.27 ms, n = 11 1.76 against 1.56, n = 12 6.3 against 4.8, n =
-// 13 26.6 against 19.6; FP32 alike), up to the kernel's 14 qubits.
-int g_tile_qubits[17] = {0, 0, 0, 0, 0, 0, 0, 0, 6, 6, 6, 7, 7, 7, 7, 6, 6};
+// workgroup of 1,024 threads per tile: they pay from the n whose tiles come
+// near the 256 CUs (FP64, 6 against 7 qubits: 5,000 random gates at n = 8 0.73
+// against 0.89 ms, n = 9 0.85 against 1.09, n = 10 1.27 against 1.22; 3,000 at
+// n = 11 1.76 against 1.56, n = 12 6.3 against 4.8, n = 13 26.6 against 19.6;
+// 32 circuits of n = 10 4.40 against 3.74; FP32 alike), up to the kernel's 14.
+int g_tile_qubits[17] = {0, 0, 0, 0, 0, 0, 0, 0, 6, 6, 7, 7, 7, 7, 7, 6, 6};
 int default_tile_qubits(int n) { return n >= 8 && n <= 16 ? g_tile_qubits[n] : (n > 16 ? 6 : 5); }
 
 // pinned staging for small asynchronous uploads, reused once the previous
@@ -680,18 +681,21 @@ void free_state_buffers(pp_circuit *c) {
     c->fb = pp::FrameBuffers{};
 }
 
-int64_t dense_slots(int n) { return (int64_t)1 << (2 * n); }
-
 // Tiled circuits of up to kMeetMaxN qubits are evaluated from both ends: their
 // 4^(n - k) tiles leave most of the chip idle and each pass is mostly latency,
 // so two halves side by side take half the launches.  From 11 qubits on a
 // pass fills the chip, and the second array would double a circuit's memory.
 constexpr int kMeetMaxN = 10;
+int64_t dense_slots(int n) { return (int64_t)1 << (2 * n); }
+
 bool meets(const pp_circuit *c, int k) { return k < c->n && c->n <= kMeetMaxN && !c->track && !c->keep_coef; }
 
 std::atomic<uint64_t> g_plan_gen{0};
 
-int tile_qubits_for(const pp_circuit *c) {
+// Circuits run from one end (tracked, density matrices, a gradient's sweep)
+// have half the tiles in flight: at n = 10 their 64 tiles of 7 qubits are
+// slower than 256 of 6 (3,000 gates 1.27 against 1.12 ms).
+int tile_qubits_for(const pp_circuit *c, bool one_end = false) {
     if (c->n <= kResidentMaxN &&
         pp::resident_lds_bytes(c->n, c->dbytes, c->track != 0) + pp::kStaticLdsReserve <= (size_t)pp::max_lds_bytes())
         return c->n;
@@ -699,6 +703,8 @@ int tile_qubits_for(const pp_circuit *c) {
     k = std::min(k, c->n - 1);
     k = std::max(k, kLowQubits + 2);
     k = std::min(k, 7);
+    one_end = one_end || c->track || c->keep_coef;
+    if (c->tile_opt <= 0 && one_end && k == 7 && c->n <= kMeetMaxN) k = 6;
     while (k > kLowQubits + 2 &&
            pp::resident_lds_bytes(k, c->dbytes, c->track != 0) + pp::kStaticLdsReserve > (size_t)pp::max_lds_bytes())
         --k;
@@ -1952,6 +1958,13 @@ struct BatchCache {
     // LDS-resident circuits run on a second stream, overlapping the tile passes
     hipStream_t aux = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
+    // and passes over 7-qubit tiles on a third, where there are others too
+    hipStream_t aux7 = nullptr;
+    hipEvent_t fork7 = nullptr, join7 = nullptr;
+    bool split = false;
+    // descriptors are uploaded on a stream of their own, ahead of the passes
+    hipStream_t copy = nullptr;
+    hipEvent_t sent = nullptr;
     struct Launch { int kind; int group_n; size_t off; int nd; int nblocks; pp::TileGroups tg; };
     std::vector<Launch> head;      // kind 0 compose, 1 resident
     std::vector<Launch> tiles;     // tile passes
@@ -1972,6 +1985,9 @@ void free_batch_graph(BatchCache &B) {
     B.gexec = nullptr;
     B.graph = nullptr;
 }
+
+// While passes are timed they stay on one stream.
+bool split_now(const BatchCache &B) { return B.split && (!g_prof.on || g_prof.capturing); }
 
 // The device work of one batch step on stream s, in three parts: start
 // weights, composed maps and the LDS-resident circuits on the second stream;
@@ -1999,16 +2015,24 @@ pp_status enqueue_batch_head(BatchCache &B, int dbytes, hipStream_t s) {
         else
             HIPCHK(pp::launch_chain((const pp::ResidentDesc *)(base + L.off), L.nd, L.group_n, dbytes, true, nullptr, ls));
     }
+    if (split_now(B)) {
+        HIPCHK(hipEventRecord(B.fork7, s));
+        HIPCHK(hipStreamWaitEvent(B.aux7, B.fork7, 0));
+    }
     return PP_OK;
 }
 
+// The passes over 7-qubit tiles run beside the others, on a stream of their
+// own: neither kind waits for the last tiles of the other (96 circuits of 4 to
+// 10 qubits in FP32 take 12.9 ms, 15.5 on one stream; 512 in FP64 49.5, 53.6).
 pp_status enqueue_batch_tiles(BatchCache &B, size_t first, int dbytes, hipStream_t s, TileSpan &span) {
     unsigned char *base = (unsigned char *)B.buf[B.cur].d;
     for (size_t i = first; i < B.tiles.size(); ++i) {
         const auto &L = B.tiles[i];
-        span.begin(s);
-        HIPCHK(pp::launch_tile_pass((const pp::TilePassDesc *)(base + L.off), L.tg, L.group_n, dbytes, false, s));
-        span.count();
+        hipStream_t ls = split_now(B) && L.group_n == pp::kChainTileDigits ? B.aux7 : s;
+        if (ls == s) span.begin(s);
+        HIPCHK(pp::launch_tile_pass((const pp::TilePassDesc *)(base + L.off), L.tg, L.group_n, dbytes, false, ls));
+        if (ls == s) span.count();
     }
     return PP_OK;
 }
@@ -2018,6 +2042,10 @@ pp_status enqueue_batch_tail(BatchCache &B, int dbytes, hipStream_t s) {
     if (!B.head.empty() && B.head.back().kind == 1) {
         HIPCHK(hipEventRecord(B.join, B.aux));
         HIPCHK(hipStreamWaitEvent(s, B.join, 0));
+    }
+    if (split_now(B)) {
+        HIPCHK(hipEventRecord(B.join7, B.aux7));
+        HIPCHK(hipStreamWaitEvent(s, B.join7, 0));
     }
     if (!B.tiled.empty()) {
         ProfScope ps(PC_READOUT, s);
@@ -2143,12 +2171,32 @@ pp_status build_batch(BatchCache &B, pp_circuit *const *cs, int64_t count, doubl
         HIPCHK(hipEventCreateWithFlags(&B.fork, hipEventDisableTiming));
         HIPCHK(hipEventCreateWithFlags(&B.join, hipEventDisableTiming));
     }
-    if ((r = out.send(s)) != PP_OK) return r;
+    size_t kinds = 0;
+    for (int k = 4; k <= 7; ++k) kinds += !by_k[k].empty();
+    B.split = kinds > 1 && !by_k[pp::kChainTileDigits].empty();
+    if (B.split && !B.aux7) {
+        HIPCHK(hipStreamCreateWithFlags(&B.aux7, hipStreamNonBlocking));
+        HIPCHK(hipEventCreateWithFlags(&B.fork7, hipEventDisableTiming));
+        HIPCHK(hipEventCreateWithFlags(&B.join7, hipEventDisableTiming));
+    }
+    if (!B.copy) {
+        HIPCHK(hipStreamCreateWithFlags(&B.copy, hipStreamNonBlocking));
+        HIPCHK(hipEventCreateWithFlags(&B.sent, hipEventDisableTiming));
+    }
+    auto send = [&]() -> pp_status {
+        pp_status e = out.send(B.copy);
+        if (e != PP_OK) return e;
+        HIPCHK(hipEventRecord(B.sent, B.copy));
+        HIPCHK(hipStreamWaitEvent(s, B.sent, 0));
+        if (split_now(B)) HIPCHK(hipStreamWaitEvent(B.aux7, B.sent, 0));
+        return PP_OK;
+    };
+    if ((r = send()) != PP_OK) return r;
     if (launch && (r = enqueue_batch_head(B, dbytes, s)) != PP_OK) return r;
     TileSpan span;
     size_t launched = 0;
     auto flush = [&]() -> pp_status {
-        pp_status e = out.send(s);
+        pp_status e = send();
         if (e == PP_OK && launch) e = enqueue_batch_tiles(B, launched, dbytes, s, span);
         launched = B.tiles.size();
         return e;
@@ -2159,8 +2207,10 @@ pp_status build_batch(BatchCache &B, pp_circuit *const *cs, int64_t count, doubl
     // stride, so the last round of tiles is the light one
     std::vector<std::pair<uint64_t, const pp::TilePassDesc *>> order;
     std::vector<pp::TilePassDesc> td;
-    for (int k = 4; k <= 7 && r == PP_OK; ++k) {
-        for (size_t l = 0; l < maxp[k] && r == PP_OK; ++l) {
+    const size_t steps = *std::max_element(maxp.begin(), maxp.end());
+    for (size_t l = 0; l < steps && r == PP_OK; ++l) {
+        for (int k = 4; k <= 7 && r == PP_OK; ++k) {
+            if (l >= maxp[k]) continue;
             order.clear();
             for (size_t j = 0; j < by_k[k].size(); ++j) {
                 const pp_circuit *c = cs[by_k[k][j]];
@@ -2250,6 +2300,8 @@ extern "C" pp_status pp_evaluate_batch(pp_circuit *const *cs, int64_t count, voi
         if ((r = build_batch(B, cs, count, d_expvals, dbytes, !graph, s)) != PP_OK) {
             (void)hipStreamSynchronize(s);
             if (B.aux) (void)hipStreamSynchronize(B.aux);
+            if (B.aux7) (void)hipStreamSynchronize(B.aux7);
+            if (B.copy) (void)hipStreamSynchronize(B.copy);
             return r;
         }
         enqueued = !graph;
@@ -2307,7 +2359,7 @@ pp_status ensure_grad(pp_circuit *c, int64_t every) {
     if (G.valid && G.every == every) return PP_OK;
     free_grad(c);
     const int n = c->n;
-    const int k_heis = tile_qubits_for(c);
+    const int k_heis = tile_qubits_for(c, true);
     const int k_fwd = n <= 6 ? n : 6;
     G.plan = pp::plan_gradient(c->g, k_heis, k_fwd, kLowQubits, every);
     const pp::GradPlan &P = G.plan;
