@@ -804,7 +804,7 @@ pp_status ensure_state(pp_circuit *c, bool weights = true) {
         f.n = c->n;
         hipError_t e = dalloc(&f.keys, (size_t)cap);
         if (e == hipSuccess) e = dev_alloc(&f.coef, (size_t)cap * c->dbytes);
-        if (e == hipSuccess) e = dalloc(&f.index, (size_t)(2 * f.slots));
+        if (e == hipSuccess) e = dalloc(&f.index, (size_t)f.slots);
         if (e == hipSuccess) e = dalloc(&f.cnt, 8);
         if (e == hipSuccess) e = dalloc(&f.updates, 1);
         if (e != hipSuccess) {

@@ -212,8 +212,7 @@ struct FramePassDesc {
 struct FrameBuffers {
     uint64_t *keys;            // list of stored strings: packed keys
     void *coef;                // their weights (FP64 or FP32)
-    uint64_t *index;           // hash index, 16-byte slots: [2s] key
-                               // (kFrameEmpty when free), [2s + 1] list position
+    uint32_t *index;           // hash index: list positions (kFrameEmpty when free)
     unsigned long long *cnt;   // pass p reads the list length L and child
                                // count D of pass p - 1 from slot (p-1) mod 3
                                // ([slot] and [3 + slot]), records its own
@@ -225,8 +224,8 @@ struct FrameBuffers {
     int32_t slot_bits;
     int32_t n;
 };
-constexpr uint64_t kFrameEmpty = ~0ull;
-constexpr int kFrameMaxN = 31;  // 2n key bits below the empty marker
+constexpr uint32_t kFrameEmpty = ~0u;
+constexpr int kFrameMaxN = 31;  // a key's 2n bits in one word
 
 // ------------------------------------------------------------ launchers
 // Dense engine (dense.hip)

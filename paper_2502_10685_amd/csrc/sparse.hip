@@ -838,42 +838,28 @@ __device__ __forceinline__ uint64_t frame_home(uint64_t key, int bits) {
     return (key * 0x9E3779B97F4A7C15ull) >> (64 - bits);
 }
 
-typedef unsigned long long FrameSlot __attribute__((ext_vector_type(2)));  // key, list position
-
-__device__ __forceinline__ FrameSlot frame_slot(const FrameBuffers &f, uint64_t s) {
-    return *reinterpret_cast<const FrameSlot *>(f.index + 2 * s);
-}
-
-// List position of `key`, or -1, given the slot `e` already read at probe
-// position `s` (its home slot).  Slots only ever go from empty to a key, so
-// an empty slot met on the probe path means the key was never inserted;
-// keys this thread looks up are either older than the kernel or its own.
-__device__ __forceinline__ long long frame_resolve(const FrameBuffers &f, uint64_t key, uint64_t s, FrameSlot e) {
+// List position of `key` among the first `len` strings, or -1, from the entry
+// `e` already read at slot `s`.  Slots only ever go from empty to a position,
+// and a string lies no further along its probe path than the slot that was
+// empty when it was entered: an empty slot, or one entered since (a position
+// from len on), means that the key is not among them.
+__device__ __forceinline__ long long frame_resolve(const FrameBuffers &f, uint64_t key, uint64_t s, uint32_t e,
+                                                   long long len) {
     const uint64_t mask = (uint64_t)f.slots - 1;
     for (long long probe = 0; probe < f.slots; ++probe) {
-        if (e.x == key) return (long long)e.y;
-        if (e.x == kFrameEmpty) return -1;
+        if ((long long)e >= len) return -1;
+        if (f.keys[e] == key) return (long long)e;
         s = (s + 1) & mask;
-        e = frame_slot(f, s);
+        e = f.index[s];
     }
     return -1;
 }
 
-__device__ __forceinline__ long long frame_find(const FrameBuffers &f, uint64_t key) {
-    const uint64_t s = frame_home(key, f.slot_bits);
-    return frame_resolve(f, key, s, frame_slot(f, s));
-}
-
-__device__ __forceinline__ void frame_insert(const FrameBuffers &f, uint64_t key, uint64_t pos) {
+__device__ __forceinline__ void frame_insert(const FrameBuffers &f, uint64_t key, uint32_t pos) {
     const uint64_t mask = (uint64_t)f.slots - 1;
     uint64_t s = frame_home(key, f.slot_bits);
     for (long long probe = 0; probe < f.slots; ++probe) {
-        const unsigned long long prev = atomicCAS((unsigned long long *)(f.index + 2 * s),
-                                                  (unsigned long long)kFrameEmpty, (unsigned long long)key);
-        if (prev == kFrameEmpty || prev == key) {
-            f.index[2 * s + 1] = pos;
-            return;
-        }
+        if (atomicCAS(f.index + s, kFrameEmpty, pos) == kFrameEmpty) return;
         s = (s + 1) & mask;
     }
 }
@@ -896,13 +882,18 @@ __device__ __forceinline__ double frame_merge2(double p, double q) {
     return (double)(T)p + (double)(T)q;
 }
 
-// Whole 16-byte slots (key empty, position 0) in one store each: writing
-// only the key word would leave every cache line half written, which the
-// memory side completes with a read.
-__global__ void frame_clear_kernel(uint64_t *__restrict__ index, long long slots) {
-    FrameSlot *sl = reinterpret_cast<FrameSlot *>(index);
-    const FrameSlot empty = {kFrameEmpty, 0ull};
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < slots; i += (long long)gridDim.x * blockDim.x)
+// Four slots per store.  A slot is a position alone: the key it stands for is
+// read from the list, so the index of the default capacity (2^25 slots) takes
+// 22 us to clear and stays in the memory-side cache, 87 us with the key in it.
+__global__ void frame_clear_kernel(uint32_t *__restrict__ index, long long slots) {
+    if (slots < 4) {
+        if (blockIdx.x == 0 && (long long)threadIdx.x < slots) index[threadIdx.x] = kFrameEmpty;
+        return;
+    }
+    uint4 *sl = reinterpret_cast<uint4 *>(index);
+    const uint4 empty = {kFrameEmpty, kFrameEmpty, kFrameEmpty, kFrameEmpty};
+    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < slots / 4;
+         i += (long long)gridDim.x * blockDim.x)
         sl[i] = empty;
 }
 
@@ -915,13 +906,14 @@ __global__ void frame_init_kernel(FrameBuffers f, const uint64_t *ox, const uint
     unsigned long long len = 0, over = 0;
     for (int t = 0; t < nterms; ++t) {
         const uint64_t key = (oz[t] << f.n) | ox[t];
-        const long long j = frame_find(f, key);
+        const uint64_t home = frame_home(key, f.slot_bits);
+        const long long j = frame_resolve(f, key, home, f.index[home], (long long)len);
         if (j >= 0) {
             stc<T>(f.coef, j, ldc<T>(f.coef, j) + oc[t]);
         } else if ((long long)len < f.cap) {
             f.keys[len] = key;
             stc<T>(f.coef, len, oc[t]);
-            frame_insert(f, key, len);
+            frame_insert(f, key, (uint32_t)len);
             ++len;
         } else {
             over = 1;
@@ -947,10 +939,106 @@ __device__ __forceinline__ long long frame_len(const FrameBuffers &f, int last) 
 // length entering pass `pass` is L + D of the previous slot (stable during
 // this pass), this pass records it in its own slot and counts its children
 // there, and clears the next slot for the pass after.
+//
+// While the list fits one string per thread of the grid (2^19 strings at the
+// default capacity) that is what a thread takes: such passes are bound by the
+// latency of one string's chain, and more per thread leaves CUs idle.  Longer
+// lists keep four lookups of a thread in flight (eight cost more registers
+// than they hide: 1.23 ms).  n = 20, 300 gates, 158 passes up to 2.66 M
+// strings: 1.17 ms, 1.70 with eight throughout and the key in the index; 3^5
+// 2^9 strings at n = 14 0.22 ms, 0.47 before.
+template <typename T, int ITEMS>
+__device__ __forceinline__ void frame_tile(const FrameBuffers &f, const FramePassDesc &p, long long b0, long long T0,
+                                           int q, double cs, double ssn, int *wsum, unsigned long long *tbase) {
+#pragma clang fp contract(off)
+    const int n = f.n, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint64_t lo = (1ull << n) - 1ull;
+    const uint64_t xp = p.pmask & lo, zp = p.pmask >> n;
+    // all items' keys, then the first probe of every anticommuting item, then
+    // what it points at, each issued together: the lookups are random accesses
+    uint64_t key[ITEMS], kc[ITEMS];
+    uint32_t e[ITEMS];
+    double vc[ITEMS], cw[ITEMS];
+    unsigned anti = 0, kids = 0;
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const long long i = b0 + it * SP_BLOCK + threadIdx.x;
+        key[it] = i < T0 ? f.keys[i] : 0;
+        cw[it] = i < T0 ? ldc<T>(f.coef, i) : 0.0;
+        const bool a = i < T0 && ((__popcll((key[it] & lo) & zp) + __popcll((key[it] >> n) & xp)) & 1);
+        anti |= (unsigned)a << it;
+    }
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it)
+        e[it] = ((anti >> it) & 1u) ? f.index[frame_home(key[it] ^ p.pmask, f.slot_bits)] : kFrameEmpty;
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        kc[it] = (long long)e[it] < T0 ? f.keys[e[it]] : 0;
+        vc[it] = (long long)e[it] < T0 ? ldc<T>(f.coef, e[it]) : 0.0;
+    }
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        if (!((anti >> it) & 1u)) {
+            vc[it] = 0.0;
+            continue;
+        }
+        const long long i = b0 + it * SP_BLOCK + threadIdx.x;
+        const uint64_t K = key[it] ^ p.pmask;
+        const double cS = cw[it];
+        long long j = (long long)e[it] < T0 ? (long long)e[it] : -1;
+        double cK = vc[it];
+        if (j >= 0 && kc[it] != K) {  // another key's slot: on along the probe path
+            j = frame_resolve(f, K, frame_home(K, f.slot_bits), e[it], T0);
+            cK = j >= 0 ? ldc<T>(f.coef, j) : 0.0;
+        }
+        if (j < 0) {
+            stc<T>(f.coef, i, cS * cs);
+            kids |= 1u << it;
+            kc[it] = K;
+            vc[it] = cS * (frame_child_sign(key[it], p.pmask, p.a, n) * ssn);
+        } else if (key[it] < K) {
+            // both present: S's child lands on K and K's on S
+            const double gS = frame_child_sign(key[it], p.pmask, p.a, n) * ssn;
+            const double gK = frame_child_sign(K, p.pmask, p.a, n) * ssn;
+            stc<T>(f.coef, i, frame_merge2<T>(cS * cs, cK * gK));
+            stc<T>(f.coef, j, frame_merge2<T>(cK * cs, cS * gS));
+        }
+    }
+    // the tile's children: one counter update per tile, positions from
+    // a workgroup scan of the per-thread counts
+    const int mine = __popc(kids);
+    int incl = mine;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += o;
+    }
+    if (lane == 63) wsum[w] = incl;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int total = 0;
+        for (int u = 0; u < SP_BLOCK / 64; ++u) total += wsum[u];
+        *tbase = total ? atomicAdd(f.cnt + 3 + q, (unsigned long long)total) : 0ull;
+    }
+    __syncthreads();
+    int woff = 0;
+    for (int u = 0; u < w; ++u) woff += wsum[u];
+    unsigned long long pos = (unsigned long long)T0 + *tbase + (unsigned long long)(woff + incl - mine);
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        if (!((kids >> it) & 1u)) continue;
+        if ((long long)pos < f.cap) {
+            f.keys[pos] = kc[it];
+            stc<T>(f.coef, (long long)pos, vc[it]);
+            frame_insert(f, kc[it], (uint32_t)pos);
+        }
+        ++pos;
+    }
+    __syncthreads();  // wsum and tbase are reused by the next tile
+}
+
 template <typename T>
 __global__ __launch_bounds__(SP_BLOCK) void frame_pass_kernel(FrameBuffers f, FramePassDesc p,
                                                              const double *__restrict__ theta, int pass) {
-#pragma clang fp contract(off)
     __shared__ int wsum[SP_BLOCK / 64];
     __shared__ unsigned long long tbase;
     const int q = frame_slot_of(pass), qprev = frame_slot_of(pass - 1), qnext = frame_slot_of(pass + 1);
@@ -961,91 +1049,16 @@ __global__ __launch_bounds__(SP_BLOCK) void frame_pass_kernel(FrameBuffers f, Fr
         f.cnt[3 + qnext] = 0;
         if (f.cnt[qprev] + f.cnt[3 + qprev] > (unsigned long long)f.cap) f.cnt[6] = 1;
     }
-    const int n = f.n, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (p.rot_param < 0) return;
+    if (p.rot_param < 0 || (long long)blockIdx.x * SP_BLOCK >= T0) return;
     double sn, cs;
     sincos(theta[p.rot_param], &sn, &cs);
     const double ssn = p.sign > 0 ? sn : -sn;
-    const uint64_t lo = (1ull << n) - 1ull;
-    const uint64_t xp = p.pmask & lo, zp = p.pmask >> n;
-    const long long L = live_tiles(T0);
-    for (long long t = blockIdx.x; t < L; t += gridDim.x) {
-        // all items' keys, then the first probe of every anticommuting item,
-        // issued together: the lookups are random accesses, so they are
-        // kept in flight side by side rather than one by one
-        uint64_t key[SP_ITEMS], slot[SP_ITEMS], kc[SP_ITEMS];
-        FrameSlot e[SP_ITEMS];
-        double vc[SP_ITEMS], cw[SP_ITEMS];
-        unsigned anti = 0, kids = 0;
-#pragma unroll
-        for (int it = 0; it < SP_ITEMS; ++it) {
-            const long long i = t * SP_TILE + it * SP_BLOCK + threadIdx.x;
-            key[it] = i < T0 ? f.keys[i] : 0;
-            const bool a = i < T0 && ((__popcll((key[it] & lo) & zp) + __popcll((key[it] >> n) & xp)) & 1);
-            anti |= (unsigned)a << it;
-            slot[it] = frame_home(key[it] ^ p.pmask, f.slot_bits);
-        }
-        // the first probe and the weight of every anticommuting item, all
-        // in flight before any is used
-#pragma unroll
-        for (int it = 0; it < SP_ITEMS; ++it)
-            if ((anti >> it) & 1u) {
-                e[it] = frame_slot(f, slot[it]);
-                cw[it] = ldc<T>(f.coef, t * SP_TILE + it * SP_BLOCK + threadIdx.x);
-            }
-#pragma unroll
-        for (int it = 0; it < SP_ITEMS; ++it) {
-            kc[it] = 0;
-            vc[it] = 0.0;
-            if (!((anti >> it) & 1u)) continue;
-            const long long i = t * SP_TILE + it * SP_BLOCK + threadIdx.x;
-            const uint64_t K = key[it] ^ p.pmask;
-            const long long j = frame_resolve(f, K, slot[it], e[it]);
-            const double cS = cw[it];
-            if (j < 0) {
-                stc<T>(f.coef, i, cS * cs);
-                kids |= 1u << it;
-                kc[it] = K;
-                vc[it] = cS * (frame_child_sign(key[it], p.pmask, p.a, n) * ssn);
-            } else if (key[it] < K) {
-                // both present: S's child lands on K and K's on S
-                const double cK = ldc<T>(f.coef, j);
-                const double gS = frame_child_sign(key[it], p.pmask, p.a, n) * ssn;
-                const double gK = frame_child_sign(K, p.pmask, p.a, n) * ssn;
-                stc<T>(f.coef, i, frame_merge2<T>(cS * cs, cK * gK));
-                stc<T>(f.coef, j, frame_merge2<T>(cK * cs, cS * gS));
-            }
-        }
-        // the tile's children: one counter update per tile, positions from
-        // a workgroup scan of the per-thread counts
-        const int mine = __popc(kids);
-        int incl = mine;
-        for (int off = 1; off < 64; off <<= 1) {
-            const int o = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += o;
-        }
-        if (lane == 63) wsum[w] = incl;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int total = 0;
-            for (int u = 0; u < SP_BLOCK / 64; ++u) total += wsum[u];
-            tbase = total ? atomicAdd(f.cnt + 3 + q, (unsigned long long)total) : 0ull;
-        }
-        __syncthreads();
-        int woff = 0;
-        for (int u = 0; u < w; ++u) woff += wsum[u];
-        unsigned long long pos = (unsigned long long)T0 + tbase + (unsigned long long)(woff + incl - mine);
-#pragma unroll
-        for (int it = 0; it < SP_ITEMS; ++it) {
-            if (!((kids >> it) & 1u)) continue;
-            if ((long long)pos < f.cap) {
-                f.keys[pos] = kc[it];
-                stc<T>(f.coef, (long long)pos, vc[it]);
-                frame_insert(f, kc[it], pos);
-            }
-            ++pos;
-        }
-        __syncthreads();  // wsum and tbase are reused by the next tile
+    if (T0 <= (long long)gridDim.x * SP_BLOCK) {
+        frame_tile<T, 1>(f, p, (long long)blockIdx.x * SP_BLOCK, T0, q, cs, ssn, wsum, &tbase);
+    } else {
+        for (long long b0 = (long long)blockIdx.x * SP_BLOCK * 4; b0 < T0;
+             b0 += (long long)gridDim.x * SP_BLOCK * 4)
+            frame_tile<T, 4>(f, p, b0, T0, q, cs, ssn, wsum, &tbase);
     }
 }
 
@@ -1355,7 +1368,7 @@ hipError_t launch_sparse_readout(SparseBuffers &b, int dtype_bytes, double *part
 }
 
 static int frame_grid(const FrameBuffers &f) {
-    const long long tiles = (f.cap + SP_TILE - 1) / SP_TILE;
+    const long long tiles = (f.cap + SP_BLOCK - 1) / SP_BLOCK;
     return (int)std::max<long long>(1, std::min<long long>(tiles, SP_GRID));
 }
 
