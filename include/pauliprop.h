@@ -75,8 +75,8 @@ typedef enum pp_dtype { PP_F64 = 0, PP_F32 = 1 } pp_dtype;
  *          one kernel, pairing duplicates through a hash index.  Otherwise
  *          each pass, one kernel too, applies one rotation and the run of
  *          Clifford gates before the next, pairs duplicates through a hash
- *          table and writes the list anew; a radix sort at the end gives it
- *          the canonical order.
+ *          table and writes the list anew; pp_get_terms sorts it into the
+ *          canonical order.  <O> is summed exactly.
  *          n <= 64; the capacity is set with PP_OPT_MAX_TERMS.
  *  AUTO  : DENSE when 4^n slots fit the memory budget, else SPARSE. */
 typedef enum pp_engine { PP_ENGINE_AUTO = 0, PP_ENGINE_DENSE = 1, PP_ENGINE_SPARSE = 2 } pp_engine;

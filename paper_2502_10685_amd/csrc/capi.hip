@@ -507,8 +507,8 @@ struct pp_circuit {
     bool plan_frame = false;     // the plan's engine: frame (true) or sort-merge
     bool frame_ran = false;      // the last SPARSE evaluation used the frame
     bool frame_terms = false;    // sb holds the frame run's full final set
+    bool list_raw = false;       // sb holds the last SPARSE run's final list in no order
     uint32_t *d_codes = nullptr;
-    double *d_partials = nullptr;
 
     // graph of one evaluation (tiled dense path)
     hipGraphExec_t gexec = nullptr;
@@ -662,7 +662,6 @@ void free_state_buffers(pp_circuit *c) {
     dfree(c->pres);
     dfree(c->d_counters);
     dfree(c->d_result);
-    dfree(c->d_partials);
     for (void *&p : c->sb_base) dfree(p);
     dfree(c->sb.count);
     dfree(c->sb.scan);
@@ -670,6 +669,7 @@ void free_state_buffers(pp_circuit *c) {
     dfree(c->sb.hist);
     dfree(c->sb.tile_flags);
     dfree(c->sb.lens);
+    dfree(c->sb.exact);
     dfree(c->sb.table);
     dfree(c->d_dropped);
     c->sb = pp::SparseBuffers{};
@@ -678,6 +678,7 @@ void free_state_buffers(pp_circuit *c) {
     dfree(c->fb.index);
     dfree(c->fb.cnt);
     dfree(c->fb.updates);
+    dfree(c->fb.exact);
     c->fb = pp::FrameBuffers{};
 }
 
@@ -782,6 +783,7 @@ pp_status ensure_state(pp_circuit *c, bool weights = true) {
         HIPCHK(dalloc(&c->sb.hist, (size_t)pp::sort_hist_entries(cap2)));
         HIPCHK(dalloc(&c->sb.tile_flags, (size_t)tiles));
         HIPCHK(dalloc(&c->sb.lens, 4));
+        HIPCHK(dalloc(&c->sb.exact, (size_t)(2 * pp::kExactWords)));
         c->sb.table_bits = 8;
         while (((int64_t)1 << c->sb.table_bits) <= cap2) ++c->sb.table_bits;
         if (dalloc(&c->sb.table, (size_t)pp::kListTables << c->sb.table_bits) != hipSuccess) {
@@ -789,7 +791,6 @@ pp_status ensure_state(pp_circuit *c, bool weights = true) {
             return fail(PP_ERR_NOMEM, "sparse term tables");
         }
         HIPCHK(dalloc(&c->d_dropped, (size_t)tiles + 1));
-        HIPCHK(dalloc(&c->d_partials, 256));
     }
     const bool ramp = ramp_wanted(c);
     if (((c->engine == PP_ENGINE_SPARSE && c->n <= pp::kFrameMaxN && c->frame_opt) || ramp) && !c->fb.keys) {
@@ -807,7 +808,9 @@ pp_status ensure_state(pp_circuit *c, bool weights = true) {
         if (e == hipSuccess) e = dalloc(&f.index, (size_t)f.slots);
         if (e == hipSuccess) e = dalloc(&f.cnt, 8);
         if (e == hipSuccess) e = dalloc(&f.updates, 1);
+        if (e == hipSuccess) e = dalloc(&f.exact, (size_t)pp::kExactWords);
         if (e != hipSuccess) {
+            dfree(f.exact);
             dfree(f.keys);
             dev_free(f.coef);
             dfree(f.index);
@@ -1058,11 +1061,10 @@ void fill_plan_stats(pp_circuit *c) {
         s.tile_qubits = 0;
         int rot = 0;
         for (auto &p : P.passes) rot += p.rot_op >= 3;
-        const int dig = (2 * c->n + 7) / 8;
-        if (c->plan_frame)  // clear + init, one per pass, x0 + sort + readout
-            s.launches = 2 + (int64_t)P.passes.size() + 2 + (3 * dig + 4) + 2;
+        if (c->plan_frame)  // clear + init, one per pass, readout
+            s.launches = 2 + (int64_t)P.passes.size() + 2;
         else
-            s.launches = 2 + rot + 1 + (4 * dig + 5) + 2;  // clear + enter, one per rotation, leave, sort, readout
+            s.launches = 2 + rot + 1 + 2;  // clear + enter, one per rotation, leave, readout
         s.bytes_per_eval = 0;  // known after the run (48 or 40 bytes per update)
     }
 }
@@ -1143,7 +1145,7 @@ pp_status enqueue_dense_body(pp_circuit *c, hipStream_t s, double *out) {
 
 // Exact SPARSE evaluation in the Clifford frame: the observable into the
 // list and index, one kernel per pass, then the strings whose actual form
-// is made of I and Z sorted into canonical order and summed in that order.
+// is made of I and Z summed exactly.
 pp_status enqueue_frame(pp_circuit *c, hipStream_t s, double *out) {
     if ((int64_t)c->ox.size() > c->fb.cap) return fail(PP_ERR_CAPACITY, "observable larger than the term capacity");
     HIPCHK(pp::launch_frame_init(c->fb, c->dbytes, c->d_ox, c->d_oz, c->d_oc, (int)c->ox.size(), s));
@@ -1152,16 +1154,8 @@ pp_status enqueue_frame(pp_circuit *c, hipStream_t s, double *out) {
         ProfScope ps(PC_SPASS, s);
         HIPCHK(pp::launch_frame_pass(c->fb, c->dbytes, c->fplan.passes[(size_t)i], c->d_theta, i, s));
     }
-    {
-        ProfScope ps(PC_SMERGE, s);
-        HIPCHK(pp::launch_frame_x0(c->fb, c->dbytes, c->d_xrows, c->d_codes, (int)c->splan.codes.size(), np, c->sb,
-                                   s));
-        HIPCHK(pp::launch_sparse_merge(c->sb, c->n, c->dbytes, s));
-    }
-    {
-        ProfScope ps(PC_READOUT, s);
-        HIPCHK(pp::launch_sparse_readout(c->sb, c->dbytes, c->d_partials, out, s));
-    }
+    ProfScope ps(PC_READOUT, s);
+    HIPCHK(pp::launch_frame_readout(c->fb, c->dbytes, c->d_xrows, c->d_codes, (int)c->splan.codes.size(), np, out, s));
     return PP_OK;
 }
 
@@ -1177,6 +1171,7 @@ pp_status enqueue_sparse(pp_circuit *c, hipStream_t s, double *out) {
     const int np = (int)P.passes.size(), m = (int)c->ox.size();
     const uint32_t *codes = c->d_codes;
     int first = 0;  // the list passes begin here
+    c->list_raw = false;
     if (np == 0 || !c->obs_distinct)
         HIPCHK(pp::launch_sparse_init(c->sb, c->dbytes, c->d_ox, c->d_oz, c->d_oc, m, s,
                                       c->d_dropped + c->sb.max_tiles));
@@ -1204,14 +1199,13 @@ pp_status enqueue_sparse(pp_circuit *c, hipStream_t s, double *out) {
                                         i + 1 < np ? &P.passes[(size_t)i + 1] : nullptr, step, c->d_theta, s, tr));
         }
         ProfScope ps(PC_SMERGE, s);
-        HIPCHK(pp::launch_list_leave(c->sb, clifford_only, step, s));
-        // canonical order; a closing Clifford run may have made strings heavier
-        HIPCHK(pp::launch_sparse_merge(c->sb, c->n, c->dbytes, s, clifford_only ? tr : pp::SparseTrunc{}));
+        HIPCHK(pp::launch_list_leave(c->sb, clifford_only, step, s, tr));
+        // a closing Clifford run may have made strings heavier
+        c->list_raw = !(clifford_only && tr.on);
+        if (!c->list_raw) HIPCHK(pp::launch_sparse_merge(c->sb, c->n, c->dbytes, s, tr));
     }
-    {
-        ProfScope ps(PC_READOUT, s);
-        HIPCHK(pp::launch_sparse_readout(c->sb, c->dbytes, c->d_partials, out, s));
-    }
+    ProfScope ps(PC_READOUT, s);
+    HIPCHK(pp::launch_sparse_readout(c->sb, c->dbytes, out, s));
     return PP_OK;
 }
 
@@ -1538,6 +1532,7 @@ pp_status pp_circuit_set_option(pp_circuit *c, pp_option key, int64_t value) {
             dfree(c->fb.index);
             dfree(c->fb.cnt);
             dfree(c->fb.updates);
+            dfree(c->fb.exact);
             c->fb = pp::FrameBuffers{};
         }
         c->ramp_opt = (int)value;
@@ -1696,10 +1691,14 @@ pp_status pp_get_stats(pp_circuit *c, pp_stats *out) {
 
 namespace {
 
-// Takes the weights of a circuit run from both ends the rest of the way: the
-// forward half's gates, last first, with the maps of the evaluation that left
-// them (the forward maps' transposes).
-pp_status finish_met(pp_circuit *c, hipStream_t s) {
+// The weights of a circuit run from both ends taken the rest of the way, in a
+// copy: the forward half's gates, last first, with the maps of the evaluation
+// that left them (the forward maps' transposes).
+pp_status finish_met(pp_circuit *c, hipStream_t s, void **out) {
+    const size_t bytes = (size_t)dense_slots(c->n) * c->dbytes;
+    void *coef = nullptr;
+    if (dev_alloc(&coef, bytes) != hipSuccess) return fail(PP_ERR_NOMEM, "terms dump scratch");
+    *out = coef;
     const pp::DensePlan &P = c->met_maps ? c->met_plan : c->dplan;
     const double *maps = c->met_maps ? c->met_maps : c->d_maps;
     const pp::DensePlan R = pp::plan_reversed_forward(P);
@@ -1713,7 +1712,7 @@ pp_status finish_met(pp_circuit *c, hipStream_t s) {
     if (e == hipSuccess) {
         for (const pp::DensePass &ps : R.passes) {
             pp::TilePassDesc d{};
-            d.coef = c->coef;
+            d.coef = coef;
             d.ops = ops;
             d.maps = back;
             d.n = c->n;
@@ -1725,6 +1724,7 @@ pp_status finish_met(pp_circuit *c, hipStream_t s) {
             td.push_back(d);
         }
         if ((r = upload_vec(&pass, td)) == PP_OK) e = pp::launch_transpose_maps(maps, back, P.fwd_from, P.nmaps(), s);
+        if (r == PP_OK && e == hipSuccess) e = hipMemcpyAsync(coef, c->coef, bytes, hipMemcpyDeviceToDevice, s);
         for (size_t p = 0; r == PP_OK && e == hipSuccess && p < td.size(); ++p) {
             pp::TileGroups grp{};
             grp.ngroups = 1;
@@ -1740,7 +1740,6 @@ pp_status finish_met(pp_circuit *c, hipStream_t s) {
     dfree(back);
     if (r != PP_OK) return r;
     if (e != hipSuccess) return fail(PP_ERR_DEVICE, std::string("rest of the evaluation: ") + hipGetErrorString(e));
-    drop_met(c);
     return PP_OK;
 }
 
@@ -1757,9 +1756,13 @@ pp_status pp_get_terms(pp_circuit *c, void *stream, int64_t capacity, uint64_t *
     if (c->engine == PP_ENGINE_DENSE && !c->last_track && c->dplan.resident)
         return fail(PP_ERR_STATE, "an untracked LDS-resident evaluation keeps its weights on chip: set "
                                   "PP_OPT_TRACK_TERMS = 1 for the evaluation");
+    void *whole = nullptr;  // a met circuit's weights at the first gate
     if (c->met) {
-        pp_status mr = finish_met(c, s);
-        if (mr != PP_OK) return mr;
+        pp_status mr = finish_met(c, s, &whole);
+        if (mr != PP_OK) {
+            dev_free(whole);
+            return mr;
+        }
     }
     const uint64_t *sx = nullptr, *sz = nullptr;
     const void *sc = nullptr;
@@ -1784,6 +1787,40 @@ pp_status pp_get_terms(pp_circuit *c, void *stream, int64_t capacity, uint64_t *
         sx = c->sb.x;
         sz = c->sb.z;
         sc = c->sb.c;
+        if (!c->frame_ran && c->list_raw && count > 0) {
+            // the list of the last pass, sorted into canonical order in a copy
+            tmp.cap2 = count;
+            tmp.max_tiles = (count + 2047) / 2048;
+            bool ok = true;
+            for (int i = 0; i < 6 && ok; ++i)
+                ok = dev_alloc(&tmp_base[i], (size_t)count * ((i % 3) == 2 ? c->dbytes : 8)) == hipSuccess;
+            ok = ok && dalloc(&tmp.count, 8) == hipSuccess;
+            ok = ok && dalloc(&tmp.scan, 256) == hipSuccess;
+            ok = ok && dalloc(&tmp.hist, (size_t)pp::sort_hist_entries(count)) == hipSuccess;
+            ok = ok && dalloc(&tmp.tile_flags, (size_t)tmp.max_tiles) == hipSuccess;
+            if (ok) {
+                tmp.x = (uint64_t *)tmp_base[0];
+                tmp.z = (uint64_t *)tmp_base[1];
+                tmp.c = tmp_base[2];
+                tmp.x2 = (uint64_t *)tmp_base[3];
+                tmp.z2 = (uint64_t *)tmp_base[4];
+                tmp.c2 = tmp_base[5];
+                hipError_t e = hipMemcpyAsync(tmp.x, sx, sizeof(uint64_t) * count, hipMemcpyDeviceToDevice, s);
+                if (e == hipSuccess) e = hipMemcpyAsync(tmp.z, sz, sizeof(uint64_t) * count, hipMemcpyDeviceToDevice, s);
+                if (e == hipSuccess)
+                    e = hipMemcpyAsync(tmp.c, sc, (size_t)c->dbytes * count, hipMemcpyDeviceToDevice, s);
+                if (e == hipSuccess)
+                    e = hipMemcpyAsync(tmp.count, c->sb.count, 2 * sizeof(long long), hipMemcpyDeviceToDevice, s);
+                if (e == hipSuccess) e = pp::launch_sparse_merge(tmp, c->n, c->dbytes, s);
+                if (e == hipSuccess) e = hipStreamSynchronize(s);
+                if (e != hipSuccess) r = fail(PP_ERR_DEVICE, std::string("terms dump: ") + hipGetErrorString(e));
+            } else {
+                r = fail(PP_ERR_NOMEM, "terms dump scratch");
+            }
+            sx = tmp.x;
+            sz = tmp.z;
+            sc = tmp.c;
+        }
     } else {
         // compact present slots, then sort them into canonical order
         const int64_t slots = dense_slots(c->n);
@@ -1805,7 +1842,7 @@ pp_status pp_get_terms(pp_circuit *c, void *stream, int64_t capacity, uint64_t *
             tmp.x2 = (uint64_t *)tmp_base[3];
             tmp.z2 = (uint64_t *)tmp_base[4];
             tmp.c2 = tmp_base[5];
-            hipError_t e = pp::launch_dense_compact(c->coef, c->last_track ? c->pres : nullptr, c->n, c->dbytes,
+            hipError_t e = pp::launch_dense_compact(whole ? whole : c->coef, c->last_track ? c->pres : nullptr, c->n, c->dbytes,
                                                     tmp.x, tmp.z, (double *)tmp.c,
                                                     total, tmp.tile_flags, nullptr, nullptr, s);
             if (e == hipSuccess) {
@@ -1842,6 +1879,7 @@ pp_status pp_get_terms(pp_circuit *c, void *stream, int64_t capacity, uint64_t *
         }
         if (r == PP_OK && count > capacity) r = fail(PP_ERR_CAPACITY, "capacity smaller than the term count");
     }
+    dev_free(whole);
     for (void *&p : tmp_base) dfree(p);
     dfree(tmp.count);
     dfree(tmp.scan);

@@ -219,6 +219,7 @@ struct FrameBuffers {
                                // length in slot p mod 3 and counts its
                                // children in [3 + p mod 3]; [6] overflow
     unsigned long long *updates;
+    unsigned long long *exact; // exact sum of the readout
     int64_t cap;               // list capacity
     int64_t slots;             // index slots (power of two, >= 2 cap)
     int32_t slot_bits;
@@ -304,6 +305,7 @@ struct SparseBuffers {
     uint32_t *table;      // list passes: three hash tables of 2^table_bits positions
     int table_bits;       // 2^table_bits > cap2
     unsigned long long *lens;  // list lengths, rotating over four passes
+    unsigned long long *exact; // exact sums: the readout, then the dropped weight
     int64_t cap2;         // capacity of each array (2x the term capacity)
     int64_t max_tiles;
 };
@@ -325,7 +327,7 @@ long long sort_hist_entries(long long cap2);
 // string with more letters or with |weight| < eps is dropped.  The absolute
 // weight dropped is summed per tile into dropped[0, tiles) and added, in a
 // fixed order, to dropped[max_tiles] (reset by launch_sparse_init; the list
-// passes add theirs per wave, in no fixed order).
+// passes' is summed exactly and added by launch_list_leave).
 struct SparseTrunc {
     int32_t on = 0;
     int32_t max_weight = 64;
@@ -350,23 +352,26 @@ hipError_t launch_list_enter(SparseBuffers &b, int dtype_bytes, const uint64_t *
 hipError_t launch_list_pass(SparseBuffers &b, int dtype_bytes, const uint32_t *cliff_codes, const SparsePassDesc &p,
                             const SparsePassDesc *next, int step, const double *theta, hipStream_t s,
                             const SparseTrunc &tr);
-hipError_t launch_list_leave(SparseBuffers &b, const SparsePassDesc *last, int step, hipStream_t s);
+hipError_t launch_list_leave(SparseBuffers &b, const SparsePassDesc *last, int step, hipStream_t s,
+                             const SparseTrunc &tr);
 constexpr int kListTables = 3;
-hipError_t launch_sparse_readout(SparseBuffers &b, int dtype_bytes, double *partials, double *out,
-                                 hipStream_t s);
+// words of an exact sum (see exact_add)
+constexpr int kExactWords = 70;
+// <O>: the weights of the I/Z strings of the list, in any order (NaN after an
+// overflow)
+hipError_t launch_sparse_readout(SparseBuffers &b, int dtype_bytes, double *out, hipStream_t s);
 // Clifford-frame engine (sparse.hip)
 hipError_t launch_frame_init(FrameBuffers &f, int dtype_bytes, const uint64_t *x, const uint64_t *z,
                              const double *c, int nterms, hipStream_t s);
 // pass: its index in the schedule (selects the counter slots)
 hipError_t launch_frame_pass(FrameBuffers &f, int dtype_bytes, const FramePassDesc &p, const double *theta,
                              int pass, hipStream_t s);
-// Strings whose actual form D^dag S D (codes: every Clifford in processing
-// order) is made of I and Z only, with their signed weights, into the
-// SparseBuffers list out (x = 0, z, weight as FP64), count into out.count[0]
-// and the frame's overflow flag into out.count[1].  xrows[j]: mask of the key
-// bits whose parity is bit j of the actual x part.
-hipError_t launch_frame_x0(FrameBuffers &f, int dtype_bytes, const uint64_t *xrows, const uint32_t *codes,
-                           int ncodes, int npasses, SparseBuffers &out, hipStream_t s);
+// <O>: the signed weights of the strings whose actual form D^dag S D (codes:
+// every Clifford in processing order) is made of I and Z only (NaN after an
+// overflow).  xrows[j]: mask of the key bits whose parity is bit j of the
+// actual x part.
+hipError_t launch_frame_readout(FrameBuffers &f, int dtype_bytes, const uint64_t *xrows, const uint32_t *codes,
+                                int ncodes, int npasses, double *out, hipStream_t s);
 // Every string in its actual form into out (x, z, weight in out's type),
 // count and overflow flag into out.count[0], [1].
 // The frame's strings after its last pass, in their actual form, into a

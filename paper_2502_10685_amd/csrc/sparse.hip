@@ -13,13 +13,14 @@
 //   3. merging of equal strings (reduce(), eq. (7), Examples 3-4): a string
 //      and its child's twin find each other through a hash table, all of it
 //      in one kernel per pass (list_pass_kernel).
-// At the end the list is brought into canonical order: LSD radix sort on the
+// pp_get_terms brings the list into canonical order: LSD radix sort on the
 // 2n-bit key (z, x) with LDS-staged stable tiles, then a segmented FP64 sum
 // that keeps one string per key, zero sums included.  The first pass over an
 // observable with repeated strings is merged by that sort as well, its
-// children appended in term order (count, scan, write).  Strings, weights and
-// <O> are reproducible bit for bit: the list's order between the passes is
-// not fixed, but a merged weight is one sum of two rounded products.
+// children appended in term order (count, scan, write).  Everything is
+// reproducible bit for bit: the list's order between the passes is not fixed,
+// but a merged weight is one sum of two rounded products, and <O> and the
+// dropped weight are summed exactly.
 #include "pp_device.h"
 
 namespace pp {
@@ -306,6 +307,78 @@ __global__ __launch_bounds__(SP_BLOCK) void trunc_total_kernel(double *__restric
     if (threadIdx.x == 0) dropped[total_at] += v;
 }
 
+// ----------------------------------------------------------- exact sums
+// Lists have no fixed order, so what is summed over them is summed exactly: a
+// double adds its mantissa to 64-bit words that stand for 2^(32 w - 1074), in
+// three 32-bit pieces, and integer sums do not depend on their order.  A
+// workgroup's words hold 2^31 values; they reach the sum in pieces of 32 bits
+// again, so that holds 2^31 workgroups' shares.  Words 67 to 69 count NaN,
+// +inf and -inf.
+constexpr int kExactNan = 67;
+
+__device__ __forceinline__ void exact_add(unsigned long long *acc, double v) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const int E = (int)(u >> 52) & 2047;
+    unsigned long long m = u & 0xfffffffffffffull;
+    const bool neg = (long long)u < 0;
+    if (E == 2047) {
+        atomicAdd(acc + kExactNan + (m ? 0 : (neg ? 2 : 1)), 1ull);
+        return;
+    }
+    if (E) m |= 1ull << 52;
+    if (!m) return;
+    const int pos = E ? E - 1 : 0, w = pos >> 5, sh = pos & 31;
+    const unsigned long long lo = m << sh, hi = sh ? m >> (64 - sh) : 0ull;
+    const unsigned long long c[3] = {lo & 0xffffffffull, lo >> 32, hi};
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        if (c[i]) atomicAdd(acc + w + i, neg ? 0ull - c[i] : c[i]);
+}
+
+// A workgroup's words: cleared (a barrier follows in the caller), and added to
+// the sum in global memory behind a barrier.
+__device__ __forceinline__ void exact_clear(unsigned long long *acc) {
+    for (int i = threadIdx.x; i < kExactWords; i += blockDim.x) acc[i] = 0ull;
+}
+__device__ __forceinline__ void exact_flush(const unsigned long long *acc, unsigned long long *sum) {
+    __syncthreads();
+    for (int i = threadIdx.x; i < kExactWords; i += blockDim.x) {
+        const long long w = (long long)acc[i], high = i < kExactNan - 1 ? w >> 32 : 0;
+        const unsigned long long low = i < kExactNan - 1 ? acc[i] & 0xffffffffull : acc[i];
+        if (low) atomicAdd(sum + i, low);
+        if (high) atomicAdd(sum + i + 1, (unsigned long long)high);
+    }
+}
+
+// The sum as a double, by one wave (its lane 0): each word exactly as two
+// doubles, added up in a tree of two-sums.
+__device__ __forceinline__ double exact_value(const unsigned long long *sum, int lane) {
+#pragma clang fp contract(off)
+    auto two_sum = [](double a, double b, double &err) {
+        const double t = a + b, bb = t - a;
+        err = (a - (t - bb)) + (b - bb);
+        return t;
+    };
+    double hi = 0.0, lo = 0.0;
+    for (int i = lane; i < kExactNan; i += 64) {
+        const long long w = (long long)sum[i];
+        const double h = (double)w, l = (double)(w - (long long)h);
+        double e;
+        hi = two_sum(hi, ldexp(h, 32 * i - 1074), e);
+        lo += e + ldexp(l, 32 * i - 1074);
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        const double h = __shfl_down(hi, off, 64), l = __shfl_down(lo, off, 64);
+        double e;
+        hi = two_sum(hi, h, e);
+        lo += l + e;
+    }
+    const unsigned long long nan = sum[kExactNan], pinf = sum[kExactNan + 1], ninf = sum[kExactNan + 2];
+    if (nan || (pinf && ninf)) return __builtin_nan("");
+    if (pinf || ninf) return pinf ? __builtin_inf() : -__builtin_inf();
+    return hi + lo;
+}
+
 // ------------------------------------------------- rotations on a list
 // A rotation mixes a string S that anticommutes with it only with K = S ^
 // sigma, and strings keep no order in between, so each pass is one kernel: the
@@ -374,7 +447,9 @@ __global__ void list_clear_kernel(SparseBuffers b, int nterms, double *dropped_t
     const unsigned long long T = nterms >= 0 ? (unsigned long long)nterms : (unsigned long long)b.count[0];
     list_clear(b, 0, T);
     list_clear(b, 1, T);
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+    if (blockIdx.x != 0) return;
+    for (int i = threadIdx.x; i < 2 * kExactWords; i += blockDim.x) b.exact[i] = 0ull;
+    if (threadIdx.x != 0) return;
     b.lens[0] = b.lens[3] = T;
     b.lens[1] = b.lens[2] = 0;
     if (nterms >= 0) {
@@ -409,9 +484,9 @@ __global__ __launch_bounds__(SP_BLOCK) void list_enter_kernel(SparseBuffers b, c
 template <typename T>
 __global__ __launch_bounds__(LIST_BLOCK) void list_pass_kernel(SparseBuffers b, SparsePassDesc p, SparsePassDesc nx,
                                                               const uint32_t *__restrict__ codes, int step,
-                                                              const double *__restrict__ theta, SparseTrunc tr,
-                                                              double *__restrict__ dropped_total) {
+                                                              const double *__restrict__ theta, SparseTrunc tr) {
 #pragma clang fp contract(off)
+    __shared__ unsigned long long acc[kExactWords];
     __shared__ unsigned wsum[LIST_BLOCK / 64];
     __shared__ unsigned long long tbase;
     const unsigned long long now = b.lens[step & 3], was = b.lens[(step + 3) & 3] & 0xffffffffull;
@@ -428,9 +503,13 @@ __global__ __launch_bounds__(LIST_BLOCK) void list_pass_kernel(SparseBuffers b, 
     const uint32_t *table = list_table(b, step);
     const uint32_t mask = (uint32_t)((1ull << bits) - 1ull);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    double sn = 0.0, cs = 1.0;
-    if ((long long)blockIdx.x * LIST_BLOCK < Tn) sincos(theta[p.rot_param], &sn, &cs);
-    double lost = 0.0;
+    if ((long long)blockIdx.x * LIST_BLOCK >= Tn) return;
+    if (tr.on) {
+        exact_clear(acc);
+        __syncthreads();
+    }
+    double sn, cs;
+    sincos(theta[p.rot_param], &sn, &cs);
     for (long long b0 = (long long)blockIdx.x * LIST_BLOCK; b0 < Tn; b0 += (long long)gridDim.x * LIST_BLOCK) {
         const long long i = b0 + threadIdx.x;
         bool keep = i < Tn, born = false, kid = false;
@@ -460,15 +539,15 @@ __global__ __launch_bounds__(LIST_BLOCK) void list_pass_kernel(SparseBuffers b, 
             born = pauli_weight(kx, kz) <= tr.max_weight;
             kid = born && !paired;
             child = (double)(T)grown;
-            if (!born) lost += fabs(grown);
+            if (!born) exact_add(acc, fabs(grown));
         }
         if (tr.on) {
             if (kid && !(fabs(child) >= tr.eps)) {
-                lost += fabs(child);
+                exact_add(acc, fabs(child));
                 kid = false;
             }
             if (keep && !(fits && fabs(own) >= tr.eps)) {
-                lost += fabs(own);
+                exact_add(acc, fabs(own));
                 keep = false;
             }
         }
@@ -511,21 +590,21 @@ __global__ __launch_bounds__(LIST_BLOCK) void list_pass_kernel(SparseBuffers b, 
         }
         __syncthreads();  // wsum and tbase are reused by the next tile
     }
-    if (tr.on) {
-        for (int off = 32; off > 0; off >>= 1) lost += __shfl_xor(lost, off, 64);
-        if (lane == 0 && lost != 0.0) atomicAdd(dropped_total, lost);
-    }
+    if (tr.on) exact_flush(acc, b.exact + kExactWords);
 }
 
-// The list's length and overflow flag for the kernels that follow; ngates: of
-// a closing Clifford run, for the term updates.
-__global__ void list_leave_kernel(SparseBuffers b, int step, int ngates) {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+// The list's length and overflow flag for the kernels that follow, and the
+// dropped weight; ngates: of a closing Clifford run, for the term updates.
+__global__ __launch_bounds__(64) void list_leave_kernel(SparseBuffers b, int step, int ngates,
+                                                       double *__restrict__ dropped_total) {
+    const double lost = exact_value(b.exact + kExactWords, threadIdx.x);
+    if (threadIdx.x != 0) return;
     const unsigned long long now = b.lens[step & 3], was = b.lens[(step + 3) & 3] & 0xffffffffull;
     if (step > 0 && was + (now >> 32) > (unsigned long long)b.cap2) b.count[1] = 1;
     const long long Tn = list_len(b, step);
     b.count[0] = Tn;
     *b.updates += (unsigned long long)Tn * (unsigned long long)ngates;
+    *dropped_total += lost;
 }
 
 // ---------------------------------------------------------- radix sort
@@ -778,38 +857,38 @@ __global__ __launch_bounds__(SP_BLOCK) void seg_write_kernel(const uint64_t *__r
 }
 
 // -------------------------------------------------------------- readout
-constexpr int RO_BLOCKS = 256;
+// The weights of the I/Z strings, summed exactly: no sort has to give the
+// list an order first (n = 32, 400 gates: 1.18 ms, 1.40 with the sort; 2^14
+// strings of a spread circuit at n = 14: 0.10 ms, 0.19).
+constexpr int RO_GRID = 1024;
 
 template <typename T>
-__global__ __launch_bounds__(256) void sp_readout_partial_kernel(const uint64_t *__restrict__ x, const void *c,
-                                                                const long long *__restrict__ count,
-                                                                double *__restrict__ partials) {
-    __shared__ double red[4];
+__global__ __launch_bounds__(SP_BLOCK) void sp_readout_kernel(const uint64_t *__restrict__ x, const T *__restrict__ c,
+                                                             const long long *__restrict__ count,
+                                                             unsigned long long *__restrict__ sum) {
+    __shared__ unsigned long long acc[kExactWords];
     const long long Tn = count[0];
-    const long long per = (Tn + RO_BLOCKS - 1) / RO_BLOCKS;
-    const long long lo = blockIdx.x * per, hi = lo + per < Tn ? lo + per : Tn;
-    double s = 0.0;
-    for (long long i = lo + threadIdx.x; i < hi; i += 256)
-        if (x[i] == 0) s += ldc<T>(c, i);
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    if ((long long)blockIdx.x * SP_BLOCK >= Tn) return;
+    exact_clear(acc);
     __syncthreads();
-    if (threadIdx.x == 0) partials[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+    for (long long i = (long long)blockIdx.x * SP_BLOCK + threadIdx.x; i < Tn; i += (long long)gridDim.x * SP_BLOCK)
+        if (x[i] == 0) exact_add(acc, (double)c[i]);
+    exact_flush(acc, sum);
 }
 
-__global__ void sp_readout_final_kernel(const double *__restrict__ partials, const long long *__restrict__ count,
-                                        double *__restrict__ out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double s = 0.0;
-    for (int b = 0; b < RO_BLOCKS; ++b) s += partials[b];
-    *out = count[1] ? __builtin_nan("") : s;
+__global__ __launch_bounds__(64) void readout_final_kernel(const unsigned long long *__restrict__ sum,
+                                                          const long long *__restrict__ overflow,
+                                                          double *__restrict__ out) {
+    const double v = exact_value(sum, threadIdx.x);
+    if (threadIdx.x == 0) *out = *overflow ? __builtin_nan("") : v;
 }
 
 // ---------------------------------------------------------------- init
 template <typename T>
 __global__ void sp_init_kernel(uint64_t *x, uint64_t *z, void *c, long long *count, unsigned long long *updates,
                                const uint64_t *ox, const uint64_t *oz, const double *oc, int nterms,
-                               double *dropped_total) {
+                               double *dropped_total, unsigned long long *exact) {
+    for (int i = threadIdx.x; i < 2 * kExactWords; i += blockDim.x) exact[i] = 0ull;
     if (blockIdx.x != 0 || threadIdx.x != 0) return;
     if (dropped_total) *dropped_total = 0.0;
     for (int t = 0; t < nterms; ++t) {
@@ -902,6 +981,7 @@ __global__ void frame_clear_kernel(uint32_t *__restrict__ index, long long slots
 template <typename T>
 __global__ void frame_init_kernel(FrameBuffers f, const uint64_t *ox, const uint64_t *oz, const double *oc,
                                   int nterms) {
+    for (int i = threadIdx.x; i < kExactWords; i += blockDim.x) f.exact[i] = 0ull;
     if (blockIdx.x != 0 || threadIdx.x != 0) return;
     unsigned long long len = 0, over = 0;
     for (int t = 0; t < nterms; ++t) {
@@ -1062,59 +1142,39 @@ __global__ __launch_bounds__(SP_BLOCK) void frame_pass_kernel(FrameBuffers f, Fr
     }
 }
 
-// Strings whose actual form is made of I and Z only: the x part of the
+// <O>: strings whose actual form is made of I and Z only.  The x part of the
 // actual string is linear in the key (xrows), so the others are skipped at
-// the cost of n parities; the kept ones replay every Clifford for their
-// actual z and sign.
+// the cost of a few parities; the kept ones replay every Clifford for their
+// sign.
 template <typename T>
-__global__ __launch_bounds__(SP_BLOCK) void frame_x0_kernel(FrameBuffers f, const uint64_t *__restrict__ xrows,
-                                                           const uint32_t *__restrict__ codes, int ncodes, int npasses,
-                                                           uint64_t *__restrict__ ox, uint64_t *__restrict__ oz, void *oc,
-                                                           long long *__restrict__ ocount) {
+__global__ __launch_bounds__(SP_BLOCK) void frame_readout_kernel(FrameBuffers f, const uint64_t *__restrict__ xrows,
+                                                                const uint32_t *__restrict__ codes, int ncodes,
+                                                                int npasses) {
+    __shared__ unsigned long long acc[kExactWords];
     __shared__ uint64_t rows[64];
-    const int n = f.n, lane = threadIdx.x & 63;
-    if (threadIdx.x < n) rows[threadIdx.x] = xrows[threadIdx.x];
-    __syncthreads();
+    const int n = f.n;
     const long long T0 = frame_len(f, npasses - 1);
-    const int ql = frame_slot_of(npasses - 1);
-    const uint64_t lo = (1ull << n) - 1ull;
-    if (blockIdx.x == 0 && threadIdx.x == 0)
-        ocount[1] = (f.cnt[6] || f.cnt[ql] + f.cnt[3 + ql] > (unsigned long long)f.cap) ? 1 : 0;
-    const long long L = live_tiles(T0);
-    for (long long t = blockIdx.x; t < L; t += gridDim.x) {
-        for (int it = 0; it < SP_ITEMS; ++it) {
-            const long long i = t * SP_TILE + it * SP_BLOCK + threadIdx.x;
-            bool keep = false;
-            uint64_t zz = 0;
-            double v = 0.0;
-            if (i < T0) {
-                const uint64_t key = f.keys[i];
-                unsigned odd = 0;
-                for (int j = 0; j < n; ++j) odd |= (unsigned)__popcll(key & rows[j]) & 1u;
-                if (!odd) {
-                    uint64_t x = key & lo, z = key >> n;
-                    unsigned neg = 0;
-                    clifford_apply(x, z, neg, codes, 0, ncodes);
-                    keep = true;
-                    zz = z;
-                    v = ldc<T>(f.coef, i);
-                    if (neg) v = -v;
-                }
-            }
-            const unsigned long long bal = __ballot(keep);
-            if (bal) {
-                unsigned long long base = 0;
-                if (lane == 0) base = atomicAdd((unsigned long long *)ocount, (unsigned long long)__popcll(bal));
-                base = __shfl(base, 0, 64);
-                if (keep) {
-                    const long long pos = (long long)(base + (unsigned long long)__popcll(bal & ((1ull << lane) - 1ull)));
-                    ox[pos] = 0;
-                    oz[pos] = zz;
-                    stc<T>(oc, pos, v);
-                }
-            }
-        }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        const int ql = frame_slot_of(npasses - 1);
+        if (f.cnt[ql] + f.cnt[3 + ql] > (unsigned long long)f.cap) f.cnt[6] = 1;
     }
+    if ((long long)blockIdx.x * SP_BLOCK >= T0) return;
+    if (threadIdx.x < n) rows[threadIdx.x] = xrows[threadIdx.x];
+    exact_clear(acc);
+    __syncthreads();
+    const uint64_t lo = (1ull << n) - 1ull;
+    for (long long i = (long long)blockIdx.x * SP_BLOCK + threadIdx.x; i < T0; i += (long long)gridDim.x * SP_BLOCK) {
+        const uint64_t key = f.keys[i];
+        unsigned odd = 0;
+        for (int j = 0; j < n && !odd; ++j) odd = (unsigned)__popcll(key & rows[j]) & 1u;
+        if (odd) continue;
+        uint64_t x = key & lo, z = key >> n;
+        unsigned neg = 0;
+        clifford_apply(x, z, neg, codes, 0, ncodes);
+        const double v = ldc<T>(f.coef, i);
+        exact_add(acc, neg ? -v : v);
+    }
+    exact_flush(acc, f.exact);
 }
 
 // Every string in its actual form, at its list position.
@@ -1234,10 +1294,10 @@ hipError_t launch_sparse_init(SparseBuffers &b, int dtype_bytes, const uint64_t 
                               const double *c, int nterms, hipStream_t s, double *dropped_total) {
     if (dtype_bytes == 8)
         hipLaunchKernelGGL(sp_init_kernel<double>, dim3(1), dim3(64), 0, s, b.x, b.z, b.c, b.count, b.updates, x, z,
-                           c, nterms, dropped_total);
+                           c, nterms, dropped_total, b.exact);
     else
         hipLaunchKernelGGL(sp_init_kernel<float>, dim3(1), dim3(64), 0, s, b.x, b.z, b.c, b.count, b.updates, x, z, c,
-                           nterms, dropped_total);
+                           nterms, dropped_total, b.exact);
     return hipGetLastError();
 }
 
@@ -1302,19 +1362,19 @@ hipError_t launch_list_pass(SparseBuffers &b, int dtype_bytes, const uint32_t *c
     if (next) nx = *next;
     const dim3 grid(list_grid(b)), block(LIST_BLOCK);
     if (dtype_bytes == 8)
-        hipLaunchKernelGGL(list_pass_kernel<double>, grid, block, 0, s, b, p, nx, codes, step, theta, tr,
-                           tr.dropped + b.max_tiles);
+        hipLaunchKernelGGL(list_pass_kernel<double>, grid, block, 0, s, b, p, nx, codes, step, theta, tr);
     else
-        hipLaunchKernelGGL(list_pass_kernel<float>, grid, block, 0, s, b, p, nx, codes, step, theta, tr,
-                           tr.dropped + b.max_tiles);
+        hipLaunchKernelGGL(list_pass_kernel<float>, grid, block, 0, s, b, p, nx, codes, step, theta, tr);
     std::swap(b.x, b.x2);
     std::swap(b.z, b.z2);
     std::swap(b.c, b.c2);
     return hipGetLastError();
 }
 
-hipError_t launch_list_leave(SparseBuffers &b, const SparsePassDesc *last, int step, hipStream_t s) {
-    hipLaunchKernelGGL(list_leave_kernel, dim3(1), dim3(64), 0, s, b, step, last ? last->ngates : 0);
+hipError_t launch_list_leave(SparseBuffers &b, const SparsePassDesc *last, int step, hipStream_t s,
+                             const SparseTrunc &tr) {
+    hipLaunchKernelGGL(list_leave_kernel, dim3(1), dim3(64), 0, s, b, step, last ? last->ngates : 0,
+                       tr.dropped + b.max_tiles);
     return hipGetLastError();
 }
 
@@ -1356,14 +1416,15 @@ hipError_t launch_sparse_merge(SparseBuffers &b, int n, int dtype_bytes, hipStre
     return hipGetLastError();
 }
 
-hipError_t launch_sparse_readout(SparseBuffers &b, int dtype_bytes, double *partials, double *out, hipStream_t s) {
+hipError_t launch_sparse_readout(SparseBuffers &b, int dtype_bytes, double *out, hipStream_t s) {
+    const int g = (int)std::max<long long>(1, std::min<long long>((b.cap2 + SP_BLOCK - 1) / SP_BLOCK, RO_GRID));
     if (dtype_bytes == 8)
-        hipLaunchKernelGGL(sp_readout_partial_kernel<double>, dim3(RO_BLOCKS), dim3(256), 0, s, b.x, b.c, b.count,
-                           partials);
+        hipLaunchKernelGGL(sp_readout_kernel<double>, dim3(g), dim3(SP_BLOCK), 0, s, b.x, (const double *)b.c, b.count,
+                           b.exact);
     else
-        hipLaunchKernelGGL(sp_readout_partial_kernel<float>, dim3(RO_BLOCKS), dim3(256), 0, s, b.x, b.c, b.count,
-                           partials);
-    hipLaunchKernelGGL(sp_readout_final_kernel, dim3(1), dim3(64), 0, s, partials, b.count, out);
+        hipLaunchKernelGGL(sp_readout_kernel<float>, dim3(g), dim3(SP_BLOCK), 0, s, b.x, (const float *)b.c, b.count,
+                           b.exact);
+    hipLaunchKernelGGL(readout_final_kernel, dim3(1), dim3(64), 0, s, b.exact, b.count + 1, out);
     return hipGetLastError();
 }
 
@@ -1394,16 +1455,16 @@ hipError_t launch_frame_pass(FrameBuffers &f, int dtype_bytes, const FramePassDe
     return hipGetLastError();
 }
 
-hipError_t launch_frame_x0(FrameBuffers &f, int dtype_bytes, const uint64_t *xrows, const uint32_t *codes, int ncodes,
-                           int npasses, SparseBuffers &out, hipStream_t s) {
-    hipLaunchKernelGGL(zero_ll_kernel, dim3(1), dim3(64), 0, s, out.count, 8);
-    const int g = frame_grid(f);
+hipError_t launch_frame_readout(FrameBuffers &f, int dtype_bytes, const uint64_t *xrows, const uint32_t *codes,
+                                int ncodes, int npasses, double *out, hipStream_t s) {
+    const int g = (int)std::max<long long>(1, std::min<long long>((f.cap + SP_BLOCK - 1) / SP_BLOCK, SP_GRID));
     if (dtype_bytes == 8)
-        hipLaunchKernelGGL(frame_x0_kernel<double>, dim3(g), dim3(SP_BLOCK), 0, s, f, xrows, codes, ncodes, npasses,
-                           out.x, out.z, out.c, out.count);
+        hipLaunchKernelGGL(frame_readout_kernel<double>, dim3(g), dim3(SP_BLOCK), 0, s, f, xrows, codes, ncodes,
+                           npasses);
     else
-        hipLaunchKernelGGL(frame_x0_kernel<float>, dim3(g), dim3(SP_BLOCK), 0, s, f, xrows, codes, ncodes, npasses,
-                           out.x, out.z, out.c, out.count);
+        hipLaunchKernelGGL(frame_readout_kernel<float>, dim3(g), dim3(SP_BLOCK), 0, s, f, xrows, codes, ncodes,
+                           npasses);
+    hipLaunchKernelGGL(readout_final_kernel, dim3(1), dim3(64), 0, s, f.exact, (const long long *)f.cnt + 6, out);
     return hipGetLastError();
 }
 
