@@ -12,7 +12,7 @@ BUILD = os.path.join(HERE, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("PP_OFFLOAD_ARCH", "gfx950")
 
-SOURCES = ["dense.hip", "resident.hip", "tile7.hip", "adjoint.hip", "sparse.hip", "capi.hip", "plan.cpp"]
+SOURCES = ["dense.hip", "resident.hip", "tile_chain.hip", "adjoint.hip", "sparse.hip", "capi.hip", "plan.cpp"]
 
 FLAGS = [
     f"--offload-arch={ARCH}", "-O3", "-fPIC", "-std=c++17",

@@ -281,15 +281,17 @@ int g_resident_block[8] = {64, 64, 64, 64, 64, 512, 512, 1024};
 // FP64) are never needed at once
 constexpr int64_t kSweepChunk = 512;
 // Weights and states of a sweep's tiled circuits run from both ends that are
-// held at once: 64 sets of 10 qubits in FP64 give 32,768 tiles per launch
-constexpr int64_t kSweepMeetBytes = (int64_t)1 << 30;
+// held at once: 16 sets of 10 qubits in FP64 give 2,048 tiles of 7 qubits per
+// launch, and a new sweep allocates no more than one end of them took
+constexpr int64_t kSweepMeetBytes = (int64_t)256 << 20;
 
 // Tile qubits by n.  7-qubit tiles take about a third fewer passes, but a
 // workgroup of 1,024 threads per tile: they pay from the n whose tiles come
-// near the 256 CUs (FP64, 6 against 7 qubits: 5,000 random gates at n = 8 0.73
-// against 0.89 ms, n = 9 0.85 against 1.09, n = 10 1.27 against 1.22; 3,000 at
-// n = 11 1.76 against 1.56, n = 12 6.3 against 4.8, n = 13 26.6 against 19.6;
-// 32 circuits of n = 10 4.40 against 3.74; FP32 alike), up to the kernel's 14.
+// near the 256 CUs, or from the n of which a batch's do (FP64, 6 against 7
+// qubits: 5,000 random gates at n = 8 0.67 against 0.89 ms, n = 9 0.77 against
+// 1.08, n = 10 1.16 against 1.21; 32 circuits of n = 9 1.12 against 1.21, of n
+// = 10 4.23 against 3.74; 3,000 gates at n = 11 1.76 against 1.56, n = 12 6.3
+// against 4.8, n = 13 26.6 against 19.6; FP32 alike), up to the kernel's 14.
 int g_tile_qubits[17] = {0, 0, 0, 0, 0, 0, 0, 0, 6, 6, 7, 7, 7, 7, 7, 6, 6};
 int default_tile_qubits(int n) { return n >= 8 && n <= 16 ? g_tile_qubits[n] : (n > 16 ? 6 : 5); }
 
@@ -518,6 +520,7 @@ struct pp_circuit {
     struct Grad {
         bool valid = false;
         int64_t every = -1;
+        bool seg = false;  // register segments, as the plan's
         int k_heis = 0, k_fwd = 0;
         pp::GradPlan plan;
         pp::DOp *hops = nullptr;
@@ -898,6 +901,7 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
             pp::PlanOptions o;
             o.g_end = c->ramp_gate;  // the dense sweep takes the gates before the frame's
             o.segments = seg;
+            o.chain = pp::chain_tiles(k, seg);
             c->dplan = k == c->n || meets(c, k)
                            ? pp::plan_meet(c->g, k, kLowQubits, c->ramp_gate, seg, c->dbytes, &c->pass_recs)
                            : pp::plan_dense_opts(c->g, k, kLowQubits, o);
@@ -907,10 +911,11 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
             pp::PlanOptions o;
             o.compose = o.group = o.reorder = c->track == 0;
             o.segments = seg;
+            o.chain = pp::chain_tiles(k, seg);
             c->dplan = pp::plan_dense_opts(c->g, k, kLowQubits, o);
             if (k == c->n && !c->track) pp::build_chain(c->dplan, c->dbytes);
         }
-        if (k < c->n && k == pp::kChainTileDigits && !c->track && c->dplan.fwd_from < 0)
+        if (k < c->n && pp::chain_tiles(k, seg) && !c->track && c->dplan.fwd_from < 0)
             pp::build_chain(c->dplan, c->dbytes, &c->pass_recs);
         const pp::DensePlan &P = c->dplan;
         {
@@ -966,7 +971,7 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
         } else {
             c->h_pass.clear();
             std::vector<int> rec;
-            if (k == pp::kChainTileDigits && !c->track) {
+            if (pp::chain_tiles(k, seg) && !c->track) {
                 if ((r = upload_vec(&c->d_chain, P.chain)) != PP_OK) return r;
                 rec = c->pass_recs;
             }
@@ -1082,6 +1087,7 @@ pp::TileGroups step_groups(const pp_circuit *c, size_t l) {
     pp::TileGroups grp{};
     const int shift = 2 * (c->n - c->dplan.k);
     grp.ngroups = 1;
+    grp.chain = pp::chain_tiles(c->dplan.k, c->plan_seg);
     grp.first_block[1] = (c->step[l + 1] - c->step[l]) << shift;
     grp.first_desc[0] = c->step[l];
     grp.shift[0] = shift;
@@ -2263,8 +2269,11 @@ pp_status build_batch(BatchCache &B, pp_circuit *const *cs, int64_t count, doubl
             td.clear();
             pp::TileGroups tg{};
             int run = 0, last_n = -1;
+            bool chain = true;
+            for (int i : by_k[k]) chain = chain && pp::chain_tiles(k, cs[i]->plan_seg);
             auto close = [&] {
                 tg.first_block[tg.ngroups] = run;
+                tg.chain = chain;
                 B.tiles.push_back({2, k, out.put(td), (int)td.size(), run, tg});
                 td.clear();
                 tg = pp::TileGroups{};
@@ -2394,18 +2403,20 @@ namespace {
 
 pp_status ensure_grad(pp_circuit *c, int64_t every) {
     auto &G = c->gr;
-    if (G.valid && G.every == every) return PP_OK;
+    const int tv6 = pp::tile_kernel_variant(6);  // as in ensure_plan
+    const bool seg = tv6 == 3 || tv6 == 4;
+    if (G.valid && G.every == every && G.seg == seg) return PP_OK;
     free_grad(c);
     const int n = c->n;
     const int k_heis = tile_qubits_for(c, true);
     const int k_fwd = n <= 6 ? n : 6;
-    G.plan = pp::plan_gradient(c->g, k_heis, k_fwd, kLowQubits, every);
+    G.plan = pp::plan_gradient(c->g, k_heis, k_fwd, kLowQubits, every, seg);
     const pp::GradPlan &P = G.plan;
     for (const pp::DensePlan *part : {&P.heis, &P.fwd}) {
         const std::string bad = pp::plan_check(*part, n);
         if (!bad.empty()) return fail(PP_ERR_STATE, "planner self-check: " + bad);
     }
-    if (!pp::plan_segmented(P.heis)) return fail(PP_ERR_STATE, "planner self-check: unsegmented pass");
+    if (seg && !pp::plan_segmented(P.heis)) return fail(PP_ERR_STATE, "planner self-check: unsegmented pass");
     pp_status r;
     if ((r = upload_vec(&G.hops, P.heis.ops)) != PP_OK) return r;
     if ((r = upload_vec(&G.hroff, P.heis.roff)) != PP_OK) return r;
@@ -2451,7 +2462,7 @@ pp_status ensure_grad(pp_circuit *c, int64_t every) {
         }
         if ((r = upload_vec(&G.hres, rd)) != PP_OK) return r;
     } else {
-        if (k_heis == pp::kChainTileDigits && (r = upload_vec(&G.hchain, P.heis.chain)) != PP_OK) return r;
+        if (pp::chain_tiles(k_heis, seg) && (r = upload_vec(&G.hchain, P.heis.chain)) != PP_OK) return r;
         std::vector<pp::TilePassDesc> td;
         for (const pp::DensePass &ps : P.heis.passes) {
             pp::TilePassDesc d{};
@@ -2465,7 +2476,7 @@ pp_status ensure_grad(pp_circuit *c, int64_t every) {
             d.ntiles = (int)((int64_t)1 << (2 * (n - k_heis)));
             for (int j = 0; j < k_heis; ++j) d.qubits |= (uint64_t)ps.qubit[j] << (8 * j);
             d.reg_entry = pp::pass_reg_entry(P.heis, ps);
-            if (k_heis == pp::kChainTileDigits)
+            if (pp::chain_tiles(k_heis, seg))
                 set_chain(d, P.heis, ps, G.hchain, P.heis_chain_begin[td.size()], P.heis_chain_begin[td.size() + 1], 8);
             td.push_back(d);
         }
@@ -2508,6 +2519,7 @@ pp_status ensure_grad(pp_circuit *c, int64_t every) {
     G.k_heis = k_heis;
     G.k_fwd = k_fwd;
     G.every = every;
+    G.seg = seg;
     G.valid = true;
     return PP_OK;
 }
@@ -2662,6 +2674,7 @@ extern "C" pp_status pp_evaluate_thetas(pp_circuit *c, int64_t count, const doub
             // one launch: the sets' descriptors of a pass are consecutive
             pp::TileGroups grp{};
             grp.ngroups = 1;
+            grp.chain = pp::chain_tiles(P.k, c->plan_seg);
             grp.first_block[1] = (int32_t)((c->step[l + 1] - c->step[l]) * cs * ntiles);
             grp.shift[0] = shift;
             HIPCHK(pp::launch_tile_pass(pass + (size_t)c->step[l] * cs, grp, P.k, c->dbytes, false, s));
@@ -2840,6 +2853,7 @@ pp_status enqueue_gradient_body(pp_circuit *c, hipStream_t s, double *d_expval, 
             for (int p = P.heis_pass_begin[sg]; p < P.heis_pass_begin[sg + 1]; ++p) {
                 pp::TileGroups grp{};
                 grp.ngroups = 1;
+                grp.chain = pp::chain_tiles(G.k_heis, G.seg);
                 grp.first_block[1] = 1 << shift;
                 grp.first_desc[0] = p;
                 grp.shift[0] = shift;
@@ -3353,6 +3367,8 @@ void server_loop(pp_server *S) {
                         }
                     }
                     tg.first_block[tg.ngroups] = run;
+                    tg.chain = 1;
+                    for (size_t j = i0; j < i; ++j) tg.chain &= pp::chain_tiles(k, grp[j]->c->plan_seg);
                     std::vector<unsigned char> blob(td.size() * sizeof(pp::TilePassDesc));
                     std::memcpy(blob.data(), td.data(), blob.size());
                     void *dd = nullptr;

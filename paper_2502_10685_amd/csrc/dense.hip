@@ -1733,9 +1733,9 @@ static hipError_t launch_tile_t(const TilePassDesc *d, const TileGroups &grp, si
         hipLaunchKernelGGL(fn, dim3(nblocks), dim3(64), lds, s, d, grp);
         return hipGetLastError();
     }
-    if constexpr (!TRACK && K == 7)
-        if (g_tile_variant[7] == 1 && max_n <= 14) return launch_tile7(d, grp, (int)sizeof(T), s);
-    if constexpr (!TRACK && K <= 6) if (g_tile_variant[K] == 1 && max_n <= 14) {
+    if constexpr (!TRACK && K >= 6)
+        if (g_tile_variant[K] == 1 && max_n <= 14 && grp.chain) return launch_tile_chain(d, grp, K, (int)sizeof(T), s);
+    if constexpr (!TRACK && K < 6) if (g_tile_variant[K] == 1 && max_n <= 14) {
         auto fn = tile_stream_kernel<T, K>;
         constexpr int SB = kStreamBlock<K>;
         static int rb = 0;

@@ -285,6 +285,12 @@ void split_waves(std::vector<DOp> &ops, DensePass &ps) {
         for (int d = 0; d < ps.k; ++d) q[to[d]] = ps.qubit[d];
         for (int d = 0; d < ps.k; ++d) ps.qubit[d] = q[d];
     }
+}
+
+// Marks the barriers of a 6-digit pass that its sweeps can skip.
+void tag_barriers(std::vector<DOp> &ops) {
+    for (DOp &d : ops)
+        if (d.kind != DOP_SEG) d.perm &= (uint16_t)~kSkipBarrier;
     DOp *prev = nullptr;
     for (size_t i = 0; i < ops.size();) {
         DOp &d = ops[i];
@@ -299,13 +305,13 @@ void split_waves(std::vector<DOp> &ops, DensePass &ps) {
     }
 }
 
-// 7-digit tiles run as record chains: a group becomes groups of one CX and at
+// Tiles of 7 and 6 digits run as record chains: a group becomes groups of one CX and at
 // most one map per digit behind it, the lower digit's first (maps on different
 // digits commute).  Then a unit (group or lone op) on digits above 1 that
 // commutes with every unit before it comes first, and one that commutes with
 // every unit behind it last: those two are applied between registers and HBM,
 // where the 128-byte runs need digits 0 and 1 across the lanes.
-// One entry per piece of at most kTile7Units units.
+// One entry per piece of at most kTileUnits units.
 std::vector<std::vector<DOp>> chain_order(const std::vector<DOp> &in) {
     std::vector<std::vector<DOp>> all;
     for (size_t i = 0; i < in.size();) {
@@ -377,13 +383,13 @@ std::vector<std::vector<DOp>> chain_order(const std::vector<DOp> &in) {
         return out;
     };
     std::vector<std::vector<DOp>> pieces;
-    for (size_t u = 0; u < all.size(); u += kTile7Units)
+    for (size_t u = 0; u < all.size(); u += kTileUnits)
         pieces.push_back(piece({all.begin() + (long)u,
-                                all.begin() + (long)std::min(all.size(), u + (size_t)kTile7Units)}));
+                                all.begin() + (long)std::min(all.size(), u + (size_t)kTileUnits)}));
     return pieces;
 }
 
-void group_all(DensePlan &P, bool segments) {
+void group_all(DensePlan &P, bool segments, bool chain) {
     std::vector<DOp> ops;
     std::vector<DensePass> passes;
     for (DensePass &ps : P.passes) {
@@ -392,9 +398,10 @@ void group_all(DensePlan &P, bool segments) {
             (segments && !P.resident && ps.k == kSegTileDigits) ? segment_ops(in, ps.k) : group_ops(in, ps.k);
         if (!P.resident && ps.k == 6) split_waves(out, ps);
         std::vector<std::vector<DOp>> pieces;
-        if (!P.resident && ps.k == kChainTileDigits && !out.empty()) pieces = chain_order(out);
+        if (!P.resident && (ps.k == kChainTileDigits || (ps.k == 6 && chain)) && !out.empty()) pieces = chain_order(out);
         else pieces.push_back(std::move(out));
-        for (const auto &piece : pieces) {
+        for (auto &piece : pieces) {
+            if (!P.resident && ps.k == 6) tag_barriers(piece);
             ps.op_begin = (int)ops.size();
             ops.insert(ops.end(), piece.begin(), piece.end());
             ps.op_end = (int)ops.size();
@@ -412,7 +419,7 @@ static DensePlan plan_dense_core(const GateList &g, int k, int low, const PlanOp
 
 DensePlan plan_dense_opts(const GateList &g, int k, int low, const PlanOptions &o) {
     DensePlan P = plan_dense_core(g, k, low, o);
-    if (o.group && o.compose) group_all(P, o.segments);
+    if (o.group && o.compose) group_all(P, o.segments, o.chain);
     return P;
 }
 
@@ -817,8 +824,8 @@ void plan_append(DensePlan &all, const DensePlan &part) {
     all.resident = part.resident;
 }
 
-void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin) {
-    const bool tile7 = !P.resident && P.k == kChainTileDigits;
+void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin, bool ends) {
+    const bool tiled = !P.resident && ends;
     std::vector<int> order;  // new map index -> old
     std::vector<uint32_t> renum((size_t)P.nmaps(), 0);
     // maps are numbered pair member by pair member, the lower digit first
@@ -851,13 +858,13 @@ void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin) {
                 count = h.ngates;
             } else {
                 int other = h.kind == DOP_CX ? h.b : (h.a == 0 ? 1 : h.a - 1);
-                if (tile7 && h.kind == DOP_U1 && h.a == 2) other = 3;  // away from digits 0 and 1
+                if (tiled && h.kind == DOP_U1 && h.a == 2) other = 3;  // away from digits 0 and 1
                 lo = std::min<int>(h.a, other);
                 hi = std::max<int>(h.a, other);
             }
             i = first + count;
             ends_high = lo >= 2;
-            if (tile7 && P.chain.size() == first_rec && !ends_high) P.chain.push_back(pass_through());
+            if (tiled && P.chain.size() == first_rec && !ends_high) P.chain.push_back(pass_through());
             // a record holds a CX and one map per digit behind it; longer
             // groups become several records (one in twelve on random circuits)
             unsigned cx = 0;
@@ -898,7 +905,7 @@ void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin) {
             }
             flush();
         }
-        if (tile7 && (!ends_high || P.chain.size() < first_rec + 2)) {
+        if (tiled && (!ends_high || P.chain.size() < first_rec + 2)) {
             while (P.chain.size() < first_rec + 1) P.chain.push_back(pass_through());
             P.chain.push_back(pass_through());
         }
@@ -956,18 +963,20 @@ DensePlan plan_meet(const GateList &g, int k, int low, int64_t g_end, bool segme
     for (int64_t i = 0; i < g_end; ++i) ncx += g.op[(size_t)i] == 2;
     int64_t s = ncx ? 0 : g_end / 2;
     for (int64_t seen = 0; ncx && seen < ncx / 2; ++s) seen += g.op[(size_t)s] == 2;
-    const bool chains = k == g.n || k == kChainTileDigits;
+    const bool chains = k == g.n || chain_tiles(k, segments);
     std::vector<int> hrec, frec;
     PlanOptions o;
     o.g_begin = s;
     o.g_end = g_end;
     o.segments = segments;
+    o.chain = chains;
     DensePlan P = plan_dense_opts(g, k, low, o);
     if (chains) build_chain(P, dbytes, &hrec);
     PlanOptions f;
     f.g_end = s;
     f.forward = true;
     f.segments = segments;
+    f.chain = chains;
     DensePlan F = plan_dense_opts(g, k, low, f);
     if (chains) build_chain(F, dbytes, &frec);
     const int base = P.nmaps();
@@ -1012,7 +1021,7 @@ DensePlan plan_reversed_forward(const DensePlan &P) {
     return R;
 }
 
-GradPlan plan_gradient(const GateList &g, int k_heis, int k_fwd, int low, int64_t every) {
+GradPlan plan_gradient(const GateList &g, int k_heis, int k_fwd, int low, int64_t every, bool segments) {
     GradPlan G;
     const int64_t m = g.m;
     if (every <= 0) every = m > 0 ? m : 1;
@@ -1040,6 +1049,8 @@ GradPlan plan_gradient(const GateList &g, int k_heis, int k_fwd, int low, int64_
         PlanOptions h;
         h.g_begin = G.bounds[s];
         h.g_end = G.bounds[s + 1];
+        h.segments = segments;
+        h.chain = chain_tiles(k_heis, segments);
         G.heis_pass_begin.push_back((int)G.heis.passes.size());
         plan_append(G.heis, plan_dense_opts(g, k_heis, low, h));
         PlanOptions f;
@@ -1054,9 +1065,9 @@ GradPlan plan_gradient(const GateList &g, int k_heis, int k_fwd, int low, int64_
     G.heis_pass_begin.push_back((int)G.heis.passes.size());
     G.fwd_pass_begin.push_back((int)G.fwd.passes.size());
     G.fwd_map_begin.push_back(G.fwd.nmaps());
-    build_chain(G.fwd, 8, &G.fwd_chain_begin);
+    build_chain(G.fwd, 8, &G.fwd_chain_begin, false);
     for (size_t r = 0; r < G.fwd.rgate.size(); ++r) G.rslot.push_back(slot[(size_t)G.fwd.rgate[r]]);
-    if (G.heis.resident || k_heis == kChainTileDigits) build_chain(G.heis, 8, &G.heis_chain_begin);
+    if (G.heis.resident || chain_tiles(k_heis, segments)) build_chain(G.heis, 8, &G.heis_chain_begin);
     return G;
 }
 

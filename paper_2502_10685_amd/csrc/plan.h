@@ -70,18 +70,22 @@ int group_shape(const DOp *members, int count, int lo);
 // segments (see segment_ops in plan.cpp).
 constexpr int kSegTileDigits = 6;
 
-// Tile size whose untracked passes run as record chains (tile7.hip).
+// Larger of the tile sizes whose untracked passes run as record chains
+// (tile_chain.hip); the other is 6.
 constexpr int kChainTileDigits = 7;
 // Records of a pass at most (one per lane of a wave); a pass with more units
-// than kTile7Units, which leaves room for the records that only move the
+// than kTileUnits, which leaves room for the records that only move the
 // tile, is split.
-constexpr int kTile7Records = 64;
-constexpr int kTile7Units = kTile7Records - 2;
+constexpr int kTileRecords = 64;
+constexpr int kTileUnits = kTileRecords - 2;
 
 // General form: gates [g_begin, g_end) only; forward = g_begin first (the
 // adjoint sweep) instead of Heisenberg order; slot (optional, size m): for
 // each rotation gate its join slot, stored in DOp::reserved with DOp::b set
 // to the rotation's op code.
+// tiles whose passes run as record chains
+inline bool chain_tiles(int k, bool segments) { return k == kChainTileDigits || (k == 6 && !segments); }
+
 struct PlanOptions {
     bool compose = true;
     bool group = true;  // pack ops on a common digit pair into GROUP ops
@@ -91,6 +95,9 @@ struct PlanOptions {
     // (SEG headers, which the register-tile kernel needs); the LDS kernels
     // skip SEG headers, so without segments they decode fewer ops
     bool segments = true;
+    // order passes over 6-qubit tiles for the record chain (7-qubit tiles
+    // always are): units of a CX and a map per digit, at most kTileUnits
+    bool chain = false;
     bool forward = false;
     int64_t g_begin = 0, g_end = -1;
 };
@@ -134,7 +141,7 @@ struct GradPlan {
 // dbytes: size of a weight.  A tiled pass begins and ends with records whose
 // pairs avoid digits 0 and 1 (without a CX or map where the schedule has no
 // such op there), and has at least two.
-void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin = nullptr);
+void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin = nullptr, bool ends = true);
 // Byte offsets, in the 4^n array, of the letters of record r's pair: as it
 // reads them (after = false) or writes them.
 void record_offsets(const ChainOp &r, const DensePass &ps, int dbytes, bool after, uint32_t out[4]);
@@ -149,7 +156,7 @@ DensePlan plan_meet(const GateList &g, int k, int low, int64_t g_end, bool segme
 // schedule of the same gates: its passes and ops in reverse order (no GROUP or
 // SEG headers), whose maps are the transposes of the forward maps.
 DensePlan plan_reversed_forward(const DensePlan &P);
-GradPlan plan_gradient(const GateList &g, int k_heis, int k_fwd, int low, int64_t every);
+GradPlan plan_gradient(const GateList &g, int k_heis, int k_fwd, int low, int64_t every, bool segments);
 SparsePlan plan_sparse(const GateList &g);
 
 // Clifford frame of a sparse schedule (n <= kFrameMaxN): the rotation axis of

@@ -146,6 +146,7 @@ struct GradRunsDesc {
 constexpr int kMaxTileGroups = 8;
 struct TileGroups {
     int32_t ngroups;
+    int32_t chain;  // every descriptor holds its pass as records too
     int32_t first_block[kMaxTileGroups + 1];
     int32_t first_desc[kMaxTileGroups];
     int32_t shift[kMaxTileGroups];
@@ -244,8 +245,10 @@ hipError_t launch_chain(const ResidentDesc *d_descs, int ndescs, int n, int dtyp
 size_t chain_exchange_bytes(int n, int dtype_bytes);
 hipError_t launch_tile_pass(const TilePassDesc *d_descs, const TileGroups &groups, int k, int dtype_bytes,
                             bool track, hipStream_t s);
-// Untracked passes over 7-qubit tiles of at most 14 qubits (tile7.hip).
-hipError_t launch_tile7(const TilePassDesc *d_descs, const TileGroups &groups, int dtype_bytes, hipStream_t s);
+// Untracked passes over 6- and 7-qubit tiles of at most 14 qubits
+// (tile_chain.hip).
+hipError_t launch_tile_chain(const TilePassDesc *d_descs, const TileGroups &groups, int k, int dtype_bytes,
+                             hipStream_t s);
 int num_cus();
 // 0: one workgroup per tile; 1: persistent prefetching workgroups (k <= 6)
 void set_tile_kernel_variant(int k, int variant);

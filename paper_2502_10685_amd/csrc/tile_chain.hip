@@ -1,11 +1,12 @@
-// Passes over 7-qubit tiles (untracked, n <= 14): persistent workgroups of 1,024
-// threads, each with one tile of 4^7 weights in LDS (128 KiB in FP64), run the
-// pass's record chain.
+// Passes over 7- and 6-qubit tiles (untracked, n <= 14): persistent workgroups,
+// one thread per 16 weights of a tile of 4^k weights in LDS (1,024 threads and
+// 128 KiB in FP64 at k = 7, 256 and 32 KiB at k = 6), run the pass's record
+// chain.
 //
-// What bounds it: a tile's HBM traffic (256 KiB in FP64, 12.8 us of a CU's
-// share of the bandwidth) and its LDS sweeps (16 waves, 1.4 us each, bound by
-// the LDS pipe and the VALU in turn) take about the same time, so the two must
-// overlap and both must be few.  A 7-qubit pass holds 1.5 to 1.8 times the
+// What bounds it at k = 7: a tile's HBM traffic (256 KiB in FP64, 12.8 us of a
+// CU's share of the bandwidth) and its LDS sweeps (16 waves, 1.4 us each, bound
+// by the LDS pipe and the VALU in turn) take about the same time, so the two
+// must overlap and both must be few.  A 7-qubit pass holds 1.5 to 1.8 times the
 // gates of a 6-qubit one for the same bytes per weight.
 //   - The first record is applied to the weights as they arrive from HBM (the
 //     registers then hold its blocks) and the last as they leave, so two of a
@@ -20,6 +21,11 @@
 // Random n = 12 circuits of 20,000 gates take 32.1 ms (42.4 over 6-qubit
 // tiles).  One workgroup per CU leaves 128 VGPRs per thread: 32 for a block,
 // 32 for the traffic, 32 for the results, 16 for addresses.
+//
+// At k = 6 four workgroups share a CU and small circuits have fewer tiles than
+// that: a lone workgroup's chain of records counts (5,000 random gates at n = 8
+// 0.67 ms, 0.73 when each op of a pass was decoded and swept by itself; n = 9
+// 0.77, 0.85); in large batches the traffic does, 5.6 TB/s.
 #include <algorithm>
 #include <type_traits>
 
@@ -32,16 +38,13 @@ namespace pp {
 
 namespace {
 
-constexpr int K7 = 7;
-constexpr int kT7Block = 1024;
-constexpr int kT7Size = 1 << (2 * K7);
-constexpr int kT7Pairs = kNumPairs<K7>;
-
-template <typename T>
-struct T7 {
-    static constexpr size_t OFF_LANE = (size_t)kT7Size * sizeof(T);
-    static constexpr size_t OFF_WAVE = OFF_LANE + (size_t)kT7Pairs * 64 * 2;
-    static constexpr size_t LDS = OFF_WAVE + (size_t)kT7Pairs * 16 * 2;
+template <typename T, int K>
+struct TileChain {
+    static constexpr int BLOCK = 1 << (2 * (K - 2));  // one thread per 16-weight block of a sweep
+    static constexpr int PAIRS = kNumPairs<K>;
+    static constexpr size_t OFF_LANE = sizeof(T) << (2 * K);
+    static constexpr size_t OFF_WAVE = OFF_LANE + (size_t)PAIRS * 64 * 2;
+    static constexpr size_t LDS = OFF_WAVE + (size_t)PAIRS * 16 * 2;
 };
 
 typedef unsigned U4 __attribute__((ext_vector_type(4)));
@@ -74,20 +77,22 @@ __device__ __forceinline__ void read_words(unsigned (&r)[4], const unsigned (&c)
     r[3] = lo ? t2 : c[3];
 }
 
-template <typename T>
-__global__ __launch_bounds__(kT7Block) void tile7_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) {
+template <typename T, int K>
+__global__ __launch_bounds__((TileChain<T, K>::BLOCK), 4)
+void tile_chain_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) {
+    using S = TileChain<T, K>;
     constexpr int SH = sizeof(T) == 8 ? 3 : 2;
     extern __shared__ __align__(256) unsigned char smem[];
-    uint16_t *lanetab = reinterpret_cast<uint16_t *>(smem + T7<T>::OFF_LANE);
-    uint16_t *wavetab = reinterpret_cast<uint16_t *>(smem + T7<T>::OFF_WAVE);
+    uint16_t *lanetab = reinterpret_cast<uint16_t *>(smem + S::OFF_LANE);
+    uint16_t *wavetab = reinterpret_cast<uint16_t *>(smem + S::OFF_WAVE);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     typedef __attribute__((address_space(3))) unsigned char LB;
     const unsigned tile0 = (unsigned)(size_t)(LB *)smem;
     const int total = grp.first_block[grp.ngroups];
     int blk = blockIdx.x;
     if (blk >= total) return;
-    for (int i = tid; i < kT7Pairs * 64; i += kT7Block) lanetab[i] = (&kPairTable<K7>.lane[0][0])[i];
-    for (int i = tid; i < kT7Pairs * 16; i += kT7Block) wavetab[i] = (&kPairTable<K7>.wave[0][0])[i];
+    for (int i = tid; i < S::PAIRS * 64; i += S::BLOCK) lanetab[i] = (&kPairTable<K>.lane[0][0])[i];
+    for (int i = tid; i < S::PAIRS * 16; i += S::BLOCK) wavetab[i] = (&kPairTable<K>.wave[0][0])[i];
 
     auto word = [](unsigned v, int i) { return (unsigned)__builtin_amdgcn_readlane((int)v, i); };
     // swizzled slot of this thread's block of pair p
@@ -97,11 +102,11 @@ __global__ __launch_bounds__(kT7Block) void tile7_kernel(const TilePassDesc *__r
         const unsigned i = (unsigned)sw((int)block_slot(p));  // sw is its own inverse
         unsigned v = 0;
 #pragma unroll
-        for (int j = 0; j < K7; ++j)
+        for (int j = 0; j < K; ++j)
             v |= ((i >> (2 * j)) & 3u) << (2u * (unsigned)((qubits >> (8 * j)) & 0xff));
         return v * (unsigned)sizeof(T);
     };
-    // the records of a pass, one per lane (at most kTile7Records): word and map
+    // the records of a pass, one per lane (at most kTileRecords): word and map
     // in R0, write words in R1
     U2 R0;
     U4 R1;
@@ -148,7 +153,7 @@ __global__ __launch_bounds__(kT7Block) void tile7_kernel(const TilePassDesc *__r
         }
     };
 
-    TileBase cur = tile_base<K7>(descs, grp, blk);
+    TileBase cur = tile_base<K>(descs, grp, blk);
     load_records(cur.d);
     lds_barrier();
     // io holds, in turn, a tile's weights as they come from HBM, the results
@@ -207,7 +212,7 @@ __global__ __launch_bounds__(kT7Block) void tile7_kernel(const TilePassDesc *__r
         unsigned nvo = 0;
         uint32_t ni[4] = {0u, 0u, 0u, 0u};
         if (has_next) {
-            nxt = tile_base<K7>(descs, grp, nblk);
+            nxt = tile_base<K>(descs, grp, nblk);
             typedef const __attribute__((address_space(4))) uint32_t *CW;
             const CW first = (CW)nxt.d->chain;  // word and map of its first record
             nbase = reinterpret_cast<T *>(nxt.d->coef) + nxt.base;
@@ -259,7 +264,8 @@ __global__ __launch_bounds__(kT7Block) void tile7_kernel(const TilePassDesc *__r
 #pragma unroll
                     for (int e = 0; e < 16; ++e) lds_put<T>(wa[e], v[e]);
                 });
-                lds_barrier();
+                if (K == 6 && ((w >> kChainNoBarrierBit) & 1u)) wave_lds_order();
+                else lds_barrier();
                 w = word(R0.x, r + 1);
                 slot = block_slot(w & 0xffu);
             }
@@ -314,29 +320,34 @@ __global__ __launch_bounds__(kT7Block) void tile7_kernel(const TilePassDesc *__r
     for (int e = 0; e < 16; ++e) BufIO<T>::st(rs, pvo, letter_offset(po, e), res[e]);
 }
 
-template <typename T>
-hipError_t launch_tile7_t(const TilePassDesc *d, const TileGroups &grp, hipStream_t s) {
-    static_assert(T7<T>::LDS <= 160 * 1024, "one tile and the pair tables fit one CU's LDS");
-    auto fn = tile7_kernel<T>;
+template <typename T, int K>
+hipError_t launch_tile_chain_t(const TilePassDesc *d, const TileGroups &grp, hipStream_t s) {
+    using S = TileChain<T, K>;
+    static_assert(S::LDS <= 160 * 1024, "a tile and the pair tables fit one CU's LDS");
+    auto fn = tile_chain_kernel<T, K>;
     static int resident = 0;
     if (!resident) {
-        hipError_t e =
-            hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)T7<T>::LDS);
+        hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS);
         if (e != hipSuccess) return e;
         int per_cu = 0;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)fn, kT7Block, T7<T>::LDS);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)fn, S::BLOCK, S::LDS);
         if (e != hipSuccess) return e;
         resident = std::max(per_cu, 1) * num_cus();
     }
     const int nblocks = grp.first_block[grp.ngroups];
-    hipLaunchKernelGGL(fn, dim3(std::min(nblocks, resident)), dim3(kT7Block), T7<T>::LDS, s, d, grp);
+    hipLaunchKernelGGL(fn, dim3(std::min(nblocks, resident)), dim3(S::BLOCK), S::LDS, s, d, grp);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_tile7(const TilePassDesc *d_descs, const TileGroups &grp, int dtype_bytes, hipStream_t s) {
-    return dtype_bytes == 8 ? launch_tile7_t<double>(d_descs, grp, s) : launch_tile7_t<float>(d_descs, grp, s);
+hipError_t launch_tile_chain(const TilePassDesc *d_descs, const TileGroups &grp, int k, int dtype_bytes,
+                             hipStream_t s) {
+    if (k == 6)
+        return dtype_bytes == 8 ? launch_tile_chain_t<double, 6>(d_descs, grp, s)
+                                : launch_tile_chain_t<float, 6>(d_descs, grp, s);
+    return dtype_bytes == 8 ? launch_tile_chain_t<double, 7>(d_descs, grp, s)
+                            : launch_tile_chain_t<float, 7>(d_descs, grp, s);
 }
 
 }  // namespace pp
