@@ -471,6 +471,8 @@ struct pp_circuit {
     // descriptors of step l of an evaluation (a pass of each half that has
     // one): d_pass[step[l], step[l + 1])
     std::vector<int> step;
+    pp::TileStart *d_start = nullptr;
+    bool start_c = false, start_r = false;  // the first pass of the half holds d_start
     // coef holds the observable's weights at the gate where the halves met;
     // pp_get_terms takes them the rest of the way with the maps of that
     // evaluation (met_maps once the schedule they belong to is gone)
@@ -626,6 +628,7 @@ void free_plan_buffers(pp_circuit *c) {
     dfree(c->d_pass);
     dfree(c->d_res);
     dfree(c->d_chain);
+    dfree(c->d_start);
     dfree(c->d_xbuf);
     dfree(c->d_comp);
     dfree(c->d_codes);
@@ -988,6 +991,14 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
                     HIPCHK(hipMemset(c->d_part, 0, sizeof(double) * pp::kMeetDoubles));  // the ticket
                 }
             }
+            c->start_c = c->start_r = false;
+            if (!rec.empty()) {
+                const pp::TileStart st{c->d_ox, c->d_oz, c->d_oc, (int32_t)c->ox.size()};
+                HIPCHK(dalloc(&c->d_start, 1));
+                HIPCHK(hipMemcpy(c->d_start, &st, sizeof(st), hipMemcpyHostToDevice));
+                c->start_c = nh > 0 && c->ramp_gate < 0 && c->ox.size() <= (size_t)pp::kStartTerms;
+                c->start_r = nf > 0;
+            }
             c->step.assign(1, 0);
             for (size_t l = 0; l < std::max(nh, nf); ++l) {
                 for (size_t pi : {l < nh ? l : SIZE_MAX, l < nf ? nh + l : SIZE_MAX}) {
@@ -996,6 +1007,7 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
                     pp::TilePassDesc d{};
                     if (!rec.empty()) set_chain(d, P, ps, c->d_chain, rec[pi], rec[pi + 1], c->dbytes);
                     d.forward = pi >= nh;
+                    if ((pi == 0 && c->start_c) || (pi == nh && c->start_r)) d.start = c->d_start;
                     d.coef = d.forward ? c->rcoef : c->coef;
                     d.pres = c->track ? c->pres : nullptr;
                     d.ops = c->d_ops;
@@ -1074,6 +1086,20 @@ void fill_plan_stats(pp_circuit *c) {
     }
 }
 
+// What the first passes leave to dense_init: they begin the halves themselves
+// where both can (a half without passes cannot).
+struct DenseStart {
+    bool coef, state;
+};
+DenseStart dense_start(const pp_circuit *c) {
+    const pp::DensePlan &P = c->dplan;
+    const bool meet = P.fwd_pass >= 0;
+    const bool chained = !c->track && pp::tile_pass_chained(P.k, c->n, pp::chain_tiles(P.k, c->plan_seg));
+    DenseStart d{!(chained && c->start_c), meet && !(chained && c->start_r)};
+    d.coef = d.coef || d.state;  // one kernel begins both
+    return d;
+}
+
 // An evaluation that leaves its weights with the circuit was enqueued.
 void mark_evaluated(pp_circuit *c) {
     c->evaluated = true;
@@ -1088,6 +1114,7 @@ pp::TileGroups step_groups(const pp_circuit *c, size_t l) {
     const int shift = 2 * (c->n - c->dplan.k);
     grp.ngroups = 1;
     grp.chain = pp::chain_tiles(c->dplan.k, c->plan_seg);
+    grp.start = l == 0;
     grp.first_block[1] = (c->step[l + 1] - c->step[l]) << shift;
     grp.first_desc[0] = c->step[l];
     grp.shift[0] = shift;
@@ -1109,7 +1136,7 @@ pp_status enqueue_dense_body(pp_circuit *c, hipStream_t s, double *out) {
         }
         ProfScope ps(PC_INIT, s);
         HIPCHK(pp::launch_dense_init(c->coef, nullptr, c->n, c->dbytes, c->d_ox, c->d_oz, c->d_oc, 0, true, s, 1,
-                                     P.fwd_pass >= 0 ? c->rcoef : nullptr));
+                                     dense_start(c).state ? c->rcoef : nullptr));
         HIPCHK(pp::launch_frame_to_dense(c->fb, c->dbytes, c->d_codes, (int)c->splan.codes.size(), np, c->coef, s));
     }
     if (P.nmaps() > 0) {
@@ -1128,10 +1155,11 @@ pp_status enqueue_dense_body(pp_circuit *c, hipStream_t s, double *out) {
         return PP_OK;
     }
     const bool meet = P.fwd_pass >= 0;
-    if (c->ramp_gate < 0) {
+    const DenseStart st = dense_start(c);
+    if (c->ramp_gate < 0 && st.coef) {
         ProfScope ps(PC_INIT, s);
         HIPCHK(pp::launch_dense_init(c->coef, c->track ? c->pres : nullptr, c->n, c->dbytes, c->d_ox, c->d_oz,
-                                     c->d_oc, (int)c->ox.size(), c->obs_distinct, s, 1, meet ? c->rcoef : nullptr));
+                                     c->d_oc, (int)c->ox.size(), c->obs_distinct, s, 1, st.state ? c->rcoef : nullptr));
     }
     TileSpan span;
     span.begin(s);
@@ -1650,8 +1678,10 @@ pp_status pp_evaluate_noalloc(pp_circuit *c, void *stream, double *d_expval) {
         HIPCHK(pp::launch_chain(res, 1, c->n, c->dbytes, P.fwd_from >= 0, nullptr, s));
         return PP_OK;
     }
-    HIPCHK(pp::launch_dense_init(coef, nullptr, c->n, c->dbytes, c->d_ox, c->d_oz, c->d_oc, (int)c->ox.size(),
-                                 c->obs_distinct, s, 1, state));
+    const DenseStart st = dense_start(c);
+    if (st.coef)
+        HIPCHK(pp::launch_dense_init(coef, nullptr, c->n, c->dbytes, c->d_ox, c->d_oz, c->d_oc, (int)c->ox.size(),
+                                     c->obs_distinct, s, 1, st.state ? state : nullptr));
     for (size_t l = 0; l + 1 < c->step.size(); ++l)
         HIPCHK(pp::launch_tile_pass(pass, step_groups(c, l), P.k, c->dbytes, false, s));
     if (meet) HIPCHK(pp::launch_meet_readout(coef, state, c->n, c->dbytes, part, d_expval, s));
@@ -1991,6 +2021,7 @@ namespace {
 struct BatchCache {
     std::vector<const pp_circuit *> key;
     std::vector<uint64_t> gens;
+    int tv6 = -1, tv7 = -1;  // the kernels it was built for: they decide who writes the start weights
     double *out = nullptr;
     struct Buf {
         void *d = nullptr;  // device
@@ -2014,6 +2045,8 @@ struct BatchCache {
     std::vector<Launch> tiles;     // tile passes
     size_t io_off = 0;             // start/readout descriptors of the tiled circuits
     int io_max_n = 0;
+    size_t init_off = 0;           // those whose start weights the passes do not write themselves
+    int init_count = 0;
     int io_meet = 0;               // the first io_meet of them are run from both ends
     std::vector<int> tiled;        // indices of tiled circuits
     std::vector<int> single;       // indices evaluated one by one
@@ -2040,10 +2073,10 @@ bool split_now(const BatchCache &B) { return B.split && (!g_prof.on || g_prof.ca
 // captured.
 pp_status enqueue_batch_head(BatchCache &B, int dbytes, hipStream_t s) {
     unsigned char *base = (unsigned char *)B.buf[B.cur].d;
-    if (!B.tiled.empty()) {
+    if (B.init_count > 0) {
         ProfScope ps(PC_INIT, s);
-        HIPCHK(pp::launch_dense_init_many((const pp::DenseIODesc *)(base + B.io_off), (int)B.tiled.size(),
-                                          B.io_max_n, dbytes, s));
+        HIPCHK(pp::launch_dense_init_many((const pp::DenseIODesc *)(base + B.init_off), B.init_count, B.io_max_n,
+                                          dbytes, s));
     }
     bool forked = false;
     for (const auto &L : B.head) {
@@ -2137,6 +2170,7 @@ pp_status build_batch(BatchCache &B, pp_circuit *const *cs, int64_t count, doubl
     B.tiled.clear();
     B.single.clear();
     B.io_max_n = 0;
+    B.init_count = 0;
     std::vector<pp::ComposeDesc> comp;
     int comp_max = 1;
     std::vector<std::vector<int>> res_by_n(kResidentMaxN + 1);
@@ -2155,7 +2189,7 @@ pp_status build_batch(BatchCache &B, pp_circuit *const *cs, int64_t count, doubl
     std::vector<std::vector<int>> by_k(8);
     std::vector<size_t> maxp(8, 0);
     size_t bytes = BatchWriter::padded(comp.size() * sizeof(pp::ComposeDesc)) +
-                   BatchWriter::padded(B.tiled.size() * sizeof(pp::DenseIODesc));
+                   2 * BatchWriter::padded(B.tiled.size() * sizeof(pp::DenseIODesc));
     for (auto &v : res_by_n) bytes += BatchWriter::padded(v.size() * sizeof(pp::ResidentDesc));
     for (int i : B.tiled) {
         const int k = cs[i]->dplan.k;
@@ -2183,7 +2217,7 @@ pp_status build_batch(BatchCache &B, pp_circuit *const *cs, int64_t count, doubl
         // those run from both ends first: the two kinds are read out apart
         std::vector<int> by_end(B.tiled);
         std::stable_partition(by_end.begin(), by_end.end(), [&](int i) { return cs[i]->dplan.fwd_pass >= 0; });
-        std::vector<pp::DenseIODesc> io;
+        std::vector<pp::DenseIODesc> io, init;
         B.io_meet = 0;
         for (int i : by_end) {
             pp_circuit *c = cs[i];
@@ -2192,9 +2226,16 @@ pp_status build_batch(BatchCache &B, pp_circuit *const *cs, int64_t count, doubl
                                          (int32_t)c->ox.size(), c->obs_distinct, 0, meet ? c->rcoef : nullptr,
                                          meet ? c->d_part : nullptr});
             B.io_meet += meet;
-            B.io_max_n = std::max(B.io_max_n, c->n);
+            const DenseStart st = dense_start(c);
+            if (st.coef) {
+                init.push_back(io.back());
+                if (!st.state) init.back().state = nullptr;
+                B.io_max_n = std::max(B.io_max_n, c->n);
+            }
         }
         B.io_off = out.put(io);
+        B.init_off = out.put(init);
+        B.init_count = (int)init.size();
     }
     // resident groups, largest size class first, longest circuits first
     for (int n = kResidentMaxN; n >= 1; --n) {
@@ -2274,6 +2315,7 @@ pp_status build_batch(BatchCache &B, pp_circuit *const *cs, int64_t count, doubl
             auto close = [&] {
                 tg.first_block[tg.ngroups] = run;
                 tg.chain = chain;
+                tg.start = l == 0;
                 B.tiles.push_back({2, k, out.put(td), (int)td.size(), run, tg});
                 td.clear();
                 tg = pp::TileGroups{};
@@ -2333,7 +2375,8 @@ extern "C" pp_status pp_evaluate_batch(pp_circuit *const *cs, int64_t count, voi
     bool graph = true;
     for (int64_t i = 0; graph && i < count; ++i)
         graph = cs[i]->use_graph != 0 && cs[i]->engine == PP_ENGINE_DENSE && !cs[i]->track && cs[i]->ramp_gate < 0;
-    bool hit = B.out == d_expvals && B.key.size() == (size_t)count;
+    const int tv6 = pp::tile_kernel_variant(6), tv7 = pp::tile_kernel_variant(7);
+    bool hit = B.out == d_expvals && B.key.size() == (size_t)count && B.tv6 == tv6 && B.tv7 == tv7;
     for (int64_t i = 0; hit && i < count; ++i) hit = B.key[i] == cs[i] && B.gens[i] == cs[i]->plan_gen;
     bool enqueued = false;
     if (!hit) {
@@ -2356,6 +2399,8 @@ extern "C" pp_status pp_evaluate_batch(pp_circuit *const *cs, int64_t count, voi
         B.gens.resize(count);
         for (int64_t i = 0; i < count; ++i) B.gens[i] = cs[i]->plan_gen;
         B.out = d_expvals;
+        B.tv6 = tv6;
+        B.tv7 = tv7;
     }
     if (graph) {
         if (!B.gexec) {
@@ -2659,12 +2704,13 @@ extern "C" pp_status pp_evaluate_thetas(pp_circuit *c, int64_t count, const doub
     const int shift = 2 * (c->n - P.k);
     const int64_t ntiles = (int64_t)1 << shift;
     if (2 * std::min(count, W.chunk) * ntiles > INT32_MAX) return fail(PP_ERR_INVALID, "too many tiles in one sweep launch");
+    const DenseStart st = dense_start(c);
     for (int64_t i0 = 0; i0 < count; i0 += W.chunk) {
         const int cs = (int)std::min(count - i0, W.chunk);
-        {
+        if (st.coef) {
             ProfScope ps(PC_INIT, s);
             HIPCHK(pp::launch_dense_init(W.coef, nullptr, c->n, c->dbytes, c->d_ox, c->d_oz, c->d_oc,
-                                         (int)c->ox.size(), c->obs_distinct, s, cs, W.state));
+                                         (int)c->ox.size(), c->obs_distinct, s, cs, st.state ? W.state : nullptr));
         }
         const pp::TilePassDesc *pass =
             (const pp::TilePassDesc *)(base + W.pass_off) + (size_t)i0 * c->h_pass.size();
@@ -2675,6 +2721,7 @@ extern "C" pp_status pp_evaluate_thetas(pp_circuit *c, int64_t count, const doub
             pp::TileGroups grp{};
             grp.ngroups = 1;
             grp.chain = pp::chain_tiles(P.k, c->plan_seg);
+            grp.start = l == 0;
             grp.first_block[1] = (int32_t)((c->step[l + 1] - c->step[l]) * cs * ntiles);
             grp.shift[0] = shift;
             HIPCHK(pp::launch_tile_pass(pass + (size_t)c->step[l] * cs, grp, P.k, c->dbytes, false, s));

@@ -1652,6 +1652,10 @@ void set_tile_kernel_variant(int k, int variant) {
 }
 int tile_kernel_variant(int k) { return (k >= 0 && k < 8) ? g_tile_variant[k] : 0; }
 
+bool tile_pass_chained(int k, int n, bool chain) {
+    return (k == 6 || k == 7) && g_tile_variant[k] == 1 && n <= 14 && chain;
+}
+
 int num_cus() {
     static int cached = 0;
     if (cached) return cached;
@@ -1734,7 +1738,7 @@ static hipError_t launch_tile_t(const TilePassDesc *d, const TileGroups &grp, si
         return hipGetLastError();
     }
     if constexpr (!TRACK && K >= 6)
-        if (g_tile_variant[K] == 1 && max_n <= 14 && grp.chain) return launch_tile_chain(d, grp, K, (int)sizeof(T), s);
+        if (tile_pass_chained(K, max_n, grp.chain)) return launch_tile_chain(d, grp, K, (int)sizeof(T), s);
     if constexpr (!TRACK && K < 6) if (g_tile_variant[K] == 1 && max_n <= 14) {
         auto fn = tile_stream_kernel<T, K>;
         constexpr int SB = kStreamBlock<K>;

@@ -89,6 +89,16 @@ struct ResidentDesc {
 };
 
 // One pass of one circuit over its 4^(n-k) tiles of 4^k slots.
+// Where an evaluation's first pass over 6- or 7-qubit tiles begins: the
+// observable of at most kStartTerms strings (the forward half begins with
+// |0...0>).
+constexpr int kStartTerms = 64;
+struct TileStart {
+    const uint64_t *obs_x, *obs_z;
+    const double *obs_c;
+    int32_t nterms;
+};
+
 struct TilePassDesc {
     void *coef;                    // 4^n weights of the circuit
     uint8_t *pres;                 // presence bytes (tracked runs) or nullptr
@@ -110,6 +120,7 @@ struct TilePassDesc {
     const ChainOp *chain;
     int32_t nrec;
     uint32_t in[4], out[4];
+    const TileStart *start;        // the first pass of a half: coef is not read but begun here (or nullptr)
 };
 
 // One pass of the adjoint sweep over tiles of 4^k slots (k = n: one tile).
@@ -147,6 +158,7 @@ constexpr int kMaxTileGroups = 8;
 struct TileGroups {
     int32_t ngroups;
     int32_t chain;  // every descriptor holds its pass as records too
+    int32_t start;  // some may hold first passes, whose weights were not filled in
     int32_t first_block[kMaxTileGroups + 1];
     int32_t first_desc[kMaxTileGroups];
     int32_t shift[kMaxTileGroups];
@@ -247,6 +259,10 @@ hipError_t launch_tile_pass(const TilePassDesc *d_descs, const TileGroups &group
                             bool track, hipStream_t s);
 // Untracked passes over 6- and 7-qubit tiles of at most 14 qubits
 // (tile_chain.hip).
+// Whether launch_tile_pass would run untracked passes of circuits of n qubits
+// with such records (TileGroups::chain) through launch_tile_chain, which begins
+// first passes itself; the other kernels read coef.
+bool tile_pass_chained(int k, int n, bool chain);
 hipError_t launch_tile_chain(const TilePassDesc *d_descs, const TileGroups &groups, int k, int dtype_bytes,
                              hipStream_t s);
 int num_cus();

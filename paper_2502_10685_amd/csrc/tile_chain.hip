@@ -77,7 +77,9 @@ __device__ __forceinline__ void read_words(unsigned (&r)[4], const unsigned (&c)
     r[3] = lo ? t2 : c[3];
 }
 
-template <typename T, int K>
+// START: first passes begin their weights (a template, since its code costs the
+// others registers); without it they are read like any other's.
+template <typename T, int K, bool START>
 __global__ __launch_bounds__((TileChain<T, K>::BLOCK), 4)
 void tile_chain_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) {
     using S = TileChain<T, K>;
@@ -160,7 +162,8 @@ void tile_chain_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) {
     // of the tile before on their way out, and the next tile's weights
     T io[16];
     {
-        const __amdgpu_buffer_rsrc_t rs = tile_rsrc(reinterpret_cast<T *>(cur.d->coef) + cur.base);
+        const __amdgpu_buffer_rsrc_t rs =
+            tile_rsrc(reinterpret_cast<T *>(cur.d->coef) + cur.base, START && cur.d->start != nullptr);
         const unsigned vo = block_voff(word(R0.x, 0) & 0xffu, cur.d->qubits);
         const uint32_t c[4] = {cur.d->in[0], cur.d->in[1], cur.d->in[2], cur.d->in[3]};
 #pragma unroll
@@ -183,9 +186,43 @@ void tile_chain_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) {
     uint32_t po[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int e = 0; e < 16; ++e) res[e] = (T)0;
+    // The weights of a tile of a half's first pass, whose loads gave 0: the
+    // state's, or the observable's strings in input order.  Filled and
+    // scattered by kernels before it and read back they cost 7 us at n = 8, two
+    // passes over both arrays in large sweeps (300 sets at n = 9 6.28 ms, 6.04
+    // without), and 5,000 gates at n = 10 took 1.25 ms, 1.18 without.
+    auto begin = [&](const TileStart *st) {
+        const unsigned vs = block_voff(word(R0.x, 0) & 0xffu, cur.d->qubits) >> SH;  // slots, not bytes
+        const uint32_t c[4] = {cur.d->in[0] >> SH, cur.d->in[1] >> SH, cur.d->in[2] >> SH, cur.d->in[3] >> SH};
+        const unsigned xbits = 0x55555555u;
+        if (cur.d->forward) {
+            const bool z = (((unsigned)cur.base | vs) & xbits) == 0;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) io[e] = z && (letter_offset(c, e) & xbits) == 0 ? (T)1 : (T)0;
+            return;
+        }
+        unsigned inside = 0;
+#pragma unroll
+        for (int j = 0; j < K; ++j) inside |= 3u << (2u * (unsigned)((cur.d->qubits >> (8 * j)) & 0xff));
+        const int l = lane < st->nterms ? lane : 0;
+        const unsigned slot = (unsigned)morton_slot(st->obs_x[l], st->obs_z[l], cur.d->n);
+        const double coef = st->obs_c[l];
+        uint64_t here = __ballot(lane < st->nterms && (slot & ~inside) == (unsigned)cur.base);
+        while (here) {
+            const int t = __builtin_ctzll(here);
+            here &= here - 1;
+            const unsigned at = word(slot, t) & inside;
+            const double v = lane_double(coef, t);
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                if ((vs ^ letter_offset(c, e)) == at) io[e] = (T)((double)io[e] + v);
+        }
+    };
     for (;;) {
         const int nrec = cur.d->nrec;
         const ConstMaps gmaps = (ConstMaps)cur.d->maps;
+        if constexpr (START)
+            if (cur.d->start) begin(cur.d->start);
         // ---- the first record, on the weights from HBM
         {
             const unsigned w = word(R0.x, 0), map = word(R0.y, 0);
@@ -209,6 +246,7 @@ void tile_chain_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) {
         unsigned nmap = 0;   // the next tile's first map
         double touch = 0.0;  // brings its maps into L2 ahead of the scalar loads
         T *nbase = nullptr;
+        bool nstart = false;
         unsigned nvo = 0;
         uint32_t ni[4] = {0u, 0u, 0u, 0u};
         if (has_next) {
@@ -216,6 +254,7 @@ void tile_chain_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) {
             typedef const __attribute__((address_space(4))) uint32_t *CW;
             const CW first = (CW)nxt.d->chain;  // word and map of its first record
             nbase = reinterpret_cast<T *>(nxt.d->coef) + nxt.base;
+            nstart = START && nxt.d->start != nullptr;
             nvo = block_voff(first[0] & 0xffu, nxt.d->qubits);
 #pragma unroll
             for (int q = 0; q < 4; ++q) ni[q] = nxt.d->in[q];
@@ -235,7 +274,7 @@ void tile_chain_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) {
         auto io_in = [&](auto q_c) {
             constexpr int q = 4 * decltype(q_c)::value;
             if (!has_next) return;
-            const __amdgpu_buffer_rsrc_t rs = tile_rsrc(nbase);
+            const __amdgpu_buffer_rsrc_t rs = tile_rsrc(nbase, nstart);
 #pragma unroll
             for (int e = q; e < q + 4; ++e) io[e] = BufIO<T>::ld(rs, nvo, letter_offset(ni, e));
         };
@@ -320,11 +359,11 @@ void tile_chain_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) {
     for (int e = 0; e < 16; ++e) BufIO<T>::st(rs, pvo, letter_offset(po, e), res[e]);
 }
 
-template <typename T, int K>
+template <typename T, int K, bool START>
 hipError_t launch_tile_chain_t(const TilePassDesc *d, const TileGroups &grp, hipStream_t s) {
     using S = TileChain<T, K>;
     static_assert(S::LDS <= 160 * 1024, "a tile and the pair tables fit one CU's LDS");
-    auto fn = tile_chain_kernel<T, K>;
+    auto fn = tile_chain_kernel<T, K, START>;
     static int resident = 0;
     if (!resident) {
         hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS);
@@ -339,15 +378,18 @@ hipError_t launch_tile_chain_t(const TilePassDesc *d, const TileGroups &grp, hip
     return hipGetLastError();
 }
 
+template <typename T>
+hipError_t launch_tile_chain_k(const TilePassDesc *d, const TileGroups &grp, int k, hipStream_t s) {
+    if (k == 6) return grp.start ? launch_tile_chain_t<T, 6, true>(d, grp, s) : launch_tile_chain_t<T, 6, false>(d, grp, s);
+    return grp.start ? launch_tile_chain_t<T, 7, true>(d, grp, s) : launch_tile_chain_t<T, 7, false>(d, grp, s);
+}
+
 }  // namespace
 
 hipError_t launch_tile_chain(const TilePassDesc *d_descs, const TileGroups &grp, int k, int dtype_bytes,
                              hipStream_t s) {
-    if (k == 6)
-        return dtype_bytes == 8 ? launch_tile_chain_t<double, 6>(d_descs, grp, s)
-                                : launch_tile_chain_t<float, 6>(d_descs, grp, s);
-    return dtype_bytes == 8 ? launch_tile_chain_t<double, 7>(d_descs, grp, s)
-                            : launch_tile_chain_t<float, 7>(d_descs, grp, s);
+    return dtype_bytes == 8 ? launch_tile_chain_k<double>(d_descs, grp, k, s)
+                            : launch_tile_chain_k<float>(d_descs, grp, k, s);
 }
 
 }  // namespace pp

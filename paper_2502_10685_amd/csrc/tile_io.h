@@ -14,8 +14,9 @@ namespace pp {
 // weight is read once and written once per pass, so both carry the
 // non-temporal hint (nt): the streamed array then does not push the op
 // lists and maps, which every tile re-reads, out of L2.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(void *p) {
-    return __builtin_amdgcn_make_buffer_rsrc(p, (short)0, -1, 0x00020000);
+// empty: loads give 0 and touch nothing
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(void *p, bool empty = false) {
+    return __builtin_amdgcn_make_buffer_rsrc(p, (short)0, empty ? 0 : -1, 0x00020000);
 }
 // cache-policy operand of the buffer builtins: bit 1 is nt on gfx950
 constexpr int kNonTemporal = 2;
