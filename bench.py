@@ -166,7 +166,7 @@ def timed_steps(fn, steps, torch):
     return time.perf_counter() - t0, np.array(lat)
 
 
-TILE_KERNEL_NAMES = {0: "tile_kernel", 1: "tile_stream_kernel", 2: "tile_kernel", 3: "tile_reg_kernel",
+TILE_KERNEL_NAMES = {0: "tile_kernel", 1: "tile_chain_kernel", 2: "tile_kernel", 3: "tile_reg_kernel",
                      4: "tile_reg_kernel"}
 
 

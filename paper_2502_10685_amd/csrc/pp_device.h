@@ -125,9 +125,7 @@ struct TilePassDesc {
 
 // One pass of the adjoint sweep over tiles of 4^k slots (k = n: one tile).
 // c: the observable's weights, r: the Pauli coefficients Tr(P rho) of the
-// state, both FP64, both propagated forward through the pass's ops.  A U1 op
-// of a rotation (b = 3, 4, 5 for RX, RY, RZ) first writes the tile's share of
-// its join c^T A r to partials[(reserved - slot_base) * ntiles + tile].
+// state, both FP64, both propagated forward through the pass's records.
 struct GradPassDesc {
     double *c;
     double *r;
@@ -181,7 +179,7 @@ struct DenseIODesc {
 // Where the product c . r of a circuit run from both ends is summed up: one
 // sum per block (at most kMeetBlocks), then the blocks' ticket (0 between
 // launches).
-constexpr int kMeetBlocks = 64;
+constexpr int kMeetBlocks = 256;
 constexpr int kMeetDoubles = kMeetBlocks + 8;
 
 // Per-circuit composition job: maps[i] = product of the gate matrices of
