@@ -2291,7 +2291,6 @@ pp_status build_batch(BatchCache &B, pp_circuit *const *cs, int64_t count, doubl
     // pass l holds more ops come first: workgroups take tiles with a fixed
     // stride, so the last round of tiles is the light one
     std::vector<std::pair<uint64_t, const pp::TilePassDesc *>> order;
-    std::vector<pp::TilePassDesc> td;
     const size_t steps = *std::max_element(maxp.begin(), maxp.end());
     for (size_t l = 0; l < steps && r == PP_OK; ++l) {
         for (int k = 4; k <= 7 && r == PP_OK; ++k) {
@@ -2303,11 +2302,13 @@ pp_status build_batch(BatchCache &B, pp_circuit *const *cs, int64_t count, doubl
                 for (int q = c->step[l]; q < c->step[l + 1]; ++q) {
                     const pp::TilePassDesc &p = c->h_pass[(size_t)q];
                     const uint64_t light = 0xffff - std::min(p.op_end - p.op_begin, 0xffff);
-                    order.push_back({((uint64_t)(64 - c->n) << 48) | (light << 32) | j, &p});
+                    order.push_back({((uint64_t)(64 - c->n) << 48) | (light << 32) | (2 * j + p.forward), &p});
                 }
             }
-            std::stable_sort(order.begin(), order.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
-            td.clear();
+            std::sort(order.begin(), order.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
+            // straight into the pinned memory
+            pp::TilePassDesc *td = (pp::TilePassDesc *)(out.host + out.used);
+            int32_t ntd = 0;
             pp::TileGroups tg{};
             int run = 0, last_n = -1;
             bool chain = true;
@@ -2316,24 +2317,26 @@ pp_status build_batch(BatchCache &B, pp_circuit *const *cs, int64_t count, doubl
                 tg.first_block[tg.ngroups] = run;
                 tg.chain = chain;
                 tg.start = l == 0;
-                B.tiles.push_back({2, k, out.put(td), (int)td.size(), run, tg});
-                td.clear();
+                B.tiles.push_back({2, k, out.used, (int)ntd, run, tg});
+                out.used += BatchWriter::padded(ntd * sizeof(pp::TilePassDesc));
+                td = (pp::TilePassDesc *)(out.host + out.used);
+                ntd = 0;
                 tg = pp::TileGroups{};
                 run = 0;
             };
             for (const auto &o : order) {
-                pp::TilePassDesc d = *o.second;
-                if (d.n != last_n) {
+                if (o.second->n != last_n) {
                     if (tg.ngroups == pp::kMaxTileGroups) close();
                     tg.first_block[tg.ngroups] = run;
-                    tg.first_desc[tg.ngroups] = (int32_t)td.size();
-                    tg.shift[tg.ngroups] = 2 * (d.n - k);
+                    tg.first_desc[tg.ngroups] = ntd;
+                    tg.shift[tg.ngroups] = 2 * (o.second->n - k);
                     tg.ngroups++;
-                    last_n = d.n;
+                    last_n = o.second->n;
                 }
+                pp::TilePassDesc &d = td[ntd++];
+                d = *o.second;
                 d.tile_begin = run;
                 run += d.ntiles;
-                td.push_back(d);
             }
             close();
             if (B.tiles.size() - launched >= 16) r = flush();
