@@ -293,6 +293,7 @@ constexpr int64_t kSweepMeetBytes = (int64_t)256 << 20;
 // = 10 4.23 against 3.74; 3,000 gates at n = 11 1.76 against 1.56, n = 12 6.3
 // against 4.8, n = 13 26.6 against 19.6; FP32 alike), up to the kernel's 14.
 int g_tile_qubits[17] = {0, 0, 0, 0, 0, 0, 0, 0, 6, 6, 7, 7, 7, 7, 7, 6, 6};
+bool g_tile_tuned[17] = {};  // set by pp_tune_set: taken as it is
 int default_tile_qubits(int n) { return n >= 8 && n <= 16 ? g_tile_qubits[n] : (n > 16 ? 6 : 5); }
 
 // pinned staging for small asynchronous uploads, reused once the previous
@@ -701,7 +702,10 @@ std::atomic<uint64_t> g_plan_gen{0};
 
 // Circuits run from one end (tracked, density matrices, a gradient's sweep)
 // have half the tiles in flight: at n = 10 their 64 tiles of 7 qubits are
-// slower than 256 of 6 (3,000 gates 1.27 against 1.12 ms).
+// slower than 256 of 6 (3,000 gates 1.27 against 1.12 ms).  So are short
+// circuits alone, whose few passes are all latency (31, 120 and 300 gates 40,
+// 69 and 97 us with 6, 48, 77 and 111 with 7; 800 gates 231 against 223).
+constexpr int64_t kShortGates = 500;
 int tile_qubits_for(const pp_circuit *c, bool one_end = false) {
     if (c->n <= kResidentMaxN &&
         pp::resident_lds_bytes(c->n, c->dbytes, c->track != 0) + pp::kStaticLdsReserve <= (size_t)pp::max_lds_bytes())
@@ -711,7 +715,9 @@ int tile_qubits_for(const pp_circuit *c, bool one_end = false) {
     k = std::max(k, kLowQubits + 2);
     k = std::min(k, 7);
     one_end = one_end || c->track || c->keep_coef;
-    if (c->tile_opt <= 0 && one_end && k == 7 && c->n <= kMeetMaxN) k = 6;
+    if (c->tile_opt <= 0 && k == 7 && c->n <= kMeetMaxN && !g_tile_tuned[c->n] &&
+        (one_end || c->g.m < kShortGates))
+        k = 6;
     while (k > kLowQubits + 2 &&
            pp::resident_lds_bytes(k, c->dbytes, c->track != 0) + pp::kStaticLdsReserve > (size_t)pp::max_lds_bytes())
         --k;
@@ -3633,6 +3639,7 @@ extern "C" pp_status pp_tune_set(pp_tune_key key, int32_t index, int32_t value) 
     if (key == PP_TUNE_TILE_QUBITS) {
         if (index < 8 || index > 16 || value < 4 || value > 7) return fail(PP_ERR_INVALID, "tile qubits: n in 8..16, k in 4..7");
         g_tile_qubits[index] = value;
+        g_tile_tuned[index] = true;
         return PP_OK;
     }
     if (key == PP_TUNE_TILE_KERNEL) {
