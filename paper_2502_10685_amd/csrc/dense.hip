@@ -620,7 +620,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((BLOCK ==
 }
 
 // ------------------------------------------------- streaming tile kernel
-// Persistent form of tile_kernel for untracked runs: a co-resident grid
+// Persistent form of tile_kernel for untracked runs over 4- and 5-qubit tiles
+// (those of 6 and 7 qubits run as record chains): a co-resident grid
 // walks the launch's tiles with stride gridDim.x, and every workgroup issues
 // the global loads of its next tile into registers before it runs the ops of
 // the current one, so HBM latency overlaps the LDS work (the barriers in
@@ -662,15 +663,14 @@ __device__ __forceinline__ unsigned stream_soff(uint64_t qubits, int r) {
     return g;
 }
 
-// 256 threads, four workgroups per CU: at most 128 VGPRs, and 4 x 37 KiB of
-// LDS in FP64 at K = 6
+// 256 threads, four workgroups per CU: at most 128 VGPRs
 template <int K>
 constexpr int kStreamBlock = 256;
 template <int K>
 constexpr int kStreamWaves = 4;
 
-// ops held per workgroup: every 6-qubit pass of the planner fits (its passes
-// have at most 64 op entries); longer passes reload chunks inside run_ops
+// ops held per workgroup: most passes fit; longer ones reload chunks inside
+// run_ops
 constexpr int kStreamOps = 64;
 
 template <typename T, int K>

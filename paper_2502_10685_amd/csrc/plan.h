@@ -135,12 +135,12 @@ struct GradPlan {
     std::vector<int32_t> rslot;                        // rotation of every entry of fwd's recipes (-1: a Clifford)
     std::vector<int32_t> param_off, param_slot;        // each parameter's rotations, in gate order
 };
-// Renumbers the maps of grouped passes (resident, or over 7-qubit tiles) in op
-// order and appends each pass's records to P.chain; begin[p] (optional)
-// receives the first record of pass p, with the total behind the last.
-// dbytes: size of a weight.  A tiled pass begins and ends with records whose
-// pairs avoid digits 0 and 1 (without a CX or map where the schedule has no
-// such op there), and has at least two.
+// Renumbers the maps of grouped passes (resident, or over tiles) in op order
+// and appends each pass's records to P.chain; begin[p] (optional) receives the
+// first record of pass p, with the total behind the last.  dbytes: size of a
+// weight.  ends: a tiled pass begins and ends with records whose pairs avoid
+// digits 0 and 1 (without a CX or map where the schedule has no such op
+// there), and has at least two.
 void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin = nullptr, bool ends = true);
 // Byte offsets, in the 4^n array, of the letters of record r's pair: as it
 // reads them (after = false) or writes them.
