@@ -1097,10 +1097,14 @@ void fill_plan_stats(pp_circuit *c) {
 struct DenseStart {
     bool coef, state;
 };
+// Whether the circuit's tile passes run through launch_tile_chain: alone, and in
+// every launch it shares (circuits of more than kChainMaxN qubits have launches
+// of their own).
+bool runs_chained(const pp_circuit *c) {
+    return !c->track && pp::tile_pass_chained(c->dplan.k, c->n, pp::chain_tiles(c->dplan.k, c->plan_seg));
+}
 DenseStart dense_start(const pp_circuit *c) {
-    const pp::DensePlan &P = c->dplan;
-    const bool meet = P.fwd_pass >= 0;
-    const bool chained = !c->track && pp::tile_pass_chained(P.k, c->n, pp::chain_tiles(P.k, c->plan_seg));
+    const bool meet = c->dplan.fwd_pass >= 0, chained = runs_chained(c);
     DenseStart d{!(chained && c->start_c), meet && !(chained && c->start_r)};
     d.coef = d.coef || d.state;  // one kernel begins both
     return d;
@@ -1120,7 +1124,7 @@ pp::TileGroups step_groups(const pp_circuit *c, size_t l) {
     const int shift = 2 * (c->n - c->dplan.k);
     grp.ngroups = 1;
     grp.chain = pp::chain_tiles(c->dplan.k, c->plan_seg);
-    grp.start = l == 0;
+    grp.start = l == 0 && runs_chained(c);
     grp.first_block[1] = (c->step[l + 1] - c->step[l]) << shift;
     grp.first_desc[0] = c->step[l];
     grp.shift[0] = shift;
@@ -2322,7 +2326,7 @@ pp_status build_batch(BatchCache &B, pp_circuit *const *cs, int64_t count, doubl
             auto close = [&] {
                 tg.first_block[tg.ngroups] = run;
                 tg.chain = chain;
-                tg.start = l == 0;
+                tg.start = l == 0 && pp::tile_pass_chained(k, last_n, chain);
                 B.tiles.push_back({2, k, out.used, (int)ntd, run, tg});
                 out.used += BatchWriter::padded(ntd * sizeof(pp::TilePassDesc));
                 td = (pp::TilePassDesc *)(out.host + out.used);
@@ -2332,7 +2336,12 @@ pp_status build_batch(BatchCache &B, pp_circuit *const *cs, int64_t count, doubl
             };
             for (const auto &o : order) {
                 if (o.second->n != last_n) {
-                    if (tg.ngroups == pp::kMaxTileGroups) close();
+                    // a launch runs one kernel, the chain's for the circuits
+                    // whose first passes begin their weights: it never holds
+                    // circuits on both sides of kChainMaxN (n falls)
+                    if (tg.ngroups == pp::kMaxTileGroups ||
+                        (last_n > pp::kChainMaxN && o.second->n <= pp::kChainMaxN))
+                        close();
                     tg.first_block[tg.ngroups] = run;
                     tg.first_desc[tg.ngroups] = ntd;
                     tg.shift[tg.ngroups] = 2 * (o.second->n - k);
@@ -2730,7 +2739,7 @@ extern "C" pp_status pp_evaluate_thetas(pp_circuit *c, int64_t count, const doub
             pp::TileGroups grp{};
             grp.ngroups = 1;
             grp.chain = pp::chain_tiles(P.k, c->plan_seg);
-            grp.start = l == 0;
+            grp.start = l == 0 && runs_chained(c);
             grp.first_block[1] = (int32_t)((c->step[l + 1] - c->step[l]) * cs * ntiles);
             grp.shift[0] = shift;
             HIPCHK(pp::launch_tile_pass(pass + (size_t)c->step[l] * cs, grp, P.k, c->dbytes, false, s));

@@ -1669,7 +1669,7 @@ void set_tile_kernel_variant(int k, int variant) {
 int tile_kernel_variant(int k) { return (k >= 0 && k < 8) ? g_tile_variant[k] : 0; }
 
 bool tile_pass_chained(int k, int n, bool chain) {
-    return (k == 6 || k == 7) && g_tile_variant[k] == 1 && n <= 14 && chain;
+    return (k == 6 || k == 7) && g_tile_variant[k] == 1 && n <= kChainMaxN && chain;
 }
 
 int num_cus() {
@@ -1722,6 +1722,9 @@ static hipError_t launch_tile_t(const TilePassDesc *d, const TileGroups &grp, si
     // most 14 qubits; every group of a launch shares one n = k + shift / 2
     int max_n = K;
     for (int gi = 0; gi < grp.ngroups; ++gi) max_n = std::max(max_n, K + grp.shift[gi] / 2);
+    // only the chain kernel begins weights: the others would read what nobody wrote
+    const bool chained = !TRACK && tile_pass_chained(K, max_n, grp.chain);
+    if (grp.start && !chained) return hipErrorInvalidValue;
     if (!TRACK && K == 6 && g_tile_variant[6] == 3 && max_n <= 14) {
         // one wave per tile, tile in registers; LDS only for re-layouts
         hipLaunchKernelGGL((tile_reg_kernel<T, false>), dim3(nblocks), dim3(64), 0, s, d, grp);
@@ -1754,7 +1757,7 @@ static hipError_t launch_tile_t(const TilePassDesc *d, const TileGroups &grp, si
         return hipGetLastError();
     }
     if constexpr (!TRACK && K >= 6)
-        if (tile_pass_chained(K, max_n, grp.chain)) return launch_tile_chain(d, grp, K, (int)sizeof(T), s);
+        if (chained) return launch_tile_chain(d, grp, K, (int)sizeof(T), s);
     if constexpr (!TRACK && K < 6) if (g_tile_variant[K] == 1 && max_n <= 14) {
         auto fn = tile_stream_kernel<T, K>;
         constexpr int SB = kStreamBlock<K>;

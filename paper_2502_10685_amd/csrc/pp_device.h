@@ -156,7 +156,7 @@ constexpr int kMaxTileGroups = 8;
 struct TileGroups {
     int32_t ngroups;
     int32_t chain;  // every descriptor holds its pass as records too
-    int32_t start;  // some may hold first passes, whose weights were not filled in
+    int32_t start;  // some may hold first passes, whose weights were not filled in (chain kernel only)
     int32_t first_block[kMaxTileGroups + 1];
     int32_t first_desc[kMaxTileGroups];
     int32_t shift[kMaxTileGroups];
@@ -260,6 +260,8 @@ hipError_t launch_tile_pass(const TilePassDesc *d_descs, const TileGroups &group
 // Whether launch_tile_pass would run untracked passes of circuits of n qubits
 // with such records (TileGroups::chain) through launch_tile_chain, which begins
 // first passes itself; the other kernels read coef.
+// kChainMaxN: their 32-bit offsets in HBM.
+constexpr int kChainMaxN = 14;
 bool tile_pass_chained(int k, int n, bool chain);
 hipError_t launch_tile_chain(const TilePassDesc *d_descs, const TileGroups &groups, int k, int dtype_bytes,
                              hipStream_t s);
