@@ -910,7 +910,7 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
             pp::PlanOptions o;
             o.g_end = c->ramp_gate;  // the dense sweep takes the gates before the frame's
             o.segments = seg;
-            o.chain = pp::chain_tiles(k, seg);
+            o.chain = pp::chain_tiles(k, c->n, seg);
             c->dplan = k == c->n || meets(c, k)
                            ? pp::plan_meet(c->g, k, kLowQubits, c->ramp_gate, seg, c->dbytes, &c->pass_recs)
                            : pp::plan_dense_opts(c->g, k, kLowQubits, o);
@@ -920,11 +920,11 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
             pp::PlanOptions o;
             o.compose = o.group = o.reorder = c->track == 0;
             o.segments = seg;
-            o.chain = pp::chain_tiles(k, seg);
+            o.chain = pp::chain_tiles(k, c->n, seg);
             c->dplan = pp::plan_dense_opts(c->g, k, kLowQubits, o);
             if (k == c->n && !c->track) pp::build_chain(c->dplan, c->dbytes);
         }
-        if (k < c->n && pp::chain_tiles(k, seg) && !c->track && c->dplan.fwd_from < 0)
+        if (k < c->n && pp::chain_tiles(k, c->n, seg) && !c->track && c->dplan.fwd_from < 0)
             pp::build_chain(c->dplan, c->dbytes, &c->pass_recs);
         const pp::DensePlan &P = c->dplan;
         {
@@ -980,7 +980,7 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
         } else {
             c->h_pass.clear();
             std::vector<int> rec;
-            if (pp::chain_tiles(k, seg) && !c->track) {
+            if (pp::chain_tiles(k, c->n, seg) && !c->track) {
                 if ((r = upload_vec(&c->d_chain, P.chain)) != PP_OK) return r;
                 rec = c->pass_recs;
             }
@@ -1101,7 +1101,7 @@ struct DenseStart {
 // every launch it shares (circuits of more than kChainMaxN qubits have launches
 // of their own).
 bool runs_chained(const pp_circuit *c) {
-    return !c->track && pp::tile_pass_chained(c->dplan.k, c->n, pp::chain_tiles(c->dplan.k, c->plan_seg));
+    return !c->track && pp::tile_pass_chained(c->dplan.k, c->n, pp::chain_tiles(c->dplan.k, c->n, c->plan_seg));
 }
 DenseStart dense_start(const pp_circuit *c) {
     const bool meet = c->dplan.fwd_pass >= 0, chained = runs_chained(c);
@@ -1123,7 +1123,7 @@ pp::TileGroups step_groups(const pp_circuit *c, size_t l) {
     pp::TileGroups grp{};
     const int shift = 2 * (c->n - c->dplan.k);
     grp.ngroups = 1;
-    grp.chain = pp::chain_tiles(c->dplan.k, c->plan_seg);
+    grp.chain = pp::chain_tiles(c->dplan.k, c->n, c->plan_seg);
     grp.start = l == 0 && runs_chained(c);
     grp.first_block[1] = (c->step[l + 1] - c->step[l]) << shift;
     grp.first_desc[0] = c->step[l];
@@ -2321,12 +2321,12 @@ pp_status build_batch(BatchCache &B, pp_circuit *const *cs, int64_t count, doubl
             int32_t ntd = 0;
             pp::TileGroups tg{};
             int run = 0, last_n = -1;
-            bool chain = true;
-            for (int i : by_k[k]) chain = chain && pp::chain_tiles(k, cs[i]->plan_seg);
+            bool seg = false;
+            for (int i : by_k[k]) seg = seg || cs[i]->plan_seg;
             auto close = [&] {
                 tg.first_block[tg.ngroups] = run;
-                tg.chain = chain;
-                tg.start = l == 0 && pp::tile_pass_chained(k, last_n, chain);
+                tg.chain = pp::chain_tiles(k, last_n, seg);
+                tg.start = l == 0 && pp::tile_pass_chained(k, last_n, tg.chain);
                 B.tiles.push_back({2, k, out.used, (int)ntd, run, tg});
                 out.used += BatchWriter::padded(ntd * sizeof(pp::TilePassDesc));
                 td = (pp::TilePassDesc *)(out.host + out.used);
@@ -2525,7 +2525,7 @@ pp_status ensure_grad(pp_circuit *c, int64_t every) {
         }
         if ((r = upload_vec(&G.hres, rd)) != PP_OK) return r;
     } else {
-        if (pp::chain_tiles(k_heis, seg) && (r = upload_vec(&G.hchain, P.heis.chain)) != PP_OK) return r;
+        if (pp::chain_tiles(k_heis, n, seg) && (r = upload_vec(&G.hchain, P.heis.chain)) != PP_OK) return r;
         std::vector<pp::TilePassDesc> td;
         for (const pp::DensePass &ps : P.heis.passes) {
             pp::TilePassDesc d{};
@@ -2539,7 +2539,7 @@ pp_status ensure_grad(pp_circuit *c, int64_t every) {
             d.ntiles = (int)((int64_t)1 << (2 * (n - k_heis)));
             for (int j = 0; j < k_heis; ++j) d.qubits |= (uint64_t)ps.qubit[j] << (8 * j);
             d.reg_entry = pp::pass_reg_entry(P.heis, ps);
-            if (pp::chain_tiles(k_heis, seg))
+            if (pp::chain_tiles(k_heis, n, seg))
                 set_chain(d, P.heis, ps, G.hchain, P.heis_chain_begin[td.size()], P.heis_chain_begin[td.size() + 1], 8);
             td.push_back(d);
         }
@@ -2738,7 +2738,7 @@ extern "C" pp_status pp_evaluate_thetas(pp_circuit *c, int64_t count, const doub
             // one launch: the sets' descriptors of a pass are consecutive
             pp::TileGroups grp{};
             grp.ngroups = 1;
-            grp.chain = pp::chain_tiles(P.k, c->plan_seg);
+            grp.chain = pp::chain_tiles(P.k, c->n, c->plan_seg);
             grp.start = l == 0 && runs_chained(c);
             grp.first_block[1] = (int32_t)((c->step[l + 1] - c->step[l]) * cs * ntiles);
             grp.shift[0] = shift;
@@ -2918,7 +2918,7 @@ pp_status enqueue_gradient_body(pp_circuit *c, hipStream_t s, double *d_expval, 
             for (int p = P.heis_pass_begin[sg]; p < P.heis_pass_begin[sg + 1]; ++p) {
                 pp::TileGroups grp{};
                 grp.ngroups = 1;
-                grp.chain = pp::chain_tiles(G.k_heis, G.seg);
+                grp.chain = pp::chain_tiles(G.k_heis, n, G.seg);
                 grp.first_block[1] = 1 << shift;
                 grp.first_desc[0] = p;
                 grp.shift[0] = shift;
@@ -3433,7 +3433,7 @@ void server_loop(pp_server *S) {
                     }
                     tg.first_block[tg.ngroups] = run;
                     tg.chain = 1;
-                    for (size_t j = i0; j < i; ++j) tg.chain &= pp::chain_tiles(k, grp[j]->c->plan_seg);
+                    for (size_t j = i0; j < i; ++j) tg.chain &= pp::chain_tiles(k, grp[j]->c->n, grp[j]->c->plan_seg);
                     std::vector<unsigned char> blob(td.size() * sizeof(pp::TilePassDesc));
                     std::memcpy(blob.data(), td.data(), blob.size());
                     void *dd = nullptr;

@@ -398,7 +398,7 @@ void group_all(DensePlan &P, bool segments, bool chain) {
             (segments && !P.resident && ps.k == kSegTileDigits) ? segment_ops(in, ps.k) : group_ops(in, ps.k);
         if (!P.resident && ps.k == 6) split_waves(out, ps);
         std::vector<std::vector<DOp>> pieces;
-        if (!P.resident && (ps.k == kChainTileDigits || (ps.k == 6 && chain)) && !out.empty()) pieces = chain_order(out);
+        if (!P.resident && chain && !out.empty()) pieces = chain_order(out);
         else pieces.push_back(std::move(out));
         for (auto &piece : pieces) {
             if (!P.resident && ps.k == 6) tag_barriers(piece);
@@ -963,7 +963,7 @@ DensePlan plan_meet(const GateList &g, int k, int low, int64_t g_end, bool segme
     for (int64_t i = 0; i < g_end; ++i) ncx += g.op[(size_t)i] == 2;
     int64_t s = ncx ? 0 : g_end / 2;
     for (int64_t seen = 0; ncx && seen < ncx / 2; ++s) seen += g.op[(size_t)s] == 2;
-    const bool chains = k == g.n || chain_tiles(k, segments);
+    const bool chains = k == g.n || chain_tiles(k, g.n, segments);
     std::vector<int> hrec, frec;
     PlanOptions o;
     o.g_begin = s;
@@ -1050,7 +1050,7 @@ GradPlan plan_gradient(const GateList &g, int k_heis, int k_fwd, int low, int64_
         h.g_begin = G.bounds[s];
         h.g_end = G.bounds[s + 1];
         h.segments = segments;
-        h.chain = chain_tiles(k_heis, segments);
+        h.chain = chain_tiles(k_heis, g.n, segments);
         G.heis_pass_begin.push_back((int)G.heis.passes.size());
         plan_append(G.heis, plan_dense_opts(g, k_heis, low, h));
         PlanOptions f;
@@ -1067,7 +1067,7 @@ GradPlan plan_gradient(const GateList &g, int k_heis, int k_fwd, int low, int64_
     G.fwd_map_begin.push_back(G.fwd.nmaps());
     build_chain(G.fwd, 8, &G.fwd_chain_begin, false);
     for (size_t r = 0; r < G.fwd.rgate.size(); ++r) G.rslot.push_back(slot[(size_t)G.fwd.rgate[r]]);
-    if (G.heis.resident || chain_tiles(k_heis, segments)) build_chain(G.heis, 8, &G.heis_chain_begin);
+    if (G.heis.resident || chain_tiles(k_heis, g.n, segments)) build_chain(G.heis, 8, &G.heis_chain_begin);
     return G;
 }
 

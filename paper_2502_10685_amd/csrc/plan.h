@@ -79,13 +79,16 @@ constexpr int kChainTileDigits = 7;
 constexpr int kTileRecords = 64;
 constexpr int kTileUnits = kTileRecords - 2;
 
-// General form: gates [g_begin, g_end) only; forward = g_begin first (the
-// adjoint sweep) instead of Heisenberg order; slot (optional, size m): for
-// each rotation gate its join slot, stored in DOp::reserved with DOp::b set
-// to the rotation's op code.
-// tiles whose passes run as record chains
-inline bool chain_tiles(int k, bool segments) { return k == kChainTileDigits || (k == 6 && !segments); }
+// Whether untracked passes over k-qubit tiles of an n-qubit circuit run as
+// record chains.  Beyond kChainMaxN they run op by op, a group at a time: units
+// of a CX and a map per digit are more sweeps there (3,000 random gates at n =
+// 16: 484, 462 in groups).
+inline bool chain_tiles(int k, int n, bool segments) {
+    return n <= kChainMaxN && (k == kChainTileDigits || (k == 6 && !segments));
+}
 
+// General form: gates [g_begin, g_end) only; forward = g_begin first (the
+// adjoint sweep) instead of Heisenberg order.
 struct PlanOptions {
     bool compose = true;
     bool group = true;  // pack ops on a common digit pair into GROUP ops
@@ -95,8 +98,8 @@ struct PlanOptions {
     // (SEG headers, which the register-tile kernel needs); the LDS kernels
     // skip SEG headers, so without segments they decode fewer ops
     bool segments = true;
-    // order passes over 6-qubit tiles for the record chain (7-qubit tiles
-    // always are): units of a CX and a map per digit, at most kTileUnits
+    // order passes over tiles for the record chain (see chain_tiles): units of
+    // a CX and a map per digit, at most kTileUnits
     bool chain = false;
     bool forward = false;
     int64_t g_begin = 0, g_end = -1;
