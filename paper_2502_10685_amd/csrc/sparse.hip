@@ -350,33 +350,63 @@ __device__ __forceinline__ void exact_flush(const unsigned long long *acc, unsig
     }
 }
 
-// The sum as a double, by one wave (its lane 0): each word exactly as two
-// doubles, added up in a tree of two-sums.
+// Carries the words, two per lane (2 lane and 2 lane + 1), up until each is below
+// 2^32: how the workgroups shared the sum then no longer shows.  Lane 33's
+// upper word takes what is left, a negative sum's sign.
+__device__ __forceinline__ void exact_carry(long long &a, long long &b, int lane) {
+    long long carry;
+    do {
+        b += a >> 32;
+        a &= 0xffffffffll;
+        carry = lane < kExactNan / 2 ? b >> 32 : 0;
+        b -= carry << 32;
+        const long long up = __shfl_up(carry, 1, 64);
+        a += lane > 0 ? up : 0;
+    } while (__ballot(carry != 0));
+}
+
+// The sum rounded to a double, to nearest even, by one wave (every lane).
 __device__ __forceinline__ double exact_value(const unsigned long long *sum, int lane) {
-#pragma clang fp contract(off)
-    auto two_sum = [](double a, double b, double &err) {
-        const double t = a + b, bb = t - a;
-        err = (a - (t - bb)) + (b - bb);
-        return t;
-    };
-    double hi = 0.0, lo = 0.0;
-    for (int i = lane; i < kExactNan; i += 64) {
-        const long long w = (long long)sum[i];
-        const double h = (double)w, l = (double)(w - (long long)h);
-        double e;
-        hi = two_sum(hi, ldexp(h, 32 * i - 1074), e);
-        lo += e + ldexp(l, 32 * i - 1074);
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        const double h = __shfl_down(hi, off, 64), l = __shfl_down(lo, off, 64);
-        double e;
-        hi = two_sum(hi, h, e);
-        lo += l + e;
-    }
     const unsigned long long nan = sum[kExactNan], pinf = sum[kExactNan + 1], ninf = sum[kExactNan + 2];
     if (nan || (pinf && ninf)) return __builtin_nan("");
     if (pinf || ninf) return pinf ? __builtin_inf() : -__builtin_inf();
-    return hi + lo;
+    long long a = 2 * lane < kExactNan ? (long long)sum[2 * lane] : 0;
+    long long b = 2 * lane + 1 < kExactNan ? (long long)sum[2 * lane + 1] : 0;
+    exact_carry(a, b, lane);
+    const bool neg = __shfl(b, kExactNan / 2, 64) < 0;
+    if (neg) {
+        a = -a;
+        b = -b;
+        exact_carry(a, b, lane);
+    }
+    const unsigned long long has_a = __ballot(a != 0), has_b = __ballot(b != 0);
+    if (!(has_a | has_b)) return 0.0;
+    const int ha = has_a ? 2 * (63 - __clzll((long long)has_a)) : -1;
+    const int hb = has_b ? 2 * (63 - __clzll((long long)has_b)) + 1 : -1;
+    const int h = ha > hb ? ha : hb;  // the highest word
+    const double huge = neg ? -__builtin_inf() : __builtin_inf();
+    if (h >= kExactNan) return huge;
+    auto word = [&](int i) -> unsigned long long {
+        const long long va = __shfl(a, (i < 0 ? 0 : i) >> 1, 64), vb = __shfl(b, (i < 0 ? 0 : i) >> 1, 64);
+        return i < 0 ? 0ull : (unsigned long long)((i & 1) ? vb : va);
+    };
+    const unsigned long long w2 = word(h), w1 = word(h - 1), w0 = word(h - 2);
+    const bool below = __ballot((a != 0 && 2 * lane < h - 2) || (b != 0 && 2 * lane + 1 < h - 2)) != 0;
+    // M: the highest bit and the 63 behind it; p: its place, worth 2^(p - 1074)
+    const int z = __clz((int)(unsigned)w2), p = 32 * h + 31 - z;
+    const unsigned long long M = (((w2 << 32) | w1) << z) | (w0 >> (32 - z));
+    const bool rest = ((w0 << z) & 0xffffffffull) != 0 || below;
+    unsigned long long bits;
+    if (p <= 52) {
+        bits = M >> (63 - p);
+    } else {
+        const unsigned long long m = M >> 11, low = M & 0x7ffull;
+        const bool up = low > 0x400ull || (low == 0x400ull && (rest || (m & 1ull)));
+        if (p - 51 >= 2047) return huge;
+        bits = ((unsigned long long)(p - 52) << 52) + m + (up ? 1ull : 0ull);
+    }
+    const double v = __builtin_bit_cast(double, bits);
+    return neg ? -v : v;
 }
 
 // ------------------------------------------------- rotations on a list
