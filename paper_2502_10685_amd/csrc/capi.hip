@@ -2468,10 +2468,10 @@ pp_status ensure_grad(pp_circuit *c, int64_t every) {
     auto &G = c->gr;
     const int tv6 = pp::tile_kernel_variant(6);  // as in ensure_plan
     const bool seg = tv6 == 3 || tv6 == 4;
-    if (G.valid && G.every == every && G.seg == seg) return PP_OK;
+    const int k_heis = tile_qubits_for(c, true);
+    if (G.valid && G.every == every && G.seg == seg && G.k_heis == k_heis) return PP_OK;
     free_grad(c);
     const int n = c->n;
-    const int k_heis = tile_qubits_for(c, true);
     const int k_fwd = n <= 6 ? n : 6;
     G.plan = pp::plan_gradient(c->g, k_heis, k_fwd, kLowQubits, every, seg);
     const pp::GradPlan &P = G.plan;
