@@ -435,8 +435,9 @@ PP_API void pp_server_destroy(pp_server *s);
  * built or a kernel launched):
  *   PP_TUNE_TILE_QUBITS: index = n (8..16), value = default tile qubits k
  *                        (4..7) for circuits without PP_OPT_TILE_QUBITS
- *                        (until it is set, the default of 7 at n = 10 is 6
- *                        for circuits below 500 gates or run from one end);
+ *                        (the default, 7 at n = 10, stands for 6 in circuits
+ *                        below 500 gates or run from one end; another value,
+ *                        for every circuit);
  *   PP_TUNE_TILE_KERNEL: index = k (4..7), value = 0 one 256-thread
  *                        workgroup per tile (512 for k = 7), 1 persistent
  *                        workgroups (256 threads; 1,024 for k = 7) that

@@ -292,8 +292,10 @@ constexpr int64_t kSweepMeetBytes = (int64_t)256 << 20;
 // 1.08, n = 10 1.16 against 1.21; 32 circuits of n = 9 1.12 against 1.21, of n
 // = 10 4.23 against 3.74; 3,000 gates at n = 11 1.76 against 1.56, n = 12 6.3
 // against 4.8, n = 13 26.6 against 19.6; FP32 alike), up to the kernel's 14.
+constexpr int kTileQubits[17] = {0, 0, 0, 0, 0, 0, 0, 0, 6, 6, 7, 7, 7, 7, 7, 6, 6};
 int g_tile_qubits[17] = {0, 0, 0, 0, 0, 0, 0, 0, 6, 6, 7, 7, 7, 7, 7, 6, 6};
-bool g_tile_tuned[17] = {};  // set by pp_tune_set: taken as it is
+// another value set by pp_tune_set: taken as it is
+bool tile_tuned(int n) { return n <= 16 && g_tile_qubits[n] != kTileQubits[n]; }
 int default_tile_qubits(int n) { return n >= 8 && n <= 16 ? g_tile_qubits[n] : (n > 16 ? 6 : 5); }
 
 // pinned staging for small asynchronous uploads, reused once the previous
@@ -715,7 +717,7 @@ int tile_qubits_for(const pp_circuit *c, bool one_end = false) {
     k = std::max(k, kLowQubits + 2);
     k = std::min(k, 7);
     one_end = one_end || c->track || c->keep_coef;
-    if (c->tile_opt <= 0 && k == 7 && c->n <= kMeetMaxN && !g_tile_tuned[c->n] &&
+    if (c->tile_opt <= 0 && k == 7 && c->n <= kMeetMaxN && !tile_tuned(c->n) &&
         (one_end || c->g.m < kShortGates))
         k = 6;
     while (k > kLowQubits + 2 &&
@@ -3648,7 +3650,6 @@ extern "C" pp_status pp_tune_set(pp_tune_key key, int32_t index, int32_t value) 
     if (key == PP_TUNE_TILE_QUBITS) {
         if (index < 8 || index > 16 || value < 4 || value > 7) return fail(PP_ERR_INVALID, "tile qubits: n in 8..16, k in 4..7");
         g_tile_qubits[index] = value;
-        g_tile_tuned[index] = true;
         return PP_OK;
     }
     if (key == PP_TUNE_TILE_KERNEL) {
