@@ -460,7 +460,10 @@ PP_API void pp_server_destroy(pp_server *s);
  *   PP_TUNE_SORT_SHAPE: index = capacity class of a SPARSE circuit's term
  *                        buffers (0: up to 2^17 terms, 1: up to 2^21, 2:
  *                        larger), value = shape of the radix sort that
- *                        merges equal strings (reduce(), eq. (7)): 0 = 8 key
+ *                        orders lists and merges equal strings (reduce(),
+ *                        eq. (7)) where that takes a sort: pp_get_terms,
+ *                        repeated strings of an observable, truncated lists
+ *                        whose last gates are Clifford gates: 0 = 8 key
  *                        bits per pass, 8 terms per thread (256 threads);
  *                        1 = 8 bits, 4 terms; 2 = 8 bits, 16 terms; 3 = 7
  *                        bits, 8 terms (128 threads); 4 = 7 bits, 16 terms;

@@ -1,7 +1,7 @@
 """Project autotuner: picks, by timing on the device, the tile-pass kernel
 variant per tile size and the tile size (qubits per LDS tile) per register
 size n, for batched throughput, and the radix-sort shape (key bits per pass,
-terms per thread) of the SPARSE engine's merge per term-capacity class.
+terms per thread) of the SPARSE engine's sorted lists per term-capacity class.
 Results are cached as JSON keyed by the device name and weight dtype, and
 applied through pp_tune_set.
 
@@ -23,11 +23,12 @@ from . import _lib as L
 
 VARIANT_NAMES = {0: "workgroup-per-tile", 1: "persistent-prefetch", 2: "wave-per-tile",
                  3: "register-tile", 4: "register-tile-prefetch"}
-# radix-sort shapes of the SPARSE merge: (key bits per pass, terms per thread)
+# radix-sort shapes of SPARSE lists: (key bits per pass, terms per thread)
 SORT_SHAPES = {0: (8, 8), 1: (8, 4), 2: (8, 16), 3: (7, 8), 4: (7, 16), 5: (6, 16)}
-# per capacity class: the largest term capacity of the class and a probe
-# circuit (qubits, gates) whose string set grows to a sizeable part of it
-SORT_CLASSES = {0: (1 << 17, 16, 70), 1: (1 << 21, 20, 130), 2: (1 << 23, 20, 200)}
+# per capacity class: the largest term capacity of the class (of the last: one
+# of its range) and a probe (n, k) whose 2^(n-k) 3^k strings are a quarter to a
+# half of it
+SORT_CLASSES = {0: (1 << 17, 16, 0), 1: (1 << 21, 20, 0), 2: (1 << 23, 20, 3)}
 
 
 def _device_name():
@@ -94,49 +95,40 @@ def _count_for(n):
     return max(2, min(64, (1 << 16) // (4 ** (n - 6))))
 
 
-def _sort_probe(api, cls, dtype, say):
-    """A sort-merge SPARSE circuit of capacity class cls whose strings fill
-    a sizeable part of the capacity (fewer gates until nothing overflows)."""
+def _sort_probe(api, cls, dtype):
+    """A SPARSE circuit of capacity class cls every evaluation of which sorts
+    its strings: a truncated list that a closing Clifford run has been taken
+    through is sorted, other lists only when they are read."""
     from . import workloads as W
-    cap, n, m = SORT_CLASSES[cls]
-    for _ in range(8):
-        w = W.random_circuit(np.random.default_rng(9300 + cls), n, m, W.obs_z(n, [0, 1]))
-        c = api.Circuit.from_workload(w, dtype=dtype, engine="sparse", max_terms=cap)
-        c.set_option(L.PP_OPT_SPARSE_FRAME, 0)
-        c.evaluate()
-        st = c.stats()
-        if not st["overflow"]:
-            return c, st
-        c.close()
-        m = m * 3 // 4
-    say(f"sort class {cls}: no probe fits the capacity")
-    return None, None
+    cap, n, k = SORT_CLASSES[cls]
+    w = W.spread_circuit(9300 + cls, n, k)  # its first gates, the last processed, are Clifford gates
+    c = api.Circuit.from_workload(w, dtype=dtype, engine="sparse", max_terms=cap)
+    c.set_truncation(min_abs_coeff=1e-300)  # drops nothing but zeros
+    c.evaluate()
+    return c, c.stats()
 
 
 def tune_sort(dtype="f64", log=None, reps=3):
-    """Times every radix-sort shape on one sort-merge probe per capacity class
-    and applies the fastest; returns {"sort_shape": {cls: shape}, "timings":
-    ...}.  Every shape must give the same <O> bit for bit."""
+    """Times every radix-sort shape on one probe per capacity class and applies
+    the fastest; returns {"sort_shape": {cls: shape}, "timings": ...}.  Every
+    shape must give the same list bit for bit."""
     import torch
     from . import api
     say = log or (lambda s: None)
     res = {"sort_shape": {}, "timings": {}}
     for cls in SORT_CLASSES:
-        c, st = _sort_probe(api, cls, dtype, say)
-        if c is None:
-            continue
+        c, st = _sort_probe(api, cls, dtype)
         best, times, ref = None, {}, None
         old = L.tune_get(L.PP_TUNE_SORT_SHAPE, cls)
         for v in SORT_SHAPES:
             L.tune_set(L.PP_TUNE_SORT_SHAPE, cls, v)
-            ev = c.evaluate()
-            torch.cuda.synchronize()
-            bits = np.float64(ev.item()).view(np.uint64)
+            c.evaluate()
+            got = c.terms(capacity=SORT_CLASSES[cls][0])
             if ref is None:
-                ref = bits
-            elif bits != ref:
+                ref = got
+            elif any(a.tobytes() != b.tobytes() for a, b in zip(ref, got)):
                 L.tune_set(L.PP_TUNE_SORT_SHAPE, cls, old)
-                raise RuntimeError(f"sort shape {v} changed <O> in class {cls}")
+                raise RuntimeError(f"sort shape {v} changed the list in class {cls}")
             ts = []
             for _ in range(reps):
                 t0 = time.perf_counter()
@@ -159,28 +151,17 @@ def tune_sort(dtype="f64", log=None, reps=3):
 def tune(sizes=(8, 9, 10, 11, 12), dtype="f64", m=1200, save=True, log=None, resident=(5, 6, 7), sort=True):
     """Times every candidate and returns (and applies, and caches) the table
     {"tile_kernel": {k: variant}, "tile_qubits": {n: k},
-     "resident_block": {n: threads}, "sort_shape": {class: shape},
+     "resident_block": {n: threads (not tuned)}, "sort_shape": {class: shape},
      "timings": ...}."""
     from . import api
     say = log or (lambda s: None)
     table = {"tile_kernel": {}, "tile_qubits": {}, "resident_block": {},
              "timings": {"tile_kernel": {}, "tile_qubits": {}, "resident_block": {}},
              "device": _device_name(), "dtype": dtype, "probe_gates": m}
-    # 0. threads of the LDS-resident kernel (one circuit per workgroup)
+    # 0. threads of the LDS-resident kernel: they follow from n, so there is
+    # nothing to time; the table holds the value in force
     for n in resident:
-        circs = _probe_batch(api, n, 256, m, dtype, seed=8900 + n)
-        best, times = None, {}
-        for b in (256, 512, 1024):
-            L.tune_set(L.PP_TUNE_RESIDENT_BLOCK, n, b)
-            times[b] = _time_batch(api, circs)
-            if best is None or times[b] < times[best]:
-                best = b
-        L.tune_set(L.PP_TUNE_RESIDENT_BLOCK, n, best)
-        table["resident_block"][str(n)] = best
-        table["timings"]["resident_block"][str(n)] = {str(b): t for b, t in times.items()}
-        say(f"resident block n={n}: {best} ({ {b: round(t * 1e3, 2) for b, t in times.items()} } ms)")
-        for c in circs:
-            c.close()
+        table["resident_block"][str(n)] = L.tune_get(L.PP_TUNE_RESIDENT_BLOCK, n)
     # 1. kernel variant per tile size k, on circuits with n = k + 3 tiled at k
     for k in (4, 5, 6, 7):
         n = k + 3
@@ -215,7 +196,7 @@ def tune(sizes=(8, 9, 10, 11, 12), dtype="f64", m=1200, save=True, log=None, res
         table["tile_qubits"][str(n)] = best
         table["timings"]["tile_qubits"][str(n)] = {str(k): t for k, t in times.items()}
         say(f"tile qubits n={n}: k={best} ({ {k: round(t * 1e3, 2) for k, t in times.items()} } ms)")
-    # 3. radix-sort shape of the SPARSE merge per capacity class
+    # 3. radix-sort shape of SPARSE lists per capacity class
     if sort:
         srt = tune_sort(dtype, log=log)
         table["sort_shape"] = srt["sort_shape"]
