@@ -775,36 +775,42 @@ pp_status ensure_state(pp_circuit *c, bool weights = true) {
         cap = std::max<int64_t>(cap, 1);
         const int64_t cap2 = 2 * cap;
         const int64_t tiles = (cap2 + 2047) / 2048;
-        c->sb.cap2 = cap2;
-        c->sb.max_tiles = tiles;
-        for (int i = 0; i < 6; ++i) {
-            const size_t bytes = (size_t)cap2 * ((i == 2 || i == 5) ? c->dbytes : 8);
-            hipError_t e = dev_alloc(&c->sb_base[i], bytes);
-            if (e != hipSuccess) {
-                c->sb_base[i] = nullptr;
-                return fail(PP_ERR_NOMEM, "sparse term buffers");
-            }
+        // all of them or none: an evaluation after a failed one starts anew
+        pp::SparseBuffers b{};
+        void *base[6] = {};
+        double *dropped = nullptr;
+        b.cap2 = cap2;
+        b.max_tiles = tiles;
+        hipError_t e = hipSuccess;
+        for (int i = 0; i < 6 && e == hipSuccess; ++i)
+            e = dev_alloc(&base[i], (size_t)cap2 * ((i == 2 || i == 5) ? c->dbytes : 8));
+        if (e == hipSuccess) e = dalloc(&b.count, 8);
+        if (e == hipSuccess) e = dalloc(&b.scan, 256);
+        if (e == hipSuccess) e = dalloc(&b.updates, 1);
+        if (e == hipSuccess) e = dalloc(&b.hist, (size_t)pp::sort_hist_entries(cap2));
+        if (e == hipSuccess) e = dalloc(&b.tile_flags, (size_t)tiles);
+        if (e == hipSuccess) e = dalloc(&b.lens, 4);
+        if (e == hipSuccess) e = dalloc(&b.exact, (size_t)(2 * pp::kExactWords));
+        b.table_bits = 8;
+        while (((int64_t)1 << b.table_bits) <= cap2) ++b.table_bits;
+        if (e == hipSuccess) e = dalloc(&b.table, (size_t)pp::kListTables << b.table_bits);
+        if (e == hipSuccess) e = dalloc(&dropped, (size_t)tiles + 1);
+        if (e != hipSuccess) {
+            for (void *p : base) dev_free(p);
+            for (void *p : {(void *)b.count, (void *)b.scan, (void *)b.updates, (void *)b.hist, (void *)b.tile_flags,
+                            (void *)b.lens, (void *)b.exact, (void *)b.table})
+                dev_free(p);
+            return fail(PP_ERR_NOMEM, "sparse term buffers");
         }
-        c->sb.x = (uint64_t *)c->sb_base[0];
-        c->sb.z = (uint64_t *)c->sb_base[1];
-        c->sb.c = c->sb_base[2];
-        c->sb.x2 = (uint64_t *)c->sb_base[3];
-        c->sb.z2 = (uint64_t *)c->sb_base[4];
-        c->sb.c2 = c->sb_base[5];
-        HIPCHK(dalloc(&c->sb.count, 8));
-        HIPCHK(dalloc(&c->sb.scan, 256));
-        HIPCHK(dalloc(&c->sb.updates, 1));
-        HIPCHK(dalloc(&c->sb.hist, (size_t)pp::sort_hist_entries(cap2)));
-        HIPCHK(dalloc(&c->sb.tile_flags, (size_t)tiles));
-        HIPCHK(dalloc(&c->sb.lens, 4));
-        HIPCHK(dalloc(&c->sb.exact, (size_t)(2 * pp::kExactWords)));
-        c->sb.table_bits = 8;
-        while (((int64_t)1 << c->sb.table_bits) <= cap2) ++c->sb.table_bits;
-        if (dalloc(&c->sb.table, (size_t)pp::kListTables << c->sb.table_bits) != hipSuccess) {
-            c->sb.table = nullptr;
-            return fail(PP_ERR_NOMEM, "sparse term tables");
-        }
-        HIPCHK(dalloc(&c->d_dropped, (size_t)tiles + 1));
+        for (int i = 0; i < 6; ++i) c->sb_base[i] = base[i];
+        c->d_dropped = dropped;
+        b.x = (uint64_t *)base[0];
+        b.z = (uint64_t *)base[1];
+        b.c = base[2];
+        b.x2 = (uint64_t *)base[3];
+        b.z2 = (uint64_t *)base[4];
+        b.c2 = base[5];
+        c->sb = b;
     }
     const bool ramp = ramp_wanted(c);
     if (((c->engine == PP_ENGINE_SPARSE && c->n <= pp::kFrameMaxN && c->frame_opt) || ramp) && !c->fb.keys) {
