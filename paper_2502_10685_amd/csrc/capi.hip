@@ -758,6 +758,20 @@ int64_t ramp_switch_gate(const pp_circuit *c) {
     return s;
 }
 
+// Strings that each array of a SPARSE circuit holds (twice the term capacity),
+// and log2 of the slots of each of its list passes' tables.
+int64_t sparse_cap2(const pp_circuit *c) {
+    int64_t cap = c->max_terms > 0 ? c->max_terms : (c->n <= 12 ? dense_slots(c->n) : ((int64_t)1 << 24));
+    if (c->n <= 12) cap = std::min<int64_t>(cap, dense_slots(c->n));
+    return 2 * std::max<int64_t>(cap, 1);
+}
+int table_bits(int64_t cap2) {
+    int bits = 8;
+    while (((int64_t)1 << bits) <= cap2) ++bits;
+    return bits;
+}
+int64_t table_bytes(int64_t cap2) { return (int64_t)(pp::kListTables * sizeof(uint32_t)) << table_bits(cap2); }
+
 pp_status ensure_state(pp_circuit *c, bool weights = true) {
     if (c->engine == PP_ENGINE_DENSE) {
         const int64_t slots = dense_slots(c->n);
@@ -770,10 +784,7 @@ pp_status ensure_state(pp_circuit *c, bool weights = true) {
         }
         if (c->track && !c->pres) HIPCHK(dalloc(&c->pres, (size_t)slots));
     } else if (!c->sb.x) {
-        int64_t cap = c->max_terms > 0 ? c->max_terms : (c->n <= 12 ? dense_slots(c->n) : ((int64_t)1 << 24));
-        if (c->n <= 12) cap = std::min<int64_t>(cap, dense_slots(c->n));
-        cap = std::max<int64_t>(cap, 1);
-        const int64_t cap2 = 2 * cap;
+        const int64_t cap2 = sparse_cap2(c);
         const int64_t tiles = (cap2 + 2047) / 2048;
         // all of them or none: an evaluation after a failed one starts anew
         pp::SparseBuffers b{};
@@ -791,14 +802,12 @@ pp_status ensure_state(pp_circuit *c, bool weights = true) {
         if (e == hipSuccess) e = dalloc(&b.tile_flags, (size_t)tiles);
         if (e == hipSuccess) e = dalloc(&b.lens, 4);
         if (e == hipSuccess) e = dalloc(&b.exact, (size_t)(2 * pp::kExactWords));
-        b.table_bits = 8;
-        while (((int64_t)1 << b.table_bits) <= cap2) ++b.table_bits;
-        if (e == hipSuccess) e = dalloc(&b.table, (size_t)pp::kListTables << b.table_bits);
+        b.table_bits = table_bits(cap2);  // the tables: ensure_plan, for the list passes
         if (e == hipSuccess) e = dalloc(&dropped, (size_t)tiles + 1);
         if (e != hipSuccess) {
             for (void *p : base) dev_free(p);
             for (void *p : {(void *)b.count, (void *)b.scan, (void *)b.updates, (void *)b.hist, (void *)b.tile_flags,
-                            (void *)b.lens, (void *)b.exact, (void *)b.table})
+                            (void *)b.lens, (void *)b.exact})
                 dev_free(p);
             return fail(PP_ERR_NOMEM, "sparse term buffers");
         }
@@ -875,6 +884,11 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
     if (r != PP_OK) return r;
     const int k = c->engine == PP_ENGINE_DENSE ? tile_qubits_for(c) : 0;
     const bool frame = wants_frame(c);
+    if (c->engine == PP_ENGINE_SPARSE && !frame && !c->sb.table &&
+        dalloc(&c->sb.table, (size_t)pp::kListTables << c->sb.table_bits) != hipSuccess) {
+        c->sb.table = nullptr;
+        return fail(PP_ERR_NOMEM, "sparse term tables");
+    }
     // 6-qubit tiles are ordered into register segments only for the
     // register-tile kernel; selecting it (or another kernel) re-plans
     const int tv6 = pp::tile_kernel_variant(6);
@@ -3173,6 +3187,9 @@ pp_status prepare_request(ServedReq *r, int64_t budget) {
     // do not fit the budget together, so one is enough
     r->spare = r->pooled && c->dplan.fwd_pass >= 0 && 2 * r->foot > budget;
     if (r->pooled && c->dplan.fwd_pass >= 0 && !r->spare) r->foot *= 2;
+    // a list's tables; what fits the budget without them runs alone
+    if (c->engine == PP_ENGINE_SPARSE && !c->plan_frame)
+        r->foot = std::max(r->foot, std::min(r->foot + table_bytes(c->sb.cap2), budget));
     return PP_OK;
 }
 
