@@ -1856,38 +1856,20 @@ pp_status pp_get_terms(pp_circuit *c, void *stream, int64_t capacity, uint64_t *
         sz = c->sb.z;
         sc = c->sb.c;
         if (!c->frame_ran && c->list_raw && count > 0) {
-            // the list of the last pass, sorted into canonical order in a copy
-            tmp.cap2 = count;
-            tmp.max_tiles = (count + 2047) / 2048;
-            bool ok = true;
-            for (int i = 0; i < 6 && ok; ++i)
-                ok = dev_alloc(&tmp_base[i], (size_t)count * ((i % 3) == 2 ? c->dbytes : 8)) == hipSuccess;
-            ok = ok && dalloc(&tmp.count, 8) == hipSuccess;
-            ok = ok && dalloc(&tmp.scan, 256) == hipSuccess;
-            ok = ok && dalloc(&tmp.hist, (size_t)pp::sort_hist_entries(count)) == hipSuccess;
-            ok = ok && dalloc(&tmp.tile_flags, (size_t)tmp.max_tiles) == hipSuccess;
-            if (ok) {
-                tmp.x = (uint64_t *)tmp_base[0];
-                tmp.z = (uint64_t *)tmp_base[1];
-                tmp.c = tmp_base[2];
-                tmp.x2 = (uint64_t *)tmp_base[3];
-                tmp.z2 = (uint64_t *)tmp_base[4];
-                tmp.c2 = tmp_base[5];
-                hipError_t e = hipMemcpyAsync(tmp.x, sx, sizeof(uint64_t) * count, hipMemcpyDeviceToDevice, s);
-                if (e == hipSuccess) e = hipMemcpyAsync(tmp.z, sz, sizeof(uint64_t) * count, hipMemcpyDeviceToDevice, s);
+            // the last pass's list, sorted into canonical order where it is (a
+            // captured evaluation leaves its list at these addresses)
+            const pp::SparseBuffers was = c->sb;
+            hipError_t e = pp::launch_sparse_merge(c->sb, c->n, c->dbytes, s);
+            if (e == hipSuccess && c->sb.x != was.x) {
+                e = hipMemcpyAsync(was.x, c->sb.x, sizeof(uint64_t) * count, hipMemcpyDeviceToDevice, s);
                 if (e == hipSuccess)
-                    e = hipMemcpyAsync(tmp.c, sc, (size_t)c->dbytes * count, hipMemcpyDeviceToDevice, s);
+                    e = hipMemcpyAsync(was.z, c->sb.z, sizeof(uint64_t) * count, hipMemcpyDeviceToDevice, s);
                 if (e == hipSuccess)
-                    e = hipMemcpyAsync(tmp.count, c->sb.count, 2 * sizeof(long long), hipMemcpyDeviceToDevice, s);
-                if (e == hipSuccess) e = pp::launch_sparse_merge(tmp, c->n, c->dbytes, s);
-                if (e == hipSuccess) e = hipStreamSynchronize(s);
-                if (e != hipSuccess) r = fail(PP_ERR_DEVICE, std::string("terms dump: ") + hipGetErrorString(e));
-            } else {
-                r = fail(PP_ERR_NOMEM, "terms dump scratch");
+                    e = hipMemcpyAsync(was.c, c->sb.c, (size_t)c->dbytes * count, hipMemcpyDeviceToDevice, s);
             }
-            sx = tmp.x;
-            sz = tmp.z;
-            sc = tmp.c;
+            c->sb = was;
+            if (e == hipSuccess) e = hipStreamSynchronize(s);
+            if (e != hipSuccess) r = fail(PP_ERR_DEVICE, std::string("terms dump: ") + hipGetErrorString(e));
         }
     } else {
         // compact present slots, then sort them into canonical order
