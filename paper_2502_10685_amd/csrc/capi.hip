@@ -1076,7 +1076,31 @@ pp_status check_ready(pp_circuit *c) {
     return PP_OK;
 }
 
+// What the first passes leave to dense_init: they begin the halves themselves
+// where both can (a half without passes cannot).
+struct DenseStart {
+    bool coef, state;
+};
+// Whether the circuit's tile passes run through launch_tile_chain: alone, and in
+// every launch it shares (circuits of more than kChainMaxN qubits have launches
+// of their own).
+bool runs_chained(const pp_circuit *c) {
+    return !c->track && pp::tile_pass_chained(c->dplan.k, c->n, pp::chain_tiles(c->dplan.k, c->n, c->plan_seg));
+}
+DenseStart dense_start(const pp_circuit *c) {
+    const bool meet = c->dplan.fwd_pass >= 0, chained = runs_chained(c);
+    DenseStart d{!(chained && c->start_c), meet && !(chained && c->start_r)};
+    d.coef = d.coef || d.state;  // one kernel begins both
+    return d;
+}
+
 void fill_plan_stats(pp_circuit *c) {
+    // tiled: compose, fill and scatter where the first passes do not begin the
+    // weights, the steps, readout, count of the strings (the tile kernels may
+    // change under a schedule)
+    if (c->engine == PP_ENGINE_DENSE && !c->dplan.resident)
+        c->st.launches = (int64_t)c->step.size() - 1 + (c->dplan.nmaps() > 0 ? 1 : 0) + (dense_start(c).coef ? 2 : 0) +
+                         1 + (c->track ? 1 : 0);
     if (c->st_gen == c->plan_gen) return;  // it walks the whole schedule
     c->st_gen = c->plan_gen;
     pp_stats &s = c->st;
@@ -1096,7 +1120,6 @@ void fill_plan_stats(pp_circuit *c) {
             s.launches = 1 + (P.nmaps() > 0 ? 1 : 0);
             s.bytes_per_eval = 0;
         } else {
-            s.launches = steps + 3 + (P.nmaps() > 0 ? 1 : 0) + (c->track ? 1 : 0);
             s.bytes_per_eval = per * (int64_t)P.passes.size();
         }
     } else {
@@ -1112,24 +1135,6 @@ void fill_plan_stats(pp_circuit *c) {
             s.launches = 2 + rot + 1 + 2;  // clear + enter, one per rotation, leave, readout
         s.bytes_per_eval = 0;  // known after the run (48 or 40 bytes per update)
     }
-}
-
-// What the first passes leave to dense_init: they begin the halves themselves
-// where both can (a half without passes cannot).
-struct DenseStart {
-    bool coef, state;
-};
-// Whether the circuit's tile passes run through launch_tile_chain: alone, and in
-// every launch it shares (circuits of more than kChainMaxN qubits have launches
-// of their own).
-bool runs_chained(const pp_circuit *c) {
-    return !c->track && pp::tile_pass_chained(c->dplan.k, c->n, pp::chain_tiles(c->dplan.k, c->n, c->plan_seg));
-}
-DenseStart dense_start(const pp_circuit *c) {
-    const bool meet = c->dplan.fwd_pass >= 0, chained = runs_chained(c);
-    DenseStart d{!(chained && c->start_c), meet && !(chained && c->start_r)};
-    d.coef = d.coef || d.state;  // one kernel begins both
-    return d;
 }
 
 // An evaluation that leaves its weights with the circuit was enqueued.

@@ -873,7 +873,6 @@ void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin, bool ends) {
                 ChainOp r{};
                 r.word = (uint32_t)(hi * (hi - 1) / 2 + lo) |
                          (((unsigned)(mlo >= 0) + 2 * (unsigned)(mhi >= 0)) << kChainKindShift);
-                r.word |= (4 * cx + ((r.word >> kChainKindShift) & 3u)) << kChainSelectShift;
                 r.map = (uint32_t)order.size();
                 if (mlo >= 0) take((uint32_t)mlo);
                 if (mhi >= 0) take((uint32_t)mhi);

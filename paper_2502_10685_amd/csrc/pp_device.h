@@ -42,9 +42,10 @@ constexpr unsigned kSkipBarrier = 0x8000u;
 // One record of an LDS-resident chain: an optional CX, then an optional 3x3
 // map on each digit of one digit pair a < b.  word: pair index b (b - 1) / 2 +
 // a in bits 0-7; 1 for a map on the lower digit + 2 for one on the higher in
-// bits 8-9; kChainNoBarrierBit; 4 x the CX (0 none, 1 control = lower digit, 2
-// control = higher) + bits 8-9 in bits 16-19; the sign flips of the CX.  map: the first of
-// its maps (lower digit first); a chain's maps are stored in record order.
+// bits 8-9; kChainNoBarrierBit; the sign flips of the CX in bits 29-31 (bit 29:
+// there is a CX; bit 30: its control is the lower digit; bit 31: the higher).
+// map: the first of its maps (lower digit first); a chain's maps are stored in
+// record order.
 // The 16 letters of a block, e = letter of a + 4 letter of b, are read at the
 // block's base XOR the words read[k] of e's set bits k and written at it XOR
 // write[k]: swizzled byte offsets, those of read being the letters' images
@@ -55,7 +56,6 @@ struct ChainOp {
 };
 static_assert(sizeof(ChainOp) == 48, "records are read as three 16-byte words");
 constexpr unsigned kChainKindShift = 8;
-constexpr unsigned kChainSelectShift = 16;
 // no workgroup barrier behind it: it and the next record avoid digit 5 of a
 // six-qubit circuit, so each wave stays in its quarter of the tile
 constexpr unsigned kChainNoBarrierBit = 12;
