@@ -96,49 +96,50 @@ void set_shape_maps(DOp &h, const DOp *members) {
 // commute).  Groups of two or more ops get a GROUP header.
 std::vector<DOp> group_ops(const std::vector<DOp> &in, int k) {
     std::vector<DOp> out;
+    out.reserve(in.size() + in.size() / 2);
     std::vector<char> used(in.size(), 0);
+    const unsigned all = (1u << k) - 1u;
     for (size_t i = 0; i < in.size(); ++i) {
         if (used[i]) continue;
         unsigned pair = op_digits(in[i]), skipped = 0;
-        std::vector<size_t> mem{i};
+        DOp mem[kMaxGroupOps];
+        int count = 1;
+        mem[0] = in[i];
         used[i] = 1;
-        for (size_t j = i + 1; j < in.size() && (int)mem.size() < kMaxGroupOps; ++j) {
+        for (size_t j = i + 1; j < in.size() && count < kMaxGroupOps; ++j) {
             if (used[j]) continue;
             const unsigned d = op_digits(in[j]);
             if (d & skipped) {
                 skipped |= d;
-                continue;
-            }
-            if (__builtin_popcount(pair | d) <= 2) {
+            } else if (__builtin_popcount(pair | d) <= 2) {
                 pair |= d;
-                mem.push_back(j);
+                mem[count++] = in[j];
                 used[j] = 1;
+                continue;
             } else {
                 skipped |= d;
             }
+            // nothing can join any more
+            if (!((__builtin_popcount(pair) == 2 ? pair : all) & ~skipped)) break;
         }
-        if (mem.size() > 1 && __builtin_popcount(pair) == 1) {
+        if (count > 1 && __builtin_popcount(pair) == 1) {
             if (k < 2) {  // a one-digit tile has no pair: keep the ops as they are
-                for (size_t j : mem) out.push_back(in[j]);
+                out.insert(out.end(), mem, mem + count);
                 continue;
             }
             pair |= 1u << (pair == 1u ? 1 : 0);  // any second digit completes the block
         }
-        if (mem.size() == 1) {
-            out.push_back(in[i]);
-            continue;
+        if (count > 1) {
+            DOp h{};
+            h.kind = DOP_GROUP;
+            h.a = (uint8_t)__builtin_ctz(pair);
+            h.b = (uint8_t)(31 - __builtin_clz(pair));
+            h.ngates = (uint8_t)count;
+            h.perm = (uint16_t)group_shape(mem, count, h.a);
+            set_shape_maps(h, mem);
+            out.push_back(h);
         }
-        DOp h{};
-        h.kind = DOP_GROUP;
-        h.a = (uint8_t)__builtin_ctz(pair);
-        h.b = (uint8_t)(31 - __builtin_clz(pair));
-        h.ngates = (uint8_t)mem.size();
-        std::vector<DOp> body;
-        for (size_t j : mem) body.push_back(in[j]);
-        h.perm = (uint16_t)group_shape(body.data(), (int)body.size(), h.a);
-        set_shape_maps(h, body.data());
-        out.push_back(h);
-        out.insert(out.end(), body.begin(), body.end());
+        out.insert(out.end(), mem, mem + count);
     }
     return out;
 }
@@ -287,12 +288,13 @@ void split_waves(std::vector<DOp> &ops, DensePass &ps) {
     }
 }
 
-// Marks the barriers of a 6-digit pass that its sweeps can skip.
-void tag_barriers(std::vector<DOp> &ops) {
-    for (DOp &d : ops)
-        if (d.kind != DOP_SEG) d.perm &= (uint16_t)~kSkipBarrier;
+// Marks the barriers of a 6-digit pass (ops [begin, end)) that its sweeps can
+// skip.
+void tag_barriers(std::vector<DOp> &ops, size_t begin, size_t end) {
+    for (size_t i = begin; i < end; ++i)
+        if (ops[i].kind != DOP_SEG) ops[i].perm &= (uint16_t)~kSkipBarrier;
     DOp *prev = nullptr;
-    for (size_t i = 0; i < ops.size();) {
+    for (size_t i = begin; i < end;) {
         DOp &d = ops[i];
         if (d.kind == DOP_SEG) {
             ++i;
@@ -311,100 +313,106 @@ void tag_barriers(std::vector<DOp> &ops) {
 // commutes with every unit before it comes first, and one that commutes with
 // every unit behind it last: those two are applied between registers and HBM,
 // where the 128-byte runs need digits 0 and 1 across the lanes.
-// One entry per piece of at most kTileUnits units.
-std::vector<std::vector<DOp>> chain_order(const std::vector<DOp> &in) {
-    std::vector<std::vector<DOp>> all;
+// Appends the ops to `ops`; ends receives the end of every piece of at most
+// kTileUnits units.
+struct ChainUnit {
+    int begin, count;  // its ops
+    unsigned digits;
+};
+void chain_order(const std::vector<DOp> &in, std::vector<DOp> &ops, std::vector<int> &ends) {
+    std::vector<DOp> body;
+    std::vector<ChainUnit> units;
+    body.reserve(in.size());
+    units.reserve(in.size());
+    auto open = [&] { units.push_back({(int)body.size(), 0, 0u}); };
+    auto add = [&](const DOp &m) {
+        body.push_back(m);
+        ChainUnit &u = units.back();
+        u.digits |= op_digits(m);
+        if (++u.count > 1) {  // two maps: the lower digit's first
+            DOp &a = body[body.size() - 2], &b = body.back();
+            if (a.kind == DOP_U1 && b.kind == DOP_U1 && b.a < a.a) std::swap(a, b);
+        }
+    };
     for (size_t i = 0; i < in.size();) {
+        open();
         if (in[i].kind != DOP_GROUP) {
-            all.push_back({in[i]});
-            ++i;
+            add(in[i++]);
             continue;
         }
-        const DOp head = in[i];
-        std::vector<DOp> cur;
-        int nlo = 0, nhi = 0;
-        auto flush = [&] {
-            if (cur.empty()) return;
-            std::stable_sort(cur.begin(), cur.end(), [&](const DOp &a, const DOp &b) {
-                return a.kind == DOP_U1 && b.kind == DOP_U1 && a.a < b.a;
-            });
-            all.push_back(cur);
-            cur.clear();
-            nlo = nhi = 0;
-        };
+        const DOp &head = in[i];
+        bool lo = false, hi = false;
         for (int j = 1; j <= head.ngates; ++j) {
-            const DOp &m = in[i + j];
-            if (m.kind == DOP_CX ? !cur.empty() : (m.a == head.a ? nlo : nhi) != 0) flush();
-            if (m.kind == DOP_U1) ++(m.a == head.a ? nlo : nhi);
-            cur.push_back(m);
+            const DOp &m = in[i + (size_t)j];
+            bool &seen = m.a == head.a ? lo : hi;
+            if (m.kind == DOP_CX ? units.back().count > 0 : seen) {
+                open();
+                lo = hi = false;
+            }
+            if (m.kind == DOP_U1) seen = true;
+            add(m);
         }
-        flush();
-        i += 1 + head.ngates;
+        i += 1 + (size_t)head.ngates;
     }
-    auto digits = [](const std::vector<DOp> &u) {
-        unsigned d = 0;
-        for (const DOp &m : u) d |= op_digits(m);
-        return d;
-    };
-    auto piece = [&](std::vector<std::vector<DOp>> units) {
+    for (size_t first = 0; first < units.size(); first += kTileUnits) {
+        ChainUnit *u = units.data() + first;
+        const size_t count = std::min(units.size() - first, (size_t)kTileUnits);
         unsigned seen = 0;
-        for (size_t i = 0; i < units.size(); ++i) {
-            const unsigned d = digits(units[i]);
-            if (!(d & 3u) && !(d & seen)) {
-                std::rotate(units.begin(), units.begin() + (long)i, units.begin() + (long)i + 1);
+        for (size_t i = 0; i < count; ++i) {
+            if (!(u[i].digits & (3u | seen))) {
+                std::rotate(u, u + i, u + i + 1);
                 break;
             }
-            seen |= d;
+            seen |= u[i].digits;
         }
         seen = 0;
-        for (size_t i = units.size(); i-- > 1;) {  // never the first again
-            const unsigned d = digits(units[i]);
-            if (!(d & 3u) && !(d & seen)) {
-                std::rotate(units.begin() + (long)i, units.begin() + (long)i + 1, units.end());
+        for (size_t i = count; i-- > 1;) {  // never the first again
+            if (!(u[i].digits & (3u | seen))) {
+                std::rotate(u + i, u + i + 1, u + count);
                 break;
             }
-            seen |= d;
+            seen |= u[i].digits;
         }
-        std::vector<DOp> out;
-        for (const auto &u : units) {
-            if (u.size() > 1) {
-                const unsigned d = digits(u);
+        for (size_t i = 0; i < count; ++i) {
+            const DOp *m = body.data() + u[i].begin;
+            if (u[i].count > 1) {
                 DOp h{};
                 h.kind = DOP_GROUP;
-                h.a = (uint8_t)__builtin_ctz(d);
-                h.b = (uint8_t)(31 - __builtin_clz(d));
-                h.ngates = (uint8_t)u.size();
-                h.perm = (uint16_t)group_shape(u.data(), (int)u.size(), h.a);
-                set_shape_maps(h, u.data());
-                out.push_back(h);
+                h.a = (uint8_t)__builtin_ctz(u[i].digits);
+                h.b = (uint8_t)(31 - __builtin_clz(u[i].digits));
+                h.ngates = (uint8_t)u[i].count;
+                h.perm = (uint16_t)group_shape(m, u[i].count, h.a);
+                set_shape_maps(h, m);
+                ops.push_back(h);
             }
-            out.insert(out.end(), u.begin(), u.end());
+            ops.insert(ops.end(), m, m + u[i].count);
         }
-        return out;
-    };
-    std::vector<std::vector<DOp>> pieces;
-    for (size_t u = 0; u < all.size(); u += kTileUnits)
-        pieces.push_back(piece({all.begin() + (long)u,
-                                all.begin() + (long)std::min(all.size(), u + (size_t)kTileUnits)}));
-    return pieces;
+        ends.push_back((int)ops.size());
+    }
 }
 
 void group_all(DensePlan &P, bool segments, bool chain) {
     std::vector<DOp> ops;
     std::vector<DensePass> passes;
+    std::vector<int> ends;
+    ops.reserve(2 * P.ops.size());
     for (DensePass &ps : P.passes) {
         const std::vector<DOp> in(P.ops.begin() + ps.op_begin, P.ops.begin() + ps.op_end);
         std::vector<DOp> out =
             (segments && !P.resident && ps.k == kSegTileDigits) ? segment_ops(in, ps.k) : group_ops(in, ps.k);
         if (!P.resident && ps.k == 6) split_waves(out, ps);
-        std::vector<std::vector<DOp>> pieces;
-        if (!P.resident && chain && !out.empty()) pieces = chain_order(out);
-        else pieces.push_back(std::move(out));
-        for (auto &piece : pieces) {
-            if (!P.resident && ps.k == 6) tag_barriers(piece);
-            ps.op_begin = (int)ops.size();
-            ops.insert(ops.end(), piece.begin(), piece.end());
-            ps.op_end = (int)ops.size();
+        int begin = (int)ops.size();
+        ends.clear();
+        if (!P.resident && chain && !out.empty()) {
+            chain_order(out, ops, ends);
+        } else {
+            ops.insert(ops.end(), out.begin(), out.end());
+            ends.push_back((int)ops.size());
+        }
+        for (int end : ends) {
+            if (!P.resident && ps.k == 6) tag_barriers(ops, (size_t)begin, (size_t)end);
+            ps.op_begin = begin;
+            ps.op_end = begin = end;
             passes.push_back(ps);
             ps.ngates = 0;  // counted in the first piece
         }
@@ -435,61 +443,80 @@ static DensePlan plan_dense_core(const GateList &g, int k, int low, const PlanOp
     // position h in processing order <-> gate index
     auto gate_of = [&](int64_t h) { return o.forward ? gb + h : ge - 1 - h; };
 
+    // Ops of the gates at positions `sched`, in that order, on digits local[q];
+    // composed maps have their gates' recipes in one piece.
+    std::vector<int32_t> map_of, open, at;
+    auto emit_ops = [&](const std::vector<int64_t> &sched, const int *local, int digits) {
+        const int map_base = P.nmaps();
+        int maps = 0;
+        map_of.assign(sched.size(), -1);
+        open.assign((size_t)digits, -1);
+        at.clear();  // gates per map, then where its next one goes
+        for (size_t i = 0; i < sched.size(); ++i) {
+            const int64_t gi = gate_of(sched[i]);
+            const uint8_t op = g.op[(size_t)gi];
+            DOp d{};
+            d.ngates = 1;
+            if (op == 2) {
+                d.kind = DOP_CX;
+                d.a = (uint8_t)local[g.q0[(size_t)gi]];
+                d.b = (uint8_t)local[g.q1[(size_t)gi]];
+                open[d.a] = -1;
+                open[d.b] = -1;
+                P.ops.push_back(d);
+                continue;
+            }
+            const int dg = local[g.q0[(size_t)gi]];
+            const bool rot = op >= 3;
+            if (compose && open[(size_t)dg] >= 0 && P.ops[(size_t)open[(size_t)dg]].ngates < 255) {
+                DOp &u = P.ops[(size_t)open[(size_t)dg]];
+                u.ngates++;
+                u.smask = (uint16_t)smask_compose(gate_smask(op), u.smask);
+                if (rot) u.perm = 0;
+                map_of[i] = (int32_t)u.map - map_base;
+            } else {
+                d.kind = DOP_U1;
+                d.a = (uint8_t)dg;
+                d.smask = (uint16_t)gate_smask(op);
+                d.perm = rot ? 0 : 1;
+                d.map = (uint32_t)(map_base + maps);
+                map_of[i] = maps++;
+                at.push_back(0);
+                open[(size_t)dg] = (int32_t)P.ops.size();
+                P.ops.push_back(d);
+            }
+            ++at[(size_t)map_of[i]];
+        }
+        int32_t end = (int32_t)P.rop.size();
+        for (int32_t &a : at) {
+            const int32_t count = a;
+            a = end;
+            end += count;
+            P.roff.push_back(end);
+        }
+        P.rop.resize((size_t)end);
+        P.rparam.resize((size_t)end);
+        P.rgate.resize((size_t)end);
+        for (size_t i = 0; i < sched.size(); ++i) {
+            if (map_of[i] < 0) continue;
+            const int64_t gi = gate_of(sched[i]);
+            const size_t r = (size_t)at[(size_t)map_of[i]]++;
+            P.rop[r] = g.op[(size_t)gi];
+            P.rparam[r] = g.op[(size_t)gi] >= 3 ? g.param[(size_t)gi] : -1;
+            P.rgate[r] = (int32_t)gi;
+        }
+    };
+
+    std::vector<int64_t> sched;
     if (P.resident) {
         DensePass pass;
         pass.k = n;
         for (int j = 0; j < n && j < 8; ++j) pass.qubit[j] = (uint8_t)j;
-        // Composition needs each map's recipe to be contiguous; gates on
-        // other wires in between would interleave recipes.  Collect, per op,
-        // its gates first, then emit recipes in op order.
-        struct Pending { int digit; std::vector<std::pair<uint8_t, int32_t>> gates; };
-        std::vector<Pending> pend;
-        std::vector<int> open(n, -1);
-        std::vector<DOp> ops;
-        for (int64_t h = 0; h < m; ++h) {
-            const int64_t gi = gate_of(h);
-            const uint8_t op = g.op[gi];
-            if (op == 2) {
-                DOp d{};
-                d.kind = DOP_CX;
-                d.a = (uint8_t)g.q0[gi];
-                d.b = (uint8_t)g.q1[gi];
-                d.ngates = 1;
-                open[g.q0[gi]] = -1;
-                open[g.q1[gi]] = -1;
-                ops.push_back(d);
-                continue;
-            }
-            const int q = g.q0[gi];
-            const bool rot = op >= 3;
-            if (compose && open[q] >= 0 && ops[open[q]].ngates < 255) {
-                DOp &d = ops[open[q]];
-                d.ngates++;
-                d.smask = (uint16_t)smask_compose(gate_smask(op), d.smask);
-                if (rot) d.perm = 0;
-                pend[d.map].gates.push_back({op, (int32_t)gi});
-            } else {
-                DOp d{};
-                d.kind = DOP_U1;
-                d.a = (uint8_t)q;
-                d.ngates = 1;
-                d.smask = (uint16_t)gate_smask(op);
-                d.perm = rot ? 0 : 1;
-                d.map = (uint32_t)pend.size();
-                pend.push_back({q, {{op, (int32_t)gi}}});
-                open[q] = (int)ops.size();
-                ops.push_back(d);
-            }
-        }
-        for (auto &pd : pend) {
-            for (auto &e : pd.gates) {
-                P.rop.push_back(e.first);
-                P.rparam.push_back(e.first >= 3 ? g.param[(size_t)e.second] : -1);
-                P.rgate.push_back(e.second);
-            }
-            P.roff.push_back((int32_t)P.rop.size());
-        }
-        P.ops = std::move(ops);
+        int local[32];
+        for (int q = 0; q < n; ++q) local[q] = q;
+        sched.resize((size_t)m);
+        for (int64_t h = 0; h < m; ++h) sched[(size_t)h] = h;
+        emit_ops(sched, local, n);
         pass.op_begin = 0;
         pass.op_end = (int)P.ops.size();
         pass.ngates = m;
@@ -498,89 +525,129 @@ static DensePlan plan_dense_core(const GateList &g, int k, int low, const PlanOp
     }
 
     // ---- tiled passes
-    std::vector<std::vector<int64_t>> wq(n);
-    for (int64_t h = 0; h < m; ++h) {
-        const int64_t gi = gate_of(h);
-        wq[g.q0[gi]].push_back(h);
-        if (g.op[gi] == 2) wq[g.q1[gi]].push_back(h);
-    }
-    std::vector<size_t> head(n, 0);
+    // A wire's gates in processing order, as runs of single-qubit gates with a
+    // CX (or the end) behind each.
+    struct Run {
+        int32_t begin, end;     // in one[q]
+        int32_t partner = -1;   // the CX behind it: the other wire, that wire's
+        int32_t prun = 0;       // run before it, and its position
+        int64_t cx = 0;
+    };
+    std::vector<std::vector<Run>> runs((size_t)n);
+    std::vector<std::vector<int64_t>> one((size_t)n);  // positions of the single-qubit gates
+    for (int q = 0; q < n; ++q) runs[(size_t)q].push_back({0, 0});
     auto wires = [&](int64_t h) -> uint32_t {
         const int64_t gi = gate_of(h);
-        uint32_t w = 1u << g.q0[gi];
-        if (g.op[gi] == 2) w |= 1u << g.q1[gi];
+        uint32_t w = 1u << g.q0[(size_t)gi];
+        if (g.op[(size_t)gi] == 2) w |= 1u << g.q1[(size_t)gi];
         return w;
     };
-    auto ready = [&](int64_t h) {
-        uint32_t w = wires(h);
-        for (int q = 0; q < n; ++q)
-            if ((w >> q) & 1u)
-                if (head[q] >= wq[q].size() || wq[q][head[q]] != h) return false;
-        return true;
+    for (int64_t h = 0; reorder && h < m; ++h) {
+        const int64_t gi = gate_of(h);
+        const int32_t a = g.q0[(size_t)gi];
+        std::vector<Run> &ra = runs[(size_t)a];
+        if (g.op[(size_t)gi] != 2) {
+            one[(size_t)a].push_back(h);
+            ++ra.back().end;
+            continue;
+        }
+        const int32_t b = g.q1[(size_t)gi];
+        std::vector<Run> &rb = runs[(size_t)b];
+        const int32_t ia = (int32_t)ra.size() - 1, ib = (int32_t)rb.size() - 1;
+        ra.back().partner = b;
+        ra.back().prun = ib;
+        rb.back().partner = a;
+        rb.back().prun = ia;
+        ra.back().cx = rb.back().cx = h;
+        ra.push_back({(int32_t)one[(size_t)a].size(), (int32_t)one[(size_t)a].size()});
+        rb.push_back({(int32_t)one[(size_t)b].size(), (int32_t)one[(size_t)b].size()});
+    }
+    // How far each wire is: its run, and whether that run's gates are taken.
+    struct Heads {
+        int32_t run[32];
+        uint32_t taken;
+    };
+    Heads head{};
+    const Run *wire[32];
+    for (int q = 0; q < n; ++q) wire[q] = runs[(size_t)q].data();
+    auto at_cx = [&](const Heads &hd, int q) {
+        const Run &r = wire[q][hd.run[q]];
+        return ((hd.taken >> q) & 1u) || r.begin == r.end;
     };
     const uint32_t lowmask = low >= 32 ? 0xffffffffu : ((1u << std::min(low, n)) - 1u);
-    // Schedules, on the head positions hd, every gate whose wires lie in S2
-    // and that is next on all of them, until none is; returns their number.
-    auto absorb = [&](uint32_t S2, std::vector<size_t> &hd) -> int64_t {
-        auto next_on_all = [&](int64_t x) {
-            const uint32_t w = wires(x);
-            for (int r = 0; r < n; ++r)
-                if (((w >> r) & 1u) && (hd[r] >= wq[r].size() || wq[r][hd[r]] != x)) return false;
-            return true;
-        };
+    // Takes every gate whose wires lie in S2 and that is next on all of them,
+    // until none is; returns their number.  take_run and take_cx are told of
+    // them in order.
+    auto absorb = [&](uint32_t S2, Heads &hd, auto take_run, auto take_cx) -> int64_t {
         int64_t got = 0;
         for (bool prog = true; prog;) {
             prog = false;
-            for (int r = 0; r < n; ++r) {
-                if (!((S2 >> r) & 1u)) continue;
-                while (hd[r] < wq[r].size()) {
-                    const int64_t x = wq[r][hd[r]];
-                    const uint32_t w = wires(x);
-                    if ((w & ~S2) || !next_on_all(x)) break;
-                    for (int t = 0; t < n; ++t)
-                        if ((w >> t) & 1u) hd[t]++;
+            for (uint32_t left = S2; left; left &= left - 1u) {
+                const int q = __builtin_ctz(left);
+                for (;;) {
+                    const Run &r = wire[q][hd.run[q]];
+                    if (!at_cx(hd, q)) {
+                        take_run(q, r);
+                        got += r.end - r.begin;
+                        hd.taken |= 1u << q;
+                    }
+                    const int t = r.partner;
+                    if (t < 0 || !((S2 >> t) & 1u) || hd.run[t] != r.prun || !at_cx(hd, t)) break;
+                    take_cx(r.cx);
                     ++got;
+                    hd.run[q]++;
+                    hd.run[t]++;
+                    hd.taken &= ~((1u << q) | (1u << t));
                     prog = true;
                 }
             }
         }
         return got;
     };
+    auto count = [&](uint32_t S2, Heads &hd) {
+        return absorb(S2, hd, [](int, const Run &) {}, [](int64_t) {});
+    };
+    // Wires of the gate next on wire q if it is next on all of them (0: none);
+    // a CX is found on its lower wire.
+    auto next_wires = [&](const Heads &hd, int q) -> uint32_t {
+        const Run &r = wire[q][hd.run[q]];
+        if (!at_cx(hd, q)) return 1u << q;
+        const int t = r.partner;
+        if (t < q || hd.run[t] != r.prun || !at_cx(hd, t)) return 0u;
+        return (1u << q) | (1u << t);
+    };
     // Gates a pass would take if its qubit set started as S0 and were then
     // completed to k qubits greedily, each step adding the wires of the
     // ready gate after which the most gates become schedulable.
     auto rollout = [&](uint32_t S0) -> int64_t {
-        std::vector<size_t> hd(head), h2;
+        Heads hd = head, h2, best;
         uint32_t S2 = S0;
-        int64_t total = absorb(S2, hd);
+        int64_t total = count(S2, hd);
         while (__builtin_popcount(S2) < k) {
             int64_t bg = -1;
             uint32_t bw = 0;
             for (int q = 0; q < n; ++q) {
-                if (hd[q] >= wq[q].size()) continue;
-                const int64_t x = wq[q][hd[q]];
-                const uint32_t w = wires(x);
-                bool nxt = true;
-                for (int t = 0; t < n; ++t)
-                    if (((w >> t) & 1u) && (hd[t] >= wq[t].size() || wq[t][hd[t]] != x)) nxt = false;
-                if (!nxt || __builtin_popcount(S2 | w) > k) continue;
+                const uint32_t w = next_wires(hd, q);
+                if (!w || __builtin_popcount(S2 | w) > k) continue;
                 h2 = hd;
-                const int64_t gg = absorb(S2 | w, h2);
+                const int64_t gg = count(S2 | w, h2);
                 if (gg > bg) {
                     bg = gg;
                     bw = w;
+                    best = h2;
                 }
             }
             if (bg < 0) break;
             S2 |= bw;
-            total += absorb(S2, hd);
+            total += bg;
+            hd = best;
         }
         return total;
     };
     int64_t remaining = m;
     while (remaining > 0) {
         uint32_t S = lowmask;
-        std::vector<int64_t> sched;
+        sched.clear();
         if (!reorder) {
             // keep the Heisenberg gate order: a pass is a maximal run of
             // consecutive gates whose qubits fit in k
@@ -592,23 +659,12 @@ static DensePlan plan_dense_core(const GateList &g, int k, int low, const PlanOp
             }
         }
         for (; reorder;) {
-            bool progress = true;
-            while (progress) {
-                progress = false;
-                for (int q = 0; q < n; ++q) {
-                    if (!((S >> q) & 1u)) continue;
-                    while (head[q] < wq[q].size()) {
-                        const int64_t h = wq[q][head[q]];
-                        const uint32_t w = wires(h);
-                        if ((w & ~S) || !ready(h)) break;
-                        for (int r = 0; r < n; ++r)
-                            if ((w >> r) & 1u) head[r]++;
-                        sched.push_back(h);
-                        --remaining;
-                        progress = true;
-                    }
-                }
-            }
+            remaining -= absorb(
+                S, head,
+                [&](int q, const Run &r) {
+                    sched.insert(sched.end(), one[(size_t)q].begin() + r.begin, one[(size_t)q].begin() + r.end);
+                },
+                [&](int64_t h) { sched.push_back(h); });
             if (__builtin_popcount(S) >= k) break;
             // grow the tile by the wires of one ready gate: the one whose
             // greedy completion of the tile schedules the most gates
@@ -617,11 +673,11 @@ static DensePlan plan_dense_core(const GateList &g, int k, int low, const PlanOp
             // into the 6-qubit tiles of random circuits.
             int64_t best = -1, best_gain = -1;
             for (int q = 0; q < n; ++q) {
-                if (head[q] >= wq[q].size()) continue;
-                const int64_t h = wq[q][head[q]];
-                if (!ready(h)) continue;
-                if (__builtin_popcount(S | wires(h)) > k) continue;
-                const int64_t gain = o.lookahead ? rollout(S | wires(h)) : 0;
+                const uint32_t w = next_wires(head, q);
+                if (!w || __builtin_popcount(S | w) > k) continue;
+                const Run &r = wire[q][head.run[q]];
+                const int64_t h = at_cx(head, q) ? r.cx : one[(size_t)q][(size_t)r.begin];
+                const int64_t gain = o.lookahead ? rollout(S | w) : 0;
                 if (gain > best_gain || (gain == best_gain && h < best)) {
                     best = h;
                     best_gain = gain;
@@ -643,54 +699,7 @@ static DensePlan plan_dense_core(const GateList &g, int k, int low, const PlanOp
                 local[q] = j++;
             }
         pass.op_begin = (int)P.ops.size();
-        // per-pass composition with contiguous recipes (see resident case)
-        struct Pending { std::vector<std::pair<uint8_t, int32_t>> gates; };
-        std::vector<Pending> pend;
-        std::vector<int> open(k, -1);
-        const int map_base = P.nmaps();
-        for (int64_t h : sched) {
-            const int64_t gi = gate_of(h);
-            const uint8_t op = g.op[gi];
-            if (op == 2) {
-                DOp d{};
-                d.kind = DOP_CX;
-                d.a = (uint8_t)local[g.q0[gi]];
-                d.b = (uint8_t)local[g.q1[gi]];
-                d.ngates = 1;
-                open[d.a] = -1;
-                open[d.b] = -1;
-                P.ops.push_back(d);
-                continue;
-            }
-            const int dg = local[g.q0[gi]];
-            const bool rot = op >= 3;
-            if (compose && open[dg] >= 0 && P.ops[open[dg]].ngates < 255) {
-                DOp &d = P.ops[open[dg]];
-                d.ngates++;
-                d.smask = (uint16_t)smask_compose(gate_smask(op), d.smask);
-                if (rot) d.perm = 0;
-                pend[d.map - map_base].gates.push_back({op, (int32_t)gi});
-            } else {
-                DOp d{};
-                d.kind = DOP_U1;
-                d.a = (uint8_t)dg;
-                d.ngates = 1;
-                d.smask = (uint16_t)gate_smask(op);
-                d.perm = rot ? 0 : 1;
-                d.map = (uint32_t)(map_base + pend.size());
-                pend.push_back({{{op, (int32_t)gi}}});
-                open[dg] = (int)P.ops.size();
-                P.ops.push_back(d);
-            }
-        }
-        for (auto &pd : pend) {
-            for (auto &e : pd.gates) {
-                P.rop.push_back(e.first);
-                P.rparam.push_back(e.first >= 3 ? g.param[(size_t)e.second] : -1);
-                P.rgate.push_back(e.second);
-            }
-            P.roff.push_back((int32_t)P.rop.size());
-        }
+        emit_ops(sched, local, k);
         pass.op_end = (int)P.ops.size();
         pass.ngates = (int64_t)sched.size();
         P.passes.push_back(pass);
@@ -923,6 +932,7 @@ void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin, bool ends) {
     roff.reserve(P.roff.size());
     rop.reserve(P.rop.size());
     rparam.reserve(P.rparam.size());
+    rgate.reserve(P.rgate.size());
     for (int old : order) {
         rop.insert(rop.end(), P.rop.begin() + P.roff[(size_t)old], P.rop.begin() + P.roff[(size_t)old + 1]);
         rparam.insert(rparam.end(), P.rparam.begin() + P.roff[(size_t)old], P.rparam.begin() + P.roff[(size_t)old + 1]);
