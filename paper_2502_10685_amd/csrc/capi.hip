@@ -934,20 +934,20 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
             o.segments = seg;
             o.chain = pp::chain_tiles(k, c->n, seg);
             c->dplan = k == c->n || meets(c, k)
-                           ? pp::plan_meet(c->g, k, kLowQubits, c->ramp_gate, seg, c->dbytes, &c->pass_recs)
+                           ? pp::plan_meet(c->g, k, kLowQubits, c->ramp_gate, seg, &c->pass_recs)
                            : pp::plan_dense_opts(c->g, k, kLowQubits, o);
         } else if ((k == c->n && !c->track && !c->keep_coef) || meets(c, k)) {
-            c->dplan = pp::plan_meet(c->g, k, kLowQubits, c->g.m, seg, c->dbytes, &c->pass_recs);
+            c->dplan = pp::plan_meet(c->g, k, kLowQubits, c->g.m, seg, &c->pass_recs);
         } else {
             pp::PlanOptions o;
             o.compose = o.group = o.reorder = c->track == 0;
             o.segments = seg;
             o.chain = pp::chain_tiles(k, c->n, seg);
             c->dplan = pp::plan_dense_opts(c->g, k, kLowQubits, o);
-            if (k == c->n && !c->track) pp::build_chain(c->dplan, c->dbytes);
+            if (k == c->n && !c->track) pp::build_chain(c->dplan);
         }
         if (k < c->n && pp::chain_tiles(k, c->n, seg) && !c->track && c->dplan.fwd_from < 0)
-            pp::build_chain(c->dplan, c->dbytes, &c->pass_recs);
+            pp::build_chain(c->dplan, &c->pass_recs);
         const pp::DensePlan &P = c->dplan;
         {
             // the kernels trust the schedule's digits and segment bounds

@@ -555,6 +555,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(BLOCK >= 
 // pass's k qubits with the other n-k digits fixed to the tile index.  Local
 // digit j is global qubit qubit[j] (ascending), so the leading local digits
 // that equal their qubit form contiguous runs in HBM.
+//
+// A weight in LDS: untracked tiles of 6 and 7 digits hold doubles in FP32 runs
+// too, like the record chains, whose bits these passes give.
+template <typename T, bool TRACK, int K>
+using TileWeight = std::conditional_t<!TRACK && K >= 6, double, T>;
+
 template <typename T, bool TRACK, int K, int BLOCK>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((BLOCK == 64 && K >= 6) ? 1 : (K >= 7 ? 2 : 4)))) void tile_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) {
     extern __shared__ __align__(256) unsigned char smem[];
@@ -569,8 +575,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((BLOCK ==
     constexpr int k = K;
     const int n = d.n;
     constexpr int size = 1 << (2 * K);
-    T *lc = reinterpret_cast<T *>(smem);
-    uint8_t *lp = smem + (size_t)size * sizeof(T);
+    using L = TileWeight<T, TRACK, K>;
+    L *lc = reinterpret_cast<L *>(smem);
+    uint8_t *lp = smem + (size_t)size * sizeof(L);
     const int tid = threadIdx.x;
 
     unsigned inmask = 0;
@@ -597,7 +604,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((BLOCK ==
     for (int i = tid, r = 0; i < size; i += BLOCK, ++r) {
         const long long gi = toff | deposit_digits(r * BLOCK, d.qubits, 0, k);
         const int li = stid ^ sw(r * BLOCK);
-        lc[li] = g[gi];
+        lc[li] = (L)g[gi];
         if (TRACK) lp[li] = d.pres[gi];
     }
     lds_barrier();
@@ -608,12 +615,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((BLOCK ==
         for (int i = tid; i < size; i += BLOCK) mine += lp[i];
         tcount = block_sum_i<BLOCK>(mine, redi);
     }
-    run_ops<T, TRACK, K, BLOCK>(lc, lp, d.ops, d.maps, d.op_begin, d.op_end, tcount, updates, redi, &oc);
+    run_ops<L, TRACK, K, BLOCK>(lc, lp, d.ops, d.maps, d.op_begin, d.op_end, tcount, updates, redi, &oc);
 
     for (int i = tid, r = 0; i < size; i += BLOCK, ++r) {
         const long long gi = toff | deposit_digits(r * BLOCK, d.qubits, 0, k);
         const int li = stid ^ sw(r * BLOCK);
-        g[gi] = lc[li];
+        g[gi] = (T)lc[li];
         if (TRACK) d.pres[gi] = lp[li];
     }
     if (TRACK && tid == 0 && updates) atomicAdd(d.counters, (unsigned long long)updates);
@@ -1608,8 +1615,10 @@ int max_lds_bytes() {
     return v;
 }
 
+// of a tile of tracked or untracked runs, or a whole tracked circuit
 size_t resident_lds_bytes(int n, int dtype_bytes, bool track) {
     const size_t size = (size_t)1 << (2 * n);
+    if (!track && n >= 6) dtype_bytes = 8;  // see TileWeight
     return size * (size_t)dtype_bytes + (track ? size : 0);
 }
 

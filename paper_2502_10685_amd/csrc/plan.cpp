@@ -833,7 +833,7 @@ void plan_append(DensePlan &all, const DensePlan &part) {
     all.resident = part.resident;
 }
 
-void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin, bool ends) {
+void build_chain(DensePlan &P, std::vector<int> *begin, bool ends) {
     const bool tiled = !P.resident && ends;
     std::vector<int> order;  // new map index -> old
     std::vector<uint32_t> renum((size_t)P.nmaps(), 0);
@@ -853,7 +853,7 @@ void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin, bool ends) {
             r.word = (uint32_t)(b * (b - 1) / 2 + a);
             r.map = (uint32_t)order.size();
             for (int k = 0; k < 4; ++k)
-                r.read[k] = r.write[k] = (uint32_t)sw((1 + k % 2) << (2 * (k < 2 ? a : b))) * (uint32_t)dbytes;
+                r.read[k] = r.write[k] = (uint32_t)sw((1 + k % 2) << (2 * (k < 2 ? a : b))) * (uint32_t)sizeof(double);
             return r;
         };
         bool ends_high = false;  // the last unit's pair avoids digits 0 and 1
@@ -889,7 +889,7 @@ void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin, bool ends) {
                 // conjugation is (x_c, z_c ^ z_t, x_t ^ x_c, z_t), its own
                 // inverse, with the sign of (X, Z) <-> -(Y, Y)
                 for (int k = 0; k < 4; ++k)
-                    r.read[k] = r.write[k] = (uint32_t)sw((1 + k % 2) << (2 * (k < 2 ? lo : hi))) * (uint32_t)dbytes;
+                    r.read[k] = r.write[k] = (uint32_t)sw((1 + k % 2) << (2 * (k < 2 ? lo : hi))) * (uint32_t)sizeof(double);
                 if (cx) {
                     const int c = cx == 1 ? 0 : 2, t = 2 - c;
                     r.read[c] ^= r.write[t];
@@ -966,8 +966,7 @@ void record_offsets(const ChainOp &r, const DensePass &ps, int dbytes, bool afte
     }
 }
 
-DensePlan plan_meet(const GateList &g, int k, int low, int64_t g_end, bool segments, int dbytes,
-                    std::vector<int> *rec) {
+DensePlan plan_meet(const GateList &g, int k, int low, int64_t g_end, bool segments, std::vector<int> *rec) {
     int64_t ncx = 0;
     for (int64_t i = 0; i < g_end; ++i) ncx += g.op[(size_t)i] == 2;
     int64_t s = ncx ? 0 : g_end / 2;
@@ -980,14 +979,14 @@ DensePlan plan_meet(const GateList &g, int k, int low, int64_t g_end, bool segme
     o.segments = segments;
     o.chain = chains;
     DensePlan P = plan_dense_opts(g, k, low, o);
-    if (chains) build_chain(P, dbytes, &hrec);
+    if (chains) build_chain(P, &hrec);
     PlanOptions f;
     f.g_end = s;
     f.forward = true;
     f.segments = segments;
     f.chain = chains;
     DensePlan F = plan_dense_opts(g, k, low, f);
-    if (chains) build_chain(F, dbytes, &frec);
+    if (chains) build_chain(F, &frec);
     const int base = P.nmaps();
     const size_t hpass = P.passes.size();
     plan_append(P, F);
@@ -1074,9 +1073,9 @@ GradPlan plan_gradient(const GateList &g, int k_heis, int k_fwd, int low, int64_
     G.heis_pass_begin.push_back((int)G.heis.passes.size());
     G.fwd_pass_begin.push_back((int)G.fwd.passes.size());
     G.fwd_map_begin.push_back(G.fwd.nmaps());
-    build_chain(G.fwd, 8, &G.fwd_chain_begin, false);
+    build_chain(G.fwd, &G.fwd_chain_begin, false);
     for (size_t r = 0; r < G.fwd.rgate.size(); ++r) G.rslot.push_back(slot[(size_t)G.fwd.rgate[r]]);
-    if (G.heis.resident || chain_tiles(k_heis, g.n, segments)) build_chain(G.heis, 8, &G.heis_chain_begin);
+    if (G.heis.resident || chain_tiles(k_heis, g.n, segments)) build_chain(G.heis, &G.heis_chain_begin);
     return G;
 }
 

@@ -140,20 +140,20 @@ struct GradPlan {
 };
 // Renumbers the maps of grouped passes (resident, or over tiles) in op order
 // and appends each pass's records to P.chain; begin[p] (optional) receives the
-// first record of pass p, with the total behind the last.  dbytes: size of a
-// weight.  ends: a tiled pass begins and ends with records whose pairs avoid
+// first record of pass p, with the total behind the last.  The records' words
+// are for tiles of doubles.  ends: a tiled pass begins and ends with records whose pairs avoid
 // digits 0 and 1 (without a CX or map where the schedule has no such op
 // there), and has at least two.
-void build_chain(DensePlan &P, int dbytes, std::vector<int> *begin = nullptr, bool ends = true);
-// Byte offsets, in the 4^n array, of the letters of record r's pair: as it
-// reads them (after = false) or writes them.
+void build_chain(DensePlan &P, std::vector<int> *begin = nullptr, bool ends = true);
+// Byte offsets, in the 4^n array (weights of dbytes), of the letters of record
+// r's pair: as it reads them (after = false) or writes them.
 void record_offsets(const ChainOp &r, const DensePass &ps, int dbytes, bool after, uint32_t out[4]);
 // Untracked evaluation from both ends: gates [s, g_end) taken back from the
 // observable, gates [0, s) forward from the state, with s where half of the
 // CX gates lie on either side (a record holds about one).  k = n: one pass
 // of both halves' chains; k < n: tile passes, the forward half's from fwd_pass
 // on; rec receives the first record of each pass over 7-qubit tiles.
-DensePlan plan_meet(const GateList &g, int k, int low, int64_t g_end, bool segments, int dbytes,
+DensePlan plan_meet(const GateList &g, int k, int low, int64_t g_end, bool segments,
                     std::vector<int> *rec = nullptr);
 // The forward half of a tiled meet plan run backwards, as the Heisenberg
 // schedule of the same gates: its passes and ops in reverse order (no GROUP or

@@ -1,5 +1,9 @@
 // LDS-resident circuits (n <= 7, untracked): one workgroup holds all 4^n
-// weights in LDS and runs a chain of sweeps over digit pairs.
+// weights in LDS and runs a chain of sweeps over digit pairs.  They are doubles
+// there for FP32 circuits too, rounded where they leave the chip: a sweep ends
+// with every record, and rounding each time left the density matrices of 2
+// qubits 1.9 times and random circuits of 3 to 6 qubits 1.05 to 1.13 times as
+// far off as whole groups of gates between roundings.
 //
 // What bounds it: the chain.  A circuit's sweeps depend on each other, one
 // circuit occupies one or two CUs, and a lone wave issues at most one
@@ -52,7 +56,7 @@ struct ChainShape {
     // dynamic LDS: the tiles first (their addresses are XORed, so they are
     // aligned to their size), then the staged maps, the pair table, reductions
     static constexpr int MAPS = 2 * kChunkSlots + 3 * kMapStride;  // reads of absent maps may run past a chunk
-    static constexpr size_t OFF_MAPS = (size_t)DIRS * SIZE * sizeof(T) < 256 ? 256 : (size_t)DIRS * SIZE * sizeof(T);
+    static constexpr size_t OFF_MAPS = (size_t)DIRS * SIZE * 8 < 256 ? 256 : (size_t)DIRS * SIZE * 8;
     static constexpr size_t OFF_LANE = OFF_MAPS + (size_t)DIRS * MAPS * 8;
     static constexpr size_t OFF_WAVE = OFF_LANE + (size_t)NP * 64 * 2;
     static constexpr size_t OFF_RED = (OFF_WAVE + (size_t)NP * 16 * 2 + 15) & ~(size_t)15;
@@ -74,7 +78,7 @@ __device__ __forceinline__ void run_chain(unsigned tile, double *mapbuf, const u
     using S = ChainShape<T, N>;
     constexpr int TPD = 64 * S::W;
     constexpr int SPT = (kChunkDoubles + TPD - 1) / TPD;
-    constexpr int SH = sizeof(T) == 8 ? 3 : 2;
+    constexpr int SH = 3;
     constexpr bool SCALAR = S::W > 4;
     typedef unsigned U4 __attribute__((ext_vector_type(4)));
     typedef double D2 __attribute__((ext_vector_type(2)));
@@ -170,7 +174,7 @@ __device__ __forceinline__ void run_chain(unsigned tile, double *mapbuf, const u
                 constexpr int KIND = decltype(kind_c)::value;
                 double v[16];
 #pragma unroll
-                for (int e = 0; e < 16; ++e) v[e] = lds_word<T>(ra[e]);
+                for (int e = 0; e < 16; ++e) v[e] = lds_word<double>(ra[e]);
                 // where the next block is; the base of the one behind it
                 const unsigned here = base;
                 const int n1 = clamp(i + 1);
@@ -234,7 +238,7 @@ __device__ __forceinline__ void run_chain(unsigned tile, double *mapbuf, const u
                     __asm__ volatile("" : "+v"(mv));
                 }
 #pragma unroll
-                for (int e = 0; e < 16; ++e) lds_put<T>(wa[e], v[e]);
+                for (int e = 0; e < 16; ++e) lds_put<double>(wa[e], v[e]);
                 wn = w2;
             };
             const unsigned wi = w;
@@ -270,7 +274,7 @@ void chain_kernel(const ResidentDesc *__restrict__ descs, int meet, double *out)
     const int dir = S::BOTH ? __builtin_amdgcn_readfirstlane(tid / TPD) : (split ? (int)(blockIdx.x & 1) : 0);
     const int slot = S::BOTH ? dir : 0;
     const int t = S::BOTH ? tid % TPD : tid;
-    T *lc = reinterpret_cast<T *>(smem) + slot * S::SIZE;
+    double *lc = reinterpret_cast<double *>(smem) + slot * S::SIZE;
     double *mapbuf = reinterpret_cast<double *>(smem + S::OFF_MAPS) + slot * S::MAPS;
     uint16_t *lanetab = reinterpret_cast<uint16_t *>(smem + S::OFF_LANE);
     uint16_t *wavetab = reinterpret_cast<uint16_t *>(smem + S::OFF_WAVE);
@@ -278,10 +282,10 @@ void chain_kernel(const ResidentDesc *__restrict__ descs, int meet, double *out)
 
     for (int i = tid; i < S::NP * 64; i += S::BLOCK) lanetab[i] = (&kPairTable<S::K>.lane[0][0])[i];
     for (int i = tid; i < S::NP * 16; i += S::BLOCK) wavetab[i] = (&kPairTable<S::K>.wave[0][0])[i];
-    for (int i = t; i < S::SIZE; i += TPD) lc[i] = (T)0;
+    for (int i = t; i < S::SIZE; i += TPD) lc[i] = 0.0;
     lds_barrier();
     if (dir == 1) {  // |0...0>: Tr(P rho) = 1 for the strings of I and Z
-        for (int j = t; j < (1 << N); j += TPD) lc[sw((int)zonly_slot(j, N))] = (T)1;
+        for (int j = t; j < (1 << N); j += TPD) lc[sw((int)zonly_slot(j, N))] = 1.0;
     } else if (d.coef_in) {
         const T *in = reinterpret_cast<const T *>(d.coef_in);
         for (int i = t; i < (1 << (2 * N)); i += TPD) lc[sw(i)] = in[i];
@@ -289,12 +293,12 @@ void chain_kernel(const ResidentDesc *__restrict__ descs, int meet, double *out)
         // repeated strings are summed in input order by one thread
         for (int k = t; k < d.nterms; k += d.distinct ? TPD : 1) {
             const int s = sw((int)morton_slot(d.obs_x[k], d.obs_z[k], N));
-            lc[s] = (T)((double)lc[s] + d.obs_c[k]);
+            lc[s] += d.obs_c[k];
         }
     }
     lds_barrier();
     const int nrec = dir == 0 ? d.nchain : (meet ? d.nchain_fwd : 0);
-    typedef __attribute__((address_space(3))) T LT;
+    typedef __attribute__((address_space(3))) double LT;
     run_chain<T, N>((unsigned)(size_t)(LT *)lc, mapbuf, lanetab, wavetab, d.chain + (dir == 0 ? 0 : d.nchain), nrec,
                     d.maps, d.nmaps, t);
     lds_barrier();
@@ -303,15 +307,15 @@ void chain_kernel(const ResidentDesc *__restrict__ descs, int meet, double *out)
     double part = 0.0;
     if (!meet) {
         if (dir == 0) {
-            for (int j = t; j < (1 << N); j += TPD) part += (double)lc[sw((int)zonly_slot(j, N))];
+            for (int j = t; j < (1 << N); j += TPD) part += lc[sw((int)zonly_slot(j, N))];
             if (d.coef_out) {
                 T *o = reinterpret_cast<T *>(d.coef_out);
-                for (int i = t; i < (1 << (2 * N)); i += TPD) o[i] = lc[sw(i)];
+                for (int i = t; i < (1 << (2 * N)); i += TPD) o[i] = (T)lc[sw(i)];
             }
         }
     } else if constexpr (S::BOTH) {
-        const T *c = reinterpret_cast<const T *>(smem), *r = c + S::SIZE;
-        for (int i = tid; i < S::SIZE; i += S::BLOCK) part += (double)c[i] * (double)r[i];
+        const double *c = reinterpret_cast<const double *>(smem), *r = c + S::SIZE;
+        for (int i = tid; i < S::SIZE; i += S::BLOCK) part += c[i] * r[i];
     } else {
         // each workgroup publishes its vector; the one that arrives second
         // multiplies the two (the product and its order do not depend on
@@ -322,7 +326,7 @@ void chain_kernel(const ResidentDesc *__restrict__ descs, int meet, double *out)
         T *mine = reinterpret_cast<T *>(d.xbuf) + dir * S::SIZE;
         const T *theirs = reinterpret_cast<const T *>(d.xbuf) + (1 - dir) * S::SIZE;
         for (int i = tid; i < S::SIZE; i += S::BLOCK)
-            __hip_atomic_store(mine + i, lc[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(mine + i, (T)lc[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores are at the agent's point of coherence
         __syncthreads();
         unsigned *flag = reinterpret_cast<unsigned *>(red + S::BLOCK / 64 + 1);
@@ -335,7 +339,7 @@ void chain_kernel(const ResidentDesc *__restrict__ descs, int meet, double *out)
         for (int j = 0; j < PER; ++j)
             v[j] = __hip_atomic_load(theirs + tid + j * S::BLOCK, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-        for (int j = 0; j < PER; ++j) part += (double)lc[tid + j * S::BLOCK] * (double)v[j];
+        for (int j = 0; j < PER; ++j) part += (double)(T)lc[tid + j * S::BLOCK] * (double)v[j];
         if (tid == 0) *d.ticket = 0u;  // for the next launch
     }
     const double total = block_sum_d<S::BLOCK>(part, red);

@@ -1,7 +1,7 @@
 // Passes over 7- and 6-qubit tiles (untracked, n <= 14): persistent workgroups,
 // one thread per 16 weights of a tile of 4^k weights in LDS (1,024 threads and
-// 128 KiB in FP64 at k = 7, 256 and 32 KiB at k = 6), run the pass's record
-// chain.
+// 128 KiB at k = 7, 256 and 32 KiB at k = 6; doubles in FP32 circuits too, which
+// are rounded once per pass), run the pass's record chain.
 //
 // What bounds it at k = 7: a tile's HBM traffic (256 KiB in FP64, 12.8 us of a
 // CU's share of the bandwidth) and its LDS sweeps (16 waves, 1.4 us each, bound
@@ -42,7 +42,7 @@ template <typename T, int K>
 struct TileChain {
     static constexpr int BLOCK = 1 << (2 * (K - 2));  // one thread per 16-weight block of a sweep
     static constexpr int PAIRS = kNumPairs<K>;
-    static constexpr size_t OFF_LANE = sizeof(T) << (2 * K);
+    static constexpr size_t OFF_LANE = (size_t)8 << (2 * K);
     static constexpr size_t OFF_WAVE = OFF_LANE + (size_t)PAIRS * 64 * 2;
     static constexpr size_t LDS = OFF_WAVE + (size_t)PAIRS * 16 * 2;
 };
@@ -83,7 +83,8 @@ template <typename T, int K, bool START>
 __global__ __launch_bounds__((TileChain<T, K>::BLOCK), 4)
 void tile_chain_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) {
     using S = TileChain<T, K>;
-    constexpr int SH = sizeof(T) == 8 ? 3 : 2;
+    constexpr int SH = 3;                            // bytes of a weight in LDS
+    constexpr int HSH = sizeof(T) == 8 ? 3 : 2;      // in HBM
     extern __shared__ __align__(256) unsigned char smem[];
     uint16_t *lanetab = reinterpret_cast<uint16_t *>(smem + S::OFF_LANE);
     uint16_t *wavetab = reinterpret_cast<uint16_t *>(smem + S::OFF_WAVE);
@@ -192,8 +193,8 @@ void tile_chain_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) {
     // passes over both arrays in large sweeps (300 sets at n = 9 6.28 ms, 6.04
     // without), and 5,000 gates at n = 10 took 1.25 ms, 1.18 without.
     auto begin = [&](const TileStart *st) {
-        const unsigned vs = block_voff(word(R0.x, 0) & 0xffu, cur.d->qubits) >> SH;  // slots, not bytes
-        const uint32_t c[4] = {cur.d->in[0] >> SH, cur.d->in[1] >> SH, cur.d->in[2] >> SH, cur.d->in[3] >> SH};
+        const unsigned vs = block_voff(word(R0.x, 0) & 0xffu, cur.d->qubits) >> HSH;  // slots, not bytes
+        const uint32_t c[4] = {cur.d->in[0] >> HSH, cur.d->in[1] >> HSH, cur.d->in[2] >> HSH, cur.d->in[3] >> HSH};
         const unsigned xbits = 0x55555555u;
         if (cur.d->forward) {
             const bool z = (((unsigned)cur.base | vs) & xbits) == 0;
@@ -236,7 +237,7 @@ void tile_chain_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) {
             const unsigned c[4] = {word(R1.x, 0), word(R1.y, 0), word(R1.z, 0), word(R1.w, 0)};
             block_addresses(ad, at, c);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) lds_put<T>(ad[e], v[e]);
+            for (int e = 0; e < 16; ++e) lds_put<double>(ad[e], v[e]);
         }
         // ---- the tile before goes out and the next one comes in, a quarter
         // at a time through the same registers, spread over the records
@@ -294,14 +295,14 @@ void tile_chain_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) {
                         read_words(rc, c, w);
                         block_addresses(ra, tile0 + (slot << SH), rc);
 #pragma unroll
-                        for (int e = 0; e < 16; ++e) v[e] = lds_word<T>(ra[e]);
+                        for (int e = 0; e < 16; ++e) v[e] = lds_word<double>(ra[e]);
                     }
                     apply(kind, v, w, m1, gmaps + 9ull * (map + 1));
                     first_map(m1, cur.d, next_map);
                     unsigned wa[16];
                     block_addresses(wa, tile0 + (slot << SH), c);
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) lds_put<T>(wa[e], v[e]);
+                    for (int e = 0; e < 16; ++e) lds_put<double>(wa[e], v[e]);
                 });
                 if (K == 6 && ((w >> kChainNoBarrierBit) & 1u)) wave_lds_order();
                 else lds_barrier();
@@ -340,7 +341,7 @@ void tile_chain_kernel(const TilePassDesc *__restrict__ descs, TileGroups grp) {
                 read_words(rc, c, w);
                 block_addresses(ra, tile0 + (slot << SH), rc);
 #pragma unroll
-                for (int e = 0; e < 16; ++e) v[e] = lds_word<T>(ra[e]);
+                for (int e = 0; e < 16; ++e) v[e] = lds_word<double>(ra[e]);
             }
             apply_branched(v, w, m1, gmaps + 9ull * (map + 1));
             first_map(m1, nxt.d, nmap);
