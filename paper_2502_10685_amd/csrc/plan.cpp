@@ -421,245 +421,53 @@ void group_all(DensePlan &P, bool segments, bool chain) {
     P.passes = std::move(passes);
 }
 
-}  // namespace
-
-static DensePlan plan_dense_core(const GateList &g, int k, int low, const PlanOptions &o);
-
-DensePlan plan_dense_opts(const GateList &g, int k, int low, const PlanOptions &o) {
-    DensePlan P = plan_dense_core(g, k, low, o);
-    if (o.group && o.compose) group_all(P, o.segments, o.chain);
-    return P;
-}
-
-static DensePlan plan_dense_core(const GateList &g, int k, int low, const PlanOptions &o) {
+// Builds the passes of one direction over a gate list, front first.
+class Scheduler {
+public:
     DensePlan P;
-    const int n = g.n;
-    const bool compose = o.compose, reorder = o.reorder;
-    P.roff.push_back(0);
-    P.k = k;
-    P.resident = (k >= n);
-    const int64_t gb = o.g_begin, ge = o.g_end < 0 ? g.m : o.g_end;
-    const int64_t m = ge - gb;
-    // position h in processing order <-> gate index
-    auto gate_of = [&](int64_t h) { return o.forward ? gb + h : ge - 1 - h; };
+    int64_t remaining;  // gates not scheduled
 
-    // Ops of the gates at positions `sched`, in that order, on digits local[q];
-    // composed maps have their gates' recipes in one piece.
-    std::vector<int32_t> map_of, open, at;
-    auto emit_ops = [&](const std::vector<int64_t> &sched, const int *local, int digits) {
-        const int map_base = P.nmaps();
-        int maps = 0;
-        map_of.assign(sched.size(), -1);
-        open.assign((size_t)digits, -1);
-        at.clear();  // gates per map, then where its next one goes
-        for (size_t i = 0; i < sched.size(); ++i) {
-            const int64_t gi = gate_of(sched[i]);
-            const uint8_t op = g.op[(size_t)gi];
-            DOp d{};
-            d.ngates = 1;
-            if (op == 2) {
-                d.kind = DOP_CX;
-                d.a = (uint8_t)local[g.q0[(size_t)gi]];
-                d.b = (uint8_t)local[g.q1[(size_t)gi]];
-                open[d.a] = -1;
-                open[d.b] = -1;
-                P.ops.push_back(d);
-                continue;
-            }
-            const int dg = local[g.q0[(size_t)gi]];
-            const bool rot = op >= 3;
-            if (compose && open[(size_t)dg] >= 0 && P.ops[(size_t)open[(size_t)dg]].ngates < 255) {
-                DOp &u = P.ops[(size_t)open[(size_t)dg]];
-                u.ngates++;
-                u.smask = (uint16_t)smask_compose(gate_smask(op), u.smask);
-                if (rot) u.perm = 0;
-                map_of[i] = (int32_t)u.map - map_base;
-            } else {
-                d.kind = DOP_U1;
-                d.a = (uint8_t)dg;
-                d.smask = (uint16_t)gate_smask(op);
-                d.perm = rot ? 0 : 1;
-                d.map = (uint32_t)(map_base + maps);
-                map_of[i] = maps++;
-                at.push_back(0);
-                open[(size_t)dg] = (int32_t)P.ops.size();
-                P.ops.push_back(d);
-            }
-            ++at[(size_t)map_of[i]];
-        }
-        int32_t end = (int32_t)P.rop.size();
-        for (int32_t &a : at) {
-            const int32_t count = a;
-            a = end;
-            end += count;
-            P.roff.push_back(end);
-        }
-        P.rop.resize((size_t)end);
-        P.rparam.resize((size_t)end);
-        P.rgate.resize((size_t)end);
-        for (size_t i = 0; i < sched.size(); ++i) {
-            if (map_of[i] < 0) continue;
-            const int64_t gi = gate_of(sched[i]);
-            const size_t r = (size_t)at[(size_t)map_of[i]]++;
-            P.rop[r] = g.op[(size_t)gi];
-            P.rparam[r] = g.op[(size_t)gi] >= 3 ? g.param[(size_t)gi] : -1;
-            P.rgate[r] = (int32_t)gi;
-        }
-    };
+    Scheduler(const GateList &gates, int k_, int low, const PlanOptions &opts)
+        : g(gates), o(opts), n(gates.n), k(k_), gb(opts.g_begin), ge(opts.g_end < 0 ? gates.m : opts.g_end) {
+        remaining = m = ge - gb;
+        P.roff.push_back(0);
+        P.k = k;
+        P.resident = k >= n;
+        lowmask = low >= 32 ? 0xffffffffu : ((1u << std::min(low, n)) - 1u);
+        if (!P.resident && o.reorder) build_runs();
+    }
 
-    std::vector<int64_t> sched;
-    if (P.resident) {
+    // The only pass of a resident schedule: every gate.
+    void whole() {
         DensePass pass;
         pass.k = n;
-        for (int j = 0; j < n && j < 8; ++j) pass.qubit[j] = (uint8_t)j;
         int local[32];
         for (int q = 0; q < n; ++q) local[q] = q;
+        for (int j = 0; j < n && j < 8; ++j) pass.qubit[j] = (uint8_t)j;
         sched.resize((size_t)m);
         for (int64_t h = 0; h < m; ++h) sched[(size_t)h] = h;
-        emit_ops(sched, local, n);
+        emit_ops(local, n);
         pass.op_begin = 0;
         pass.op_end = (int)P.ops.size();
         pass.ngates = m;
         P.passes.push_back(pass);
-        return P;
     }
 
-    // ---- tiled passes
-    // A wire's gates in processing order, as runs of single-qubit gates with a
-    // CX (or the end) behind each.
-    struct Run {
-        int32_t begin, end;     // in one[q]
-        int32_t partner = -1;   // the CX behind it: the other wire, that wire's
-        int32_t prun = 0;       // run before it, and its position
-        int64_t cx = 0;
-    };
-    std::vector<std::vector<Run>> runs((size_t)n);
-    std::vector<std::vector<int64_t>> one((size_t)n);  // positions of the single-qubit gates
-    for (int q = 0; q < n; ++q) runs[(size_t)q].push_back({0, 0});
-    auto wires = [&](int64_t h) -> uint32_t {
-        const int64_t gi = gate_of(h);
-        uint32_t w = 1u << g.q0[(size_t)gi];
-        if (g.op[(size_t)gi] == 2) w |= 1u << g.q1[(size_t)gi];
-        return w;
-    };
-    for (int64_t h = 0; reorder && h < m; ++h) {
-        const int64_t gi = gate_of(h);
-        const int32_t a = g.q0[(size_t)gi];
-        std::vector<Run> &ra = runs[(size_t)a];
-        if (g.op[(size_t)gi] != 2) {
-            one[(size_t)a].push_back(h);
-            ++ra.back().end;
-            continue;
-        }
-        const int32_t b = g.q1[(size_t)gi];
-        std::vector<Run> &rb = runs[(size_t)b];
-        const int32_t ia = (int32_t)ra.size() - 1, ib = (int32_t)rb.size() - 1;
-        ra.back().partner = b;
-        ra.back().prun = ib;
-        rb.back().partner = a;
-        rb.back().prun = ia;
-        ra.back().cx = rb.back().cx = h;
-        ra.push_back({(int32_t)one[(size_t)a].size(), (int32_t)one[(size_t)a].size()});
-        rb.push_back({(int32_t)one[(size_t)b].size(), (int32_t)one[(size_t)b].size()});
-    }
-    // How far each wire is: its run, and whether that run's gates are taken.
-    struct Heads {
-        int32_t run[32];
-        uint32_t taken;
-    };
-    Heads head{};
-    const Run *wire[32];
-    for (int q = 0; q < n; ++q) wire[q] = runs[(size_t)q].data();
-    auto at_cx = [&](const Heads &hd, int q) {
-        const Run &r = wire[q][hd.run[q]];
-        return ((hd.taken >> q) & 1u) || r.begin == r.end;
-    };
-    const uint32_t lowmask = low >= 32 ? 0xffffffffu : ((1u << std::min(low, n)) - 1u);
-    // Takes every gate whose wires lie in S2 and that is next on all of them,
-    // until none is; returns their number.  take_run and take_cx are told of
-    // them in order.
-    auto absorb = [&](uint32_t S2, Heads &hd, auto take_run, auto take_cx) -> int64_t {
-        int64_t got = 0;
-        for (bool prog = true; prog;) {
-            prog = false;
-            for (uint32_t left = S2; left; left &= left - 1u) {
-                const int q = __builtin_ctz(left);
-                for (;;) {
-                    const Run &r = wire[q][hd.run[q]];
-                    if (!at_cx(hd, q)) {
-                        take_run(q, r);
-                        got += r.end - r.begin;
-                        hd.taken |= 1u << q;
-                    }
-                    const int t = r.partner;
-                    if (t < 0 || !((S2 >> t) & 1u) || hd.run[t] != r.prun || !at_cx(hd, t)) break;
-                    take_cx(r.cx);
-                    ++got;
-                    hd.run[q]++;
-                    hd.run[t]++;
-                    hd.taken &= ~((1u << q) | (1u << t));
-                    prog = true;
-                }
-            }
-        }
-        return got;
-    };
-    auto count = [&](uint32_t S2, Heads &hd) {
-        return absorb(S2, hd, [](int, const Run &) {}, [](int64_t) {});
-    };
-    // Wires of the gate next on wire q if it is next on all of them (0: none);
-    // a CX is found on its lower wire.
-    auto next_wires = [&](const Heads &hd, int q) -> uint32_t {
-        const Run &r = wire[q][hd.run[q]];
-        if (!at_cx(hd, q)) return 1u << q;
-        const int t = r.partner;
-        if (t < q || hd.run[t] != r.prun || !at_cx(hd, t)) return 0u;
-        return (1u << q) | (1u << t);
-    };
-    // Gates a pass would take if its qubit set started as S0 and were then
-    // completed to k qubits greedily, each step adding the wires of the
-    // ready gate after which the most gates become schedulable.
-    auto rollout = [&](uint32_t S0) -> int64_t {
-        Heads hd = head, h2, best;
-        uint32_t S2 = S0;
-        int64_t total = count(S2, hd);
-        while (__builtin_popcount(S2) < k) {
-            int64_t bg = -1;
-            uint32_t bw = 0;
-            for (int q = 0; q < n; ++q) {
-                const uint32_t w = next_wires(hd, q);
-                if (!w || __builtin_popcount(S2 | w) > k) continue;
-                h2 = hd;
-                const int64_t gg = count(S2 | w, h2);
-                if (gg > bg) {
-                    bg = gg;
-                    bw = w;
-                    best = h2;
-                }
-            }
-            if (bg < 0) break;
-            S2 |= bw;
-            total += bg;
-            hd = best;
-        }
-        return total;
-    };
-    int64_t remaining = m;
-    while (remaining > 0) {
+    // The next tiled pass; false if there is none.
+    bool pass() {
         uint32_t S = lowmask;
         sched.clear();
-        if (!reorder) {
+        if (!o.reorder) {
             // keep the Heisenberg gate order: a pass is a maximal run of
             // consecutive gates whose qubits fit in k
             int64_t h = m - remaining;
             while (h < m && __builtin_popcount(S | wires(h)) <= k) {
                 S |= wires(h);
                 sched.push_back(h++);
-                --remaining;
             }
         }
-        for (; reorder;) {
-            remaining -= absorb(
+        for (; o.reorder;) {
+            absorb(
                 S, head,
                 [&](int q, const Run &r) {
                     sched.insert(sched.end(), one[(size_t)q].begin() + r.begin, one[(size_t)q].begin() + r.end);
@@ -686,7 +494,8 @@ static DensePlan plan_dense_core(const GateList &g, int k, int low, const PlanOp
             if (best < 0) break;
             S |= wires(best);
         }
-        if (sched.empty()) break;  // cannot happen for k >= low + 2
+        if (sched.empty()) return false;
+        remaining -= (int64_t)sched.size();
         // pad the qubit set to exactly k qubits with the lowest unused ones
         for (int q = 0; q < n && __builtin_popcount(S) < k; ++q) S |= 1u << q;
         DensePass pass;
@@ -699,12 +508,240 @@ static DensePlan plan_dense_core(const GateList &g, int k, int low, const PlanOp
                 local[q] = j++;
             }
         pass.op_begin = (int)P.ops.size();
-        emit_ops(sched, local, k);
+        emit_ops(local, k);
         pass.op_end = (int)P.ops.size();
         pass.ngates = (int64_t)sched.size();
         P.passes.push_back(pass);
+        return true;
     }
-    return P;
+
+    // What a scheduler of the same gates in the other direction has taken is no
+    // longer there.
+    void give_up(const Scheduler &other) {
+        for (int q = 0; q < n; ++q) last.run[q] = (int32_t)runs[(size_t)q].size() - 1 - other.head.run[q];
+        last.taken = other.head.taken;
+        remaining = other.remaining;
+    }
+
+private:
+    // A wire's gates in processing order, as runs of single-qubit gates with a
+    // CX (or the end) behind each.
+    struct Run {
+        int32_t begin, end;    // in one[q]
+        int32_t partner = -1;  // the CX behind it: the other wire, that wire's
+        int32_t prun = 0;      // run before it, and its position
+        int64_t cx = 0;
+    };
+    // How far each wire is: its run, and whether that run's gates are taken.
+    struct Heads {
+        int32_t run[32];
+        uint32_t taken;
+    };
+
+    const GateList &g;
+    const PlanOptions &o;
+    const int n, k;
+    const int64_t gb, ge;
+    int64_t m;
+    uint32_t lowmask;
+    std::vector<std::vector<Run>> runs;
+    const Run *wire[32] = {};               // runs[q]
+    std::vector<std::vector<int64_t>> one;  // positions of the single-qubit gates
+    Heads head{}, last{};  // last: each wire's last run, and whether its gates are gone
+    std::vector<int64_t> sched;  // positions of the pass's gates, in order
+    std::vector<int32_t> map_of, open, at;
+
+    // position h in processing order <-> gate index
+    size_t gate_of(int64_t h) const { return (size_t)(o.forward ? gb + h : ge - 1 - h); }
+
+    uint32_t wires(int64_t h) const {
+        const size_t gi = gate_of(h);
+        uint32_t w = 1u << g.q0[gi];
+        if (g.op[gi] == 2) w |= 1u << g.q1[gi];
+        return w;
+    }
+
+    void build_runs() {
+        runs.resize((size_t)n);
+        one.resize((size_t)n);
+        for (auto &r : runs) r.push_back({0, 0});
+        for (int64_t h = 0; h < m; ++h) {
+            const size_t gi = gate_of(h);
+            const int32_t a = g.q0[gi];
+            std::vector<Run> &ra = runs[(size_t)a];
+            if (g.op[gi] != 2) {
+                one[(size_t)a].push_back(h);
+                ++ra.back().end;
+                continue;
+            }
+            const int32_t b = g.q1[gi];
+            std::vector<Run> &rb = runs[(size_t)b];
+            const int32_t ia = (int32_t)ra.size() - 1, ib = (int32_t)rb.size() - 1;
+            ra.back().partner = b;
+            ra.back().prun = ib;
+            rb.back().partner = a;
+            rb.back().prun = ia;
+            ra.back().cx = rb.back().cx = h;
+            ra.push_back({(int32_t)one[(size_t)a].size(), (int32_t)one[(size_t)a].size()});
+            rb.push_back({(int32_t)one[(size_t)b].size(), (int32_t)one[(size_t)b].size()});
+        }
+        for (int q = 0; q < n; ++q) {
+            wire[q] = runs[(size_t)q].data();
+            last.run[q] = (int32_t)runs[(size_t)q].size() - 1;
+        }
+    }
+
+    // Whether nothing is left of wire q's run.
+    bool at_cx(const Heads &hd, int q) const {
+        const Run &r = wire[q][hd.run[q]];
+        return ((hd.taken >> q) & 1u) || r.begin == r.end || (hd.run[q] == last.run[q] && ((last.taken >> q) & 1u));
+    }
+
+    // Takes every gate whose wires lie in S2 and that is next on all of them,
+    // until none is; returns their number.  take_run and take_cx are told of
+    // them in order.
+    template <class TakeRun, class TakeCx>
+    int64_t absorb(uint32_t S2, Heads &hd, TakeRun take_run, TakeCx take_cx) const {
+        int64_t got = 0;
+        for (bool prog = true; prog;) {
+            prog = false;
+            for (uint32_t left = S2; left; left &= left - 1u) {
+                const int q = __builtin_ctz(left);
+                for (;;) {
+                    const Run &r = wire[q][hd.run[q]];
+                    if (!at_cx(hd, q)) {
+                        take_run(q, r);
+                        got += r.end - r.begin;
+                        hd.taken |= 1u << q;
+                    }
+                    const int t = r.partner;
+                    if (hd.run[q] >= last.run[q] || !((S2 >> t) & 1u) || hd.run[t] != r.prun || !at_cx(hd, t)) break;
+                    take_cx(r.cx);
+                    ++got;
+                    hd.run[q]++;
+                    hd.run[t]++;
+                    hd.taken &= ~((1u << q) | (1u << t));
+                    prog = true;
+                }
+            }
+        }
+        return got;
+    }
+    int64_t count(uint32_t S2, Heads &hd) const {
+        return absorb(S2, hd, [](int, const Run &) {}, [](int64_t) {});
+    }
+
+    // Wires of the gate next on wire q if it is next on all of them (0: none);
+    // a CX is found on its lower wire.
+    uint32_t next_wires(const Heads &hd, int q) const {
+        if (!at_cx(hd, q)) return 1u << q;
+        if (hd.run[q] >= last.run[q]) return 0u;
+        const Run &r = wire[q][hd.run[q]];
+        const int t = r.partner;
+        if (t < q || hd.run[t] != r.prun || !at_cx(hd, t)) return 0u;
+        return (1u << q) | (1u << t);
+    }
+
+    // Gates a pass would take if its qubit set started as S0 and were then
+    // completed to k qubits greedily, each step adding the wires of the
+    // ready gate after which the most gates become schedulable.
+    int64_t rollout(uint32_t S0) const {
+        Heads hd = head, h2, best = head;
+        uint32_t S2 = S0;
+        int64_t total = count(S2, hd);
+        while (__builtin_popcount(S2) < k) {
+            int64_t bg = -1;
+            uint32_t bw = 0;
+            for (int q = 0; q < n; ++q) {
+                const uint32_t w = next_wires(hd, q);
+                if (!w || __builtin_popcount(S2 | w) > k) continue;
+                h2 = hd;
+                const int64_t gg = count(S2 | w, h2);
+                if (gg > bg) {
+                    bg = gg;
+                    bw = w;
+                    best = h2;
+                }
+            }
+            if (bg < 0) break;
+            S2 |= bw;
+            total += bg;
+            hd = best;
+        }
+        return total;
+    }
+
+    // Ops of the gates of sched, in that order, on digits local[q]; composed
+    // maps have their gates' recipes in one piece.
+    void emit_ops(const int *local, int digits) {
+        const int map_base = P.nmaps();
+        int maps = 0;
+        map_of.assign(sched.size(), -1);
+        open.assign((size_t)digits, -1);
+        at.clear();  // gates per map, then where its next one goes
+        for (size_t i = 0; i < sched.size(); ++i) {
+            const size_t gi = gate_of(sched[i]);
+            const uint8_t op = g.op[gi];
+            DOp d{};
+            d.ngates = 1;
+            if (op == 2) {
+                d.kind = DOP_CX;
+                d.a = (uint8_t)local[g.q0[gi]];
+                d.b = (uint8_t)local[g.q1[gi]];
+                open[d.a] = -1;
+                open[d.b] = -1;
+                P.ops.push_back(d);
+                continue;
+            }
+            const int dg = local[g.q0[gi]];
+            const bool rot = op >= 3;
+            if (o.compose && open[(size_t)dg] >= 0 && P.ops[(size_t)open[(size_t)dg]].ngates < 255) {
+                DOp &u = P.ops[(size_t)open[(size_t)dg]];
+                u.ngates++;
+                u.smask = (uint16_t)smask_compose(gate_smask(op), u.smask);
+                if (rot) u.perm = 0;
+                map_of[i] = (int32_t)u.map - map_base;
+            } else {
+                d.kind = DOP_U1;
+                d.a = (uint8_t)dg;
+                d.smask = (uint16_t)gate_smask(op);
+                d.perm = rot ? 0 : 1;
+                d.map = (uint32_t)(map_base + maps);
+                map_of[i] = maps++;
+                at.push_back(0);
+                open[(size_t)dg] = (int32_t)P.ops.size();
+                P.ops.push_back(d);
+            }
+            ++at[(size_t)map_of[i]];
+        }
+        int32_t end = (int32_t)P.rop.size();
+        for (int32_t &first : at) {
+            const int32_t gates = first;
+            first = end;
+            end += gates;
+            P.roff.push_back(end);
+        }
+        P.rop.resize((size_t)end);
+        P.rparam.resize((size_t)end);
+        P.rgate.resize((size_t)end);
+        for (size_t i = 0; i < sched.size(); ++i) {
+            if (map_of[i] < 0) continue;
+            const size_t gi = gate_of(sched[i]), r = (size_t)at[(size_t)map_of[i]]++;
+            P.rop[r] = g.op[gi];
+            P.rparam[r] = g.op[gi] >= 3 ? g.param[gi] : -1;
+            P.rgate[r] = (int32_t)gi;
+        }
+    }
+};
+
+}  // namespace
+
+DensePlan plan_dense_opts(const GateList &g, int k, int low, const PlanOptions &o) {
+    Scheduler s(g, k, low, o);
+    if (s.P.resident) s.whole();
+    else while (s.remaining > 0 && s.pass()) {}
+    if (o.group && o.compose) group_all(s.P, o.segments, o.chain);
+    return std::move(s.P);
 }
 
 std::string plan_check(const DensePlan &P, int n) {
@@ -967,25 +1004,34 @@ void record_offsets(const ChainOp &r, const DensePass &ps, int dbytes, bool afte
 }
 
 DensePlan plan_meet(const GateList &g, int k, int low, int64_t g_end, bool segments, std::vector<int> *rec) {
-    int64_t ncx = 0;
-    for (int64_t i = 0; i < g_end; ++i) ncx += g.op[(size_t)i] == 2;
-    int64_t s = ncx ? 0 : g_end / 2;
-    for (int64_t seen = 0; ncx && seen < ncx / 2; ++s) seen += g.op[(size_t)s] == 2;
     const bool chains = k == g.n || chain_tiles(k, g.n, segments);
     std::vector<int> hrec, frec;
     PlanOptions o;
-    o.g_begin = s;
     o.g_end = g_end;
     o.segments = segments;
     o.chain = chains;
-    DensePlan P = plan_dense_opts(g, k, low, o);
-    if (chains) build_chain(P, &hrec);
-    PlanOptions f;
-    f.g_end = s;
+    PlanOptions f = o;
     f.forward = true;
-    f.segments = segments;
-    f.chain = chains;
-    DensePlan F = plan_dense_opts(g, k, low, f);
+    DensePlan P, F;
+    if (k == g.n) {
+        int64_t ncx = 0;
+        for (int64_t i = 0; i < g_end; ++i) ncx += g.op[(size_t)i] == 2;
+        int64_t s = ncx ? 0 : g_end / 2;
+        for (int64_t seen = 0; ncx && seen < ncx / 2; ++s) seen += g.op[(size_t)s] == 2;
+        o.g_begin = s;
+        f.g_end = s;
+        P = plan_dense_opts(g, k, low, o);
+        F = plan_dense_opts(g, k, low, f);
+    } else {
+        // a pass from either end in turn, until they meet
+        Scheduler back(g, k, low, o), front(g, k, low, f);
+        for (Scheduler *s = &back, *t = &front; s->remaining > 0 && s->pass(); std::swap(s, t)) t->give_up(*s);
+        group_all(back.P, o.segments, o.chain);
+        group_all(front.P, f.segments, f.chain);
+        P = std::move(back.P);
+        F = std::move(front.P);
+    }
+    if (chains) build_chain(P, &hrec);
     if (chains) build_chain(F, &frec);
     const int base = P.nmaps();
     const size_t hpass = P.passes.size();

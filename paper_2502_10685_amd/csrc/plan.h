@@ -148,11 +148,12 @@ void build_chain(DensePlan &P, std::vector<int> *begin = nullptr, bool ends = tr
 // Byte offsets, in the 4^n array (weights of dbytes), of the letters of record
 // r's pair: as it reads them (after = false) or writes them.
 void record_offsets(const ChainOp &r, const DensePass &ps, int dbytes, bool after, uint32_t out[4]);
-// Untracked evaluation from both ends: gates [s, g_end) taken back from the
-// observable, gates [0, s) forward from the state, with s where half of the
-// CX gates lie on either side (a record holds about one).  k = n: one pass
-// of both halves' chains; k < n: tile passes, the forward half's from fwd_pass
-// on; rec receives the first record of each pass over 7-qubit tiles.
+// Untracked evaluation of gates [0, g_end) from both ends: some taken back from
+// the observable, the others forward from the state.  k = n: split where half
+// of the CX gates lie on either side (a record holds about one), one pass of
+// both halves' chains; k < n: tile passes scheduled from either end in turn,
+// the forward half's from fwd_pass on; rec receives the first record of each
+// pass over tiles that run as record chains.
 DensePlan plan_meet(const GateList &g, int k, int low, int64_t g_end, bool segments,
                     std::vector<int> *rec = nullptr);
 // The forward half of a tiled meet plan run backwards, as the Heisenberg
