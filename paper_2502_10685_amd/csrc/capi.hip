@@ -158,6 +158,13 @@ __global__ void zero_u64_kernel(unsigned long long *p, int count) {
     if (i < count) p[i] = 0;
 }
 
+// `count` 64-bit words to 0, in stream order.
+hipError_t zero_words(void *p, int64_t count, hipStream_t s) {
+    hipLaunchKernelGGL(zero_u64_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, (unsigned long long *)p,
+                       (int)count);
+    return hipGetLastError();
+}
+
 // Shifted parameter sets of the parameter-shift rule: set 2j has rotation j's
 // angle raised by pi/2, set 2j+1 lowered by pi/2, every other rotation at its
 // angle theta[rot_param[r]].
@@ -280,6 +287,7 @@ int g_resident_block[8] = {64, 64, 64, 64, 64, 512, 512, 1024};
 // twice over, and the exchange buffers of more sets (256 KiB each at n = 7 in
 // FP64) are never needed at once
 constexpr int64_t kSweepChunk = 512;
+constexpr int64_t kTicketStride = 16;
 // Weights and states of a sweep's tiled circuits run from both ends that are
 // held at once: 16 sets of 10 qubits in FP64 give 2,048 tiles of 7 qubits per
 // launch, and a new sweep allocates no more than one end of them took
@@ -474,23 +482,20 @@ struct pp_circuit {
     // descriptors of step l of an evaluation (a pass of each half that has
     // one): d_pass[step[l], step[l + 1])
     std::vector<int> step;
-    pp::TileStart *d_start = nullptr;
-    bool start_c = false, start_r = false;  // the first pass of the half holds d_start
+    bool start_c = false, start_r = false;  // the first pass of the half begins its weights
     // coef holds the observable's weights at the gate where the halves met;
     // pp_get_terms takes them the rest of the way with the maps of that
     // evaluation (met_maps once the schedule they belong to is gone)
     bool met = false;
-    double *met_maps = nullptr;
+    void *met_sched = nullptr;
+    double *met_maps = nullptr;  // in met_sched
     pp::DensePlan met_plan;
-    pp::DOp *d_ops = nullptr;
+    // the DENSE schedule on the device: one block, of which these are parts
+    void *d_sched = nullptr;
     double *d_maps = nullptr;
-    int32_t *d_roff = nullptr, *d_rparam = nullptr;
-    uint8_t *d_rop = nullptr;
     pp::TilePassDesc *d_pass = nullptr;
     pp::ResidentDesc *d_res = nullptr;
-    pp::ChainOp *d_chain = nullptr;
     std::vector<int> pass_recs;  // first record of each pass over 7-qubit tiles, with the total behind the last
-    unsigned char *d_xbuf = nullptr;  // resident evaluation, n >= 6: where its two directions meet
     pp::ComposeDesc *d_comp = nullptr;
     pp::ResidentDesc h_res{};
     pp::ComposeDesc h_comp{};
@@ -559,7 +564,8 @@ struct pp_circuit {
         void *state = nullptr;
         double *part = nullptr;
         int64_t chunk = 0;
-        unsigned char *xbuf = nullptr;  // resident circuits, n >= 6: exchange of kSweepChunk sets
+        unsigned char *xbuf = nullptr;   // resident circuits, n >= 6: exchange of kSweepChunk sets,
+        unsigned *tickets = nullptr;     // and their tickets, kTicketStride apart (0 between launches)
         void *dbuf = nullptr;
         size_t dcap = 0;
         uint64_t gen = ~0ull;
@@ -598,6 +604,7 @@ void free_sweep(pp_circuit *c) {
     dfree(c->sw.state);
     dfree(c->sw.part);
     dfree(c->sw.xbuf);
+    dfree(c->sw.tickets);
     dfree(c->sw.dbuf);
     c->sw.cap = 0;
     c->sw.dcap = 0;
@@ -609,7 +616,8 @@ void free_sweep(pp_circuit *c) {
 // The rest of a met evaluation is no longer wanted.
 void drop_met(pp_circuit *c) {
     c->met = false;
-    dfree(c->met_maps);
+    dfree(c->met_sched);
+    c->met_maps = nullptr;
     c->met_plan = pp::DensePlan{};
 }
 
@@ -617,23 +625,19 @@ void free_plan_buffers(pp_circuit *c) {
     free_graph(c);
     free_grad(c);
     free_sweep(c);
-    if (c->met && !c->met_maps && c->plan_valid) {
+    if (c->met && !c->met_sched && c->plan_valid) {
+        c->met_sched = c->d_sched;
         c->met_maps = c->d_maps;
-        c->d_maps = nullptr;
+        c->d_sched = nullptr;
         c->met_plan = std::move(c->dplan);
         c->dplan = pp::DensePlan{};
     }
-    dfree(c->d_ops);
-    dfree(c->d_maps);
-    dfree(c->d_roff);
-    dfree(c->d_rparam);
-    dfree(c->d_rop);
-    dfree(c->d_pass);
-    dfree(c->d_res);
-    dfree(c->d_chain);
-    dfree(c->d_start);
-    dfree(c->d_xbuf);
-    dfree(c->d_comp);
+    dfree(c->d_sched);
+    c->d_maps = nullptr;
+    c->d_pass = nullptr;
+    c->d_res = nullptr;
+    c->d_comp = nullptr;
+    c->d_part = nullptr;
     dfree(c->d_codes);
     dfree(c->d_xrows);
     c->plan_valid = false;
@@ -667,7 +671,6 @@ void free_state_buffers(pp_circuit *c) {
     dfree(c->coef);
     dev_free(c->rcoef);
     c->rcoef = nullptr;
-    dfree(c->d_part);
     dfree(c->pres);
     dfree(c->d_counters);
     dfree(c->d_result);
@@ -956,22 +959,53 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
             if (!c->track && seg && !pp::plan_segmented(P))
                 return fail(PP_ERR_STATE, "planner self-check: unsegmented pass");
         }
-        if ((r = upload_vec(&c->d_ops, P.ops)) != PP_OK) return r;
-        if ((r = upload_vec(&c->d_roff, P.roff)) != PP_OK) return r;
-        if ((r = upload_vec(&c->d_rop, P.rop)) != PP_OK) return r;
-        if ((r = upload_vec(&c->d_rparam, P.rparam)) != PP_OK) return r;
-        HIPCHK(dalloc(&c->d_maps, (size_t)9 * std::max(P.nmaps(), 1)));
-        c->h_comp = pp::ComposeDesc{c->d_roff, c->d_rop, c->d_rparam, c->d_theta, c->d_maps, P.nmaps(),
+        // one block: ops, recipes and records, then the descriptors, the two
+        // tickets (0 between launches) and the product's sums, all copied at
+        // once, then the maps and where the ends of a resident circuit meet
+        const bool chains = !c->track && (P.resident || pp::chain_tiles(k, c->n, seg));
+        std::vector<unsigned char> blob;
+        auto room = [&](size_t bytes) {
+            const size_t off = (blob.size() + 63) & ~(size_t)63;
+            blob.resize(off + bytes, 0);
+            return off;
+        };
+        auto put = [&](const auto &v) {
+            const size_t off = room(v.size() * sizeof(v[0]));
+            if (!v.empty()) std::memcpy(blob.data() + off, v.data(), v.size() * sizeof(v[0]));
+            return off;
+        };
+        blob.reserve(P.ops.size() * sizeof(pp::DOp) + P.roff.size() * 4 + P.rop.size() * 5 +
+                     P.chain.size() * sizeof(pp::ChainOp) + (P.passes.size() + 4) * sizeof(pp::TilePassDesc) + 8192);
+        const bool ops_used = !P.resident || c->track;
+        const size_t off_ops = ops_used ? put(P.ops) : 0, off_roff = put(P.roff), off_rop = put(P.rop),
+                     off_rparam = put(P.rparam), off_chain = chains ? put(P.chain) : 0;
+        const size_t off_comp = room(sizeof(pp::ComposeDesc)), off_start = room(sizeof(pp::TileStart));
+        const size_t off_desc = room(P.resident ? sizeof(pp::ResidentDesc) : P.passes.size() * sizeof(pp::TilePassDesc));
+        const size_t off_ticket = room(64), off_part = room(sizeof(double) * pp::kMeetDoubles);
+        const size_t copied = blob.size(), off_maps = (copied + 255) & ~(size_t)255;
+        const size_t off_xbuf = (off_maps + (size_t)72 * std::max(P.nmaps(), 1) + 255) & ~(size_t)255;
+        const size_t xb = P.resident && !c->track && P.fwd_from >= 0 ? pp::chain_exchange_bytes(c->n, c->dbytes) : 0;
+        if (dev_alloc(&c->d_sched, off_xbuf + xb) != hipSuccess) {
+            c->d_sched = nullptr;
+            return fail(PP_ERR_NOMEM, "schedule: " + std::to_string(off_xbuf + xb) + " bytes");
+        }
+        unsigned char *base = (unsigned char *)c->d_sched;
+        const pp::DOp *d_ops = ops_used ? (const pp::DOp *)(base + off_ops) : nullptr;
+        const pp::ChainOp *d_chain = (const pp::ChainOp *)(base + off_chain);
+        c->d_maps = (double *)(base + off_maps);
+        c->d_comp = (pp::ComposeDesc *)(base + off_comp);
+        c->d_part = (double *)(base + off_part);
+        c->h_comp = pp::ComposeDesc{(const int32_t *)(base + off_roff), base + off_rop,
+                                   (const int32_t *)(base + off_rparam), c->d_theta, c->d_maps, P.nmaps(),
                                    c->fwd_maps ? 0 : (P.fwd_from >= 0 ? P.fwd_from : P.nmaps())};
-        HIPCHK(dalloc(&c->d_comp, 1));
-        HIPCHK(hipMemcpy(c->d_comp, &c->h_comp, sizeof(c->h_comp), hipMemcpyHostToDevice));
+        std::memcpy(blob.data() + off_comp, &c->h_comp, sizeof(c->h_comp));
         if (P.resident) {
             pp::ResidentDesc &d = c->h_res;
             d = pp::ResidentDesc{};
             d.coef_out = (c->track || c->keep_coef) ? c->coef : nullptr;
             d.coef_in = c->ramp_gate >= 0 ? c->coef : nullptr;  // the ramp's strings
             d.pres_out = c->track ? c->pres : nullptr;
-            d.ops = c->d_ops;
+            d.ops = d_ops;
             d.maps = c->d_maps;
             d.obs_x = c->d_ox;
             d.obs_z = c->d_oz;
@@ -983,62 +1017,46 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
             d.nterms = (int32_t)c->ox.size();
             d.distinct = c->obs_distinct;
             if (!c->track) {
-                if ((r = upload_vec(&c->d_chain, P.chain)) != PP_OK) return r;
-                d.chain = c->d_chain;
+                d.chain = d_chain;
                 d.nchain = P.nchain;
                 d.nchain_fwd = (int32_t)P.chain.size() - P.nchain;
                 d.nmaps = P.nmaps();
-                const size_t xb = P.fwd_from >= 0 ? pp::chain_exchange_bytes(c->n, c->dbytes) : 0;
                 if (xb) {
-                    // the two directions' vectors, then their ticket (0 between launches)
-                    HIPCHK(dalloc(&c->d_xbuf, xb + 256));
-                    HIPCHK(hipMemset(c->d_xbuf + xb, 0, 256));
-                    d.xbuf = c->d_xbuf;
-                    d.ticket = (unsigned *)(c->d_xbuf + xb);
+                    d.xbuf = base + off_xbuf;
+                    d.ticket = (unsigned *)(base + off_ticket);
                 }
             }
-            HIPCHK(dalloc(&c->d_res, 1));
-            HIPCHK(hipMemcpy(c->d_res, &d, sizeof(d), hipMemcpyHostToDevice));
+            c->d_res = (pp::ResidentDesc *)(base + off_desc);
+            std::memcpy(blob.data() + off_desc, &d, sizeof(d));
         } else {
             c->h_pass.clear();
             std::vector<int> rec;
-            if (pp::chain_tiles(k, c->n, seg) && !c->track) {
-                if ((r = upload_vec(&c->d_chain, P.chain)) != PP_OK) return r;
-                rec = c->pass_recs;
-            }
+            if (chains) rec = c->pass_recs;
             const int ntiles = (int)((int64_t)1 << (2 * (c->n - k)));
             const size_t nh = P.fwd_pass >= 0 ? (size_t)P.fwd_pass : P.passes.size();
             const size_t nf = P.passes.size() - nh;
-            if (P.fwd_pass >= 0) {
-                if (weights && !c->rcoef && dev_alloc(&c->rcoef, (size_t)dense_slots(c->n) * c->dbytes) != hipSuccess) {
-                    c->rcoef = nullptr;
-                    return fail(PP_ERR_NOMEM, "state coefficients");
-                }
-                if (!c->d_part) {
-                    HIPCHK(dalloc(&c->d_part, (size_t)pp::kMeetDoubles));
-                    HIPCHK(hipMemset(c->d_part, 0, sizeof(double) * pp::kMeetDoubles));  // the ticket
-                }
+            if (P.fwd_pass >= 0 && weights && !c->rcoef &&
+                dev_alloc(&c->rcoef, (size_t)dense_slots(c->n) * c->dbytes) != hipSuccess) {
+                c->rcoef = nullptr;
+                return fail(PP_ERR_NOMEM, "state coefficients");
             }
-            c->start_c = c->start_r = false;
-            if (!rec.empty()) {
-                const pp::TileStart st{c->d_ox, c->d_oz, c->d_oc, (int32_t)c->ox.size()};
-                HIPCHK(dalloc(&c->d_start, 1));
-                HIPCHK(hipMemcpy(c->d_start, &st, sizeof(st), hipMemcpyHostToDevice));
-                c->start_c = nh > 0 && c->ramp_gate < 0 && c->ox.size() <= (size_t)pp::kStartTerms;
-                c->start_r = nf > 0;
-            }
+            const pp::TileStart st{c->d_ox, c->d_oz, c->d_oc, (int32_t)c->ox.size()};
+            std::memcpy(blob.data() + off_start, &st, sizeof(st));
+            c->start_c = !rec.empty() && nh > 0 && c->ramp_gate < 0 && c->ox.size() <= (size_t)pp::kStartTerms;
+            c->start_r = !rec.empty() && nf > 0;
             c->step.assign(1, 0);
             for (size_t l = 0; l < std::max(nh, nf); ++l) {
                 for (size_t pi : {l < nh ? l : SIZE_MAX, l < nf ? nh + l : SIZE_MAX}) {
                     if (pi == SIZE_MAX) continue;
                     const pp::DensePass &ps = P.passes[pi];
                     pp::TilePassDesc d{};
-                    if (!rec.empty()) set_chain(d, P, ps, c->d_chain, rec[pi], rec[pi + 1], c->dbytes);
+                    if (!rec.empty()) set_chain(d, P, ps, d_chain, rec[pi], rec[pi + 1], c->dbytes);
                     d.forward = pi >= nh;
-                    if ((pi == 0 && c->start_c) || (pi == nh && c->start_r)) d.start = c->d_start;
+                    if ((pi == 0 && c->start_c) || (pi == nh && c->start_r))
+                        d.start = (const pp::TileStart *)(base + off_start);
                     d.coef = d.forward ? c->rcoef : c->coef;
                     d.pres = c->track ? c->pres : nullptr;
-                    d.ops = c->d_ops;
+                    d.ops = d_ops;
                     d.maps = c->d_maps;
                     d.counters = c->d_counters;
                     d.n = c->n;
@@ -1054,8 +1072,11 @@ pp_status ensure_plan(pp_circuit *c, bool weights = true) {
                 }
                 c->step.push_back((int)c->h_pass.size());
             }
-            if ((r = upload_vec(&c->d_pass, c->h_pass)) != PP_OK) return r;
+            c->d_pass = (pp::TilePassDesc *)(base + off_desc);
+            if (!c->h_pass.empty())
+                std::memcpy(blob.data() + off_desc, c->h_pass.data(), c->h_pass.size() * sizeof(pp::TilePassDesc));
         }
+        HIPCHK(hipMemcpy(c->d_sched, blob.data(), copied, hipMemcpyHostToDevice));
     }
     c->plan_valid = true;
     c->plan_track = c->track;
@@ -2633,15 +2654,14 @@ extern "C" pp_status pp_evaluate_thetas(pp_circuit *c, int64_t count, const doub
         if (e == hipSuccess && meet) e = dev_alloc(&W.state, (size_t)slots * c->dbytes * W.chunk);
         if (e == hipSuccess && meet) {
             e = dalloc(&W.part, (size_t)(pp::kMeetDoubles * W.chunk));
-            if (e == hipSuccess) e = hipMemset(W.part, 0, sizeof(double) * pp::kMeetDoubles * W.chunk);  // the tickets
-            if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+            if (e == hipSuccess) e = zero_words(W.part, pp::kMeetDoubles * W.chunk, s);  // the tickets among them
         }
         const size_t xb = P.resident ? pp::chain_exchange_bytes(c->n, c->dbytes) : 0;
         if (e == hipSuccess && xb) {
-            const size_t bytes = (size_t)std::min(cap, kSweepChunk) * (xb + 256);
-            e = dalloc(&W.xbuf, bytes);
-            if (e == hipSuccess) e = hipMemset(W.xbuf, 0, bytes);  // the tickets
-            if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+            const int64_t sets = std::min(cap, kSweepChunk);
+            e = dalloc(&W.xbuf, (size_t)sets * xb);
+            if (e == hipSuccess) e = dalloc(&W.tickets, (size_t)(sets * kTicketStride));
+            if (e == hipSuccess) e = zero_words(W.tickets, sets * kTicketStride / 2, s);
         }
         if (e != hipSuccess) {
             (void)hipGetLastError();
@@ -2682,9 +2702,8 @@ extern "C" pp_status pp_evaluate_thetas(pp_circuit *c, int64_t count, const doub
                 rd[i].pres_out = nullptr;
                 rd[i].counters = nullptr;
                 if (xb) {
-                    unsigned char *x = W.xbuf + (size_t)(i % kSweepChunk) * (xb + 256);
-                    rd[i].xbuf = x;
-                    rd[i].ticket = (unsigned *)(x + xb);
+                    rd[i].xbuf = W.xbuf + (size_t)(i % kSweepChunk) * xb;
+                    rd[i].ticket = W.tickets + (i % kSweepChunk) * kTicketStride;
                 }
             }
             W.res_off = append(rd.data(), rd.size() * sizeof(rd[0]));
