@@ -253,11 +253,12 @@ PP_API pp_status pp_evaluate_noalloc(pp_circuit *c, void *stream, double *d_expv
 
 /* Enqueues one evaluation of <O> = <0...0| U^dag O U |0...0> (measurement
  * of Sec. II-A from the propagated strings: only strings of I and Z have a
- * nonzero expectation in |0...0>).  An untracked LDS-resident circuit (n <= 7)
- * is run from both ends: the observable's weights c back to a middle gate and
- * the state's Pauli coefficients r (eqs. (2)-(3)) forward to it, side by side,
- * then <O> = sum_P c(P) r(P).  d_expval is caller-owned device memory
- * for one double.  PP_ERR_STATE if gates, theta or the observable are
+ * nonzero expectation in |0...0>).  An untracked DENSE circuit of up to 10
+ * qubits is run from both ends: the observable's weights c back to the middle
+ * and the state's Pauli coefficients r (eqs. (2)-(3)) forward to it, side by
+ * side, then <O> = sum_P c(P) r(P); with 8 to 10 qubits that takes a second 4^n
+ * array.  d_expval is caller-owned device memory for one double.  A circuit's
+ * evaluations share its buffers: those on different streams must be ordered.  PP_ERR_STATE if gates, theta or the observable are
  * missing; PP_ERR_NOMEM if the first evaluation's buffers cannot be
  * allocated (the circuit stays usable). */
 PP_API pp_status pp_evaluate(pp_circuit *c, void *stream, double *d_expval);
@@ -273,7 +274,9 @@ PP_API pp_status pp_evaluate(pp_circuit *c, void *stream, double *d_expval);
  * circuit sets PP_OPT_USE_GRAPH (and all are untracked DENSE), the step is
  * captured as one hipGraph the first time this set of circuits meets this
  * output array, and replayed afterwards (same results bit for bit); the
- * capture is dropped when the set, a schedule or the array changes. */
+ * capture is dropped when the set, a schedule or the array changes.  A call
+ * that the caller captures reads the launch descriptors of this batch, which
+ * later batches overwrite: replay it only until another batch is evaluated. */
 PP_API pp_status pp_evaluate_batch(pp_circuit *const *cs, int64_t count, void *stream, double *d_expvals);
 
 /* Parameter sweep (the 2m parameter-shift evaluations of Sec. I, a scan
@@ -281,10 +284,11 @@ PP_API pp_status pp_evaluate_batch(pp_circuit *const *cs, int64_t count, void *s
  * thetas: count x n_params doubles, row-major, host memory (on_device = 0,
  * copied before return) or device memory (on_device = 1, read on `stream`).
  * d_expvals: caller-owned device array of `count` doubles.  All sets share
- * the schedule: each tile pass of all of them is one launch (LDS-resident
- * circuits: one launch), with per-set maps and 4^n weights that the circuit
- * keeps between calls (count x 4^n x sizeof(weight) bytes of device memory;
- * PP_ERR_NOMEM when that does not fit).  Each result is bit-identical to
+ * the schedule: each tile pass of all of them is one launch (of 512 sets each
+ * for LDS-resident circuits, of 256 MiB of weights for circuits run from both
+ * ends), with per-set maps and 4^n weights that the circuit keeps between calls
+ * (at most count x 4^n x sizeof(weight) bytes of device memory, and exchange
+ * buffers of circuits of 6 and 7 qubits; PP_ERR_NOMEM when that does not fit).  Each result is bit-identical to
  * pp_evaluate with the same theta.  DENSE engine without term tracking only
  * (else PP_ERR_STATE); theta set with pp_circuit_set_theta is not used. */
 PP_API pp_status pp_evaluate_thetas(pp_circuit *c, int64_t count, const double *thetas, int32_t on_device,
@@ -354,7 +358,9 @@ PP_API pp_status pp_get_truncation(pp_circuit *c, void *stream, double *dropped_
  * zero weights included, as the paper's expand/reduce keeps them); without it,
  * the strings whose final weight is nonzero (tiled circuits only: an untracked
  * LDS-resident evaluation, n <= 7, keeps its weights on chip and gives
- * PP_ERR_STATE).  At most `capacity` strings are
+ * PP_ERR_STATE; one of 8 to 10 qubits, run from both ends, is taken the rest of
+ * the way in a copy of its 4^n weights at every call, which costs about half an
+ * evaluation).  A SPARSE list is sorted in place at every call.  At most `capacity` strings are
  * written; *n_out receives the full count (PP_ERR_CAPACITY if larger). */
 PP_API pp_status pp_get_terms(pp_circuit *c, void *stream, int64_t capacity, uint64_t *x, uint64_t *z,
                        double *coeff, int64_t *n_out);

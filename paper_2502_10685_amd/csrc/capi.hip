@@ -296,10 +296,14 @@ constexpr int64_t kSweepMeetBytes = (int64_t)256 << 20;
 // Tile qubits by n.  7-qubit tiles take about a third fewer passes, but a
 // workgroup of 1,024 threads per tile: they pay from the n whose tiles come
 // near the 256 CUs, or from the n of which a batch's do (FP64, 6 against 7
-// qubits: 5,000 random gates at n = 8 0.67 against 0.89 ms, n = 9 0.77 against
-// 1.08, n = 10 1.16 against 1.21; 32 circuits of n = 9 1.12 against 1.21, of n
-// = 10 4.23 against 3.74; 3,000 gates at n = 11 1.76 against 1.56, n = 12 6.3
-// against 4.8, n = 13 26.6 against 19.6; FP32 alike), up to the kernel's 14.
+// qubits: 5,000 random gates at n = 8 0.69 against 0.93 ms, n = 9 0.79 against
+// 1.05; 32 circuits of 2,000 gates at n = 9 1.71 against 1.72; 3,000 gates at n
+// = 11 1.70 against 1.55, n = 12 6.4 against 4.9, n = 13 26.9 against 20.4; FP32
+// alike), up to the kernel's 14.  At n = 10 it depends on how a circuit is
+// evaluated: alone 6 are 7 % faster (5,000 gates 1.09 against 1.18), in batches
+// 7 are from 4 circuits on (4 of 2,000 gates 0.97 against 0.91, 32 6.5 against
+// 5.6).  A circuit has one schedule, so that it gives the same bits either way:
+// 7, the throughput's, from kShortGates on.
 constexpr int kTileQubits[17] = {0, 0, 0, 0, 0, 0, 0, 0, 6, 6, 7, 7, 7, 7, 7, 6, 6};
 int g_tile_qubits[17] = {0, 0, 0, 0, 0, 0, 0, 0, 6, 6, 7, 7, 7, 7, 7, 6, 6};
 // another value set by pp_tune_set: taken as it is
@@ -476,7 +480,7 @@ struct pp_circuit {
     void *coef = nullptr;
     uint8_t *pres = nullptr;
     // tiled circuits run from both ends: the state's coefficients, and where
-    // the product of the two is summed
+    // the product of the two is summed (in d_sched)
     void *rcoef = nullptr;
     double *d_part = nullptr;
     // descriptors of step l of an evaluation (a pass of each half that has
@@ -707,9 +711,9 @@ std::atomic<uint64_t> g_plan_gen{0};
 
 // Circuits run from one end (tracked, density matrices, a gradient's sweep)
 // have half the tiles in flight: at n = 10 their 64 tiles of 7 qubits are
-// slower than 256 of 6 (3,000 gates 1.27 against 1.12 ms).  So are short
-// circuits alone, whose few passes are all latency (31, 120 and 300 gates 40,
-// 69 and 97 us with 6, 48, 77 and 111 with 7; 800 gates 231 against 223).
+// slower than 256 of 6 (density matrix of 3,000 gates 1.34 against 1.15 ms).
+// Short circuits, whose few passes are all latency, take 6 as well (31, 120 and
+// 300 gates alone 50, 67 and 106 us with 6, 49, 66 and 120 with 7).
 constexpr int64_t kShortGates = 500;
 int tile_qubits_for(const pp_circuit *c, bool one_end = false) {
     if (c->n <= kResidentMaxN &&

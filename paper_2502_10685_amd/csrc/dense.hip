@@ -1478,7 +1478,11 @@ __device__ void meet_readout(const T *__restrict__ c, const T *__restrict__ r, i
     const double tot = block_sum_d<256>(sum, redd);
     unsigned *ticket = reinterpret_cast<unsigned *>(part + kMeetBlocks);
     if (threadIdx.x == 0) {
-        // agent-scope accesses pass the L2 by: no fence has to write it back
+        // agent-scope accesses pass the L2 by: no fence has to write it back.
+        // The sum's store is ordered before the ticket by its kind (written
+        // through, acknowledged where every XCD sees it) and the wait; a plain
+        // store here would not be.  The reset below is ordered by the end of
+        // the kernel.
         __hip_atomic_store(part + b, tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

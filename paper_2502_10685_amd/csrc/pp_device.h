@@ -88,7 +88,6 @@ struct ResidentDesc {
     unsigned *ticket;  // n >= 6: 0 between launches
 };
 
-// One pass of one circuit over its 4^(n-k) tiles of 4^k slots.
 // Where an evaluation's first pass over 6- or 7-qubit tiles begins: the
 // observable of at most kStartTerms strings (the forward half begins with
 // |0...0>).
@@ -99,6 +98,7 @@ struct TileStart {
     int32_t nterms;
 };
 
+// One pass of one circuit over its 4^(n-k) tiles of 4^k slots.
 struct TilePassDesc {
     void *coef;                    // 4^n weights of the circuit
     uint8_t *pres;                 // presence bytes (tracked runs) or nullptr
@@ -112,8 +112,8 @@ struct TilePassDesc {
     uint64_t qubits;               // byte j = global qubit of local digit j (ascending)
     uint32_t forward;              // 1: a pass of the forward half (coef holds the state's coefficients)
     uint32_t reg_entry;            // register-tile kernel: digit triple (bit mask) to load into registers
-    uint32_t nmaps;                // maps of the schedule (7-qubit tiles)
-    // 7-qubit tiles: the pass's records; its first is applied to the weights
+    uint32_t nmaps;                // maps of the schedule (chained passes)
+    // chained passes: the pass's records; its first is applied to the weights
     // as they come from HBM and its last as they go there, so these are byte
     // offsets in the 4^n array of the letters of their digit pairs, as in
     // ChainOp (in: read words of the first, out: write words of the last)

@@ -323,6 +323,13 @@ void chain_kernel(const ResidentDesc *__restrict__ descs, int meet, double *out)
         // so nothing has to be written back: with a __threadfence() of every
         // wave instead, each a write-back of the whole L2, 46 parameter sets
         // of 7 qubits and 7 layers in FP32 took 108 us, not 55.
+        // The order rests on the kind of these accesses, not on the language's
+        // rules: a relaxed agent-scope store is written through (sc1) and
+        // acknowledged where every XCD sees it, which s_waitcnt vmcnt(0) waits
+        // for before the ticket is taken, and the loads behind the ticket look
+        // there.  A plain store of something else to be read by the other
+        // workgroup would not be covered and needs a release.  The plain
+        // reset of the ticket is ordered by the end of the kernel.
         T *mine = reinterpret_cast<T *>(d.xbuf) + dir * S::SIZE;
         const T *theirs = reinterpret_cast<const T *>(d.xbuf) + (1 - dir) * S::SIZE;
         for (int i = tid; i < S::SIZE; i += S::BLOCK)

@@ -420,10 +420,10 @@ __device__ __forceinline__ double exact_value(const unsigned long long *sum, int
 // a pair compute their own sum from the old list, so every weight has one
 // value whatever the order, and a final sort gives the list one order.
 // What bounds it is latency: the length, the string, its slot, its partner and
-// the append follow one another, 5.9 us per pass in lists of up to some
+// the append follow one another, 5.3 us per pass in lists of up to some
 // thousand strings, where sorting the list anew for each rotation took 165 us
 // in 46 launches (n = 32, 400 gates with 214 rotations, weights from 1e-7 on:
-// 1.36 ms, 35.5 before).  One string per thread: four of them did not fit the
+// 1.16 ms with the exact readout, 35.3 before).  One string per thread: four of them did not fit the
 // scalar registers.
 // Tables hold list positions; a table is sized by the list before it (which
 // at most doubles), so it is cleared two passes ahead: pass p reads table p,
