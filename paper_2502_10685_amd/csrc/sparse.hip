@@ -350,58 +350,65 @@ __device__ __forceinline__ void exact_flush(const unsigned long long *acc, unsig
     }
 }
 
-// Carries the words, two per lane (2 lane and 2 lane + 1), up until each is below
-// 2^32: how the workgroups shared the sum then no longer shows.  Lane 33's
-// upper word takes what is left, a negative sum's sign.
-__device__ __forceinline__ void exact_carry(long long &a, long long &b, int lane) {
-    long long carry;
-    do {
-        b += a >> 32;
-        a &= 0xffffffffll;
-        carry = lane < kExactNan / 2 ? b >> 32 : 0;
+// The sum rounded to a double, to nearest even, by one wave (every lane).  The
+// words, two per lane (2 lane and 2 lane + 1), are carried up until each lies in
+// [-2^31, 2^31): how the workgroups shared the sum then no longer shows, and
+// with digits of either sign a carry rarely goes further than one word (with
+// positive ones a negative sum's went through all of them, 2 us).
+__device__ __forceinline__ double exact_value(const unsigned long long *sum, int lane) {
+    const unsigned long long nan = sum[kExactNan], pinf = sum[kExactNan + 1], ninf = sum[kExactNan + 2];
+    long long a = 2 * lane < kExactNan ? (long long)sum[2 * lane] : 0;
+    long long b = 2 * lane + 1 < kExactNan ? (long long)sum[2 * lane + 1] : 0;
+    if (nan || (pinf && ninf)) return __builtin_nan("");
+    if (pinf || ninf) return pinf ? __builtin_inf() : -__builtin_inf();
+    constexpr long long kHalf = 1ll << 31;
+    for (long long carry = 1; __ballot(carry != 0);) {
+        const long long in = (a + kHalf) >> 32;
+        a -= in << 32;
+        b += in;
+        carry = lane < kExactNan / 2 ? (b + kHalf) >> 32 : 0;
         b -= carry << 32;
         const long long up = __shfl_up(carry, 1, 64);
         a += lane > 0 ? up : 0;
-    } while (__ballot(carry != 0));
-}
-
-// The sum rounded to a double, to nearest even, by one wave (every lane).
-__device__ __forceinline__ double exact_value(const unsigned long long *sum, int lane) {
-    const unsigned long long nan = sum[kExactNan], pinf = sum[kExactNan + 1], ninf = sum[kExactNan + 2];
-    if (nan || (pinf && ninf)) return __builtin_nan("");
-    if (pinf || ninf) return pinf ? __builtin_inf() : -__builtin_inf();
-    long long a = 2 * lane < kExactNan ? (long long)sum[2 * lane] : 0;
-    long long b = 2 * lane + 1 < kExactNan ? (long long)sum[2 * lane + 1] : 0;
-    exact_carry(a, b, lane);
-    const bool neg = __shfl(b, kExactNan / 2, 64) < 0;
-    if (neg) {
-        a = -a;
-        b = -b;
-        exact_carry(a, b, lane);
     }
     const unsigned long long has_a = __ballot(a != 0), has_b = __ballot(b != 0);
     if (!(has_a | has_b)) return 0.0;
-    const int ha = has_a ? 2 * (63 - __clzll((long long)has_a)) : -1;
-    const int hb = has_b ? 2 * (63 - __clzll((long long)has_b)) + 1 : -1;
-    const int h = ha > hb ? ha : hb;  // the highest word
+    // digit i, and the highest that is not 0 below `end`
+    auto digit = [&](int i) -> long long {
+        const int at = (i < 0 ? 0 : i) >> 1;
+        const long long va = __shfl(a, at, 64), vb = __shfl(b, at, 64);
+        return i < 0 ? 0 : ((i & 1) ? vb : va);
+    };
+    auto highest = [&](int end) {
+        const unsigned long long ma = end > 126 ? ~0ull : (1ull << ((end + 1) >> 1)) - 1ull;
+        const unsigned long long mb = end > 126 ? ~0ull : (1ull << (end >> 1)) - 1ull;
+        const int ha = has_a & ma ? 2 * (63 - __clzll((long long)(has_a & ma))) : -1;
+        const int hb = has_b & mb ? 2 * (63 - __clzll((long long)(has_b & mb))) + 1 : -1;
+        return ha > hb ? ha : hb;
+    };
+    const int h = highest(128), low = highest(h < 2 ? 0 : h - 2);
+    const long long top = digit(h), rest = digit(low);  // rest: 0, or of the sign of all below digit h - 2
+    const bool neg = top < 0;
     const double huge = neg ? -__builtin_inf() : __builtin_inf();
     if (h >= kExactNan) return huge;
-    auto word = [&](int i) -> unsigned long long {
-        const long long va = __shfl(a, (i < 0 ? 0 : i) >> 1, 64), vb = __shfl(b, (i < 0 ? 0 : i) >> 1, 64);
-        return i < 0 ? 0ull : (unsigned long long)((i & 1) ? vb : va);
-    };
-    const unsigned long long w2 = word(h), w1 = word(h - 1), w0 = word(h - 2);
-    const bool below = __ballot((a != 0 && 2 * lane < h - 2) || (b != 0 && 2 * lane + 1 < h - 2)) != 0;
-    // M: the highest bit and the 63 behind it; p: its place, worth 2^(p - 1074)
-    const int z = __clz((int)(unsigned)w2), p = 32 * h + 31 - z;
-    const unsigned long long M = (((w2 << 32) | w1) << z) | (w0 >> (32 - z));
-    const bool rest = ((w0 << z) & 0xffffffffull) != 0 || below;
+    // V: the highest three digits, made positive, less one if what is below
+    // them is negative; bit 0 of it is worth 2^(32 (h - 2) - 1074)
+    __int128 V = ((__int128)top << 64) + ((__int128)digit(h - 1) << 32) + digit(h - 2);
+    if (neg) V = -V;
+    const long long below = neg ? -rest : rest;
+    if (below < 0) V -= 1;
+    const unsigned long long hi = (unsigned long long)((unsigned __int128)V >> 64), lo = (unsigned long long)V;
+    const int z = hi ? __clzll((long long)hi) : 64 + __clzll((long long)lo);  // V >= 2^62
+    const unsigned __int128 N = (unsigned __int128)V << z;
+    const unsigned long long M = (unsigned long long)(N >> 64);  // the highest bit and the 63 behind it
+    const bool more = (unsigned long long)N != 0 || below != 0;
+    const int p = 127 - z + 32 * (h - 2);  // the highest bit is worth 2^(p - 1074)
     unsigned long long bits;
     if (p <= 52) {
         bits = M >> (63 - p);
     } else {
-        const unsigned long long m = M >> 11, low = M & 0x7ffull;
-        const bool up = low > 0x400ull || (low == 0x400ull && (rest || (m & 1ull)));
+        const unsigned long long m = M >> 11, tail = M & 0x7ffull;
+        const bool up = tail > 0x400ull || (tail == 0x400ull && (more || (m & 1ull)));
         if (p - 51 >= 2047) return huge;
         bits = ((unsigned long long)(p - 52) << 52) + m + (up ? 1ull : 0ull);
     }

@@ -18,14 +18,19 @@
 //     traffic).
 //   - A sweep's 16 waves share four SIMDs, so its VALU instructions count:
 //     maps come by scalar loads, a record ahead, as the FMAs' scalar operands.
-// Random n = 12 circuits of 20,000 gates take 32.1 ms (42.4 over 6-qubit
-// tiles).  One workgroup per CU leaves 128 VGPRs per thread: 32 for a block,
-// 32 for the traffic, 32 for the results, 16 for addresses.
+// Random n = 12 circuits of 20,000 gates take 32.4 ms (42.8 over 6-qubit
+// tiles): 67.8 us for a pass of 269 MB, 0.78 of a copy's rate, of which some 13
+// are the first loads and last stores of all CUs at once.  Its waves wait 42 %
+// of their cycles and issue 23 %.  One workgroup per CU leaves 128 VGPRs per
+// thread: 32 for a block, 32 for the traffic, 32 for the results, 16 for
+// addresses.
 //
 // At k = 6 four workgroups share a CU and small circuits have fewer tiles than
 // that: a lone workgroup's chain of records counts (5,000 random gates at n = 8
 // 0.67 ms, 0.73 when each op of a pass was decoded and swept by itself; n = 9
-// 0.77, 0.85); in large batches the traffic does, 5.6 TB/s.
+// 0.77, 0.85).  In large launches sweeps and traffic weigh about the same: 64
+// parameter sets of 9 qubits take 103 us for the 537 MB of a pass, a copy's
+// rate, and 110 for a first one, which only writes.
 #include <algorithm>
 #include <type_traits>
 
