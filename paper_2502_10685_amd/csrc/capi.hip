@@ -2060,8 +2060,9 @@ namespace {
 // unchanged schedules) are evaluated into the same output array.  Another
 // batch is built into the other of two buffers, so the host does not wait for
 // the batch before it, and its passes are uploaded and launched a piece at a
-// time while the next piece is built: alternating batches of 512 circuits
-// (3.2 M gates) take 50 to 52 ms each, the same one again 48 to 49.5.
+// time while the next piece is built: two batches of 512 circuits in turn
+// (3.2 M gates each) take 48.2 ms a call, the mean of each repeated by itself
+// (51.3 and 45.1).
 struct BatchCache {
     std::vector<const pp_circuit *> key;
     std::vector<uint64_t> gens;
@@ -2145,7 +2146,7 @@ pp_status enqueue_batch_head(BatchCache &B, int dbytes, hipStream_t s) {
 
 // The passes over 7-qubit tiles run beside the others, on a stream of their
 // own: neither kind waits for the last tiles of the other (96 circuits of 4 to
-// 10 qubits in FP32 take 12.9 ms, 15.5 on one stream; 512 in FP64 49.5, 53.6).
+// 10 qubits in FP32 take 9.6 ms, 13.0 on one stream; 512 in FP64 49.3, 54.5).
 pp_status enqueue_batch_tiles(BatchCache &B, size_t first, int dbytes, hipStream_t s, TileSpan &span) {
     unsigned char *base = (unsigned char *)B.buf[B.cur].d;
     for (size_t i = first; i < B.tiles.size(); ++i) {
